@@ -9,10 +9,13 @@
 //   d(quantized) / d(step) = round(u) - u inside the range and the clamp bound outside, c_hat moving through both operands (d v / d c = V, d z / d c = -z / c), a dynamic per-token
 //   activation step (max |z| / qmax) recomputed from the row and held constant in the derivative, a static one (one value) learnable.
 //
-// Offline work on batches of a few thousand tokens: plain fp32 kernels (row-wise fake quantization, a tiled fp32 GEMM used
-// three ways, fixed-order reductions so that results do not vary from run to run), none of it on the inference path.
+// Offline work on batches of a few thousand tokens: codes of both operands once, three matrix products on the bf16 matrix
+// instruction (a code is a bf16 number, an fp32 factor is the exact sum of three), the derivatives summed where the products are
+// still in registers, and fixed-order sums, so that results do not vary from run to run.
 #include "qvggt_common.h"
 #include "rotate_rows.h"
+
+#include <algorithm>
 
 namespace qvggt {
 
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(256) void rotate_only_kernel(const void *__restrict
     }
 }
 
-// block-wide sum / max of one float per thread (256 threads), result in every thread; fixed order
+// block-wide sum of one float per thread (256 threads), result in every thread; fixed order
 __device__ inline float block_sum(float v, float *red)
 {
     v = sum_over_64_lanes(v);
@@ -55,174 +58,403 @@ __device__ inline float block_sum(float v, float *red)
     __syncthreads();
     return s;
 }
-__device__ inline float block_max(float v, float *red)
-{
-    v = max_over_64_lanes(v);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const float s = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    return s;
-}
 
 struct QRange {
     float lo, hi;
 };
 
-// the scaled value u = a / step (a = A / c or A * c), its code, whether it was clamped: shared by the forward and the reductions
+// the scaled value (a = A / c or A * c): shared by the quantizer and the derivatives, so that both see the same code
 __device__ inline float operand_value(float a, float c, bool divide) { return divide ? a / c : a * c; }
 
-// ---- row-wise fake quantization: hat[r, j] = step_r * clamp(round(a / step_r)); one block per row.
-// step_mode 0: dynamic, step_r = max_j |a| / hi, written to steps_out[r]; 1: steps[r]; 2: steps[0] for every row
-__global__ __launch_bounds__(256) void fake_quant_rows_kernel(const float *__restrict__ A, const float *__restrict__ c, bool divide,
-                                                              const float *__restrict__ steps, int step_mode, QRange q, int K,
-                                                              float *__restrict__ hat, float *__restrict__ steps_out)
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+
+constexpr int CT = 128;                  // rows and columns of an output tile; the operands are padded to it with zeros
+constexpr int KS1 = 64, KS2 = 32;        // contraction steps of the two GEMM kernels
+
+// ---- codes and steps of both operands.  A fake-quantized value is step * code with a code of at most 8 bits, which bf16 holds
+// exactly: the code goes to memory as bf16 (half the bytes of the fp32 product) and the step is applied to the sums.  One wave per
+// row: rows 0 .. Tp - 1 are tokens (operand R / c), then Np channels (V * c); rows and columns past the end get zeros, step 0.
+// steps[r] is the step the row was quantized with, 0 if there is none (below kMinStep): such a row has codes 0.
+__global__ __launch_bounds__(256) void calib_codes_kernel(const float *__restrict__ R, const float *__restrict__ V, const float *__restrict__ c,
+                                                          const float *__restrict__ x_step, const float *__restrict__ w_step, QRange q,
+                                                          int T, int Tp, int N, int Np, int K, int Kp, uint16_t *__restrict__ codes,
+                                                          float *__restrict__ steps)
 {
-    __shared__ float red[4];
-    const size_t row = blockIdx.x;
-    const float *a = A + row * K;
-    float step;
-    if (step_mode == 0) {
-        float m = 0.0f;
-        for (int j = threadIdx.x; j < K; j += 256) m = fmaxf(m, fabsf(operand_value(a[j], c[j], divide)));
-        m = block_max(m, red);
-        step = m >= q.hi * kMinStep ? m / q.hi : 0.0f;
-        if (threadIdx.x == 0) steps_out[row] = step;
-    } else {
-        step = steps[step_mode == 1 ? row : 0];
+    const int lane = threadIdx.x & 63;
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= Tp + Np) return;
+    const bool divide = row < Tp;
+    const int r = divide ? row : row - Tp;
+    const bool exists = r < (divide ? T : N);
+    const float *a = (divide ? R : V) + (size_t)r * K;
+    uint16_t *out = codes + (size_t)row * Kp;
+    float step = 0.0f;
+    if (exists) {
+        if (divide && x_step == nullptr) {
+            float m = 0.0f;
+#pragma unroll 4
+            for (int j = 4 * lane; j < K; j += 256) {
+                const float4 v = *reinterpret_cast<const float4 *>(a + j);
+                m = fmaxf(fmaxf(m, fabsf(operand_value(v.x, c[j], true))), fabsf(operand_value(v.y, c[j + 1], true)));
+                m = fmaxf(fmaxf(m, fabsf(operand_value(v.z, c[j + 2], true))), fabsf(operand_value(v.w, c[j + 3], true)));
+            }
+            m = max_over_64_lanes(m);
+            step = m >= q.hi * kMinStep ? m / q.hi : 0.0f;
+        } else {
+            step = divide ? x_step[0] : w_step[r];
+        }
     }
     const bool live = step >= kMinStep;
-    for (int j = threadIdx.x; j < K; j += 256) {
-        const float u = operand_value(a[j], c[j], divide) / (live ? step : 1.0f);
-        const float code = fminf(fmaxf(rintf(u), q.lo), q.hi);
-        hat[row * K + j] = live ? step * code : 0.0f;
+    if (lane == 0) steps[row] = live ? step : 0.0f;
+#pragma unroll 4
+    for (int j = 4 * lane; j < Kp; j += 256) {
+        float code[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (live && j < K) {
+            const float4 v = *reinterpret_cast<const float4 *>(a + j);
+            const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) code[i] = fminf(fmaxf(rintf(operand_value(x[i], c[j + i], divide) / step), q.lo), q.hi);
+        }
+        *reinterpret_cast<uint2 *>(out + j) = make_uint2(pack_bf16x2(code[0], code[1]), pack_bf16x2(code[2], code[3]));
     }
 }
 
-// ---- C[i, j] = sum_k A(i, k) B(k, j) in fp32, operands addressed through strides (so the same kernel serves X_hat W_hat^T,
-// E W_hat and E^T X_hat).  64 x 64 tile per block, 16-deep steps through LDS, 4 x 4 outputs per thread.
-// EPI 0: C = sum.  EPI 1: C = sum + bias[j] - ref[i, j] (the residual E), and the block's sum of squares to partial[block].
-template <int EPI>
-__global__ __launch_bounds__(256) void sgemm_kernel(const float *__restrict__ A, long long sa_i, long long sa_k,
-                                                    const float *__restrict__ B, long long sb_k, long long sb_j, int M, int N, int Kd,
-                                                    float *__restrict__ Cm, const uint16_t *__restrict__ bias,
-                                                    const float *__restrict__ ref, float *__restrict__ partial)
+// contiguous ranges of work items per XCD (blocks go round-robin over the 8 XCDs): neighbours share operand panels in one L2
+__device__ inline int xcd_item(int items)
 {
-    __shared__ float As[16][64 + 4], Bs[16][64 + 4];
-    __shared__ float red[4];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-    float acc[4][4];
+    const int per = (items + 7) >> 3;
+    return (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);      // >= items: nothing to do
+}
+
+// LDS image of an operand panel of 128 rows: rows of 2 KS bytes, the 16-byte chunks of a row rotated by an XOR so that the 16 rows of
+// a fragment read fall into 16 different bank groups
+template <int KS>
+__device__ inline int panel_offset(int row, int chunk)
+{
+    return KS == 64 ? row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4) : row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4);
+}
+
+// One staged step: acc[mi][ni] += sum over the P pieces of A and the KS contraction indices; a wave owns 64 x 64 of the 128 x 128 tile
+template <int KS, int P>
+__device__ inline void tile_step(const uint8_t *As, const uint8_t *Bs, int wm, int wn, int lane, v16f (&acc)[2][2])
+{
+    const int row = lane & 31, half = lane >> 5;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int ks = 0; ks < KS / 16; ++ks) {
+        v8bf b[2];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = 0.0f;
-    for (int k0 = 0; k0 < Kd; k0 += 16) {
-        // 64 x 16 elements of each operand: four per thread
+        for (int ni = 0; ni < 2; ++ni) b[ni] = *reinterpret_cast<const v8bf *>(Bs + panel_offset<KS>(wn * 64 + ni * 32 + row, ks * 2 + half));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = e * 256 + threadIdx.x;
-            const int ii = idx & 63, kk = idx >> 6;            // consecutive threads walk the 64 rows / columns of the tile
-            const int gi = i0 + ii, gj = j0 + ii, gk = k0 + kk;
-            As[kk][ii] = (gi < M && gk < Kd) ? A[gi * sa_i + gk * sa_k] : 0.0f;
-            Bs[kk][ii] = (gj < N && gk < Kd) ? B[gk * sb_k + gj * sb_j] : 0.0f;
-        }
-        __syncthreads();
+        for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            const float4 av = *reinterpret_cast<const float4 *>(&As[kk][ty * 4]);
-            const float4 bv = *reinterpret_cast<const float4 *>(&Bs[kk][tx * 4]);
-            const float a4[4] = {av.x, av.y, av.z, av.w}, b4[4] = {bv.x, bv.y, bv.z, bv.w};
+            for (int p = 0; p < P; ++p) {
+                const v8bf a = *reinterpret_cast<const v8bf *>(As + p * CT * KS * 2 + panel_offset<KS>(wm * 64 + mi * 32 + row, ks * 2 + half));
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) acc[a][b] = fmaf(a4[a], b4[b], acc[a][b]);
-        }
-        __syncthreads();
+                for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[ni], acc[mi][ni], 0, 0, 0);
+            }
     }
+}
+
+// row of the tile that register r of sub-tile mi holds (32x32 result layout); the column is wn * 64 + ni * 32 + lane % 32
+__device__ inline int tile_row(int wm, int mi, int r, int lane) { return wm * 64 + mi * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+
+// ---- E[t, o] = step_x[t] step_w[o] sum_j qx[t, j] qw[o, j] + b[o] - y_ref[t, o], zero in the padding, and the tile's sum of squares.
+// Products of codes are exact, so the only roundings are those of the fp32 accumulation and the epilogue.  Bound by the latency of one
+// tile's chain at the sizes of a calibration batch (264 tiles of 16 steps for 1374 x 1024 -> 3072): 26 us there, 298 us as fp32 vector
+// tiles.
+__global__ __launch_bounds__(256, 2) void calib_residual_kernel(const uint16_t *__restrict__ qx, const uint16_t *__restrict__ qw,
+                                                                const float *__restrict__ xs, const float *__restrict__ ws,
+                                                                const uint16_t *__restrict__ bias, const float *__restrict__ ref, int T, int N,
+                                                                int Kp, int tiles_m, int tiles_n, float *__restrict__ E,
+                                                                float *__restrict__ partial)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][2][CT * KS1 * 2];
+    __shared__ float red[4];
+    const int item = xcd_item(tiles_m * tiles_n);
+    if (item >= tiles_m * tiles_n) return;
+    const int tm = item % tiles_m, tn = item / tiles_m;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    // eight neighbouring lanes take the 128 bytes of a row (one cache line per row and instruction), 32 rows per pass of the block
+    const int lrow = tid >> 3, lch = tid & 7;
+    const uint16_t *pa = qx + (size_t)(tm * CT + lrow) * Kp + lch * 8, *pb = qw + (size_t)(tn * CT + lrow) * Kp + lch * 8;
+    v4u ra[4], rb[4];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ra[i] = *reinterpret_cast<const v4u *>(pa + (size_t)(32 * i) * Kp + k0);
+            rb[i] = *reinterpret_cast<const v4u *>(pb + (size_t)(32 * i) * Kp + k0);
+        }
+    };
+    v16f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    fetch(0);
+    for (int k0 = 0, buf = 0; k0 < Kp; k0 += KS1, buf ^= 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            *reinterpret_cast<v4u *>(lds[buf][0] + panel_offset<KS1>(lrow + 32 * i, lch)) = ra[i];
+            *reinterpret_cast<v4u *>(lds[buf][1] + panel_offset<KS1>(lrow + 32 * i, lch)) = rb[i];
+        }
+        fetch(min(k0 + KS1, Kp - KS1));          // the last step's is not used
+        __syncthreads();
+        tile_step<KS1, 1>(lds[buf][0], lds[buf][1], wm, wn, lane, acc);
+    }
+    const int Np = tiles_n * CT;
     float sq = 0.0f;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int mi = 0; mi < 2; ++mi) {
+        // all loads of a sub-tile row before the arithmetic, so that they are in flight together
+        float rv[2][16], st[16];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int i = i0 + ty * 4 + a, j = j0 + tx * 4 + b;
-            if (i < M && j < N) {
-                float v = acc[a][b];
-                if constexpr (EPI == 1) {
-                    if (bias != nullptr) v += bf16_bits_to_float(bias[j]);
-                    v -= ref[(size_t)i * N + j];
-                    sq = fmaf(v, v, sq);
-                }
-                Cm[(size_t)i * N + j] = v;
+        for (int r = 0; r < 16; ++r) {
+            const int t = tm * CT + tile_row(wm, mi, r, lane);
+            st[r] = xs[t];
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+                rv[ni][r] = ref[(size_t)min(t, T - 1) * N + min(tn * CT + wn * 64 + ni * 32 + (lane & 31), N - 1)];
+        }
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) {
+            const int o = tn * CT + wn * 64 + ni * 32 + (lane & 31);
+            const float so = ws[o], bo = bias != nullptr ? bf16_bits_to_float(bias[min(o, N - 1)]) : 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int t = tm * CT + tile_row(wm, mi, r, lane);
+                float v = acc[mi][ni][r] * st[r] * so;
+                if (bias != nullptr) v += bo;
+                v -= rv[ni][r];
+                v = (t < T && o < N) ? v : 0.0f;
+                sq = fmaf(v, v, sq);
+                E[(size_t)t * Np + o] = v;
             }
         }
-    if constexpr (EPI == 1) {
-        sq = block_sum(sq, red);
-        if (threadIdx.x == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = sq;
     }
+    sq = block_sum(sq, red);
+    if (tid == 0) partial[item] = sq;
 }
 
-// ---- fixed-order sum of n partials, times `scale`, to out[0] (one block)
-__global__ __launch_bounds__(256) void sum_partials_kernel(const float *__restrict__ partial, int n, float scale, float *__restrict__ out)
-{
-    __shared__ float red[4];
-    float s = 0.0f;
-    for (int i = threadIdx.x; i < n; i += 256) s += partial[i];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) out[0] = s * scale;
-}
+// ---- the two products with E and what is summed over them.
+//   GX[t, j] = sum_o (E[t, o] step_w[o]) qw[o, j],     GW[o, j] = sum_t (E[t, o] step_x[t]) qx[t, j]
+// Neither is stored: the derivatives are linear in them, so a block multiplies its piece of GX or GW (one tile, one share of the
+// contraction) by the masks and step derivatives, recomputed from R, V, c and the steps, and leaves sums over its rows and columns:
+//   dL / d c[j]       <-  sum_o GW [inside] V  +  sum_t GX [inside] (-z / c)
+//   dL / d step_w[o]  <-  sum_j GW d(hat) / d(step)          dL / d step_x  <-  sum_t,j GX d(hat) / d(step)   (static step)
+// The fp32 factor E * step is split into three bf16 numbers of 8 significant bits each, which add up to it exactly, and a code is a
+// bf16 number: three bf16 MFMAs give the products of the fp32 value and the code without rounding, at five times the rate of the
+// fp32 matrix instruction.  Measured at 1374 x 1024 -> 3072: 112 us (0.48 PFLOP/s of bf16 MFMAs; the splitting and the LDS traffic of
+// its results share the time with the MFMAs), where fp32 vector tiles that stored GX and GW took 815 us and the derivatives' own
+// passes over them 901 us.
+struct CalibPlan {
+    int Tp, Np, Kp, tm, tn, tj;         // padded sizes and their 128-tiles
+    int chunk_x, split_x;               // contraction of GX (over channels): length of a share, shares
+    int chunk_w, split_w;               // contraction of GW (over tokens)
+    int items_x, items_w;
+};
 
-// ---- per row r: scale * sum_j G[r, j] * d(hat) / d(step_r), with u = a / step_r recomputed (one block per row).
-// For the weights this is dL / d step_w[o] itself; for a static activation step the rows are summed afterwards.
-__global__ __launch_bounds__(256) void grad_step_rows_kernel(const float *__restrict__ G, const float *__restrict__ A,
-                                                             const float *__restrict__ c, bool divide, const float *__restrict__ steps,
-                                                             int step_mode, QRange q, int K, float scale, float *__restrict__ out)
+__global__ __launch_bounds__(256, 2) void calib_products_kernel(const float *__restrict__ E, const uint16_t *__restrict__ qx,
+                                                                const uint16_t *__restrict__ qw, const float *__restrict__ xs,
+                                                                const float *__restrict__ ws, const float *__restrict__ R,
+                                                                const float *__restrict__ V, const float *__restrict__ c, QRange q, int T,
+                                                                int N, int K, CalibPlan pl, bool want_step_x, float *__restrict__ part_c,
+                                                                float *__restrict__ part_w, float *__restrict__ part_x)
 {
-    __shared__ float red[4];
-    const size_t row = blockIdx.x;
-    const float step = steps[step_mode == 1 ? row : 0];
-    const bool live = step >= kMinStep;
-    float s = 0.0f;
-    if (live) {
-        for (int j = threadIdx.x; j < K; j += 256) {
-            const float u = operand_value(A[row * K + j], c[j], divide) / step;
-            const float r = rintf(u), code = fminf(fmaxf(r, q.lo), q.hi);
-            const float d = (r >= q.lo && r <= q.hi) ? code - u : code;          // clamped: the rounded code left the range
-            s = fmaf(G[row * K + j], d, s);
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][4][CT * KS2 * 2];       // three pieces of A, then B
+    __shared__ float colsum[2][CT], rowsum[2][CT], red[4];
+    int item = xcd_item(pl.items_x + pl.items_w);
+    if (item >= pl.items_x + pl.items_w) return;
+    const bool is_x = item < pl.items_x;
+    const int first = is_x ? 0 : pl.items_x;
+    item -= first;
+    const int tj = item % pl.tj, rest = item / pl.tj;
+    const int split = is_x ? pl.split_x : pl.split_w;
+    const int tm = rest / split, sp = rest % split;
+    const int len = is_x ? pl.Np : pl.Tp, chunk = is_x ? pl.chunk_x : pl.chunk_w;
+    const int kb = sp * chunk, ke = min(kb + chunk, len);
+    const uint16_t *qb = (is_x ? qw : qx) + tj * CT;
+    const float *ks = is_x ? ws : xs;                       // step that goes with the contraction index
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+
+    float fa[16];                                           // A values of this thread, then their steps applied
+    uint32_t rb[8];                                         // B: codes of columns 2 lane, 2 lane + 1 at eight contraction indices
+    auto fetch = [&](int k0) {
+        if (is_x) {                                         // rows are tokens: four channels of rows tid / 8 + 32 i (a line per row)
+            const float *e = E + (size_t)(tm * CT + (tid >> 3)) * pl.Np + k0 + (tid & 7) * 4;
+            const float4 w = *reinterpret_cast<const float4 *>(ks + k0 + (tid & 7) * 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 v = *reinterpret_cast<const float4 *>(e + (size_t)(32 * i) * pl.Np);
+                fa[4 * i] = v.x * w.x; fa[4 * i + 1] = v.y * w.y; fa[4 * i + 2] = v.z * w.z; fa[4 * i + 3] = v.w * w.w;
+            }
+        } else {                                            // rows are channels 2 lane, 2 lane + 1: eight consecutive tokens of each
+            const float *e = E + (size_t)(k0 + wave * 8) * pl.Np + tm * CT + 2 * lane;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float2 v = *reinterpret_cast<const float2 *>(e + (size_t)i * pl.Np);
+                const float s = ks[k0 + wave * 8 + i];
+                fa[i] = v.x * s; fa[8 + i] = v.y * s;
+            }
+        }
+        const uint16_t *b = qb + (size_t)(k0 + wave * 8) * pl.Kp + 2 * lane;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rb[i] = *reinterpret_cast<const uint32_t *>(b + (size_t)i * pl.Kp);
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {                       // eight values: four of rows 2 h, 2 h + 1 of this thread, or a chunk of row 2 lane + h
+            uint32_t w[3][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t hi[2], mid[2], low[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float f = fa[8 * h + 2 * i + e];
+                    hi[e] = __float_as_uint(f);
+                    float rem = f - __uint_as_float(hi[e] & 0xFFFF0000u);
+                    rem = rem == rem ? rem : 0.0f;          // an infinite f is its own first piece
+                    mid[e] = __float_as_uint(rem);
+                    low[e] = __float_as_uint(rem - __uint_as_float(mid[e] & 0xFFFF0000u));
+                }
+                w[0][i] = __builtin_amdgcn_perm(hi[1], hi[0], 0x07060302);
+                w[1][i] = __builtin_amdgcn_perm(mid[1], mid[0], 0x07060302);
+                w[2][i] = __builtin_amdgcn_perm(low[1], low[0], 0x07060302);
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                if (is_x) {
+                    const int row = (tid >> 3) + 64 * h, ch = (tid & 7) >> 1, half = (tid & 1) * 8;
+                    *reinterpret_cast<uint2 *>(lds[buf][p] + panel_offset<KS2>(row, ch) + half) = make_uint2(w[p][0], w[p][1]);
+                    *reinterpret_cast<uint2 *>(lds[buf][p] + panel_offset<KS2>(row + 32, ch) + half) = make_uint2(w[p][2], w[p][3]);
+                } else {
+                    *reinterpret_cast<uint4 *>(lds[buf][p] + panel_offset<KS2>(2 * lane + h, wave)) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+                }
+            }
+            uint32_t b[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[i] = __builtin_amdgcn_perm(rb[2 * i + 1], rb[2 * i], h == 0 ? 0x05040100 : 0x07060302);
+            *reinterpret_cast<uint4 *>(lds[buf][3] + panel_offset<KS2>(2 * lane + h, wave)) = make_uint4(b[0], b[1], b[2], b[3]);
+        }
+    };
+    v16f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    fetch(kb);
+    for (int k0 = kb, buf = 0; k0 < ke; k0 += KS2, buf ^= 1) {
+        stage(buf);
+        fetch(min(k0 + KS2, ke - KS2));          // the last step's is not used
+        __syncthreads();
+        tile_step<KS2, 3>(lds[buf][0], lds[buf][3], wm, wn, lane, acc);
+    }
+
+    // sums over the tile's columns (dL / dc) and rows (dL / d step)
+    const int rows = is_x ? T : N;
+    const float *A = is_x ? R : V, *steps = is_x ? xs : ws;
+    float col[2] = {0.0f, 0.0f}, rowv[2][16], all = 0.0f;
+    float cj[2];
+    int col_j[2];
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) {
+        col_j[ni] = min(tj * CT + wn * 64 + ni * 32 + (lane & 31), K - 1);      // columns past K: discarded by whoever adds the parts
+        cj[ni] = c[col_j[ni]];
+    }
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+        float av[2][16], st[16];                            // loads first: in flight together
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int m = tm * CT + tile_row(wm, mi, r, lane);
+            st[r] = steps[m];                               // 0 in the padding
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) av[ni][r] = A[(size_t)min(m, rows - 1) * K + col_j[ni]];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const bool live = st[r] >= kMinStep;
+            float s = 0.0f;
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) {
+                const float a = av[ni][r], g = acc[mi][ni][r];
+                const float z = operand_value(a, cj[ni], is_x), u = z / st[r], code = rintf(u);
+                const bool inside = code >= q.lo && code <= q.hi;
+                const float dz = is_x ? -z / cj[ni] : a;
+                col[ni] = (live && inside) ? fmaf(g, dz, col[ni]) : col[ni];
+                const float d = inside ? code - u : fminf(fmaxf(code, q.lo), q.hi);     // clamped: the rounded code left the range
+                s = live && tj * CT + wn * 64 + ni * 32 + (lane & 31) < K ? fmaf(g, d, s) : s;
+            }
+            rowv[mi][r] = s;
         }
     }
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) out[row] = s * scale;
-}
-
-// ---- dL / d c_hat[j] = scale * ( sum_o GW[o, j] [inside] V[o, j]  +  sum_t GX[t, j] [inside] (-z[t, j] / c_j) ).
-// A block owns 64 columns; its 4 row groups walk the rows in a fixed order and are folded in a fixed order.
-__global__ __launch_bounds__(256) void grad_c_kernel(const float *__restrict__ GW, const float *__restrict__ V, const float *__restrict__ w_step,
-                                                     int N, const float *__restrict__ GX, const float *__restrict__ R,
-                                                     const float *__restrict__ x_steps, int x_step_mode, int T, const float *__restrict__ c,
-                                                     QRange q, int K, float scale, float *__restrict__ grad_c)
-{
-    __shared__ float red[4][64];
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63), grp = threadIdx.x >> 6;
-    float s = 0.0f;
-    if (col < K) {
-        const float cj = c[col];
-        for (int o = grp; o < N; o += 4) {
-            const float step = w_step[o];
-            if (step < kMinStep) continue;
-            const float v = V[(size_t)o * K + col], r = rintf(v * cj / step);
-            if (r >= q.lo && r <= q.hi) s = fmaf(GW[(size_t)o * K + col], v, s);
-        }
-        for (int t = grp; t < T; t += 4) {
-            const float step = x_steps[x_step_mode == 2 ? 0 : t];
-            if (step < kMinStep) continue;
-            const float z = R[(size_t)t * K + col] / cj, r = rintf(z / step);
-            if (r >= q.lo && r <= q.hi) s = fmaf(GX[(size_t)t * K + col], -z / cj, s);
-        }
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) {
+        col[ni] += __shfl_xor(col[ni], 32);
+        if (lane < 32) colsum[wm][wn * 64 + ni * 32 + lane] = col[ni];
     }
-    red[grp][threadIdx.x & 63] = s;
+    if (!is_x) {
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float v = rowv[mi][r];
+                v = dpp_add_step<0xB1>(v); v = dpp_add_step<0x4E>(v); v = dpp_add_step<0x141>(v); v = dpp_add_step<0x140>(v);
+                v += __shfl_xor(v, 16);
+                if ((lane & 31) == 0) rowsum[wn][tile_row(wm, mi, r, lane)] = v;
+            }
+    } else if (want_step_x) {
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) all += rowv[mi][r];
+    }
     __syncthreads();
-    if (grp == 0 && col < K) grad_c[col] = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x])) * scale;
+    const int part = (is_x ? 0 : pl.tm * pl.split_x) + rest;
+    if (tid < CT) {
+        part_c[(size_t)part * pl.Kp + tj * CT + tid] = colsum[0][tid] + colsum[1][tid];
+        if (!is_x) part_w[(size_t)(tj * split + sp) * pl.Np + tm * CT + tid] = rowsum[0][tid] + rowsum[1][tid];
+    }
+    if (is_x && want_step_x) {
+        all = block_sum(all, red);
+        if (tid == 0) part_x[item] = all;
+    }
+}
+
+// ---- the partial sums of all blocks, added in a fixed order and in double: 16 columns of grad_c per block, then 16 channels of
+// grad_w per block (16 groups of threads share the parts), then one block each for the loss and the derivative of a static step
+__global__ __launch_bounds__(256) void calib_sums_kernel(const float *__restrict__ part_c, const float *__restrict__ part_w,
+                                                         const float *__restrict__ part_x, const float *__restrict__ part_loss, int N, int K,
+                                                         CalibPlan pl, float scale, float loss_scale, float *__restrict__ grad_c,
+                                                         float *__restrict__ grad_w, float *__restrict__ grad_x, float *__restrict__ loss)
+{
+    __shared__ double red[256];
+    const int tid = threadIdx.x, blocks_c = (K + 15) / 16, blocks_w = (N + 15) / 16;
+    const int b = blockIdx.x;
+    const bool vec = b < blocks_c + blocks_w, is_c = b < blocks_c, is_loss = b == blocks_c + blocks_w;
+    const int col = vec ? (is_c ? b : b - blocks_c) * 16 + (tid & 15) : 0;
+    const float *part = vec ? (is_c ? part_c : part_w) + col : is_loss ? part_loss : part_x;
+    const size_t pitch = vec ? (is_c ? pl.Kp : pl.Np) : 1;
+    const int n = vec ? (is_c ? pl.tm * pl.split_x + pl.tn * pl.split_w : pl.tj * pl.split_w) : (is_loss ? pl.tm * pl.tn : pl.items_x);
+    double s = 0.0;
+#pragma unroll 8
+    for (int p = vec ? tid >> 4 : tid; p < n; p += vec ? 16 : 256) s += (double)part[p * pitch];
+    red[tid] = s;
+    __syncthreads();
+    for (int h = 128; h >= (vec ? 16 : 1); h >>= 1) {
+        if (tid < h) red[tid] += red[tid + h];
+        __syncthreads();
+    }
+    if (vec) {
+        if (tid < 16 && col < (is_c ? K : N)) (is_c ? grad_c : grad_w)[col] = (float)(red[tid] * (double)scale);
+    } else if (tid == 0) {
+        (is_loss ? loss : grad_x)[0] = (float)(red[0] * (double)(is_loss ? loss_scale : scale));
+    }
 }
 
 __global__ void descent_step_kernel(float *__restrict__ theta, const float *__restrict__ grad, int n, float lr, float floor_)
@@ -252,48 +484,72 @@ hipError_t run_rotate_only(const void *X, bool f32, int rows, int K, const int8_
     return hipGetLastError();
 }
 
-// workspace: x_hat [T, K], w_hat [N, K], E [T, N], GX [T, K], GW [N, K], dynamic steps [T], partial sums
+// Shares of the two contractions.  A block's work is one 128 x 128 tile over one share; 512 blocks are resident (two per compute unit),
+// and since the results are linear in the products a contraction may be cut anywhere.  Of the share lengths that are multiples of
+// 128 the one with the least (rounds of 512 blocks) x (length + the 96 steps' worth that a tile's epilogue takes) is used.
+static CalibPlan calib_plan(int T, int N, int K)
+{
+    CalibPlan p;
+    auto up = [](int v) { return (v + CT - 1) / CT * CT; };
+    p.Tp = up(T); p.Np = up(N); p.Kp = up(K);
+    p.tm = p.Tp / CT; p.tn = p.Np / CT; p.tj = p.Kp / CT;
+    long long best = -1;
+    int best_len = CT;
+    const int longest = std::max(p.Tp, p.Np);
+    for (int len = CT; len <= longest && len <= 64 * CT; len += CT) {
+        const long long blocks = (long long)p.tm * p.tj * ((p.Np + len - 1) / len) + (long long)p.tn * p.tj * ((p.Tp + len - 1) / len);
+        const long long cost = (blocks + 511) / 512 * (len + 96);
+        if (best < 0 || cost < best) { best = cost; best_len = len; }
+    }
+    auto shares = [&](int total, int &chunk, int &split) {
+        split = (total + best_len - 1) / best_len;
+        chunk = ((total + split - 1) / split + KS2 - 1) / KS2 * KS2;
+        split = (total + chunk - 1) / chunk;
+    };
+    shares(p.Np, p.chunk_x, p.split_x);
+    shares(p.Tp, p.chunk_w, p.split_w);
+    p.items_x = p.tm * p.tj * p.split_x;
+    p.items_w = p.tn * p.tj * p.split_w;
+    return p;
+}
+
+// workspace: codes of both operands [Tp + Np, Kp] bf16, their steps [Tp + Np], E [Tp, Np], partial sums
 size_t calib_workspace_bytes(int T, int N, int K)
 {
-    const size_t tk = align256((size_t)T * K * 4), nk = align256((size_t)N * K * 4), tn = align256((size_t)T * N * 4);
-    const size_t tiles = (size_t)((T + 63) / 64) * ((N + 63) / 64);
-    return 2 * tk + 2 * nk + tn + align256((size_t)T * 4) + align256(std::max<size_t>(tiles, (size_t)T) * 4);
+    const CalibPlan p = calib_plan(T, N, K);
+    return align256((size_t)(p.Tp + p.Np) * p.Kp * 2) + align256((size_t)(p.Tp + p.Np) * 4) + align256((size_t)p.Tp * p.Np * 4) +
+           align256(((size_t)p.tm * p.split_x + (size_t)p.tn * p.split_w) * p.Kp * 4) + align256((size_t)p.tj * p.split_w * p.Np * 4) +
+           align256((size_t)p.items_x * 4) + align256((size_t)p.tm * p.tn * 4);
 }
 
 hipError_t run_calib_loss_grad(const float *R, const float *V, const float *y_ref, const void *bias, const float *c_hat,
                                const float *w_step, const float *x_step, int T, int N, int K, int bits, float *loss, float *grad_c,
                                float *grad_w_step, float *grad_x_step, void *workspace, hipStream_t stream)
 {
-    const size_t tk = align256((size_t)T * K * 4), nk = align256((size_t)N * K * 4), tn = align256((size_t)T * N * 4);
+    const CalibPlan pl = calib_plan(T, N, K);
     uint8_t *p = static_cast<uint8_t *>(workspace);
-    float *x_hat = reinterpret_cast<float *>(p); p += tk;
-    float *w_hat = reinterpret_cast<float *>(p); p += nk;
-    float *E = reinterpret_cast<float *>(p); p += tn;
-    float *GX = reinterpret_cast<float *>(p); p += tk;
-    float *GW = reinterpret_cast<float *>(p); p += nk;
-    float *dyn_steps = reinterpret_cast<float *>(p); p += align256((size_t)T * 4);
-    float *partial = reinterpret_cast<float *>(p);
+    auto take = [&](size_t bytes) { uint8_t *r = p; p += align256(bytes); return r; };
+    uint16_t *codes = reinterpret_cast<uint16_t *>(take((size_t)(pl.Tp + pl.Np) * pl.Kp * 2));
+    float *steps = reinterpret_cast<float *>(take((size_t)(pl.Tp + pl.Np) * 4));
+    float *E = reinterpret_cast<float *>(take((size_t)pl.Tp * pl.Np * 4));
+    float *part_c = reinterpret_cast<float *>(take(((size_t)pl.tm * pl.split_x + (size_t)pl.tn * pl.split_w) * pl.Kp * 4));
+    float *part_w = reinterpret_cast<float *>(take((size_t)pl.tj * pl.split_w * pl.Np * 4));
+    float *part_x = reinterpret_cast<float *>(take((size_t)pl.items_x * 4));
+    float *part_loss = reinterpret_cast<float *>(take((size_t)pl.tm * pl.tn * 4));
+    const uint16_t *qx = codes, *qw = codes + (size_t)pl.Tp * pl.Kp;
+    const float *xs = steps, *ws = steps + pl.Tp;
     const QRange q{-(float)(1 << (bits - 1)), (float)((1 << (bits - 1)) - 1)};
-    const int x_mode = x_step ? 2 : 0;
-    const float *x_steps = x_step ? x_step : dyn_steps;
-    const float scale = 2.0f / (float)T;                 // dL / dy_q = (2 / T) E: folded into the last reductions
+    const float scale = 2.0f / (float)T;                 // dL / dy_q = (2 / T) E: folded into the last sums
+    auto grid8 = [](int items) { return (unsigned)((items + 7) / 8 * 8); };
 
-    fake_quant_rows_kernel<<<T, 256, 0, stream>>>(R, c_hat, true, x_step, x_mode, q, K, x_hat, dyn_steps);
-    fake_quant_rows_kernel<<<N, 256, 0, stream>>>(V, c_hat, false, w_step, 1, q, K, w_hat, nullptr);
-    // E = x_hat . w_hat^T + b - y_ref, and the loss
-    const dim3 g_tn((N + 63) / 64, (T + 63) / 64);
-    sgemm_kernel<1><<<g_tn, 256, 0, stream>>>(x_hat, K, 1, w_hat, 1, K, T, N, K, E, reinterpret_cast<const uint16_t *>(bias), y_ref, partial);
-    sum_partials_kernel<<<1, 256, 0, stream>>>(partial, (int)(g_tn.x * g_tn.y), 1.0f / (float)T, loss);
-    // GX = E . w_hat  [T, K];  GW = E^T . x_hat  [N, K]
-    const dim3 g_tk((K + 63) / 64, (T + 63) / 64), g_nk((K + 63) / 64, (N + 63) / 64);
-    sgemm_kernel<0><<<g_tk, 256, 0, stream>>>(E, N, 1, w_hat, K, 1, T, K, N, GX, nullptr, nullptr, nullptr);
-    sgemm_kernel<0><<<g_nk, 256, 0, stream>>>(E, 1, N, x_hat, K, 1, N, K, T, GW, nullptr, nullptr, nullptr);
-    grad_step_rows_kernel<<<N, 256, 0, stream>>>(GW, V, c_hat, false, w_step, 1, q, K, scale, grad_w_step);
-    if (x_step != nullptr && grad_x_step != nullptr) {
-        grad_step_rows_kernel<<<T, 256, 0, stream>>>(GX, R, c_hat, true, x_step, 2, q, K, 1.0f, partial);
-        sum_partials_kernel<<<1, 256, 0, stream>>>(partial, T, scale, grad_x_step);
-    }
-    grad_c_kernel<<<(K + 63) / 64, 256, 0, stream>>>(GW, V, w_step, N, GX, R, x_steps, x_mode, T, c_hat, q, K, scale, grad_c);
+    calib_codes_kernel<<<(pl.Tp + pl.Np) / 4, 256, 0, stream>>>(R, V, c_hat, x_step, w_step, q, T, pl.Tp, N, pl.Np, K, pl.Kp, codes, steps);
+    calib_residual_kernel<<<grid8(pl.tm * pl.tn), 256, 0, stream>>>(qx, qw, xs, ws, reinterpret_cast<const uint16_t *>(bias), y_ref, T, N, pl.Kp,
+                                                                   pl.tm, pl.tn, E, part_loss);
+    const bool static_step = x_step != nullptr;
+    calib_products_kernel<<<grid8(pl.items_x + pl.items_w), 256, 0, stream>>>(E, qx, qw, xs, ws, R, V, c_hat, q, T, N, K, pl, static_step, part_c,
+                                                                             part_w, part_x);
+    calib_sums_kernel<<<(K + 15) / 16 + (N + 15) / 16 + 1 + static_step, 256, 0, stream>>>(part_c, part_w, part_x, part_loss, N, K, pl, scale,
+                                                                                             1.0f / (float)T, grad_c, grad_w_step, grad_x_step, loss);
     return hipGetLastError();
 }
 

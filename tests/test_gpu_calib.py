@@ -145,3 +145,46 @@ def test_descent_step_floor_and_errors():
     g = torch.tensor([10.0, 1.0, -2.0], dtype=torch.float32, device=G.DEV)
     q.qvggt_calib_descent_step(th, g, calib.LR_STEP)
     assert np.allclose(th.cpu().numpy(), calib.descent_step([1.0, 1e-9, 0.5], [10.0, 1.0, -2.0], calib.LR_STEP), rtol=1e-6)
+
+
+@pytest.mark.parametrize("T,N,K,bits,static", [(1, 1, 4, 4, False), (128, 128, 128, 8, True), (129, 127, 132, 4, True), (300, 260, 1028, 6, False),
+                                               (127, 385, 8192, 8, False)])
+def test_loss_and_derivatives_at_tile_edges(T, N, K, bits, static):
+    """Sizes around the 128-wide tiles and the shares of the contractions, K not a Hadamard size (the entry point takes rotated operands),
+    against the same formulas in float64 on the codes that fp32 gives.  Products of codes are exact and an fp32 factor is split
+    exactly, so what differs is fp32 accumulation: n terms of mixed signs, about sqrt(n) 2^-24 of their 2-norm, < 1e-5 for n <= 2^14;
+    a derivative whose terms nearly cancel loses up to another factor of ten."""
+    g = torch.Generator().manual_seed(T + N + K)
+    R, V = torch.randn(T, K, generator=g), torch.randn(N, K, generator=g) * 0.02
+    bias = (torch.randn(N, generator=g) * 0.02).to(torch.bfloat16)
+    ref = R @ V.t() + 0.02 * torch.randn(T, N, generator=g)
+    hi, lo = float(2 ** (bits - 1) - 1), -float(2 ** (bits - 1))
+    c = torch.rand(K, generator=g) + 0.5
+    w_step = (V * c).abs().amax(1) / hi * 0.8
+    x_step = ((R / c).abs().amax() / hi * 0.6).reshape(1) if static else None
+    dev = [t.to(G.DEV) if t is not None else None for t in (R, V, ref, bias, c, w_step, x_step)]
+    loss, gc, gw = (torch.full((n,), float("nan"), device=G.DEV) for n in (1, K, N))
+    gx = torch.full((1,), float("nan"), device=G.DEV) if static else None
+    ws = torch.empty(q.qvggt_calib_workspace_bytes(T, N, K), dtype=torch.uint8, device=G.DEV)
+    q.qvggt_calib_loss_grad(*dev, bits, loss, gc, gw, gx, ws)
+    # codes and masks from fp32, as the library defines them; everything after that in float64
+    z, v = R / c, V * c
+    sx = x_step.expand(T)[:, None] if static else (z.abs().amax(1) / hi)[:, None]
+    ux, uw, sw = z / sx, v / w_step[:, None], w_step[:, None]
+    rx, rw = torch.round(ux).double(), torch.round(uw).double()
+    inx, inw = (rx >= lo) & (rx <= hi), (rw >= lo) & (rw <= hi)
+    qx, qw = rx.clamp(lo, hi), rw.clamp(lo, hi)
+    X, W = qx * sx.double(), qw * sw.double()
+    E = X @ W.t() + bias.double() - ref.double()
+    GX, GW = E @ W, E.t() @ X
+    cd = c.double()
+    want = [(E * E).sum().reshape(1) / T,
+            2 / T * ((GW * inw * V.double()).sum(0) - (GX * inx * (R.double() / cd / cd)).sum(0)),
+            2 / T * (GW * torch.where(inw, qw - V.double() * cd / sw.double(), qw)).sum(1)]
+    got = [loss, gc, gw]
+    if static:
+        want.append((2 / T * (GX * torch.where(inx, qx - R.double() / cd / sx.double(), qx)).sum()).reshape(1))
+        got.append(gx)
+    errs = [_rel(a.cpu().numpy(), b.numpy()) for a, b in zip(got, want)]
+    G.report("calib_tile_edges", T=T, N=N, K=K, bits=bits, static=static, errs=errs)
+    assert max(errs) <= 1e-4, errs
