@@ -38,6 +38,23 @@ def test_moments(rows, count, dtype):
         assert var[r].item() == pytest.approx(s, rel=RTOL), (r, "var")
 
 
+@pytest.mark.parametrize("blocks", [1, 63, 64, 65, 130])
+def test_reductions_at_wave_edges(blocks):
+    """A row split over `blocks` blocks (1024 16-byte vectors each): the wave that adds their partial sums at 1, 63 .. 65 and 130 of them.
+    Sums in double, one rounding to float: RTOL as above."""
+    count, rows = blocks * 1024 * 8, 3
+    x = np.random.default_rng(blocks).standard_normal((rows, count)).astype(np.float32) + 0.5
+    X = synth.f32_to_bf16_bits(x)
+    Xd, Xo = G.to_dev(X), oracle.to_f64(X)
+    mean, var = (torch.empty(rows, dtype=torch.float32, device=G.DEV) for _ in range(2))
+    q.qvggt_nfds_moments(Xd, mean, var, _ws(rows, count, Xd))
+    corr = torch.empty(1, rows - 1, dtype=torch.float32, device=G.DEV)
+    q.qvggt_nfds_frame_correlation(Xd.view(1, rows, count), corr, _ws(rows, count, Xd))
+    norm = np.linalg.norm(Xo, axis=1)
+    assert np.allclose(mean.cpu().numpy(), Xo.mean(1), rtol=RTOL) and np.allclose(var.cpu().numpy(), Xo.var(1), rtol=RTOL)
+    assert np.allclose(corr.cpu().numpy()[0], [Xo[0] @ Xo[t] / (norm[0] * norm[t]) for t in (1, 2)], rtol=RTOL)
+
+
 def test_moments_large_mean_small_spread():
     """E[x^2] - E[x]^2 in double: a mean 1e3 times the standard deviation must not hurt the variance."""
     rng = np.random.default_rng(5)
