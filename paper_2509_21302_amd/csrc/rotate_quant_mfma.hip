@@ -68,20 +68,27 @@ __device__ inline uint32_t gelu_window(uint32_t w)      // both halves of a pack
     const us2 d = a - u0;
     return *reinterpret_cast<const uint32_t *>(&d);
 }
-// both halves covered by the table (the usual case): two lookups.  Inside the window bits 12..14 of a half are zero, so twice the
-// entry number, the byte offset into the table, is (low 12 bits) << 1 | (bit 15) >> 2, formed for both halves at once (what the
-// shifts carry across the middle is masked out)
-__device__ inline uint32_t gelu_pair_table(uint32_t d, const uint16_t *lut)
+// Where the table lies in LDS: negative inputs' half at GELU_NEG, positive inputs' half 64 KiB above it.  Twice a bf16 pattern read as a
+// signed 16-bit number steps through each half in bytes and jumps by 64 KiB at the sign, so the byte offset of either half of a
+// packed pair is ONE instruction, 2 * signed half + constant.  (With the halves next to each other the offset took five shifts and
+// masks per pair and two more to take it apart; the waves' staging areas fill the gap.)  The lookups themselves, 64 per lane and tile,
+// are bound by LDS bank conflicts: 32976 x 4096 takes 75 us on one repeated value, 104 us on N(0, 0.64) (88 and 105 us before).
+constexpr int GELU_HALF_BYTES = 2 * 4096, GELU_NEG = 0, GELU_POS = 65536, GELU_LDS_BYTES = GELU_POS + GELU_HALF_BYTES;
+constexpr int GELU_OFFSET = GELU_POS - 2 * (int)GELU_U0;
+// both halves covered by the table (the usual case): two lookups
+__device__ inline uint32_t gelu_pair_table(uint32_t w, const uint8_t *table)
 {
-    const uint32_t off = ((d << 1) & 0x1FFE1FFEu) | ((d >> 2) & 0x20002000u);
-    const uint8_t *t = reinterpret_cast<const uint8_t *>(lut);
-    return (uint32_t) * reinterpret_cast<const uint16_t *>(t + (off & 0xFFFFu)) | ((uint32_t) * reinterpret_cast<const uint16_t *>(t + (off >> 16)) << 16);
+    int lo, hi;
+    asm("v_mad_i32_i16 %0, %1, 2, %2" : "=v"(lo) : "v"(w), "s"(GELU_OFFSET));
+    asm("v_mad_i32_i16 %0, %1, 2, %2 op_sel:[1,0,0,0]" : "=v"(hi) : "v"(w), "s"(GELU_OFFSET));
+    return (uint32_t) * reinterpret_cast<const uint16_t *>(table + lo) | ((uint32_t) * reinterpret_cast<const uint16_t *>(table + hi) << 16);
 }
 // any finite value
-__device__ inline uint32_t gelu_one_any(uint32_t bits, const uint16_t *lut)
+__device__ inline uint32_t gelu_one_any(uint32_t bits, const uint8_t *table)
 {
     const uint32_t d = (bits - GELU_U0) & 0xFFFFu;
-    if ((d & 0x7FFFu) < 0x1000u) return lut[(d & 0x0FFFu) | ((d >> 3) & 0x1000u)];
+    if ((d & 0x7FFFu) < 0x1000u)
+        return *reinterpret_cast<const uint16_t *>(table + ((bits & 0x8000u) ? GELU_NEG : GELU_POS) + 2 * (d & 0x0FFFu));
     if ((bits & 0x7FFFu) < GELU_U0) {                                   // tiny: x / 2, rounded as a bf16 store would (subnormals included)
         const uint32_t p = pack_bf16x2(0.5f * __uint_as_float(bits << 16), 0.0f);
         return p & 0xFFFFu;
@@ -138,12 +145,26 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
     // representable), and zero[row] receives what the GEMM's correction term needs (8 for a static step: 7.5 - 8 = -0.5)
     using C = rq::Cfg<K>;
     constexpr int REM = C::REM, TOK = C::TOK;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[rq::WAVES_PER_BLOCK * rq::LDS_PER_WAVE];
-
-    __shared__ __attribute__((aligned(16))) uint16_t gelu_lut[GELU ? rq::GELU_TABLE_ENTRIES : 8];
+    // E2M3 output at K = 4096: a token's 64 units lie 6 KiB apart in the output, 48 bytes each; the four waves of a block take
+    // four consecutive tokens and flush them together through LDS, so that memory sees runs of 192 bytes per unit (48-byte
+    // pieces cost 190 us more at 137400 tokens).  The block then iterates as one: same trip count, barriers inside the loop.
+    static_assert(!BLK8 || CB == 8, "int8 blocks hold int8 codes");
+    constexpr bool BLOCK_FLUSH = ((CB == 6 || BLK8) && REM == 5);
+    // a unit's (K-tile's) four pieces start FLUSH_PITCH apart: one 16-byte bank group more than they fill, so that the lanes of a
+    // write (consecutive units) and of a read spread over the banks
+    constexpr int FLUSH_PITCH = (BLK8 ? 256 : 192) + 16;
+    // LDS: the waves' staging rows, then the flush area; with the activation table, both inside the table's gap
+    constexpr int STAGE0 = GELU ? rq::GELU_HALF_BYTES : 0, STAGE_ALL = rq::WAVES_PER_BLOCK * rq::LDS_PER_WAVE;
+    constexpr int FLUSH0 = STAGE0 + STAGE_ALL, LDS_END = FLUSH0 + (BLOCK_FLUSH ? 64 * FLUSH_PITCH : 0);
+    static_assert(!GELU || LDS_END <= rq::GELU_POS, "staging and flush areas fit between the halves of the table");
+    __shared__ __attribute__((aligned(16))) uint8_t smem[GELU ? rq::GELU_LDS_BYTES : LDS_END];
+    uint8_t *const lds_all = smem + STAGE0, *const flush_all = smem + FLUSH0;
     if constexpr (GELU) {
-        for (int i = threadIdx.x; i < rq::GELU_TABLE_ENTRIES / 8; i += 256)
-            reinterpret_cast<uint4 *>(gelu_lut)[i] = reinterpret_cast<const uint4 *>(gelu_table)[i];
+        for (int i = threadIdx.x; i < rq::GELU_TABLE_ENTRIES / 8; i += 256) {        // 16 bytes each; positive inputs' entries come first
+            constexpr int HALF = rq::GELU_HALF_BYTES / 16;
+            *reinterpret_cast<uint4 *>(smem + (i < HALF ? rq::GELU_POS + 16 * i : rq::GELU_NEG + 16 * (i - HALF))) =
+                reinterpret_cast<const uint4 *>(gelu_table)[i];
+        }
         __syncthreads();
     }
 
@@ -267,15 +288,6 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
             for (int j = 0; j < 8; ++j) dst[j] = load16(tile_ptr(t, j));
         }
     };
-    // E2M3 output at K = 4096: a token's 64 units lie 6 KiB apart in the output, 48 bytes each; the four waves of a block take
-    // four consecutive tokens and flush them together through LDS, so that memory sees runs of 192 bytes per unit (48-byte
-    // pieces cost 190 us more at 137400 tokens).  The block then iterates as one: same trip count, barriers inside the loop.
-    static_assert(!BLK8 || CB == 8, "int8 blocks hold int8 codes");
-    constexpr bool BLOCK_FLUSH = ((CB == 6 || BLK8) && REM == 5);
-    // a unit's (K-tile's) four pieces start FLUSH_PITCH apart: one 16-byte bank group more than they fill, so that the lanes of a
-    // write (consecutive units) and of a read spread over the banks
-    constexpr int FLUSH_PITCH = (BLK8 ? 256 : 192) + 16;
-    __shared__ __attribute__((aligned(16))) uint8_t flush_all[BLOCK_FLUSH ? 64 * FLUSH_PITCH : 16];
     uint4 G[PF][8];
     int tile = wave;
 #pragma unroll
@@ -297,30 +309,30 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
 
     for (; (BLOCK_FLUSH ? tile - wave_in_block : tile) < ntiles; tile += nwaves) {
         if constexpr (GELU) {
+            // the lookups first: a wave in them waits on the LDS and leaves the vector ALU to the other wave of its SIMD
+            __builtin_amdgcn_s_setprio(3);
             // one wave-uniform test per tile: is every value inside the table's window?  (Almost always: outside are exact
             // zeros, |x| < 1e-6 and |x| >= 4096.)  Then two lookups per packed pair; otherwise the general form per value.
             // (a half is inside iff bits 12..14 of its offset from the window's start are zero: OR them all and look once)
-            uint32_t D[8][4], any = 0;
+            uint32_t any = 0;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                D[j][0] = rq::gelu_window(G[0][j].x); D[j][1] = rq::gelu_window(G[0][j].y);
-                D[j][2] = rq::gelu_window(G[0][j].z); D[j][3] = rq::gelu_window(G[0][j].w);
-                any = any | D[j][0] | D[j][1];
-                any = any | D[j][2] | D[j][3];
+                any = any | rq::gelu_window(G[0][j].x) | rq::gelu_window(G[0][j].y);
+                any = any | rq::gelu_window(G[0][j].z) | rq::gelu_window(G[0][j].w);
             }
             const bool outside = (any & 0x70007000u) != 0u;
             if (__builtin_amdgcn_ballot_w64(outside) == 0) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    G[0][j] = make_uint4(rq::gelu_pair_table(D[j][0], gelu_lut), rq::gelu_pair_table(D[j][1], gelu_lut),
-                                         rq::gelu_pair_table(D[j][2], gelu_lut), rq::gelu_pair_table(D[j][3], gelu_lut));
+                    G[0][j] = make_uint4(rq::gelu_pair_table(G[0][j].x, smem), rq::gelu_pair_table(G[0][j].y, smem),
+                                         rq::gelu_pair_table(G[0][j].z, smem), rq::gelu_pair_table(G[0][j].w, smem));
             } else {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     uint32_t w[4] = {G[0][j].x, G[0][j].y, G[0][j].z, G[0][j].w};
 #pragma unroll
                     for (int d = 0; d < 4; ++d)
-                        w[d] = rq::gelu_one_any(w[d] & 0xFFFFu, gelu_lut) | (rq::gelu_one_any(w[d] >> 16, gelu_lut) << 16);
+                        w[d] = rq::gelu_one_any(w[d] & 0xFFFFu, smem) | (rq::gelu_one_any(w[d] >> 16, smem) << 16);
                     G[0][j] = make_uint4(w[0], w[1], w[2], w[3]);
                 }
             }
@@ -370,6 +382,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
             const int row_hi = rq::row_of_seg_hi<K>(j);
             *reinterpret_cast<uint4 *>(lds + row_hi * rq::LDS_PITCH + wr_base) = v;
         }
+        if constexpr (GELU) __builtin_amdgcn_s_setprio(0);
         lanes_exchange_fence();     // the MFMA operand reads below take what other lanes staged
         // shift the prefetch queue and issue the loads of the tile PF steps ahead
 #pragma unroll
@@ -663,7 +676,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
         // the block's waves fold their maxima in LDS (non-negative floats order like their bit patterns), then every column
         // costs one global atomic per block
         unsigned int *blk = reinterpret_cast<unsigned int *>(lds_all);
-        static_assert(sizeof(lds_all) >= K * sizeof(unsigned int), "the staging area holds one value per column");
+        static_assert(STAGE_ALL >= K * (int)sizeof(unsigned int), "the staging area holds one value per column");
         __syncthreads();
         for (int j = threadIdx.x; j < K; j += 256) blk[j] = 0u;
         __syncthreads();
