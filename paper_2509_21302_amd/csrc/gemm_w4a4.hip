@@ -41,7 +41,7 @@
 #include "qvggt_common.h"
 
 #include <algorithm>
-#include <cstdlib>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -101,6 +101,13 @@ __device__ inline void dma16(uint32_t lane_off, const void *base, uint32_t lds_b
 {
     asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(lane_off), "s"(base), "s"(lds_base), "n"(OFF) : "memory", "m0");
 }
+// a pointer that is the same in all lanes, in scalar registers (the transfers' base operand has to be; the compiler does not always see it)
+__device__ inline const uint8_t *scalar_pointer(const uint8_t *p)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+}
 template <class F, int... Is>
 __device__ inline void static_for_impl(F &&f, std::integer_sequence<int, Is...>)
 {
@@ -126,18 +133,19 @@ __device__ inline void wait_vmcnt()
 // BLK (int8 codes): the operands are "int8 blocks": rows grouped in blocks of 128 with the K-tiles outermost, K-tile kt of row r at
 // ((r / 128) * (K / 64) + kt) * 8192 + (r % 128) * 64, its four 16-byte chunks already in the swizzled order of the LDS stage, so
 // that what a wave fetches of a K-tile is 8 KiB (4 KiB in the small configuration) contiguous in memory
-template <int TM, int TN, int WM, int WN, int STAGES, int MINB, int CB, bool DEBUG, bool ASYM = false, bool BLK = false>
-__global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per_eu(WM * WN * MINB / 4, WM * WN * MINB / 4))) void w4a4_gemm_kernel(
-    const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
+// LAST_FIRST: the highest-numbered blocks of every XCD take the first tiles (the ones that a preceding set of tiles in the same launch
+// left without a last one)
+template <int TM, int TN, int WM, int WN, int STAGES, int CB, bool DEBUG, bool ASYM, bool BLK, bool LAST_FIRST = false>
+__device__ __forceinline__ void w4a4_tiles(
+    uint8_t *smem, const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
     const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int N, int K,
-    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_debug, int tiles_m, int tiles_n,
-    const float *__restrict__ xzero = nullptr, const float *__restrict__ wsum = nullptr)
+    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_debug, const float *__restrict__ xzero, const float *__restrict__ wsum)
 {
     using C = StreamCfg<TM, TN, WM, WN, STAGES, ASYM>;
     constexpr int NM = C::NM, NF = C::NF, LPW = C::LPW;
     constexpr int DMA_SHIFT = (LPW > 4) ? 4096 : 0;             // keeps the transfers' instruction offsets inside [-4096, 4095]
     static_assert(LPW <= 8, "instruction offsets of a wave's transfers must fit 13 signed bits");
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
     uint8_t *sc_all = smem + STAGES * C::STAGE_BYTES;           // two buffers of SC_BYTES
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;            // LDS byte address of the dynamic segment
 
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
     // Tile assignment: workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  XCD x owns the
     // contiguous tile range [x * per_xcd, (x + 1) * per_xcd) (channel tiles fastest), its blocks take them in turn.
     const int per_xcd = (ntiles + 7) >> 3;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
+    const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3, slot = LAST_FIRST ? slots - 1 - (int)(blockIdx.x >> 3) : (int)(blockIdx.x >> 3);
     const int tile_end = min((xcd + 1) * per_xcd, ntiles);
     const int first_tile = xcd * per_xcd + slot;
     if (first_tile >= tile_end) return;
@@ -182,11 +190,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
         if constexpr (BLK) {
             const int row = row0 + wave * LPW * 16 - (loads_x ? 0 : C::BM);          // first row of this wave's share
             const int blk = min(row / 128, ((loads_x ? M : N) + 127) / 128 - 1);        // past the end: re-read the last block (unused)
-            tile_base = (loads_x ? Xq : Wq) + (size_t)blk * ktiles * 8192 + (row % 128) * KT_BYTES - BASE_SHIFT;
+            tile_base = scalar_pointer((loads_x ? Xq : Wq) + (size_t)blk * ktiles * 8192 + (row % 128) * KT_BYTES - BASE_SHIFT);
             return;
         }
         const int last = (loads_x ? M : N) - 1 - row0;          // last existing row, relative to row0 (>= 0)
-        tile_base = (loads_x ? Xq : Wq) + (size_t)row0 * KB - BASE_SHIFT;
+        tile_base = scalar_pointer((loads_x ? Xq : Wq) + (size_t)row0 * KB - BASE_SHIFT);
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
             const int r = (wave * LPW + i) * 16 + t_row - (loads_x ? 0 : C::BM);   // row inside the operand's tile
@@ -374,6 +382,14 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
         };
         ktile(BT{});
         for (int kt = 1; kt < ktiles; ++kt) ktile(BF{});
+        // The scales were sent for during the first K-tile of the tile before; 2 ktiles - 1 K-tiles' transfers have followed before the
+        // last wait above, which lets STAGES - 3 K-tiles' be outstanding.  With few K-tiles and a deep ring that does not cover them.
+        if constexpr (STAGES > 4) {
+            if (2 * ktiles - 1 < STAGES - 3) {
+                wait_vmcnt<0>();
+                __syncthreads();
+            }
+        }
 
         // ---- epilogue.  32x32 result layout: lane l holds column (l % 32) = token and rows 8*(r/4) + 4*(l/32) + r%4 = channels,
         // i.e. per register quad q four consecutive channels 8q + 4*(l/32) + 0..3.  Scale + bias + bf16 in registers.
@@ -476,6 +492,32 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
     wait_vmcnt<0>();        // transfers issued past the last tile must not outlive the block's LDS allocation
 }
 
+template <int TM, int TN, int WM, int WN, int STAGES, int MINB, int CB, bool DEBUG, bool ASYM = false, bool BLK = false>
+__global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per_eu(WM * WN * MINB / 4, WM * WN * MINB / 4))) void w4a4_gemm_kernel(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
+    const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int N, int K,
+    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_debug, const float *__restrict__ xzero, const float *__restrict__ wsum)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    w4a4_tiles<TM, TN, WM, WN, STAGES, CB, DEBUG, ASYM, BLK>(smem, Xq, sx, Wq, sw, bias, M, N, K, Y, acc_debug, xzero, wsum);
+}
+
+// The first `rows_main` token rows (a multiple of 256) in 256 x 256 tiles, which fill whole rounds of the chip, then the rest in 128 x 128
+// tiles through a ring of twice the stages (the same LDS), in one launch: a block goes on to the rest when it is done, with no second
+// launch behind the slowest block, and one block per compute unit has the LDS to keep seven K-tiles in flight, which is what a tile
+// without company is bound by.
+template <int CB, bool BLK>
+__global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void w4a4_gemm_tail_kernel(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
+    const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int rows_main, int N, int K, uint16_t *__restrict__ Y)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    w4a4_tiles<4, 4, 2, 2, 4, CB, false, false, BLK>(smem, Xq, sx, Wq, sw, bias, rows_main, N, K, Y, nullptr, nullptr, nullptr);
+    __syncthreads();                     // every wave is done with its LDS before the ring is laid out anew
+    w4a4_tiles<2, 2, 2, 2, 8, CB, false, false, BLK, true>(smem, Xq + (size_t)rows_main * (CB == 4 ? K / 2 : K), sx + rows_main, Wq, sw, bias,
+                                                           M - rows_main, N, K, Y + (size_t)rows_main * N, nullptr, nullptr, nullptr);
+}
+
 // every instantiation launched below, with the dynamic LDS it needs: packed codes (plain, accumulator dump, affine), int8 codes
 // row-major and in blocks (plain, accumulator dump)
 #define QVGGT_GEMM_KERNELS(TM, TN, WM, WN, ST, MB)                                                                                        \
@@ -486,7 +528,12 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, true, false, false>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, false, false, true>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, true, false, true>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES}
-static const LdsKernel gemm_lds_kernel_list[] = {QVGGT_GEMM_KERNELS(4, 4, 2, 2, 4, 1), QVGGT_GEMM_KERNELS(2, 2, 2, 2, 3, 2)};
+static constexpr int TAIL_LDS_BYTES = std::max(StreamCfg<4, 4, 2, 2, 4>::LDS_BYTES, StreamCfg<2, 2, 2, 2, 8>::LDS_BYTES);
+static const LdsKernel gemm_lds_kernel_list[] = {QVGGT_GEMM_KERNELS(4, 4, 2, 2, 4, 1), QVGGT_GEMM_KERNELS(2, 2, 2, 2, 3, 2),
+                                                 QVGGT_GEMM_KERNELS(2, 2, 2, 2, 8, 1),
+                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<4, false>), TAIL_LDS_BYTES},
+                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, false>), TAIL_LDS_BYTES},
+                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, true>), TAIL_LDS_BYTES}};
 #undef QVGGT_GEMM_KERNELS
 static const LdsKernels gemm_lds_kernels(gemm_lds_kernel_list);
 
@@ -511,51 +558,73 @@ static hipError_t launch_gemm(const uint8_t *Xq, const float *sx, const uint8_t 
     int grid = 256 * MINB;                                // MINB resident blocks on each of the 256 compute units
     if (grid > (ntiles + 7) / 8 * 8) grid = (ntiles + 7) / 8 * 8;
     kern<<<grid, C::THREADS, C::LDS_BYTES, stream>>>(Xq, sx, Wq, sw, reinterpret_cast<const uint16_t *>(bias), M, N, K,
-                                                     reinterpret_cast<uint16_t *>(Y), acc_debug, tiles_m, tiles_n, xzero, wsum);
+                                                     reinterpret_cast<uint16_t *>(Y), acc_debug, xzero, wsum);
     return hipGetLastError();
 }
 
-// Which tile shape runs where.  The big configuration (256 x 256 per block, four waves of 128 x 128, one per SIMD) works in
-// rounds of 256 tiles, one per compute unit; a last round that is mostly empty costs as much as a full one.  So the token rows
-// that fill whole rounds go to the big kernel and the remaining rows, when they fit better there, to the small configuration
-// (128 x 128 per block, two blocks per compute unit) in a second launch on the same stream.  Rows are independent, the two
-// launches write disjoint rows of Y.
+template <int CB, bool BLK>
+static hipError_t launch_gemm_tail(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw, const void *bias, int M,
+                                   int rows_main, int N, int K, void *Y, hipStream_t stream)
+{
+    hipError_t e = prepare_device();
+    if (e != hipSuccess) return e;
+    w4a4_gemm_tail_kernel<CB, BLK><<<256, 256, TAIL_LDS_BYTES, stream>>>(Xq, sx, Wq, sw, reinterpret_cast<const uint16_t *>(bias), M, rows_main, N,
+                                                                         K, reinterpret_cast<uint16_t *>(Y));
+    return hipGetLastError();
+}
+
+// Which tile shape runs where: the plan that the model below prices lowest, in microseconds.  Rows are independent, so token rows can be
+// divided between configurations.
+//   big    256 x 256 tiles, one per compute unit: whole rounds of 256, a last one that is mostly empty costs as much as a full one.
+//   small  128 x 128 tiles, two blocks per compute unit, one's epilogue under the other's K loop: the cost follows the number of tiles
+//          (2064 tiles are 4.03 rounds of 512, not 5), and a tile costs 1.0 of a quarter of a big one at K = 128, 1.14 at 1024, 1.4 at 4096
+//          (int8 codes: 1.2 and 1.75), the LDS traffic per MFMA being twice as much.
+//   deep   128 x 128 tiles, one block per compute unit with an eight-stage ring: for at most 256 of them, where a tile's time is its chain of
+//          transfers (int8 codes, 1374 x 4096 -> 1024: 31 -> 16 us; packed codes 22 -> 18 us for 700 x 4096 -> 4096).
+//   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch.
+// Measured (us, big / small / tail; what ran before is in brackets): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1 [39.3],
+// 32976 x 256 -> 3072 56 / 50 / 55 [56], 32976 x 1024 -> 1024 50 / 40 / 45 [47], 32976 x 4096 -> 1024 137 / 130 / 113 [121];
+// int8 blocks 32976 x 4096 -> 1024 140 / 156 / 118 [135], 20000 x 4096 -> 1024 89 / 92 / 71 [85].
 template <int CB, bool ASYM = false, bool BLK = false>
 static hipError_t gemm_by_rounds(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw, const void *bias,
                                  int M, int N, int K, void *Y, int32_t *acc_debug, hipStream_t stream,
                                  const float *xzero = nullptr, const float *wsum = nullptr)
 {
-    auto big = [&](int row0, int rows) {
-        return launch_gemm<4, 4, 2, 2, 4, 1, CB, ASYM, BLK>(Xq + (size_t)row0 * (CB == 4 ? K / 2 : K), sx + row0, Wq, sw, bias, rows, N, K,
-                                                       static_cast<uint16_t *>(Y) + (size_t)row0 * N,
-                                                       acc_debug ? acc_debug + (size_t)row0 * N : nullptr, stream,
-                                                       ASYM ? xzero + row0 : nullptr, wsum);
-    };
-    auto small = [&](int row0, int rows) {
-        return launch_gemm<2, 2, 2, 2, 3, 2, CB, ASYM, BLK>(Xq + (size_t)row0 * (CB == 4 ? K / 2 : K), sx + row0, Wq, sw, bias, rows, N, K,
-                                                       static_cast<uint16_t *>(Y) + (size_t)row0 * N,
-                                                       acc_debug ? acc_debug + (size_t)row0 * N : nullptr, stream,
-                                                       ASYM ? xzero + row0 : nullptr, wsum);
-    };
+#define QVGGT_ROWS(TM, TN, ST, MB, row0, rows)                                                                                           \
+    launch_gemm<TM, TN, 2, 2, ST, MB, CB, ASYM, BLK>(Xq + (size_t)(row0) * (CB == 4 ? K / 2 : K), sx + (row0), Wq, sw, bias, rows, N, K, \
+                                                     static_cast<uint16_t *>(Y) + (size_t)(row0) * N,                                    \
+                                                     acc_debug ? acc_debug + (size_t)(row0) * N : nullptr, stream,                       \
+                                                     ASYM ? xzero + (row0) : nullptr, wsum)
+    auto tiles128 = [&](int rows) { return (double)((rows + 127) / 128) * ((N + 127) / 128); };
+    auto rounds = [](double tiles) { return std::ceil(tiles / 256.0); };
+    const double k = K / 1024.0;
+    const double big_round = 5.0 + (CB == 4 ? 11.0 : 12.0) * k, deep_round = 8.0 + 3.7 * k;
+    const double small_share = 0.50 + (CB == 4 ? 0.055 : 0.095) * k;         // of a big round, for 512 small tiles
     const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
-    const long long big_tiles = (long long)tiles_m * tiles_n;
-    // a round of small tiles takes about 0.5 - 0.7 of a round of big ones (measured at K = 1024 and 4096): 13 / 20 below
-    if (big_tiles < 256) {
-        // less than one round of big tiles: small tiles unless they need a second round of their own
-        const long long small_rounds = ((long long)((M + 127) / 128) * ((N + 127) / 128) + 511) / 512;
-        return small_rounds * 13 < 20 ? small(0, M) : big(0, M);
-    }
+    const double big_tiles = (double)tiles_m * tiles_n;
+
+    if (tiles128(M) <= 256.0) return QVGGT_ROWS(2, 2, 8, 1, 0, M);
+    const double big_cost = rounds(big_tiles) * big_round;
+    const double small_cost = tiles128(M) / 512.0 * small_share * big_round + 3.0;
     // whole tile rows that fit into the full rounds
-    const int main_tile_rows = (int)std::min<long long>(tiles_m, big_tiles / 256 * 256 / tiles_n);
-    const int rem_tile_rows = tiles_m - main_tile_rows;
-    if (rem_tile_rows == 0) return big(0, M);
-    const int rows_main = main_tile_rows * 256, rows_rem = M - rows_main;
-    const long long rem_big_rounds = ((long long)rem_tile_rows * tiles_n + 255) / 256;
-    const long long rem_small_rounds = ((long long)((rows_rem + 127) / 128) * ((N + 127) / 128) + 511) / 512;
-    if (rem_small_rounds * 13 >= rem_big_rounds * 20) return big(0, M);
-    hipError_t e = big(0, rows_main);
-    if (e != hipSuccess) return e;
-    return small(rows_main, rows_rem);
+    const int main_tile_rows = (int)std::min<double>(tiles_m, std::floor(big_tiles / 256.0) * 256.0 / tiles_n);
+    const int rows_main = main_tile_rows * 256;
+    if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
+        // the accumulator dump and affine codes (whose two tile loops do not fit the registers together) take a second launch for the rest
+        const bool one_launch = !ASYM && acc_debug == nullptr;
+        const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + rounds(tiles128(M - rows_main)) * deep_round +
+                                 (one_launch ? 0.0 : 6.0);
+        if (tail_cost < 0.97 * std::min(big_cost, small_cost)) {
+            if constexpr (!ASYM) {
+                if (one_launch) return launch_gemm_tail<CB, BLK>(Xq, sx, Wq, sw, bias, M, rows_main, N, K, Y, stream);
+            }
+            const hipError_t e = QVGGT_ROWS(4, 4, 4, 1, 0, rows_main);
+            if (e != hipSuccess) return e;
+            return QVGGT_ROWS(2, 2, 8, 1, rows_main, M - rows_main);
+        }
+    }
+    return small_cost < big_cost ? QVGGT_ROWS(2, 2, 3, 2, 0, M) : QVGGT_ROWS(4, 4, 4, 1, 0, M);
+#undef QVGGT_ROWS
 }
 
 hipError_t run_w4a4_gemm(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw,

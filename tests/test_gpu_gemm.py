@@ -168,3 +168,38 @@ def test_matrix_ceiling_helper_runs_and_repeats(kind):
     q.qvggt_mfma_ceiling(kind, 50, sink)
     torch.cuda.synchronize()
     assert torch.equal(first, sink)
+
+
+@pytest.mark.parametrize("M,N,K,kind", [(8400, 2000, 4096, "packed"), (8400, 2000, 4096, "int8"), (8400, 2000, 4096, "blocks"),
+                                        (17000, 4096, 1024, "blocks"), (2049, 2048, 128, "packed"), (2048, 2048, 128, "int8"),
+                                        (129, 128, 8192, "blocks"), (1, 16, 256, "blocks")])
+def test_tile_plans(M, N, K, kind):
+    """The plans of the dispatch at their edges: whole rounds of big tiles and the rest in deep-ring tiles of the same launch (ragged
+    last tiles), 256 small tiles exactly and a few more, the smallest problem.  The accumulator dump takes separate launches: Y of both
+    calls must agree bit for bit, and sampled accumulators be the exact integers."""
+    import paper_2509_21302_amd as q
+    rng = np.random.default_rng(M + N + K)
+    lim = 8 if kind == "packed" else 128
+    qx, qw = rng.integers(-lim, lim, (M, K)).astype(np.int8), rng.integers(-lim, lim, (N, K)).astype(np.int8)
+    dx, dw = np.exp(rng.uniform(-3, 1, M)).astype(np.float32), np.exp(rng.uniform(-8, -4, N)).astype(np.float32)
+    if kind == "packed":
+        A, B, gemm = G.gpu_pack(qx), G.gpu_pack(qw), q.qvggt_w4a4_gemm
+    else:
+        A, B, gemm = G.gpu_layout_int8(qx, 1), G.gpu_layout_int8(qw, 1), q.qvggt_i8_gemm
+    if kind == "blocks":
+        Ab, Bb = (torch.zeros(q.qvggt_i8b_bytes(n, K), dtype=torch.int8, device=G.DEV) for n in (M, N))
+        q.qvggt_int8_to_blocks(A, M, K, Ab)
+        q.qvggt_int8_to_blocks(B, N, K, Bb)
+        A, B, gemm = Ab, Bb, q.qvggt_i8b_gemm
+    Y, Yd = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=G.DEV) for _ in range(2))
+    acc = torch.full((M, N), 12345, dtype=torch.int32, device=G.DEV)
+    sx, sw = G.to_dev(dx), G.to_dev(dw)
+    gemm(A, sx, B, sw, None, M, N, K, Y, None)
+    gemm(A, sx, B, sw, None, M, N, K, Yd, acc)
+    assert torch.equal(Y.view(torch.int16), Yd.view(torch.int16))
+    rows = np.unique(np.concatenate([np.arange(min(M, 8)), np.arange(max(M - 8, 0), M), np.clip(np.arange(8188, 8196), 0, M - 1), rng.integers(0, M, 16)]))
+    want = oracle.int_gemm(qx[rows], qw)
+    assert np.array_equal(acc[torch.from_numpy(rows).to(G.DEV)].cpu().numpy(), want)
+    Yo = oracle.dequant_bias(want, dx[rows], dw)
+    ulp_off = np.abs(G.bf16_bits(Y)[rows].astype(np.int32) - Yo.astype(np.int32))
+    assert ulp_off.max() <= 1 and (ulp_off != 0).mean() < 5e-3
