@@ -908,8 +908,11 @@ hipError_t run_rotated_col_absmax_mfma(const void *X, int rows, int K, const int
     const uint16_t *x = reinterpret_cast<const uint16_t *>(X);
     const int tok = 32 / (K / 128);
     const int ntiles = (rows + tok - 1) / tok;
-    // sixteen tiles or more per wave where there are that many: every wave ends with atomics on all K columns
-    int blocks = (ntiles + 16 * rq::WAVES_PER_BLOCK - 1) / (16 * rq::WAVES_PER_BLOCK);
+    // four tiles per wave until the chip is full: a block ends with atomics on all K columns, but a wave's tiles are a serial chain of
+    // about 1.5 us each.  1374 x 4096 (16 / 4 / 1 tiles per wave): 28 / 13 / 15 us, 4096 x 4096: 29 / 17 / 21, 1374 x 1024: 19 / 10 / 10.
+    // (Reading the column's present maximum first, to skip the atomic, was slower at every size: 27 us at 1374 x 4096.)
+    constexpr int TILES_PER_BLOCK = 4 * rq::WAVES_PER_BLOCK;
+    int blocks = (ntiles + TILES_PER_BLOCK - 1) / TILES_PER_BLOCK;
     if (blocks > 256 * 2) blocks = 256 * 2;
 #define RQS(KK) rotate_quant_mfma_kernel<KK, 1, 2, false, 0><<<blocks, 256, 0, stream>>>(x, rows, signs, nullptr, 0, nullptr, nullptr, nullptr, 0, 0.0f, absmax_bits)
     switch (K) {
