@@ -11,6 +11,8 @@ import ctypes as C
 import os
 from typing import Optional
 
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 QVGGT_BF16, QVGGT_F32 = 0, 1
 
@@ -187,18 +189,18 @@ def _ptr(t) -> Optional[int]:
 
 
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
+    dtype = t.dtype
+    if dtype == torch.bfloat16:
         return QVGGT_BF16
-    if t.dtype == torch.float32:
+    if dtype == torch.float32:
         return QVGGT_F32
     raise ValueError(f"unsupported dtype {t.dtype}: bf16 or f32")
 
 
 def _stream(stream) -> Optional[int]:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    if stream is None:      # the current device's current stream, without the two Python objects that torch.cuda.current_stream() makes
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    return stream.cuda_stream or None
 
 
 def _check(status: int, where: str):
