@@ -96,6 +96,74 @@ __device__ inline float max_over_64_lanes(float v)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// The six Walsh-Hadamard butterflies over the lane bits, for R registers that each hold one value per lane: x[l] becomes
+// x[l] + x[l ^ m] in lanes without bit m and x[l ^ m] - x[l] in the others.  Lane bits 0 .. 3 by DPP (quad permutes; 4 = a half-row
+// mirror of a quad reversal; 8 = a rotation of the row of 16), the sign in the multiplier of an exact fma.  Bits 4 and 5 by row swaps of
+// register pairs: swapped, the pair holds the two partners of each butterfly, and a second swap puts the results back.  No LDS:
+// six cross-lane reads per value through it were what the row kernels spent their time on.
+template <int CTRL>
+__device__ inline float dpp_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+template <int R>
+__device__ inline void lane_butterflies(float (&x)[R], int lane)
+{
+    static_assert(R % 2 == 0, "the row swaps work on pairs of registers");
+    const float s1 = (lane & 1) ? -1.0f : 1.0f, s2 = (lane & 2) ? -1.0f : 1.0f, s4 = (lane & 4) ? -1.0f : 1.0f, s8 = (lane & 8) ? -1.0f : 1.0f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        x[r] = fmaf(x[r], s1, dpp_move<0xB1>(x[r]));
+        x[r] = fmaf(x[r], s2, dpp_move<0x4E>(x[r]));
+        x[r] = fmaf(x[r], s4, dpp_move<0x141>(dpp_move<0x1B>(x[r])));
+        x[r] = fmaf(x[r], s8, dpp_move<0x128>(x[r]));
+    }
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+        auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[r]), __float_as_uint(x[r + 1]), false, false);
+        float a = __uint_as_float(p[0]), b = __uint_as_float(p[1]);
+        p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a + b), __float_as_uint(a - b), false, false);
+        p = __builtin_amdgcn_permlane32_swap(p[0], p[1], false, false);
+        a = __uint_as_float(p[0]); b = __uint_as_float(p[1]);
+        p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a + b), __float_as_uint(a - b), false, false);
+        x[r] = __uint_as_float(p[0]);
+        x[r + 1] = __uint_as_float(p[1]);
+    }
+}
+
+// The two butterflies over the wave number (0 .. 3) of a row that four waves of a block share, through LDS [4][R / 4][64] float4:
+// every wave leaves its values and adds up the four of each position.  Ends with a barrier: the area may be written again.
+template <int R>
+__device__ inline void wave_butterflies(float (&x)[R], float4 *area, int sub, int lane)
+{
+    static_assert(R % 4 == 0, "values move four at a time");
+#pragma unroll
+    for (int q = 0; q < R / 4; ++q) area[(sub * (R / 4) + q) * 64 + lane] = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+    __syncthreads();
+    const float s1 = (sub & 1) ? -1.0f : 1.0f, s2 = (sub & 2) ? -1.0f : 1.0f;
+    auto sum = [&](float a, float b, float c, float d) { return fmaf(s2, fmaf(s1, d, c), fmaf(s1, b, a)); };
+#pragma unroll
+    for (int q = 0; q < R / 4; ++q) {
+        const float4 a = area[q * 64 + lane], b = area[(R / 4 + q) * 64 + lane], c = area[(2 * (R / 4) + q) * 64 + lane], d = area[(3 * (R / 4) + q) * 64 + lane];
+        x[4 * q] = sum(a.x, b.x, c.x, d.x);
+        x[4 * q + 1] = sum(a.y, b.y, c.y, d.y);
+        x[4 * q + 2] = sum(a.z, b.z, c.z, d.z);
+        x[4 * q + 3] = sum(a.w, b.w, c.w, d.w);
+    }
+    __syncthreads();
+}
+// maximum over the four waves of a block (v the same in all lanes of a wave); red[4] is free again after the next barrier
+__device__ inline float max_over_4_waves(float v, float *red)
+{
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+// Adding it rounds a float of magnitude < 2^22 to the nearest integer (ties to even) and leaves that integer, two's complement, in the
+// low bits of the sum's pattern.
+constexpr float kRoundMagic = 12582912.0f;      // 1.5 * 2^23
+
 // Sum over all 64 lanes, the same butterflies with an add (every lane ends with the total).
 template <int CTRL>
 __device__ inline float dpp_add_step(float v)

@@ -31,18 +31,28 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
                                                           const float *__restrict__ step, int step_stride, float qmax,
                                                           LnParams ln, float *__restrict__ zero = nullptr)
 {
-    constexpr int V = RowMap<K>::V, C = RowMap<K>::C, R = RowMap<K>::R;
+    // waves per row: one, or the four of a block where a row would take 128 registers of a lane (two copies of it with the multipliers:
+    // one wave per SIMD).  A wave then has K / 4 consecutive elements, and two butterflies go over the wave number.
+    // 34350 x 8192 bf16: 594 us with one wave per row.
+    constexpr int WPR = K > 4096 ? 4 : 1, KW = K / WPR;
+    constexpr int V = RowMap<KW>::V, C = RowMap<KW>::C, R = RowMap<KW>::R;
     constexpr bool kPermuted = (K == 1024 || K == 2048 || K == 4096) && MODE == kQuantize;
     __shared__ __attribute__((aligned(16))) uint8_t lds_stage[kPermuted ? 4 * K : 16];
     const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int nwaves = gridDim.x * (blockDim.x >> 6);
+    const int sub = WPR > 1 ? (int)(threadIdx.x >> 6) : 0, first = sub * KW;       // this wave's part of a row
+    const int wave = WPR > 1 ? (int)blockIdx.x : (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int nwaves = WPR > 1 ? (int)gridDim.x : (int)gridDim.x * 4;
+    __shared__ float4 exchange[WPR > 1 ? K / 4 : 1];
+    __shared__ float red[2][4];
 
-    // per-lane constants: sign bits (one bit per register) and channel multipliers
-    uint32_t neg[(R + 31) / 32];
+    // per-lane constants: signs (a mask per register while there is room, one bit otherwise) and channel multipliers
+    constexpr bool SIGN_MASKS = R <= 32;
+    uint32_t neg[SIGN_MASKS ? R : (R + 31) / 32];
 #pragma unroll
-    for (int w = 0; w < (R + 31) / 32; ++w) neg[w] = 0;
-    float cm[R];
+    for (int w = 0; w < (SIGN_MASKS ? R : (R + 31) / 32); ++w) neg[w] = 0;
+    // the normalisation at K = 4096 leaves no registers for the multipliers: read again for every row there
+    constexpr bool KEEP_MUL = !(LN && R >= 64);
+    float cm[KEEP_MUL ? R : 1];
     const float rs = 1.0f / sqrtf((float)K);
     // loads first (all in flight together), arithmetic afterwards: the set-up is one memory round trip, not one per element
     if (signs != nullptr) {
@@ -50,16 +60,17 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
 #pragma unroll
         for (int c = 0; c < C; ++c)
 #pragma unroll
-            for (int i = 0; i < V; ++i) sb[c * V + i] = signs[c * 64 * V + lane * V + i];
+            for (int i = 0; i < V; ++i) sb[c * V + i] = signs[first + c * 64 * V + lane * V + i];
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if (sb[r] < 0) neg[r >> 5] |= 1u << (r & 31);
+            if (sb[r] < 0) neg[SIGN_MASKS ? r : r >> 5] |= SIGN_MASKS ? 0x80000000u : 1u << (r & 31);
     }
-    if (mul != nullptr) {
+    if (!KEEP_MUL) {
+    } else if (mul != nullptr) {
 #pragma unroll
         for (int c = 0; c < C; ++c)
 #pragma unroll
-            for (int i = 0; i < V; ++i) cm[c * V + i] = mul[c * 64 * V + lane * V + i];
+            for (int i = 0; i < V; ++i) cm[c * V + i] = mul[first + c * 64 * V + lane * V + i];
         if (mul_mode) {
 #pragma unroll
             for (int r = 0; r < R; ++r) cm[r] = 1.0f / ((float)K * cm[r]);
@@ -74,8 +85,9 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
     for (int r = 0; r < (MODE == kColAbsMax ? R : 1); ++r) colmax[r] = 0.0f;
     for (int row = wave; row < rows; row += nwaves) {
         float x[R];
-        load_row<K, F32>(X, (size_t)row, lane, x);
+        load_row<KW, F32>(X, (size_t)row * WPR + sub, lane, x);
         if constexpr (LN) {
+            static_assert(!LN || WPR == 1, "the normalisation sums over one wave");
             // LayerNorm of the token in fp32 (two passes over the registers), result rounded to the input's type as a separate
             // normalisation kernel would hand it on; gamma and beta come through the caches, this is the general path
             float s1 = 0.0f;
@@ -100,12 +112,23 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
         }
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if ((neg[r >> 5] >> (r & 31)) & 1u) x[r] = -x[r];
-        fwht_row<K>(x, lane);
+            x[r] = __uint_as_float(__float_as_uint(x[r]) ^ (SIGN_MASKS ? neg[r] : (neg[r >> 5] << (31 - (r & 31))) & 0x80000000u));
+        fwht_row<KW>(x, lane);
+        if constexpr (WPR > 1) wave_butterflies(x, exchange, sub, lane);
+        const float *row_mul = mul;
+        if constexpr (!KEEP_MUL) asm volatile("" : "+s"(row_mul));       // keeps the reads inside the loop
+        auto multiplier = [&](int r) -> float {
+            if constexpr (KEEP_MUL) {
+                return cm[r];
+            } else {
+                const float m = row_mul != nullptr ? row_mul[first + (r / V) * 64 * V + lane * V + r % V] : rs;
+                return (mul_mode && row_mul != nullptr) ? 1.0f / ((float)K * m) : m;
+            }
+        };
         float amax = 0.0f, nmin = 0.0f;       // ASYM: max(0, max z) and -min(0, min z)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            x[r] *= cm[r];
+            x[r] *= multiplier(r);
             if constexpr (ASYM) { amax = fmaxf(amax, x[r]); nmin = fmaxf(nmin, -x[r]); }
             else amax = fmaxf(amax, fabsf(x[r]));
         }
@@ -118,25 +141,35 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
             // dynamic: the step comes from the row's absmax; static: it is given (per token or one for the tensor)
             float inv, delta, off = 0.0f;
             if constexpr (ASYM) {
-                const float hi = wave_max(amax), nlo = wave_max(nmin);
+                float hi = wave_max(amax), nlo = wave_max(nmin);
+                if constexpr (WPR > 1) { hi = max_over_4_waves(hi, red[0]); nlo = max_over_4_waves(nlo, red[1]); }
                 const float range = hi + nlo;
                 const bool live = range >= 15.0f * kMinStep;
                 delta = live ? range / 15.0f : 0.0f;
                 inv = live ? 15.0f / range : 0.0f;
                 const float zp = __builtin_rintf(nlo * inv);                  // rne(-lo / step), in [0, 15]
                 off = zp - 8.0f;
-                if (lane == 0) zero[row] = zp;
+                if (lane == 0 && sub == 0) zero[row] = zp;
             } else if (step != nullptr) {
                 delta = step[(size_t)row * step_stride];
                 inv = delta >= kMinStep ? 1.0f / delta : 0.0f;
             } else {
                 amax = wave_max(amax);
+                if constexpr (WPR > 1) amax = max_over_4_waves(amax, red[0]);
                 const bool live = amax >= qmax * kMinStep;
                 delta = live ? amax / qmax : 0.0f;
                 inv = live ? qmax / amax : 0.0f;
             }
-            if (lane == 0) scale[row] = delta;
+            if (lane == 0 && sub == 0) scale[row] = delta;
             const int q_hi = (int)qmax, q_lo = -q_hi - 1;
+            // a step from the row's own maximum bounds |x * inv| by qmax (1 + 2^-22): rounding cannot leave the range, and the code is the low
+            // bits of one fma.  (inv is 0 for a row without a step, or whose values overflowed: the general form gives codes 0 there.)
+            const bool bounded = !ASYM && step == nullptr && inv > 0.0f;
+            auto code_of = [&](int r) -> uint32_t {       // two's complement in the low CB bits, anything above
+                if (bounded) return __float_as_uint(fmaf(x[r], inv, kRoundMagic));
+                const int q = (int)__builtin_rintf(ASYM ? fmaf(x[r], inv, off) : x[r] * inv);
+                return (uint32_t)min(q_hi, max(q_lo, q));
+            };
             uint8_t *out = packed + (size_t)row * (K * CB / 8);
             if constexpr (K == 1024 || K == 2048 || K == 4096) {
                 // permuted layout: scatter the codes as bytes into the wave's LDS row at their positions,
@@ -145,11 +178,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
 #pragma unroll
                 for (int c = 0; c < C; ++c)
 #pragma unroll
-                    for (int i = 0; i < V; ++i) {
-                        int q = (int)__builtin_rintf(ASYM ? fmaf(x[c * V + i], inv, off) : x[c * V + i] * inv);
-                        q = min(q_hi, max(q_lo, q));
-                        stage[code_position(c * 64 * V + lane * V + i, K)] = (uint8_t)(CB == 4 ? (q & 0xF) : q);
-                    }
+                    for (int i = 0; i < V; ++i) stage[code_position(c * 64 * V + lane * V + i, K)] = (uint8_t)code_of(c * V + i);
                 lanes_exchange_fence();
                 constexpr int PER_LANE = K / 64;      // positions per lane, a multiple of 16
                 if constexpr (CB == 8) {
@@ -161,7 +190,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
                     for (int b = 0; b < PER_LANE / 8; ++b) {
                         const uint2 v = *reinterpret_cast<const uint2 *>(stage + lane * PER_LANE + 8 * b);
                         // bytes hold one code each (low nibble): squeeze 8 bytes into 8 nibbles
-                        uint32_t lo = v.x, hi = v.y;
+                        uint32_t lo = v.x & 0x0F0F0F0Fu, hi = v.y & 0x0F0F0F0Fu;
                         lo = (lo | (lo >> 4)) & 0x00FF00FFu; lo = (lo | (lo >> 8)) & 0x0000FFFFu;
                         hi = (hi | (hi >> 4)) & 0x00FF00FFu; hi = (hi | (hi >> 8)) & 0x0000FFFFu;
                         *reinterpret_cast<uint32_t *>(out + lane * (PER_LANE / 2) + 4 * b) = lo | (hi << 16);
@@ -173,13 +202,9 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
             for (int c = 0; c < C; ++c) {
                 uint64_t word = 0;
 #pragma unroll
-                for (int i = 0; i < V; ++i) {
-                    int q = (int)__builtin_rintf(ASYM ? fmaf(x[c * V + i], inv, off) : x[c * V + i] * inv);
-                    q = min(q_hi, max(q_lo, q));
-                    word |= (uint64_t)(q & ((1 << CB) - 1)) << (CB * i);
-                }
+                for (int i = 0; i < V; ++i) word |= (uint64_t)(code_of(c * V + i) & ((1u << CB) - 1)) << (CB * i);
                 // natural order: element e -> code slot e; a lane's V codes are V * CB / 8 consecutive bytes
-                const int byte0 = (c * 64 * V + lane * V) * CB / 8;
+                const int byte0 = (first + c * 64 * V + lane * V) * CB / 8;
                 if constexpr (V * CB == 64) *reinterpret_cast<uint2 *>(out + byte0) = make_uint2((uint32_t)word, (uint32_t)(word >> 32));
                 else if constexpr (V * CB == 32) *reinterpret_cast<uint32_t *>(out + byte0) = (uint32_t)word;
                 else if constexpr (V * CB == 16) *reinterpret_cast<uint16_t *>(out + byte0) = (uint16_t)word;
@@ -195,7 +220,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
             for (int c = 0; c < C; ++c)
 #pragma unroll
                 for (int i = 0; i < V; ++i)
-                    atomicMax(&col_absmax_bits[c * 64 * V + lane * V + i], __float_as_uint(colmax[c * V + i]));
+                    atomicMax(&col_absmax_bits[first + c * 64 * V + lane * V + i], __float_as_uint(colmax[c * V + i]));
         }
     }
 }
@@ -301,11 +326,12 @@ static hipError_t launch_rotate_rows(const void *X, bool f32, int rows, int K, c
 {
     if (rows <= 0) return hipSuccess;
     const int waves_per_block = 4;
-    int blocks = (rows + waves_per_block - 1) / waves_per_block;
+    const int rows_per_block = K > 4096 ? 1 : waves_per_block;       // four waves share a row beyond 4096 values
+    int blocks = (rows + rows_per_block - 1) / rows_per_block;
     // up to eight blocks per compute unit; the column statistic takes fewer waves for small inputs so that each folds several
     // rows into its running maximum before touching the shared result
     const int max_blocks = (MODE == kColAbsMax) ? 256 * 2 : 256 * 8;
-    if (MODE == kColAbsMax) blocks = (rows + 31) / 32;     // eight rows or more per wave: the atomics at the end are what costs
+    if (MODE == kColAbsMax) blocks = (rows + 8 * rows_per_block - 1) / (8 * rows_per_block);     // eight rows or more per wave: the atomics at the end are what costs
     if (blocks > max_blocks) blocks = max_blocks;
     if (blocks < 1) blocks = 1;
 #define QVGGT_LAUNCH(KK)                                                                                     \
@@ -388,7 +414,7 @@ hipError_t run_rotate_smooth_quant_asym(const void *X, bool f32, int rows, int K
     if (!f32 && (K == 1024 || K == 2048 || K == 4096))
         return run_rotate_quant_asym_mfma(X, rows, K, signs, mul, packed, scale, zero, stream);
     if (rows <= 0) return hipSuccess;
-    int blocks = (rows + 3) / 4;
+    int blocks = K > 4096 ? rows : (rows + 3) / 4;
     if (blocks > 256 * 8) blocks = 256 * 8;
     const LnParams no_ln{nullptr, nullptr, 0.0f, 0};
 #define QVGGT_LAUNCH_ASYM(KK)                                                                                                          \

@@ -4,8 +4,8 @@
 // adds and subtracts.  Element e = a * m + b (a < 2^n, b < m); a wavefront owns a row, lane l holds the m values of every
 // a = l + 64 * c: the m-point transform is inside a lane, the six low bits of a go through cross-lane exchanges, the
 // remaining bits are register-to-register butterflies.  Codes are written in natural order (element e -> position e).
-// This is the general path: dense m x m stages cost m vector ALU ops per element, it is not tuned like the power-of-two
-// kernels and VGGT-1B itself has no layer that needs it.
+// This is the general path: VGGT-1B itself has no layer that needs it.  Bound by the vector ALU (34350 x 768 bf16: 38 us with dense
+// m-point sums and the lane bits through LDS, 28 us now).
 #include "qvggt_common.h"
 
 #include <algorithm>
@@ -46,6 +46,23 @@ constexpr int paley_entry(int r, int c)
     }
 }
 
+// Inputs 4 g .. 4 g + 3 of output c, up to the sign of the first: which of the sums x0 +- x1 +- (x2 +- x3) they make (bit 0: x1 subtracted,
+// bit 1: x3 against x2, bit 2: x2 against x0)
+template <int MM>
+constexpr int sum_of_four(int g, int c)
+{
+    const int s0 = paley_entry<MM>(4 * g, c), s1 = paley_entry<MM>(4 * g + 1, c), s2 = paley_entry<MM>(4 * g + 2, c), s3 = paley_entry<MM>(4 * g + 3, c);
+    return (s0 * s1 < 0 ? 1 : 0) | (s2 * s3 < 0 ? 2 : 0) | (s0 * s2 < 0 ? 4 : 0);
+}
+// After group g, is it the negative of output c's partial sum that is held?  (It is while every group so far entered with a minus.)
+template <int MM>
+constexpr bool partial_is_negated(int g, int c)
+{
+    for (int k = 0; k <= g; ++k)
+        if (paley_entry<MM>(4 * k, c) > 0) return false;
+    return true;
+}
+
 template <class F, int... Is>
 __device__ inline void static_for_impl(F &&f, std::integer_sequence<int, Is...>)
 {
@@ -59,6 +76,10 @@ __device__ inline void static_for(F &&f)
 
 enum Mode { kQuantize = 0, kColAbsMax = 1 };
 
+// Four waves per row at K = 5120 and 6144: with one, a row and its multipliers take more than the 256 registers of a wave that shares
+// its SIMD.  34350 rows (bf16): 667 and 817 us with one wave per row.
+constexpr int waves_per_row(int n2, int mm) { return n2 / 64 * mm >= 80 ? 4 : 1; }
+
 }  // namespace gen
 
 // mul_mode 0: mul[j] used as given (inv_smooth, or 1/sqrt(K) when mul == nullptr); 1: 1 / (K * mul[j]) (weights)
@@ -71,30 +92,36 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                                                                   unsigned int *__restrict__ col_absmax_bits,
                                                                   const float *__restrict__ step, int step_stride, float qmax)
 {
-    constexpr int K = N2 * MM, C = N2 / 64, R = C * MM;
-    static_assert(N2 >= 64 && (N2 & (N2 - 1)) == 0, "the power-of-two factor covers the 64 lanes");
+    // waves per row: one, or the four of a block where a row would take 80 registers of a lane or more (see gen::waves_per_row).  A wave then
+    // has N2 / 4 consecutive values of a, and two butterflies go over the wave number.
+    constexpr int K = N2 * MM, WPR = gen::waves_per_row(N2, MM), C = N2 / WPR / 64, R = C * MM;
+    static_assert(N2 / WPR >= 64 && (N2 & (N2 - 1)) == 0, "the power-of-two factor covers the 64 lanes");
     const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int nwaves = gridDim.x * (blockDim.x >> 6);
+    const int sub = WPR > 1 ? (int)(threadIdx.x >> 6) : 0, first = sub * (K / WPR);       // this wave's part of a row
+    const int wave = WPR > 1 ? (int)blockIdx.x : (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int nwaves = WPR > 1 ? (int)gridDim.x : (int)gridDim.x * 4;
+    __shared__ float4 exchange[WPR > 1 ? K / 4 : 1];
+    __shared__ float red[4];
 
     // per-lane constants: register r = c * MM + b holds element e = (lane + 64 c) * MM + b
+    constexpr bool SIGN_MASKS = R <= 32;       // signs as masks while there is room, one bit per register otherwise
     float cm[R];
-    uint32_t neg[(R + 31) / 32];         // one sign bit per register
+    uint32_t neg[SIGN_MASKS ? R : (R + 31) / 32];
 #pragma unroll
-    for (int w = 0; w < (R + 31) / 32; ++w) neg[w] = 0;
+    for (int w = 0; w < (SIGN_MASKS ? R : (R + 31) / 32); ++w) neg[w] = 0;
     const float rs = 1.0f / sqrtf((float)K);
     // loads first (all in flight together), arithmetic afterwards
     if (signs != nullptr) {
         int8_t sb[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) sb[r] = signs[(lane + 64 * (r / MM)) * MM + (r % MM)];
+        for (int r = 0; r < R; ++r) sb[r] = signs[first + (lane + 64 * (r / MM)) * MM + (r % MM)];
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if (sb[r] < 0) neg[r >> 5] |= 1u << (r & 31);
+            if (sb[r] < 0) neg[SIGN_MASKS ? r : r >> 5] |= SIGN_MASKS ? 0x80000000u : 1u << (r & 31);
     }
     if (mul != nullptr) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) cm[r] = mul[(lane + 64 * (r / MM)) * MM + (r % MM)];
+        for (int r = 0; r < R; ++r) cm[r] = mul[first + (lane + 64 * (r / MM)) * MM + (r % MM)];
         if (mul_mode) {
 #pragma unroll
             for (int r = 0; r < R; ++r) cm[r] = 1.0f / ((float)K * cm[r]);
@@ -112,7 +139,7 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
         // a lane's MM values of one a are contiguous: 8-byte (bf16) or 16-byte (f32) pieces of four values
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const size_t e0 = (size_t)row * K + (size_t)(lane + 64 * c) * MM;
+            const size_t e0 = (size_t)row * K + first + (size_t)(lane + 64 * c) * MM;
 #pragma unroll
             for (int q = 0; q < MM / 4; ++q) {
                 if constexpr (F32) {
@@ -127,35 +154,39 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
         }
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if ((neg[r >> 5] >> (r & 31)) & 1u) x[r] = -x[r];
+            x[r] = __uint_as_float(__float_as_uint(x[r]) ^ (SIGN_MASKS ? neg[r] : (neg[r >> 5] << (31 - (r & 31))) & 0x80000000u));
 
-        // H_m inside every group of MM registers: y[b'] = sum_b x[b] H[b][b'], signs known at compile time
+        // H_m inside every group of MM registers: y[b'] = sum_b x[b] H[b][b'], signs known at compile time.  The inputs are taken four at a
+        // time: up to a sign, an output needs one of the eight sums x0 +- x1 +- x2 +- x3, which cost twelve additions together and are
+        // shared by all outputs; an output adds MM / 4 of them.  5, 7 and 9 operations per element for m = 12, 20 and 28 instead of m.
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             float y[MM];
+            gen::static_for<MM / 4>([&](auto g_c) {
+                constexpr int g = decltype(g_c)::value;
+                const float *in = x + c * MM + 4 * g;
+                const float p[2] = {in[0] + in[1], in[0] - in[1]}, q[2] = {in[2] + in[3], in[2] - in[3]};
+                float t[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) t[k] = (k & 4) ? p[k & 1] - q[(k >> 1) & 1] : p[k & 1] + q[(k >> 1) & 1];
+                gen::static_for<MM>([&](auto bp_c) {
+                    constexpr int bp = decltype(bp_c)::value;
+                    const float v = t[gen::sum_of_four<MM>(g, bp)];
+                    constexpr bool minus = gen::paley_entry<MM>(4 * g, bp) < 0;
+                    // y[bp] holds the partial sum, or its negative (known at compile time)
+                    if constexpr (g == 0) y[bp] = v;
+                    else if constexpr (gen::partial_is_negated<MM>(g - 1, bp) == minus) y[bp] += v;
+                    else if constexpr (minus) y[bp] -= v;
+                    else y[bp] = v - y[bp];
+                });
+            });
             gen::static_for<MM>([&](auto bp_c) {
                 constexpr int bp = decltype(bp_c)::value;
-                float acc = 0.0f;
-                gen::static_for<MM>([&](auto b_c) {
-                    constexpr int b = decltype(b_c)::value;
-                    if constexpr (gen::paley_entry<MM>(b, bp) > 0) acc += x[c * MM + b];
-                    else acc -= x[c * MM + b];
-                });
-                y[bp] = acc;
+                x[c * MM + bp] = gen::partial_is_negated<MM>(MM / 4 - 1, bp) ? -y[bp] : y[bp];
             });
-#pragma unroll
-            for (int b = 0; b < MM; ++b) x[c * MM + b] = y[b];
         }
         // H_{2^n} over a = lane + 64 c: the six lane bits, then the bits of c
-#pragma unroll
-        for (int m = 1; m < kWave; m <<= 1) {
-            const bool upper = (lane & m) != 0;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const float p = __shfl_xor(x[r], m);
-                x[r] = upper ? p - x[r] : x[r] + p;
-            }
-        }
+        lane_butterflies(x, lane);
 #pragma unroll
         for (int h = 1; h < C; h <<= 1)
 #pragma unroll
@@ -169,6 +200,7 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                     }
                 }
 
+        if constexpr (WPR > 1) wave_butterflies(x, exchange, sub, lane);
         float amax = 0.0f;
 #pragma unroll
         for (int r = 0; r < R; ++r) { x[r] *= cm[r]; amax = fmaxf(amax, fabsf(x[r])); }
@@ -184,12 +216,16 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                 inv = delta >= kMinStep ? 1.0f / delta : 0.0f;
             } else {
                 amax = wave_max(amax);
+                if constexpr (WPR > 1) amax = max_over_4_waves(amax, red);
                 const bool live = amax >= qmax * kMinStep;
                 delta = live ? amax / qmax : 0.0f;
                 inv = live ? qmax / amax : 0.0f;
             }
-            if (lane == 0) scale[row] = delta;
+            if (lane == 0 && sub == 0) scale[row] = delta;
             const int q_hi = (int)qmax, q_lo = -q_hi - 1;
+            // a step from the row's own maximum bounds |x * inv| by qmax (1 + 2^-22): rounding cannot leave the range, and the code is the low
+            // bits of one fma.  (inv is 0 for a row without a step, or whose values overflowed: the general form gives codes 0 there.)
+            const bool bounded = step == nullptr && inv > 0.0f;
             uint8_t *out = packed + (size_t)row * (K * CB / 8);
 #pragma unroll
             for (int c = 0; c < C; ++c)
@@ -198,11 +234,11 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                     uint32_t word = 0;          // four codes: two bytes of nibbles, or four bytes
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        int qv = (int)__builtin_rintf(x[c * MM + 4 * g + i] * inv);
-                        qv = min(q_hi, max(q_lo, qv));
-                        word |= (uint32_t)(qv & ((1 << CB) - 1)) << (CB * i);
+                        const float v = x[c * MM + 4 * g + i];
+                        const uint32_t qv = bounded ? __float_as_uint(fmaf(v, inv, kRoundMagic)) : (uint32_t)min(q_hi, max(q_lo, (int)__builtin_rintf(v * inv)));
+                        word |= (qv & ((1u << CB) - 1)) << (CB * i);
                     }
-                    const size_t pos = (size_t)(lane + 64 * c) * MM + 4 * g;      // position of the first of the four codes
+                    const size_t pos = first + (size_t)(lane + 64 * c) * MM + 4 * g;      // position of the first of the four codes
                     if constexpr (CB == 4) *reinterpret_cast<uint16_t *>(out + pos / 2) = (uint16_t)word;
                     else *reinterpret_cast<uint32_t *>(out + pos) = word;
                 }
@@ -213,7 +249,7 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
             // non-negative floats order like their bit patterns
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                atomicMax(&col_absmax_bits[(lane + 64 * (r / MM)) * MM + (r % MM)], __float_as_uint(colmax[r]));
+                atomicMax(&col_absmax_bits[first + (lane + 64 * (r / MM)) * MM + (r % MM)], __float_as_uint(colmax[r]));
         }
     }
 }
@@ -234,9 +270,10 @@ static hipError_t launch_general(const void *X, bool f32, int rows, const int8_t
                                  int bits, hipStream_t stream)
 {
     if (rows <= 0) return hipSuccess;
-    int blocks = (rows + 3) / 4;
+    constexpr int ROWS = 4 / gen::waves_per_row(N2, MM);            // rows a block has in work
+    int blocks = (rows + ROWS - 1) / ROWS;
     if (blocks > 256 * 8) blocks = 256 * 8;
-    if (colmax != nullptr) blocks = std::max(1, std::min((rows + 31) / 32, 256 * 2));   // eight rows or more per wave for the statistic
+    if (colmax != nullptr) blocks = std::max(1, std::min((rows + 8 * ROWS - 1) / (8 * ROWS), 256 * 2));   // eight rows or more per wave for the statistic
     const float qmax = (float)((1 << (code_width(bits) - 1)) - 1);
 #define QVGGT_GEN(F32_, MODE_, CB_) \
     rotate_rows_general_kernel<N2, MM, F32_, MODE_, CB_><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, qmax)

@@ -69,16 +69,7 @@ __device__ inline void fwht_row(float (&x)[RowMap<K>::R], int lane)
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if ((r & h) == 0) { float a = x[r], b = x[r + h]; x[r] = a + b; x[r + h] = a - b; }
-    // the six lane bits
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
-        const bool upper = (lane & m) != 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            float p = __shfl_xor(x[r], m);
-            x[r] = upper ? p - x[r] : x[r] + p;
-        }
-    }
+    lane_butterflies(x, lane);
     // chunk bits
 #pragma unroll
     for (int h = V; h < R; h <<= 1)

@@ -365,3 +365,32 @@ def test_rotated_col_absmax(K, rows, dtype):
         # a column's maximum can be a small number left by cancellation (one row: it is the rotated value itself), so the
         # fp32 butterflies are held to the row's magnitude as well as to the value: |err| <= 1e-5 |want| + 2e-6 max|want|
         assert np.allclose(a.cpu().numpy(), want, rtol=G.SCALE_RTOL, atol=2e-6 * want.max()), f"K={K} rows={rows}"
+
+
+@pytest.mark.parametrize("K", [128, 512, 1024, 8192, 768, 5120, 6144, 3584])
+@pytest.mark.parametrize("static", [False, True])
+def test_row_kernels_special_rows(K, static):
+    """Rows that have no code range among ordinary ones, f32, more rows than the grid has waves at the wide sizes: zeros, a NaN, an
+    infinity and values that overflow in the transform give codes 0 under a dynamic step (a given step keeps its ordinary rows);
+    the others are the oracle's."""
+    rows = 2100 if K >= 5120 else 67
+    rng = np.random.default_rng(K)
+    X = rng.standard_t(3, (rows, K)).astype(np.float32)
+    bad = {3: 0.0, 7: np.nan, 11: np.inf, rows - 2: 3e38}
+    for r, v in bad.items():
+        X[r] = 0.0 if v == 0.0 else X[r]
+        X[r, K // 2 :: 3] = v
+    signs = (rng.integers(0, 2, K) * 2 - 1).astype(np.int8)
+    good = np.setdiff1d(np.unique(np.concatenate([np.arange(40), rng.integers(0, rows, 24), [rows - 1]])), list(bad))
+    dx, qx, Z = oracle.rotate_smooth_quant(X[good], np.ones(K), pre_signs=signs)
+    if static:
+        step = np.full(rows, np.median(dx) * 0.6, dtype=np.float32)
+        qx = oracle.quantize_rows_static(Z, step[good].astype(np.float64), 4)
+        Xq, sx = G.gpu_rsq_static(G.to_dev(X), G.to_dev(signs), None, G.to_dev(step), 1)
+    else:
+        Xq, sx = G.gpu_rsq(G.to_dev(X), G.to_dev(signs), None)
+    codes = G.gpu_unpack(Xq, K)
+    G.check_codes(codes[good], qx, f"K={K}")
+    if not static:
+        G.check_scales(sx.cpu().numpy()[good], dx, f"K={K}")
+        assert not codes[list(bad)].any()
