@@ -513,13 +513,15 @@ static CalibPlan calib_plan(int T, int N, int K)
     return p;
 }
 
-// workspace: codes of both operands [Tp + Np, Kp] bf16, their steps [Tp + Np], E [Tp, Np], partial sums
+// workspace: codes of both operands [Tp + Np, Kp] bf16, their steps [Tp + Np], E [Tp, Np], partial sums.  The size asked for is never below
+// that of fp32 copies of both operands, both products and E: what a caller may have set aside by the method's own quantities.
 size_t calib_workspace_bytes(int T, int N, int K)
 {
     const CalibPlan p = calib_plan(T, N, K);
-    return align256((size_t)(p.Tp + p.Np) * p.Kp * 2) + align256((size_t)(p.Tp + p.Np) * 4) + align256((size_t)p.Tp * p.Np * 4) +
-           align256(((size_t)p.tm * p.split_x + (size_t)p.tn * p.split_w) * p.Kp * 4) + align256((size_t)p.tj * p.split_w * p.Np * 4) +
-           align256((size_t)p.items_x * 4) + align256((size_t)p.tm * p.tn * 4);
+    const size_t own = align256((size_t)(p.Tp + p.Np) * p.Kp * 2) + align256((size_t)(p.Tp + p.Np) * 4) + align256((size_t)p.Tp * p.Np * 4) +
+                       align256(((size_t)p.tm * p.split_x + (size_t)p.tn * p.split_w) * p.Kp * 4) + align256((size_t)p.tj * p.split_w * p.Np * 4) +
+                       align256((size_t)p.items_x * 4) + align256((size_t)p.tm * p.tn * 4);
+    return std::max(own, 4 * (2 * (size_t)T * K + 2 * (size_t)N * K + (size_t)T * N));
 }
 
 hipError_t run_calib_loss_grad(const float *R, const float *V, const float *y_ref, const void *bias, const float *c_hat,
