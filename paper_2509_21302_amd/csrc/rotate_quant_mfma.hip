@@ -72,7 +72,7 @@ __device__ inline uint32_t gelu_window(uint32_t w)      // both halves of a pack
 // signed 16-bit number steps through each half in bytes and jumps by 64 KiB at the sign, so the byte offset of either half of a
 // packed pair is ONE instruction, 2 * signed half + constant.  (With the halves next to each other the offset took five shifts and
 // masks per pair and two more to take it apart; the waves' staging areas fill the gap.)  The lookups themselves, 64 per lane and tile,
-// are bound by LDS bank conflicts: 32976 x 4096 takes 75 us on one repeated value, 104 us on N(0, 0.64) (88 and 105 us before).
+// are bound by LDS bank conflicts: 32976 x 4096 takes 76 us on one repeated value, 98 us on N(0, 0.64) (87 and 104 us before).
 constexpr int GELU_HALF_BYTES = 2 * 4096, GELU_NEG = 0, GELU_POS = 65536, GELU_LDS_BYTES = GELU_POS + GELU_HALF_BYTES;
 constexpr int GELU_OFFSET = GELU_POS - 2 * (int)GELU_U0;
 // both halves covered by the table (the usual case): two lookups
@@ -308,9 +308,11 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
         for (int nt = 0; nt < 4; ++nt) cmax[h][nt] = 0.0f;
 
     for (; (BLOCK_FLUSH ? tile - wave_in_block : tile) < ntiles; tile += nwaves) {
+        // From here to the last MFMA a wave waits on LDS and the matrix pipe and issues little: it goes first, and the other wave of the
+        // SIMD has the vector ALU for its butterflies and codes.  137400 x 4096: 279 -> 271 us, 32976 x 4096: 65.9 -> 64.7; K = 1024 the
+        // same.  (Up to the staging only: 289 us; around the MFMAs only: 282.)
+        __builtin_amdgcn_s_setprio(3);
         if constexpr (GELU) {
-            // the lookups first: a wave in them waits on the LDS and leaves the vector ALU to the other wave of its SIMD
-            __builtin_amdgcn_s_setprio(3);
             // one wave-uniform test per tile: is every value inside the table's window?  (Almost always: outside are exact
             // zeros, |x| < 1e-6 and |x| >= 4096.)  Then two lookups per packed pair; otherwise the general form per value.
             // (a half is inside iff bits 12..14 of its offset from the window's start are zero: OR them all and look once)
@@ -382,7 +384,6 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
             const int row_hi = rq::row_of_seg_hi<K>(j);
             *reinterpret_cast<uint4 *>(lds + row_hi * rq::LDS_PITCH + wr_base) = v;
         }
-        if constexpr (GELU) __builtin_amdgcn_s_setprio(0);
         lanes_exchange_fence();     // the MFMA operand reads below take what other lanes staged
         // shift the prefetch queue and issue the loads of the tile PF steps ahead
 #pragma unroll
@@ -408,6 +409,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
             }
         }
 
+        __builtin_amdgcn_s_setprio(0);
         // H_{K/128} over the hi-block index: butterflies between accumulator registers
         constexpr int REG_STAGES = (REM >= 4) ? 4 : 3;
 #pragma unroll
