@@ -580,7 +580,8 @@ static hipError_t launch_gemm_tail(const uint8_t *Xq, const float *sx, const uin
 //          (2064 tiles are 4.03 rounds of 512, not 5), and a tile costs 1.0 of a quarter of a big one at K = 128, 1.14 at 1024, 1.4 at 4096
 //          (int8 codes: 1.2 and 1.75), the LDS traffic per MFMA being twice as much.
 //   deep   128 x 128 tiles, one block per compute unit with an eight-stage ring: for at most 256 of them, where a tile's time is its chain of
-//          transfers (int8 codes, 1374 x 4096 -> 1024: 31 -> 16 us; packed codes 22 -> 18 us for 700 x 4096 -> 4096).
+//          transfers (int8 codes, 1374 x 4096 -> 1024: 31 -> 16 us; packed codes 22 -> 18 us for 700 x 4096 -> 4096).  From four K-tiles on:
+//          with fewer the ring is filled with re-reads (64 x 128 -> 128: 4.8 us against 3.9).
 //   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch.
 // Measured (us, big / small / tail; what ran before is in brackets): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1 [39.3],
 // 32976 x 256 -> 3072 56 / 50 / 55 [56], 32976 x 1024 -> 1024 50 / 40 / 45 [47], 32976 x 4096 -> 1024 137 / 130 / 113 [121];
@@ -603,7 +604,8 @@ static hipError_t gemm_by_rounds(const uint8_t *Xq, const float *sx, const uint8
     const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
     const double big_tiles = (double)tiles_m * tiles_n;
 
-    if (tiles128(M) <= 256.0) return QVGGT_ROWS(2, 2, 8, 1, 0, M);
+    const int ktiles = (CB == 4 ? K / 2 : K) / KT_BYTES;
+    if (tiles128(M) <= 256.0 && ktiles >= 4) return QVGGT_ROWS(2, 2, 8, 1, 0, M);
     const double big_cost = rounds(big_tiles) * big_round;
     const double small_cost = tiles128(M) / 512.0 * small_share * big_round + 3.0;
     // whole tile rows that fit into the full rounds
