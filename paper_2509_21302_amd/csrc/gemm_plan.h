@@ -1,0 +1,58 @@
+// Which tile configuration of the int8-instruction GEMM runs where: a function of the problem's sizes alone, on the host and without HIP,
+// so that it can be looked at without a GPU.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+
+namespace qvggt {
+
+struct GemmPlan {
+    enum Shape { kBig, kSmall, kDeep, kBigThenDeep } shape;
+    int rows_main;      // kBigThenDeep: the token rows (whole 256-row tiles) that go to the big tiles
+};
+
+// The plan that the model below prices lowest, in microseconds.  Rows are independent, so token rows can be divided between configurations.
+//   big    256 x 256 tiles, one per compute unit: whole rounds of 256, a last one that is mostly empty costs as much as a full one.
+//   small  128 x 128 tiles, two blocks per compute unit, one's epilogue under the other's K loop: while all compute units have two, the cost
+//          follows the number of tiles (packed codes, 10992 x 768 -> 3072: 2064 tiles are 4.03 rounds of 512, not 5), and a tile costs 1.0 of a
+//          quarter of a big one at K = 128, 1.14 at 1024, 1.4 at 4096 (int8 codes: 1.2 and 1.75), the LDS traffic per MFMA being twice as
+//          much.  The tiles left after whole rounds run alone on their compute units: as a share of a round they cost at least
+//          LAST_ROUND however few they are (int8 blocks at K = 2048: 484 tiles 21 us, 540 tiles 34, 836 tiles 36; at K = 4096: 475 tiles 35,
+//          519 tiles 62, 830 tiles 66).
+//   deep   128 x 128 tiles, one block per compute unit with an eight-stage ring: for at most 256 of them, where a tile's time is its chain of
+//          transfers (int8 codes, 1374 x 4096 -> 1024: 31 -> 16 us; packed codes 22 -> 18 us for 700 x 4096 -> 4096).  From four K-tiles on:
+//          with fewer the ring is filled with re-reads (64 x 128 -> 128: 4.8 us against 3.9).
+//   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch.
+// Measured (us, big / small / tail): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1, 32976 x 256 -> 3072 56 / 50 / 55,
+// 32976 x 1024 -> 1024 50 / 40 / 45, 32976 x 4096 -> 1024 137 / 130 / 113; int8 blocks 32976 x 4096 -> 1024 140 / 156 / 118,
+// 20000 x 4096 -> 1024 89 / 92 / 71; just past one round of small tiles (big / small) int8 rows 9591 x 4096 -> 896 43 / 66,
+// int8 blocks 22039 x 4096 -> 304 45 / 62, 2247 x 2048 -> 4256 27 / 36, packed codes 39144 x 5120 -> 160 48 / 55.
+// affine and dump: affine activation codes, the accumulator dump (their two tile loops do not fit the registers together: two launches).
+inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, bool affine, bool dump)
+{
+    auto tiles = [&](int rows, int size) { return (double)((rows + size - 1) / size) * ((N + size - 1) / size); };
+    auto rounds = [](double t) { return std::ceil(t / 256.0); };
+    const bool packed = code_bits == 4;
+    const double k = K / 1024.0;
+    const double big_round = 5.0 + (packed ? 11.0 : 12.0) * k, deep_round = 8.0 + 3.7 * k;
+    const double small_share = 0.50 + (packed ? 0.055 : 0.095) * k;          // of a big round, for 512 small tiles
+    const double LAST_ROUND = packed ? 0.3 : 0.5;
+    const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256, ktiles = K * code_bits / (8 * 64);
+
+    if (tiles(M, 128) <= 256.0 && ktiles >= 4) return {GemmPlan::kDeep, 0};
+    const double big_cost = rounds(tiles(M, 256)) * big_round;
+    const double small_rounds = tiles(M, 128) / 512.0, whole = std::floor(small_rounds), rest = small_rounds - whole;
+    const double small_cost = (whole + (whole > 0.0 && rest > 0.0 ? std::max(rest, LAST_ROUND) : rest)) * small_share * big_round + 3.0;
+    // whole tile rows that fit into the full rounds
+    const int main_tile_rows = (int)std::min<double>(tiles_m, std::floor(tiles(M, 256) / 256.0) * 256.0 / tiles_n);
+    if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
+        const int rows_main = main_tile_rows * 256;
+        const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + rounds(tiles(M - rows_main, 128)) * deep_round +
+                                 (affine || dump ? 6.0 : 0.0);
+        if (tail_cost < 0.97 * std::min(big_cost, small_cost)) return {GemmPlan::kBigThenDeep, rows_main};
+    }
+    return {small_cost < big_cost ? GemmPlan::kSmall : GemmPlan::kBig, 0};
+}
+
+}  // namespace qvggt

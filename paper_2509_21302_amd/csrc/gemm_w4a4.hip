@@ -38,10 +38,10 @@
 // next pair of K-steps and the expansion of the next K-step's fragments are dealt out one
 // piece per MFMA, fenced so that the compiler keeps the interleave: the vector ALU and LDS
 // work runs in the shadow of the matrix pipe.
+#include "gemm_plan.h"
 #include "qvggt_common.h"
 
 #include <algorithm>
-#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -573,59 +573,30 @@ static hipError_t launch_gemm_tail(const uint8_t *Xq, const float *sx, const uin
     return hipGetLastError();
 }
 
-// Which tile shape runs where: the plan that the model below prices lowest, in microseconds.  Rows are independent, so token rows can be
-// divided between configurations.
-//   big    256 x 256 tiles, one per compute unit: whole rounds of 256, a last one that is mostly empty costs as much as a full one.
-//   small  128 x 128 tiles, two blocks per compute unit, one's epilogue under the other's K loop: the cost follows the number of tiles
-//          (2064 tiles are 4.03 rounds of 512, not 5), and a tile costs 1.0 of a quarter of a big one at K = 128, 1.14 at 1024, 1.4 at 4096
-//          (int8 codes: 1.2 and 1.75), the LDS traffic per MFMA being twice as much.
-//   deep   128 x 128 tiles, one block per compute unit with an eight-stage ring: for at most 256 of them, where a tile's time is its chain of
-//          transfers (int8 codes, 1374 x 4096 -> 1024: 31 -> 16 us; packed codes 22 -> 18 us for 700 x 4096 -> 4096).  From four K-tiles on:
-//          with fewer the ring is filled with re-reads (64 x 128 -> 128: 4.8 us against 3.9).
-//   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch.
-// Measured (us, big / small / tail; what ran before is in brackets): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1 [39.3],
-// 32976 x 256 -> 3072 56 / 50 / 55 [56], 32976 x 1024 -> 1024 50 / 40 / 45 [47], 32976 x 4096 -> 1024 137 / 130 / 113 [121];
-// int8 blocks 32976 x 4096 -> 1024 140 / 156 / 118 [135], 20000 x 4096 -> 1024 89 / 92 / 71 [85].
+// The tile shapes that the plan of gemm_plan.h names, over the token rows it gives them.
 template <int CB, bool ASYM = false, bool BLK = false>
-static hipError_t gemm_by_rounds(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw, const void *bias,
-                                 int M, int N, int K, void *Y, int32_t *acc_debug, hipStream_t stream,
-                                 const float *xzero = nullptr, const float *wsum = nullptr)
+static hipError_t gemm_by_plan(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw, const void *bias,
+                               int M, int N, int K, void *Y, int32_t *acc_debug, hipStream_t stream,
+                               const float *xzero = nullptr, const float *wsum = nullptr)
 {
 #define QVGGT_ROWS(TM, TN, ST, MB, row0, rows)                                                                                           \
     launch_gemm<TM, TN, 2, 2, ST, MB, CB, ASYM, BLK>(Xq + (size_t)(row0) * (CB == 4 ? K / 2 : K), sx + (row0), Wq, sw, bias, rows, N, K, \
                                                      static_cast<uint16_t *>(Y) + (size_t)(row0) * N,                                    \
                                                      acc_debug ? acc_debug + (size_t)(row0) * N : nullptr, stream,                       \
                                                      ASYM ? xzero + (row0) : nullptr, wsum)
-    auto tiles128 = [&](int rows) { return (double)((rows + 127) / 128) * ((N + 127) / 128); };
-    auto rounds = [](double tiles) { return std::ceil(tiles / 256.0); };
-    const double k = K / 1024.0;
-    const double big_round = 5.0 + (CB == 4 ? 11.0 : 12.0) * k, deep_round = 8.0 + 3.7 * k;
-    const double small_share = 0.50 + (CB == 4 ? 0.055 : 0.095) * k;         // of a big round, for 512 small tiles
-    const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
-    const double big_tiles = (double)tiles_m * tiles_n;
-
-    const int ktiles = (CB == 4 ? K / 2 : K) / KT_BYTES;
-    if (tiles128(M) <= 256.0 && ktiles >= 4) return QVGGT_ROWS(2, 2, 8, 1, 0, M);
-    const double big_cost = rounds(big_tiles) * big_round;
-    const double small_cost = tiles128(M) / 512.0 * small_share * big_round + 3.0;
-    // whole tile rows that fit into the full rounds
-    const int main_tile_rows = (int)std::min<double>(tiles_m, std::floor(big_tiles / 256.0) * 256.0 / tiles_n);
-    const int rows_main = main_tile_rows * 256;
-    if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
-        // the accumulator dump and affine codes (whose two tile loops do not fit the registers together) take a second launch for the rest
-        const bool one_launch = !ASYM && acc_debug == nullptr;
-        const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + rounds(tiles128(M - rows_main)) * deep_round +
-                                 (one_launch ? 0.0 : 6.0);
-        if (tail_cost < 0.97 * std::min(big_cost, small_cost)) {
-            if constexpr (!ASYM) {
-                if (one_launch) return launch_gemm_tail<CB, BLK>(Xq, sx, Wq, sw, bias, M, rows_main, N, K, Y, stream);
-            }
-            const hipError_t e = QVGGT_ROWS(4, 4, 4, 1, 0, rows_main);
-            if (e != hipSuccess) return e;
-            return QVGGT_ROWS(2, 2, 8, 1, rows_main, M - rows_main);
-        }
+    const GemmPlan plan = int8_instruction_gemm_plan(M, N, K, CB, ASYM, acc_debug != nullptr);
+    switch (plan.shape) {
+        case GemmPlan::kBig: return QVGGT_ROWS(4, 4, 4, 1, 0, M);
+        case GemmPlan::kSmall: return QVGGT_ROWS(2, 2, 3, 2, 0, M);
+        case GemmPlan::kDeep: return QVGGT_ROWS(2, 2, 8, 1, 0, M);
+        case GemmPlan::kBigThenDeep: break;
     }
-    return small_cost < big_cost ? QVGGT_ROWS(2, 2, 3, 2, 0, M) : QVGGT_ROWS(4, 4, 4, 1, 0, M);
+    if constexpr (!ASYM) {
+        if (acc_debug == nullptr) return launch_gemm_tail<CB, BLK>(Xq, sx, Wq, sw, bias, M, plan.rows_main, N, K, Y, stream);
+    }
+    const hipError_t e = QVGGT_ROWS(4, 4, 4, 1, 0, plan.rows_main);
+    if (e != hipSuccess) return e;
+    return QVGGT_ROWS(2, 2, 8, 1, plan.rows_main, M - plan.rows_main);
 #undef QVGGT_ROWS
 }
 
@@ -633,7 +604,7 @@ hipError_t run_w4a4_gemm(const uint8_t *Xq, const float *sx, const uint8_t *Wq, 
                          const void *bias, int M, int N, int K, void *Y, int32_t *acc_debug, hipStream_t stream)
 {
     if (M <= 0) return hipSuccess;
-    return gemm_by_rounds<4>(Xq, sx, Wq, sw, bias, M, N, K, Y, acc_debug, stream);
+    return gemm_by_plan<4>(Xq, sx, Wq, sw, bias, M, N, K, Y, acc_debug, stream);
 }
 
 // Packed 4-bit codes with affine activations: Xq holds u - 8, xzero the zero points, wsum the weights' code sums per channel.
@@ -641,7 +612,7 @@ hipError_t run_w4a4_gemm_asym(const uint8_t *Xq, const float *sx, const float *x
                               const float *wsum, const void *bias, int M, int N, int K, void *Y, hipStream_t stream)
 {
     if (M <= 0) return hipSuccess;
-    return gemm_by_rounds<4, true>(Xq, sx, Wq, sw, bias, M, N, K, Y, nullptr, stream, xzero, wsum);
+    return gemm_by_plan<4, true>(Xq, sx, Wq, sw, bias, M, N, K, Y, nullptr, stream, xzero, wsum);
 }
 
 // The same kernel on int8 codes (8- and 6-bit settings): rows of K bytes, no expansion, two K-steps per K-tile.
@@ -650,7 +621,7 @@ hipError_t run_i8_gemm(const int8_t *Xq, const float *sx, const int8_t *Wq, cons
 {
     if (M <= 0) return hipSuccess;
     const uint8_t *xq = reinterpret_cast<const uint8_t *>(Xq), *wq = reinterpret_cast<const uint8_t *>(Wq);
-    return gemm_by_rounds<8>(xq, sx, wq, sw, bias, M, N, K, Y, acc_debug, stream);
+    return gemm_by_plan<8>(xq, sx, wq, sw, bias, M, N, K, Y, acc_debug, stream);
 }
 
 // int8 codes in 128-row blocks (see the kernel): whole tile rows go to either launch, so row offsets stay whole blocks
@@ -658,7 +629,7 @@ hipError_t run_i8b_gemm(const int8_t *Xb, const float *sx, const int8_t *Wb, con
                         int K, void *Y, int32_t *acc_debug, hipStream_t stream)
 {
     if (M <= 0) return hipSuccess;
-    return gemm_by_rounds<8, false, true>(reinterpret_cast<const uint8_t *>(Xb), sx, reinterpret_cast<const uint8_t *>(Wb), sw, bias,
+    return gemm_by_plan<8, false, true>(reinterpret_cast<const uint8_t *>(Xb), sx, reinterpret_cast<const uint8_t *>(Wb), sw, bias,
                                           M, N, K, Y, acc_debug, stream);
 }
 

@@ -1,0 +1,46 @@
+"""The plan of the int8-instruction GEMM (csrc/gemm_plan.h), compiled for the host: which tile configuration a problem gets."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_21302_amd", "csrc")
+DRIVER = r"""
+#include "gemm_plan.h"
+#include <cstdio>
+int main()
+{
+    int M, N, K, bits, affine, dump;
+    while (std::scanf("%d %d %d %d %d %d", &M, &N, &K, &bits, &affine, &dump) == 6) {
+        const qvggt::GemmPlan p = qvggt::int8_instruction_gemm_plan(M, N, K, bits, affine, dump);
+        std::printf("%s %d\n", p.shape == p.kBig ? "big" : p.shape == p.kSmall ? "small" : p.shape == p.kDeep ? "deep" : "big+deep", p.rows_main);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    """plans([(M, N, K, bits, affine, dump), ...]) -> [(shape, rows of the big tiles), ...]"""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    folder = tmp_path_factory.mktemp("gemm_plan")
+    src, exe = folder / "driver.cpp", folder / "driver"
+    src.write_text(DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", exe, src], check=True)
+
+    def ask(problems):
+        text = "\n".join(" ".join(str(int(v)) for v in p) for p in problems)
+        lines = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")[:-1]
+        assert len(lines) == len(problems)
+        return [(s, int(r)) for s, r in (line.split() for line in lines)]
+    return ask
+
+
+# one round of 256 big tiles holds them, and one of 512 small tiles does not quite: measured 1.1 to 1.5 times slower in small tiles
+@pytest.mark.parametrize("M,N,K,bits", [(9591, 896, 4096, 8), (22039, 304, 4096, 8), (6388, 1376, 2048, 8), (2247, 4256, 2048, 8), (20356, 400, 2048, 8),
+                                        (9214, 1120, 1280, 8), (39144, 160, 5120, 4)])
+def test_just_past_a_round_of_small_tiles(plans, M, N, K, bits):
+    assert plans([(M, N, K, bits, 0, 0)]) == [("big", 0)]
