@@ -22,10 +22,11 @@ struct GemmPlan {
 //          519 tiles 62, 830 tiles 66).
 //   deep   128 x 128 tiles, one block per compute unit with an eight-stage ring: for at most 256 of them, where a tile's time is its chain of
 //          transfers (int8 codes, 1374 x 4096 -> 1024: 31 -> 16 us; packed codes 22 -> 18 us for 700 x 4096 -> 4096).  Filling the longer ring
-//          costs 0.4 us, which the chain has to be long enough to pay back: from DEEP_KTILES on, that is K = 3584 (packed codes, small /
-//          deep for 509 rows -> 1024: 7.4 / 7.7 us at K = 1024, 10.3 / 10.5 at 2048, 13.2 / 13.2 at 3072; 953 rows -> 2896 20.1 / 16.8 at 3584, 2045 rows -> 2048 22.1 / 18.8 at
-//          4096), 1024 with affine codes (their larger scale area: 1 to 2 % at 1024, 4 % at 4096) and 1024 with int8 codes (5.9 / 6.1 at
-//          512, 6.8 / 6.7 at 768, but 8.4 / 8.7 for 2045 rows -> 2048 there, 7.6 / 7.3 at 1024, 10.5 / 9.8 at 2048).
+//          costs 0.2 to 0.4 us, which the chain has to be long enough to pay back.  Packed codes, small / deep: 509 rows -> 1024 (32 tiles) 7.4 /
+//          7.7 us at K = 1024, 10.3 / 10.5 at 2048, 13.2 / 13.2 at 3072, 16.1 / 16.2 at 4096, 22.5 / 22.0 at 6144; with more tiles two
+//          small ones meet on a compute unit: 953 rows -> 2896 (184 tiles) 20.1 / 16.8 at 3584, 1021 -> 2048 (128) 21.4 / 17.4 at 4096.
+//          Affine codes, whose scale area is larger, gain 1 to 2 % at K = 1024 and 4 % at 4096.  int8 codes: 509 rows -> 1024 5.9 / 6.1
+//          at K = 512, 6.8 / 6.7 at 768 (but 2045 rows -> 2048 8.4 / 8.7), 7.6 / 7.3 at 1024, 10.5 / 9.8 at 2048.
 //   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch.
 // Measured (us, big / small / tail): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1, 32976 x 256 -> 3072 56 / 50 / 55,
 // 32976 x 1024 -> 1024 50 / 40 / 45, 32976 x 4096 -> 1024 137 / 130 / 113; int8 blocks 32976 x 4096 -> 1024 140 / 156 / 118,
@@ -43,10 +44,11 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
     const double LAST_ROUND = packed ? 0.3 : 0.5;
     const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256, ktiles = K * code_bits / (8 * 64);
 
-    const int DEEP_KTILES = packed ? (affine ? 8 : 28) : 16;
-    if (tiles(M, 128) <= 256.0 && ktiles >= DEEP_KTILES) return {GemmPlan::kDeep, 0};
+    const double small_tiles = tiles(M, 128);
+    const bool long_chain = !packed ? ktiles >= 16 : affine ? ktiles >= 8 : ktiles >= 28 && ktiles + small_tiles / 8.0 >= 40.0;
+    if (small_tiles <= 256.0 && long_chain) return {GemmPlan::kDeep, 0};
     const double big_cost = rounds(tiles(M, 256)) * big_round;
-    const double small_rounds = tiles(M, 128) / 512.0, whole = std::floor(small_rounds), rest = small_rounds - whole;
+    const double small_rounds = small_tiles / 512.0, whole = std::floor(small_rounds), rest = small_rounds - whole;
     const double small_cost = (whole + (whole > 0.0 && rest > 0.0 ? std::max(rest, LAST_ROUND) : rest)) * small_share * big_round + 3.0;
     // whole tile rows that fit into the full rounds
     const int main_tile_rows = (int)std::min<double>(tiles_m, std::floor(tiles(M, 256) / 256.0) * 256.0 / tiles_n);

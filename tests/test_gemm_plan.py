@@ -49,7 +49,7 @@ def test_just_past_a_round_of_small_tiles(plans, M, N, K, bits):
 # few tiles: the deep ring only where a tile's chain is long enough to pay for filling it (measured 3 to 7 % slower on the left ones)
 @pytest.mark.parametrize("M,N,K,bits,affine,want", [
     (1422, 192, 512, 4, 0, "small"), (18, 768, 1024, 4, 0, "small"), (211, 144, 1536, 4, 0, "small"), (19930, 64, 256, 8, 0, "small"),
-    (1600, 432, 512, 8, 0, "small"), (30, 64, 768, 8, 0, "small"), (953, 2896, 3584, 4, 0, "deep"), (2048, 2048, 4096, 4, 0, "deep"),
+    (1600, 432, 512, 8, 0, "small"), (30, 64, 768, 8, 0, "small"), (953, 2896, 3584, 4, 0, "deep"), (125, 80, 3072, 4, 0, "small"), (68, 3456, 4096, 4, 0, "small"), (21, 16, 6144, 4, 0, "deep"), (2048, 2048, 4096, 4, 0, "deep"),
     (372, 1312, 4096, 4, 1, "deep"), (20, 464, 1024, 4, 1, "deep"), (1374, 1024, 4096, 8, 0, "deep"), (360, 3696, 1024, 8, 0, "deep")])
 def test_deep_ring_needs_a_long_chain(plans, M, N, K, bits, affine, want):
     assert plans([(M, N, K, bits, affine, 0)]) == [(want, 0)]
