@@ -27,7 +27,8 @@ struct GemmPlan {
 //          small ones meet on a compute unit: 953 rows -> 2896 (184 tiles) 20.1 / 16.8 at 3584, 1021 -> 2048 (128) 21.4 / 17.4 at 4096.
 //          Affine codes, whose scale area is larger, gain 1 to 2 % at K = 1024 and 4 % at 4096.  int8 codes: 509 rows -> 1024 5.9 / 6.1
 //          at K = 512, 6.8 / 6.7 at 768 (but 2045 rows -> 2048 8.4 / 8.7), 7.6 / 7.3 at 1024, 10.5 / 9.8 at 2048.
-//   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch.
+//   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch (us, big / small / tail): packed codes
+//          17354 x 4096 -> 1184 87 / 89 / 80, 113324 x 768 -> 672 86 / 81 / 72; int8 rows 34003 x 2048 -> 480 53 / 53 / 43.
 // Measured (us, big / small / tail): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1, 32976 x 256 -> 3072 56 / 50 / 55,
 // 32976 x 1024 -> 1024 50 / 40 / 45, 32976 x 4096 -> 1024 137 / 130 / 113; int8 blocks 32976 x 4096 -> 1024 140 / 156 / 118,
 // 20000 x 4096 -> 1024 89 / 92 / 71; just past one round of small tiles (big / small) int8 rows 9591 x 4096 -> 896 43 / 66,
@@ -39,7 +40,7 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
     auto rounds = [](double t) { return std::ceil(t / 256.0); };
     const bool packed = code_bits == 4;
     const double k = K / 1024.0;
-    const double big_round = 5.0 + (packed ? 11.0 : 12.0) * k, deep_round = 8.0 + 3.7 * k;
+    const double big_round = 5.0 + (packed ? 11.0 : 12.0) * k, deep_round = 7.0 + 3.7 * k;
     const double small_share = 0.50 + (packed ? 0.055 : 0.095) * k;          // of a big round, for 512 small tiles
     const double LAST_ROUND = packed ? 0.3 : 0.5;
     const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256, ktiles = K * code_bits / (8 * 64);
@@ -55,8 +56,8 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
     if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
         const int rows_main = main_tile_rows * 256;
         const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + rounds(tiles(M - rows_main, 128)) * deep_round +
-                                 (affine || dump ? 6.0 : 0.0);
-        if (tail_cost < 0.97 * std::min(big_cost, small_cost)) return {GemmPlan::kBigThenDeep, rows_main};
+                                 (affine || dump ? 3.0 : 0.0);
+        if (tail_cost < std::min(big_cost, small_cost)) return {GemmPlan::kBigThenDeep, rows_main};
     }
     return {small_cost < big_cost ? GemmPlan::kSmall : GemmPlan::kBig, 0};
 }
