@@ -53,7 +53,7 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
     const double small_cost = (whole + (whole > 0.0 && rest > 0.0 ? std::max(rest, LAST_ROUND) : rest)) * small_share * big_round + 3.0;
     // whole tile rows that fit into the full rounds
     const int main_tile_rows = (int)std::min<double>(tiles_m, std::floor(tiles(M, 256) / 256.0) * 256.0 / tiles_n);
-    if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
+    if (main_tile_rows > 0 && main_tile_rows < tiles_m && ktiles >= 4) {        // the eight-stage ring needs three, and with few is filled with re-reads
         const int rows_main = main_tile_rows * 256;
         const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + rounds(tiles(M - rows_main, 128)) * deep_round +
                                  (affine || dump ? 3.0 : 0.0);

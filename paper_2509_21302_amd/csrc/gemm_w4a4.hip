@@ -71,6 +71,9 @@ struct StreamCfg {
     static constexpr int EP_PITCH = 128 + 16;           // bytes per token row of a wave's epilogue staging tile (64 channels + pad)
     static constexpr int EP_BYTES = NW * 32 * EP_PITCH;
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + 2 * SC_BYTES + EP_BYTES;
+    // A tile's scales are sent for during the first K-tile of the tile before, and 2 ktiles - 1 K-tiles' transfers follow before the last wait
+    // ahead of their use, which lets STAGES - 3 K-tiles' be outstanding: with fewer K-tiles it would not cover them
+    static constexpr int MIN_KTILES = (STAGES - 1) / 2;
     static_assert(TN % 2 == 0, "the epilogue handles channel sub-tiles in pairs");
     static_assert(GROUPS % NW == 0, "16-row groups do not divide among the waves");
     static_assert(BM % 128 == 0 && BN % 128 == 0, "scale transfers assume multiples of 128");
@@ -382,14 +385,6 @@ __device__ __forceinline__ void w4a4_tiles(
         };
         ktile(BT{});
         for (int kt = 1; kt < ktiles; ++kt) ktile(BF{});
-        // The scales were sent for during the first K-tile of the tile before; 2 ktiles - 1 K-tiles' transfers have followed before the
-        // last wait above, which lets STAGES - 3 K-tiles' be outstanding.  With few K-tiles and a deep ring that does not cover them.
-        if constexpr (STAGES > 4) {
-            if (2 * ktiles - 1 < STAGES - 3) {
-                wait_vmcnt<0>();
-                __syncthreads();
-            }
-        }
 
         // ---- epilogue.  32x32 result layout: lane l holds column (l % 32) = token and rows 8*(r/4) + 4*(l/32) + r%4 = channels,
         // i.e. per register quad q four consecutive channels 8q + 4*(l/32) + 0..3.  Scale + bias + bf16 in registers.
@@ -551,6 +546,7 @@ static hipError_t launch_gemm(const uint8_t *Xq, const float *sx, const uint8_t 
     } else {
         if (debug) return hipErrorInvalidValue;      // no accumulator dump with affine codes: the corrected sum is never an integer register
     }
+    if ((CB == 4 ? K / 2 : K) / KT_BYTES < C::MIN_KTILES) return hipErrorInvalidValue;      // no plan asks for it
     hipError_t e = prepare_device();                 // the kernel's dynamic-LDS limit on this device (see gemm_lds_kernels above)
     if (e != hipSuccess) return e;
     const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
@@ -566,6 +562,7 @@ template <int CB, bool BLK>
 static hipError_t launch_gemm_tail(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw, const void *bias, int M,
                                    int rows_main, int N, int K, void *Y, hipStream_t stream)
 {
+    if ((CB == 4 ? K / 2 : K) / KT_BYTES < StreamCfg<2, 2, 2, 2, 8>::MIN_KTILES) return hipErrorInvalidValue;      // no plan asks for it
     hipError_t e = prepare_device();
     if (e != hipSuccess) return e;
     w4a4_gemm_tail_kernel<CB, BLK><<<256, 256, TAIL_LDS_BYTES, stream>>>(Xq, sx, Wq, sw, reinterpret_cast<const uint16_t *>(bias), M, rows_main, N,

@@ -1,5 +1,7 @@
 """The plan of the int8-instruction GEMM (csrc/gemm_plan.h), compiled for the host: which tile configuration a problem gets."""
+import math
 import os
+import random
 import shutil
 import subprocess
 
@@ -61,3 +63,23 @@ def test_deep_ring_needs_a_long_chain(plans, M, N, K, bits, affine, want):
 def test_rows_are_divided(plans, M, N, K, bits, affine):
     (shape, rows), = plans([(M, N, K, bits, affine, 0)])
     assert shape == "big+deep" and rows % 256 == 0 and 0 < rows < M
+
+
+def test_deep_ring_never_with_fewer_than_four_k_tiles(plans):
+    """The eight-stage ring's waits cover a tile's scales from three K-tiles on.  Rows that a plan divides are whole 256-row tiles that
+    leave some over."""
+    rng = random.Random(3)
+    sizes = [128, 256, 384, 512, 768, 1024, 1280, 1536, 1792, 2048, 2560, 3072, 3584, 4096, 5120, 6144, 8192]
+    problems = []
+    for i in range(200000):
+        K = rng.choice(sizes[:5] if i % 2 else sizes)
+        bits = rng.choice((4, 8))
+        problems.append((int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(4096)))), K, bits,
+                         bits == 4 and rng.random() < 0.3, rng.random() < 0.1))
+    seen = set()
+    for (M, N, K, bits, _, _), (shape, rows) in zip(problems, plans(problems)):
+        if "deep" in shape:
+            assert K * bits // 512 >= 4, (M, N, K, bits, shape)
+        assert (rows % 256 == 0 and 0 < rows < M) if shape == "big+deep" else rows == 0
+        seen.add(shape)
+    assert seen == {"big", "small", "deep", "big+deep"}
