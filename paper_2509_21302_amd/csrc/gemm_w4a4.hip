@@ -140,10 +140,13 @@ __device__ inline void wait_vmcnt()
 // left without a last one)
 template <int TM, int TN, int WM, int WN, int STAGES, int CB, bool DEBUG, bool ASYM, bool BLK, bool LAST_FIRST = false>
 __device__ __forceinline__ void w4a4_tiles(
-    uint8_t *smem, const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
+    const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
     const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int N, int K,
     uint16_t *__restrict__ Y, int32_t *__restrict__ acc_debug, const float *__restrict__ xzero, const float *__restrict__ wsum)
 {
+    // the dynamic segment by its own name: handed in as a pointer it costs registers in the address arithmetic, and the affine small kernel
+    // had none left (8 bytes of scratch, 32 x 256 -> 2784 5.7 -> 5.95 us)
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     using C = StreamCfg<TM, TN, WM, WN, STAGES, ASYM>;
     constexpr int NM = C::NM, NF = C::NF, LPW = C::LPW;
     constexpr int DMA_SHIFT = (LPW > 4) ? 4096 : 0;             // keeps the transfers' instruction offsets inside [-4096, 4095]
@@ -493,8 +496,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
     const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int N, int K,
     uint16_t *__restrict__ Y, int32_t *__restrict__ acc_debug, const float *__restrict__ xzero, const float *__restrict__ wsum)
 {
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    w4a4_tiles<TM, TN, WM, WN, STAGES, CB, DEBUG, ASYM, BLK>(smem, Xq, sx, Wq, sw, bias, M, N, K, Y, acc_debug, xzero, wsum);
+    w4a4_tiles<TM, TN, WM, WN, STAGES, CB, DEBUG, ASYM, BLK>(Xq, sx, Wq, sw, bias, M, N, K, Y, acc_debug, xzero, wsum);
 }
 
 // The first `rows_main` token rows (a multiple of 256) in 256 x 256 tiles, which fill whole rounds of the chip, then the rest in 128 x 128
@@ -506,10 +508,9 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
     const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int rows_main, int N, int K, uint16_t *__restrict__ Y)
 {
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    w4a4_tiles<4, 4, 2, 2, 4, CB, false, false, BLK>(smem, Xq, sx, Wq, sw, bias, rows_main, N, K, Y, nullptr, nullptr, nullptr);
+    w4a4_tiles<4, 4, 2, 2, 4, CB, false, false, BLK>(Xq, sx, Wq, sw, bias, rows_main, N, K, Y, nullptr, nullptr, nullptr);
     __syncthreads();                     // every wave is done with its LDS before the ring is laid out anew
-    w4a4_tiles<2, 2, 2, 2, 8, CB, false, false, BLK, true>(smem, Xq + (size_t)rows_main * (CB == 4 ? K / 2 : K), sx + rows_main, Wq, sw, bias,
+    w4a4_tiles<2, 2, 2, 2, 8, CB, false, false, BLK, true>(Xq + (size_t)rows_main * (CB == 4 ? K / 2 : K), sx + rows_main, Wq, sw, bias,
                                                            M - rows_main, N, K, Y + (size_t)rows_main * N, nullptr, nullptr, nullptr);
 }
 

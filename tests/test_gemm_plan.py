@@ -1,7 +1,8 @@
-"""The plan of the int8-instruction GEMM (csrc/gemm_plan.h), compiled for the host: which tile configuration a problem gets."""
+"""The int8-instruction GEMM without a GPU: the plan (csrc/gemm_plan.h, compiled for the host), and what the compiler says of its kernels."""
 import math
 import os
 import random
+import re
 import shutil
 import subprocess
 
@@ -83,3 +84,16 @@ def test_deep_ring_never_with_fewer_than_four_k_tiles(plans):
         assert (rows % 256 == 0 and 0 < rows < M) if shape == "big+deep" else rows == 0
         seen.add(shape)
     assert seen == {"big", "small", "deep", "big+deep"}
+
+
+def test_no_kernel_uses_scratch_memory(tmp_path):
+    """Every instantiation fits its registers: a kernel that spills pays for its scratch memory in every wave's start."""
+    from paper_2509_21302_amd import build as B
+    if not os.path.exists(B.HIPCC) and shutil.which(B.HIPCC) is None:
+        pytest.skip("hipcc is not installed")
+    r = subprocess.run([B.HIPCC, *B.FLAGS, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, "gemm_w4a4.hip"),
+                        "-o", str(tmp_path / "gemm.o")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    names, scratch = re.findall(r"Function Name: (\S+)", r.stderr), re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)
+    assert len(names) == len(scratch) and sum("w4a4_gemm" in n for n in names) >= 24
+    assert not [n for n, b in zip(names, scratch) if int(b)]
