@@ -160,11 +160,16 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
     __shared__ __attribute__((aligned(16))) uint8_t smem[GELU ? rq::GELU_LDS_BYTES : LDS_END];
     uint8_t *const lds_all = smem + STAGE0, *const flush_all = smem + FLUSH0;
     if constexpr (GELU) {
-        for (int i = threadIdx.x; i < rq::GELU_TABLE_ENTRIES / 8; i += 256) {        // 16 bytes each; positive inputs' entries come first
-            constexpr int HALF = rq::GELU_HALF_BYTES / 16;
-            *reinterpret_cast<uint4 *>(smem + (i < HALF ? rq::GELU_POS + 16 * i : rq::GELU_NEG + 16 * (i - HALF))) =
-                reinterpret_cast<const uint4 *>(gelu_table)[i];
-        }
+        // 16 bytes each, positive inputs' entries first; all loads before the first store, or every round of the block waits for memory anew
+        // (for a launch of one tile per wave that is most of the time: 1374 x 1024 8.1 -> 7.7 us; 53 x 1024 5.9 -> 5.5)
+        constexpr int VECS = rq::GELU_TABLE_ENTRIES / 8 / 256, HALF = VECS / 2;
+        static_assert(VECS % 2 == 0 && VECS * 256 * 8 == rq::GELU_TABLE_ENTRIES, "the block copies each half in whole rounds");
+        uint4 v[VECS];
+#pragma unroll
+        for (int i = 0; i < VECS; ++i) v[i] = reinterpret_cast<const uint4 *>(gelu_table)[256 * i + threadIdx.x];
+#pragma unroll
+        for (int i = 0; i < VECS; ++i)
+            *reinterpret_cast<uint4 *>(smem + (i < HALF ? rq::GELU_POS + 4096 * i : rq::GELU_NEG + 4096 * (i - HALF)) + 16 * threadIdx.x) = v[i];
         __syncthreads();
     }
 
