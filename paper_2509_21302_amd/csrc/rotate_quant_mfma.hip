@@ -127,7 +127,7 @@ __host__ __device__ constexpr int row_of_seg_hi(int seg_hi /* seg >> 2 */)
 // ((r / 128) * (K / 64) + kt) * 8192 + (r % 128) * 64, its 16-byte chunk ch in slot ch ^ ((r % 16) >> 2)
 // GELU: the activation between fc1 and fc2 applied to every loaded value (fp32, result rounded to bf16 as a separate activation
 // kernel would hand it on) before anything else: X is fc1's output as stored, the kernel is fc2's kernel 1
-template <int K, int PF, int OCC, bool STATIC, int CB, bool LN = false, bool ASYM = false, bool BLK8 = false, bool GELU = false>
+template <int K, int PF, int OCC, bool STATIC, int CB, bool LN = false, bool ASYM = false, bool BLK8 = false, bool GELU = false, bool LONG = false>
 __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint16_t *__restrict__ X, int rows,
                                                                    const int8_t *__restrict__ signs,
                                                                    const float *__restrict__ mul, int mul_mode,
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
     uint8_t *const lds_all = smem + STAGE0, *const flush_all = smem + FLUSH0;
     if constexpr (GELU) {
         // 16 bytes each, positive inputs' entries first; all loads before the first store, or every round of the block waits for memory anew
-        // (for a launch of one tile per wave that is most of the time: 1374 x 1024 8.1 -> 7.7 us; 53 x 1024 5.9 -> 5.5)
+        // (1374 x 1024 8.1 -> 7.7 us, 53 x 1024 5.9 -> 5.5)
         constexpr int VECS = rq::GELU_TABLE_ENTRIES / 8 / 256, HALF = VECS / 2;
         static_assert(VECS % 2 == 0 && VECS * 256 * 8 == rq::GELU_TABLE_ENTRIES, "the block copies each half in whole rounds");
         uint4 v[VECS];
@@ -312,11 +312,19 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) cmax[h][nt] = 0.0f;
 
+    // Wave priority from the start of a tile to its last MFMA.  With the activation lookups or the normalisation in front, a tile starts with
+    // a long stretch before its first MFMA: the wave that is in it goes first, and the other wave of the SIMD fills in with its butterflies and
+    // codes (raised after the normalisation instead, the gain is gone).  Without them a tile's start is staging and MFMAs, and going first
+    // pays only over many tiles at K = 4096 (LONG), or with a static step.  The codes are the same either way.  us without / with:
+    //   GELU           32976 x 4096 84.6 / 80.2, 10992 x 4096 32.2 / 31.0, 10992 x 2048 19.2 / 17.7, 32976 x 1024 24.5 / 23.8
+    //   LayerNorm      32976 x 1024 31.0 / 29.3, 137400 x 1024 91.6 / 84.0, 5207 x 1024 13.8 / 13.8
+    //   static, E2M3   32976 x 4096 70.6 / 64.9, 5207 x 4096 15.6 / 14.1, 10992 x 1024 9.0 / 8.7, but 5207 x 2048 11.3 / 11.9
+    //   plain          137400 x 4096 302 / 294, 32976 x 4096 68.0 / 66.6 (int8 blocks 307 / 301, 71.4 / 70.7), but 5207 x 4096 14.7 / 15.1
+    //                  (14.1 / 14.5), 1374 x 4096 7.7 / 7.9 (7.2 / 7.4); K = 1024 and 2048 within 1 %
+    //   affine         32976 x 4096 70.0 / 72.1, 1374 x 4096 7.9 / 8.2; column statistic 1 to 2 % slower; packed codes and int8 rows within 1 %
+    constexpr bool RAISE = LN || GELU || (STATIC && CB == 6 && K != 2048) || LONG;
     for (; (BLOCK_FLUSH ? tile - wave_in_block : tile) < ntiles; tile += nwaves) {
-        // From here to the last MFMA a wave waits on LDS and the matrix pipe and issues little: it goes first, and the other wave of the
-        // SIMD has the vector ALU for its butterflies and codes.  137400 x 4096: 279 -> 271 us, 32976 x 4096: 65.9 -> 64.7; K = 1024 the
-        // same.  (Up to the staging only: 289 us; around the MFMAs only: 282.)
-        __builtin_amdgcn_s_setprio(3);
+        if constexpr (RAISE) __builtin_amdgcn_s_setprio(3);
         if constexpr (GELU) {
             // one wave-uniform test per tile: is every value inside the table's window?  (Almost always: outside are exact
             // zeros, |x| < 1e-6 and |x| >= 4096.)  Then two lookups per packed pair; otherwise the general form per value.
@@ -414,7 +422,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
             }
         }
 
-        __builtin_amdgcn_s_setprio(0);
+        if constexpr (RAISE) __builtin_amdgcn_s_setprio(0);
         // H_{K/128} over the hi-block index: butterflies between accumulator registers
         constexpr int REG_STAGES = (REM >= 4) ? 4 : 3;
 #pragma unroll
@@ -807,6 +815,10 @@ hipError_t run_gelu_rotate_quant_mfma(const void *X, int rows, int K, const int8
     return hipGetLastError();
 }
 
+// sixteen tiles or more per wave (32768 rows at K = 4096): where the raised wave priority of the plain kernels pays, see the tile loop
+// (8192 to 24000 x 4096 within 2 %, either way; 32976 x 4096 71 us without, 68 with)
+static bool many_tiles(int ntiles, int blocks) { return ntiles >= 16 * rq::WAVES_PER_BLOCK * blocks; }
+
 // rotation + smoothing + per-token int8 codes of `bits` bits as int8 blocks (what the blocked int8 GEMM reads), bf16 rows
 hipError_t run_rotate_quant_i8b_mfma(const void *X, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out,
                                      float *scale, int bits, hipStream_t stream)
@@ -819,11 +831,11 @@ hipError_t run_rotate_quant_i8b_mfma(const void *X, int rows, int K, const int8_
     if (blocks > 256 * 2) blocks = 256 * 2;
     const float qmax8 = (float)((1 << (bits - 1)) - 1);
     const LnParams no_ln{nullptr, nullptr, 0.0f, 0};
-#define RQB(KK) rotate_quant_mfma_kernel<KK, 1, 2, false, 8, false, false, true><<<blocks, 256, 0, stream>>>(x, rows, signs, mul, 0, out, scale, nullptr, 0, qmax8, nullptr, no_ln, nullptr)
+#define RQB(KK, LONG) rotate_quant_mfma_kernel<KK, 1, 2, false, 8, false, false, true, false, LONG><<<blocks, 256, 0, stream>>>(x, rows, signs, mul, 0, out, scale, nullptr, 0, qmax8, nullptr, no_ln, nullptr)
     switch (K) {
-        case 1024: RQB(1024); break;
-        case 2048: RQB(2048); break;
-        case 4096: RQB(4096); break;
+        case 1024: RQB(1024, false); break;
+        case 2048: RQB(2048, false); break;
+        case 4096: if (many_tiles(ntiles, blocks)) RQB(4096, true); else RQB(4096, false); break;
         default: return hipErrorInvalidValue;
     }
 #undef RQB
@@ -840,11 +852,11 @@ hipError_t run_rotate_quant_e2m3_mfma(const void *X, int rows, int K, const int8
     const int ntiles = (rows + tok - 1) / tok;
     int blocks = (ntiles + rq::WAVES_PER_BLOCK - 1) / rq::WAVES_PER_BLOCK;
     if (blocks > 256 * 2) blocks = 256 * 2;
-#define RQE(KK) rotate_quant_mfma_kernel<KK, 1, 2, false, 6><<<blocks, 256, 0, stream>>>(x, rows, signs, mul, 0, out, scale, nullptr, 0, 7.0f, nullptr)
+#define RQE(KK, LONG) rotate_quant_mfma_kernel<KK, 1, 2, false, 6, false, false, false, false, LONG><<<blocks, 256, 0, stream>>>(x, rows, signs, mul, 0, out, scale, nullptr, 0, 7.0f, nullptr)
     switch (K) {
-        case 1024: RQE(1024); break;
-        case 2048: RQE(2048); break;
-        case 4096: RQE(4096); break;
+        case 1024: RQE(1024, false); break;
+        case 2048: RQE(2048, false); break;
+        case 4096: if (many_tiles(ntiles, blocks)) RQE(4096, true); else RQE(4096, false); break;
         default: return hipErrorInvalidValue;
     }
 #undef RQE

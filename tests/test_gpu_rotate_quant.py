@@ -394,3 +394,23 @@ def test_row_kernels_special_rows(K, static):
     if not static:
         G.check_scales(sx.cpu().numpy()[good], dx, f"K={K}")
         assert not codes[list(bad)].any()
+
+
+@pytest.mark.parametrize("M", [32767, 32768, 32781])
+def test_many_tiles_per_wave_write_the_same_codes(M):
+    """K = 4096 on both sides of sixteen tiles per wave: every row's codes and step are those of smaller launches (rows are independent)."""
+    K, cut = 4096, 16384                     # a whole number of the formats' 128-row blocks
+    gen = torch.Generator(device=G.DEV).manual_seed(M)
+    X = (torch.randn(M, K, generator=gen, device=G.DEV) * (1.0 + (torch.arange(M, device=G.DEV) % 7)[:, None])).to(torch.bfloat16)
+    signs = (torch.randint(0, 2, (K,), generator=gen, device=G.DEV, dtype=torch.int8) * 2 - 1).contiguous()
+    inv = torch.rand(K, generator=gen, device=G.DEV) + 0.5
+    for size, run in ((G.q.qvggt_e2m3_bytes, lambda x, out, step: G.q.qvggt_rotate_smooth_quant_e2m3(x, signs, inv, out, step)),
+                      (G.q.qvggt_i8b_bytes, lambda x, out, step: G.q.qvggt_rotate_smooth_quant_i8b(x, signs, inv, 8, out.view(torch.int8), step))):
+        out, step = torch.full((size(M, K),), 0x5A, dtype=torch.uint8, device=G.DEV), torch.full((M,), -1.0, device=G.DEV)
+        run(X, out, step)
+        parts, steps = [], []
+        for x in (X[:cut], X[cut:]):
+            parts.append(torch.full((size(x.shape[0], K),), 0x5A, dtype=torch.uint8, device=G.DEV))
+            steps.append(torch.full((x.shape[0],), -1.0, device=G.DEV))
+            run(x, parts[-1], steps[-1])
+        assert torch.equal(out, torch.cat(parts)) and torch.equal(step, torch.cat(steps))
