@@ -28,6 +28,8 @@ __host__ inline int blocks_per_row(int rows, long long count, int elt_bytes)
     return (int)want;
 }
 
+constexpr int MAX_PAIRS_PER_THREAD = 8;      // a row's partial sums are added by one thread up to here, by a wave beyond
+
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 // the 8 bf16 or 4 f32 values of one 16-byte vector, as doubles
@@ -48,10 +50,11 @@ __device__ inline int unpack(const v4u &v, double (&x)[8])
     }
 }
 
-__device__ inline double wave_sum(double v)      // fixed order, result in every lane
+template <int LANES = kWave>
+__device__ inline double wave_sum(double v)      // over groups of LANES lanes (a power of two); fixed order, result in every lane
 {
 #pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) v += __shfl_xor(v, m);
+    for (int m = 1; m < LANES; m <<= 1) v += __shfl_xor(v, m);
     return v;
 }
 
@@ -105,45 +108,49 @@ __global__ __launch_bounds__(nfds::THREADS) void nfds_partial_kernel(const void 
     }
 }
 
-// The partial sums of a row (up to MAX_BLOCKS_PER_ROW pairs) are added by one wave, 64 at a time: one thread walking them pays a
-// memory round trip each (25 us for the 85 pairs per row of a 24-frame sample, 5 us this way).
+// The partial sums of a row (up to MAX_BLOCKS_PER_ROW pairs) are added by LANES lanes: a wave, since one thread walking them pays a memory
+// round trip for every few (25 us for the 85 pairs per row of a 24-frame sample, 3.9 us this way), or one thread where there are few pairs
+// and many rows (the whole call on 4000 rows of one pair: 9.3 us with a thread each, 10.5 with a wave; 300 rows of two pairs 6.6 / 7.2,
+// 100 rows of 20 pairs 12.3 / 11.1).
 // mean = S1 / n, var = S2 / n - mean^2 (population variance)
+template <int LANES>
 __global__ __launch_bounds__(nfds::THREADS) void nfds_moments_final_kernel(const double2 *__restrict__ partial, int rows, int bpr,
                                                                            long long count, float *__restrict__ mean, float *__restrict__ var)
 {
-    const int row = blockIdx.x * (nfds::THREADS / kWave) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int row = blockIdx.x * (nfds::THREADS / LANES) + threadIdx.x / LANES, lane = threadIdx.x % LANES;
     if (row >= rows) return;
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll 4
-    for (int b = lane; b < bpr; b += kWave) {
+    for (int b = lane; b < bpr; b += LANES) {
         const double2 p = partial[(size_t)row * bpr + b];
         s1 += p.x; s2 += p.y;
     }
-    s1 = nfds::wave_sum(s1);
-    s2 = nfds::wave_sum(s2);
+    s1 = nfds::wave_sum<LANES>(s1);
+    s2 = nfds::wave_sum<LANES>(s2);
     if (lane != 0) return;
     const double m = s1 / (double)count;
     mean[row] = (float)m;
     var[row] = (float)fmax(s2 / (double)count - m * m, 0.0);
 }
 
-// c[sample, t - 1] = <a_0, a_t> / (|a_0| |a_t|), one wave per (sample, t >= 1)
+// c[sample, t - 1] = <a_0, a_t> / (|a_0| |a_t|), LANES lanes per (sample, t >= 1)
+template <int LANES>
 __global__ __launch_bounds__(nfds::THREADS) void nfds_corr_final_kernel(const double2 *__restrict__ partial, int samples, int f, int bpr,
                                                                         float *__restrict__ c)
 {
-    const int idx = blockIdx.x * (nfds::THREADS / kWave) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int idx = blockIdx.x * (nfds::THREADS / LANES) + threadIdx.x / LANES, lane = threadIdx.x % LANES;
     if (idx >= samples * (f - 1)) return;
     const int i = idx / (f - 1), t = idx % (f - 1) + 1;
     double dot = 0.0, nt = 0.0, n0 = 0.0;
 #pragma unroll 4
-    for (int b = lane; b < bpr; b += kWave) {
+    for (int b = lane; b < bpr; b += LANES) {
         const double2 p = partial[(size_t)(i * f + t) * bpr + b];
         dot += p.x; nt += p.y;
         n0 += partial[(size_t)(i * f) * bpr + b].y;
     }
-    dot = nfds::wave_sum(dot);
-    nt = nfds::wave_sum(nt);
-    n0 = nfds::wave_sum(n0);
+    dot = nfds::wave_sum<LANES>(dot);
+    nt = nfds::wave_sum<LANES>(nt);
+    n0 = nfds::wave_sum<LANES>(n0);
     if (lane == 0) c[idx] = (float)(dot / (sqrt(n0) * sqrt(nt)));
 }
 
@@ -235,7 +242,9 @@ hipError_t run_nfds_moments(const void *A, bool f32, int rows, long long count, 
     else nfds_partial_kernel<false, false><<<rows * bpr, nfds::THREADS, 0, stream>>>(A, count, bpr, 1, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    nfds_moments_final_kernel<<<(rows + 3) / 4, nfds::THREADS, 0, stream>>>(reinterpret_cast<const double2 *>(ws), rows, bpr, count, mean, var);
+    const double2 *pairs = reinterpret_cast<const double2 *>(ws);
+    if (bpr <= nfds::MAX_PAIRS_PER_THREAD) nfds_moments_final_kernel<1><<<(rows + 255) / 256, nfds::THREADS, 0, stream>>>(pairs, rows, bpr, count, mean, var);
+    else nfds_moments_final_kernel<kWave><<<(rows + 3) / 4, nfds::THREADS, 0, stream>>>(pairs, rows, bpr, count, mean, var);
     return hipGetLastError();
 }
 
@@ -250,7 +259,9 @@ hipError_t run_nfds_frame_correlation(const void *A, bool f32, int samples, int 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int n = samples * (f - 1);
-    nfds_corr_final_kernel<<<(n + 3) / 4, nfds::THREADS, 0, stream>>>(reinterpret_cast<const double2 *>(ws), samples, f, bpr, c);
+    const double2 *pairs = reinterpret_cast<const double2 *>(ws);
+    if (bpr <= nfds::MAX_PAIRS_PER_THREAD) nfds_corr_final_kernel<1><<<(n + 255) / 256, nfds::THREADS, 0, stream>>>(pairs, samples, f, bpr, c);
+    else nfds_corr_final_kernel<kWave><<<(n + 3) / 4, nfds::THREADS, 0, stream>>>(pairs, samples, f, bpr, c);
     return hipGetLastError();
 }
 

@@ -55,6 +55,22 @@ def test_reductions_at_wave_edges(blocks):
     assert np.allclose(corr.cpu().numpy()[0], [Xo[0] @ Xo[t] / (norm[0] * norm[t]) for t in (1, 2)], rtol=RTOL)
 
 
+@pytest.mark.parametrize("blocks,rows", [(1, 300), (2, 257), (6, 301), (8, 255), (9, 213), (20, 100), (1, 4093)])
+def test_reductions_of_many_short_rows(blocks, rows):
+    """Rows of up to eight partial sums are added by a thread each, of more by a wave each, the last block of rows a partial one: the same bars."""
+    count = blocks * 1024 * 8 if rows < 1000 else 128
+    g = torch.Generator(device=G.DEV).manual_seed(blocks)
+    X = (torch.randn(rows, count, generator=g, device=G.DEV) + 0.5).to(torch.bfloat16)
+    mean, var = (torch.empty(rows, dtype=torch.float32, device=G.DEV) for _ in range(2))
+    q.qvggt_nfds_moments(X, mean, var, _ws(rows, count, X))
+    corr = torch.empty(1, rows - 1, dtype=torch.float32, device=G.DEV)
+    q.qvggt_nfds_frame_correlation(X.view(1, rows, count), corr, _ws(rows, count, X))
+    Xo = X.double()
+    norm = Xo.square().sum(1).sqrt()
+    assert np.allclose(mean.cpu().numpy(), Xo.mean(1).cpu().numpy(), rtol=RTOL) and np.allclose(var.cpu().numpy(), Xo.var(1, correction=0).cpu().numpy(), rtol=RTOL)
+    assert np.allclose(corr.cpu().numpy()[0], (((Xo[1:] * Xo[0]).sum(1)) / (norm[0] * norm[1:])).cpu().numpy(), rtol=RTOL)
+
+
 def test_moments_large_mean_small_spread():
     """E[x^2] - E[x]^2 in double: a mean 1e3 times the standard deviation must not hurt the variance."""
     rng = np.random.default_rng(5)
