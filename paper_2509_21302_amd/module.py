@@ -63,20 +63,21 @@ class DsfqLinear:
             if self.K in (1024, 2048, 4096):
                 self.Wb = torch.empty(q.qvggt_i8b_bytes(self.N, self.K), dtype=torch.int8, device=dev)
                 q.qvggt_int8_to_blocks(self.Wq, self.N, self.K, self.Wb)
-        self._ws, self._ws_rows = None, -1
+        self._ws = (-1, None)       # rows the workspace is large enough for, the workspace
 
     def _workspace(self, M: int, dev) -> torch.Tensor:
-        if M <= self._ws_rows and self._ws.device == dev:       # what M rows need grows with M
-            return self._ws
+        rows, ws = self._ws         # read and replaced as a pair: several threads may be here
+        if M <= rows and ws.device == dev:       # what M rows need grows with M
+            return ws
         need = q.qvggt_workspace_bytes(M, self.N, self.K) if self.packed else q.qvggt_workspace_bytes_i8(M, self.N, self.K)
         if self.packed and self.Wf is not None:
             need = max(need, q.qvggt_workspace_bytes_e2m3(M, self.N, self.K))
         if not self.packed and self.Wb is not None:
             need = max(need, q.qvggt_workspace_bytes_i8b(M, self.N, self.K))
-        if self._ws is None or self._ws.numel() < need or self._ws.device != dev:
-            self._ws = torch.empty(need, dtype=torch.uint8, device=dev)
-        self._ws_rows = M
-        return self._ws
+        if ws is None or ws.numel() < need or ws.device != dev:
+            ws = torch.empty(need, dtype=torch.uint8, device=dev)
+        self._ws = (M, ws)
+        return ws
 
     def __call__(self, X: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
         """X: [M, K] bf16 or f32 on the GPU; returns bf16 [M, N] (written into `out` when given)."""
