@@ -277,6 +277,28 @@ def test_binding_rejects_host_tensors():
         q.qvggt_rotate_smooth_quant(x, None, None, torch.zeros(4, 512, dtype=torch.uint8), torch.zeros(4))
 
 
+def test_current_stream_without_torchs_private_names(monkeypatch):
+    """The handle comes from torch's internal functions where this torch has them, from torch.cuda.current_stream() where it does not."""
+    import importlib.util
+    import types
+
+    import torch
+    spec = importlib.util.spec_from_file_location("binding_copy", os.path.join(ROOT, "paper_2509_21302_amd", "binding.py"))
+
+    def load():
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        return module
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4321))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1000 + device, raising=False)
+    assert load()._stream(None) == 1003 and load()._stream(types.SimpleNamespace(cuda_stream=7)) == 7
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        with monkeypatch.context() as m:
+            m.delattr(torch._C, name)
+            assert load()._stream(None) == 4321
+
+
 def test_nfds_argument_validation_needs_no_gpu():
     lib = q.load_library()
     dbl = C.c_double
