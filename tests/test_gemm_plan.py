@@ -97,3 +97,21 @@ def test_no_kernel_uses_scratch_memory(tmp_path):
     names, scratch = re.findall(r"Function Name: (\S+)", r.stderr), re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)
     assert len(names) == len(scratch) and sum("w4a4_gemm" in n for n in names) >= 24
     assert not [n for n, b in zip(names, scratch) if int(b)]
+
+
+def test_gpu_tests_reach_the_plans_they_are_named_for(plans):
+    """A change of the plan must not leave a GPU test on another kernel than its table says."""
+    from tests.test_gpu_asym import ASYM_PLANS
+    from tests.test_gpu_gemm import ROWS_SPLIT, TILE_PLANS
+    from tests.test_gpu_int8_blocks import BOTH_TILE_SHAPES
+    cases = [((M, N, K, 8 if wide else 4, 0, 1), want) for M, N, K, wide, want in ROWS_SPLIT]
+    cases += [((M, N, K, 4 if kind == "packed" else 8, 0, 0), want) for M, N, K, kind, want in TILE_PLANS]
+    cases += [((M, N, K, 8, 0, 0), want) for M, N, K, want in BOTH_TILE_SHAPES] + [((M, N, K, 4, 1, 0), want) for M, N, K, want in ASYM_PLANS]
+    for (problem, want), (shape, rows) in zip(cases, plans([c[0] for c in cases])):
+        assert shape == want, (problem, shape)
+        if want == "big+deep":          # the seam the tests look at
+            M, N = problem[:2]
+            tiles_n = (N + 255) // 256
+            assert rows == ((M + 255) // 256 * tiles_n // 256 * 256 // tiles_n) * 256
+    for plan in ("big", "small", "deep", "big+deep"):
+        assert any(want == plan for _, _, _, want in ASYM_PLANS) and any(p[4] == plan for p in TILE_PLANS)

@@ -99,10 +99,16 @@ def test_gemm_asym_small_integers_are_exact(M, N, K):
     assert np.array_equal(Y, oracle.bf16_from_f64(want.astype(np.float64)))
 
 
-@pytest.mark.parametrize("M,N,K", [(64, 128, 128), (1374, 3072, 1024), (257, 1024, 4096), (4200, 4096, 1024)])
+# tests/test_gemm_plan.py holds the plan to what this table says of each problem
+ASYM_PLANS = [(64, 128, 128, "small"), (1374, 3072, 1024, "small"), (257, 1024, 4096, "deep"), (4200, 4096, 1024, "small"),
+              (10992, 4096, 1024, "big"), (8400, 2000, 4096, "big+deep")]
+
+
+@pytest.mark.parametrize("M,N,K", [p[:3] for p in ASYM_PLANS])
 def test_gemm_asym_against_the_oracle_on_identical_codes(M, N, K):
-    """Random codes and zero points, the oracle's integer sum with the same fp32-stored scales applied in double; the largest
-    shape runs the 256 x 256 kernel and the tail kernel and is compared on sampled token rows (rows are independent)."""
+    """Random codes and zero points, the oracle's integer sum with the same fp32-stored scales applied in double, in every plan: small
+    tiles, the deep ring, 256 x 256 tiles, and these with the rest of the rows (8192 and on) in the deep ring of a second launch.  Large
+    shapes are compared on sampled token rows (rows are independent)."""
     rng = np.random.default_rng(M * 3 + N)
     u = rng.integers(0, 16, (M, K)).astype(np.uint8)
     zp = rng.integers(0, 16, M)
@@ -111,7 +117,8 @@ def test_gemm_asym_against_the_oracle_on_identical_codes(M, N, K):
     dw = np.exp(rng.uniform(-5, -2, N)).astype(np.float32)
     bias_bits = synth.f32_to_bf16_bits((rng.standard_normal(N) * 0.02).astype(np.float32))
     Y = _run_gemm_asym(u, zp, qw, dx, dw, bias_bits)
-    rows = np.arange(M) if M <= 1400 else np.unique(np.concatenate([np.arange(0, 260), np.arange(M - 140, M), rng.integers(0, M, 200)]))
+    rows = np.arange(M) if M <= 1400 else np.unique(np.concatenate([np.arange(0, 260), np.clip(np.arange(8160, 8230), 0, M - 1), np.arange(M - 140, M),
+                                                                        rng.integers(0, M, 200)]))
     acc = oracle.int_gemm_asym(u[rows], zp[rows], qw)
     y = acc.astype(np.float64) * dx[rows].astype(np.float64)[:, None] * dw.astype(np.float64)[None, :] + oracle.to_f64(bias_bits)[None, :]
     Yo = oracle.bf16_from_f64(y)

@@ -122,10 +122,16 @@ def test_shape_sweep_both_code_widths():
         assert ulp_off.max() <= 1 and (ulp_off != 0).mean() < 5e-3, what
 
 
-@pytest.mark.parametrize("M,N,K,wide", [(66000, 512, 256, False), (33000, 1024, 512, True), (65700, 768, 128, False)])
+# tests/test_gemm_plan.py holds the plan to what these tables say of each problem (with the accumulator dump, as it is called here)
+ROWS_SPLIT = [(66000, 512, 256, False, "small"), (33000, 1024, 512, True, "small"), (65700, 768, 128, False, "small"),
+              (8400, 2000, 4096, False, "big+deep"), (32976, 1024, 4096, False, "big+deep"), (17000, 4096, 1024, True, "big+deep")]
+
+
+@pytest.mark.parametrize("M,N,K,wide", [p[:4] for p in ROWS_SPLIT])
 def test_rows_split_between_the_two_tile_shapes(M, N, K, wide):
-    """Shapes whose 256 x 256 tiles fill whole rounds of 256 plus a small remainder: the remainder rows go to the 128 x 128
-    configuration in a second launch.  Accumulators of rows on both sides of the seam, and the last rows, are bit-exact."""
+    """Shapes whose 256 x 256 tiles fill whole rounds of 256 plus a small remainder: with the accumulator dump the remainder rows go to
+    the 128 x 128 configuration in a second launch, or, at small K, all rows do in one.  Accumulators of rows on both sides of the seam, and
+    the last rows, are bit-exact."""
     import paper_2509_21302_amd as q
     tiles_n = (N + 255) // 256
     seam = ((M + 255) // 256 * tiles_n // 256 * 256 // tiles_n) * 256
@@ -170,13 +176,19 @@ def test_matrix_ceiling_helper_runs_and_repeats(kind):
     assert torch.equal(first, sink)
 
 
-@pytest.mark.parametrize("M,N,K,kind", [(8400, 2000, 4096, "packed"), (8400, 2000, 4096, "int8"), (8400, 2000, 4096, "blocks"),
-                                        (17000, 4096, 1024, "blocks"), (2049, 2048, 128, "packed"), (2048, 2048, 128, "int8"),
-                                        (129, 128, 8192, "blocks"), (1, 16, 256, "blocks")])
+TILE_PLANS = [(8400, 2000, 4096, "packed", "big+deep"), (8400, 2000, 4096, "int8", "big+deep"), (8400, 2000, 4096, "blocks", "big+deep"),
+              (17000, 4096, 1024, "blocks", "big+deep"), (2049, 2048, 128, "packed", "small"), (2048, 2048, 128, "int8", "small"),
+              (129, 128, 8192, "blocks", "deep"), (1, 16, 256, "blocks", "small"),
+              (2048, 2048, 4096, "packed", "deep"), (2049, 2048, 4096, "packed", "small"), (2048, 2048, 1024, "int8", "deep"),
+              (2049, 2048, 1024, "int8", "small"), (2247, 4256, 2048, "blocks", "big"), (130, 272, 2048, "blocks", "deep")]
+
+
+@pytest.mark.parametrize("M,N,K,kind", [p[:4] for p in TILE_PLANS])
 def test_tile_plans(M, N, K, kind):
     """The plans of the dispatch at their edges: whole rounds of big tiles and the rest in deep-ring tiles of the same launch (ragged
-    last tiles), 256 small tiles exactly and a few more, the smallest problem.  The accumulator dump takes separate launches: Y of both
-    calls must agree bit for bit, and sampled accumulators be the exact integers."""
+    last tiles), 256 small tiles exactly (the deep ring) and a few more (not any longer), little K, just past a round of small tiles (big
+    ones), the smallest problem.  The accumulator dump takes separate launches: Y of both calls must agree bit for bit, and sampled
+    accumulators be the exact integers."""
     import paper_2509_21302_amd as q
     rng = np.random.default_rng(M + N + K)
     lim = 8 if kind == "packed" else 128

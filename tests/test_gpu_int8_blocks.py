@@ -54,9 +54,14 @@ def test_i8b_gemm_bit_exact(M, N, K):
     assert torch.equal(Y, Y8)
 
 
-@pytest.mark.parametrize("M,N,K", [(66000, 512, 256), (33000, 1024, 512)])
+# tests/test_gemm_plan.py holds the plan to what this table says of each problem
+BOTH_TILE_SHAPES = [(66000, 512, 256, "small"), (33000, 1024, 512, "small"), (17000, 4096, 1024, "big+deep"), (8400, 2000, 4096, "big+deep")]
+
+
+@pytest.mark.parametrize("M,N,K", [p[:3] for p in BOTH_TILE_SHAPES])
 def test_i8b_gemm_both_tile_shapes(M, N, K):
-    """Whole rounds of big tiles plus a remainder in the small configuration: every row equals the row-major kernel's."""
+    """Whole rounds of big tiles plus a remainder in 128 x 128 tiles, in one launch or, for the accumulator dump, in two (at small K all rows
+    in one launch of small tiles): every row equals the row-major kernel's."""
     gen = torch.Generator(device="cpu").manual_seed(M)
     qx = torch.randint(-128, 128, (M, K), generator=gen, dtype=torch.int8).numpy()
     qw = torch.randint(-128, 128, (N, K), generator=gen, dtype=torch.int8).numpy()
@@ -69,7 +74,9 @@ def test_i8b_gemm_both_tile_shapes(M, N, K):
     Y8 = torch.empty_like(Y)
     G.q.qvggt_i8_gemm(Xl, G.to_dev(dx), Wl, G.to_dev(dw), None, M, N, K, Y8, None)
     assert torch.equal(Y, Y8)
-    rows = np.unique(np.concatenate([np.arange(0, 8), np.arange(M - 200, M), rng.choice(M, 200, replace=False)]))
+    tiles_n = (N + 255) // 256
+    seam = ((M + 255) // 256 * tiles_n // 256 * 256 // tiles_n) * 256          # where the rest begins, if there is one
+    rows = np.unique(np.concatenate([np.arange(0, 8), np.arange(seam - 8, min(seam + 8, M)), np.arange(M - 200, M), rng.choice(M, 200, replace=False)]))
     acc = torch.full((M, N), 12345, dtype=torch.int32, device=G.DEV)
     G.q.qvggt_i8b_gemm(Xb, G.to_dev(dx), Wb, G.to_dev(dw), None, M, N, K, Y, acc)
     assert np.array_equal(acc[torch.from_numpy(rows).to(G.DEV)].cpu().numpy(), oracle.int_gemm(qx[rows], qw))

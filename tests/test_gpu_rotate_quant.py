@@ -325,9 +325,10 @@ def test_rotate_quant_sizes_with_a_paley_factor(K, dtype):
         G.check_scales(sx.cpu().numpy(), dx, f"K={K} bits={bits}")
 
 
-@pytest.mark.parametrize("K,N", [(768, 256), (2560, 144), (3584, 512)])
+@pytest.mark.parametrize("K,N", [(768, 256), (2560, 144), (3584, 512), (5120, 144), (6144, 80), (8192, 48)])
 def test_linear_end_to_end_with_a_paley_factor(K, N):
-    """Whole path (statistic, weight preparation, rotate-quantize, integer GEMM, epilogue) on a size 2^n * m."""
+    """Whole path (statistic, weight preparation, rotate-quantize, integer GEMM, epilogue) on a size 2^n * m, and on the sizes whose rows,
+    the weights' among them, are shared by four waves (5120, 6144, 8192)."""
     rng = np.random.default_rng(K + N)
     M = 300
     X = _heavy(M, K, K)
@@ -348,12 +349,12 @@ def test_linear_end_to_end_with_a_paley_factor(K, N):
     assert np.linalg.norm(oracle.bf16_bits_to_f64(Y) - exact) / np.linalg.norm(exact) < 0.35
 
 
-@pytest.mark.parametrize("K", [256, 1024, 2048, 4096])
+@pytest.mark.parametrize("K", [256, 1024, 2048, 4096, 5120, 6144, 8192])
 @pytest.mark.parametrize("rows", [1, 37, 1374, 5003])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_rotated_col_absmax(K, rows, dtype):
     """The smoothing statistic max_t |X H|[t, j] (Sec. 3.2): matrix-core kernel for bf16 at K = 1024 / 2048 / 4096, the generic
-    one otherwise; ragged row counts leave the last tile partial."""
+    one otherwise (four waves per row from K = 5120 on); ragged row counts leave the last tile partial."""
     import paper_2509_21302_amd as q
     X = _heavy(rows, K, rows + K, dtype)
     rng = np.random.default_rng(rows * K)
