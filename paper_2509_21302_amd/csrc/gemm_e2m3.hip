@@ -474,6 +474,10 @@ static hipError_t launch_e2m3(const uint8_t *Xf, const float *sx, const uint8_t 
 // rows of Y, and row offsets that are multiples of 256 are whole 128-row blocks of the operand format).  The split has to win by
 // 3 % to be taken.  Measured: 32976 x 4096 -> 1024 (2.02 big rounds) 85.5 -> 78.3 us; at K = 1024 the same token count is left as it
 // was (a split that ignored the launch cost made 32976 x 1024 -> 1024 11 % slower), and so is 137400 x 4096 -> 1024 (8.4 rounds).
+// Counting whole rounds overstates small tiles just past one (K = 1024, 2048 tiles 29.9 us, 2064 31.3; K = 4096, 512 tiles 24.1, 528 32.3), as
+// the int8-instruction kernel's plan, which prices the last round by its tiles, does not.  It matters little here: with the codes of real rows,
+// 4093 to 65533 rows -> 1024, the plan is within 3 % of the best at K = 2048 and 4096; at K = 1024 it gives away 8 to 10 % at 12285 and 65533
+// rows (14.4 us for 13.3, 62 for 56) and at most 6 % elsewhere.
 template <class Big, class Small>
 static hipError_t e2m3_by_rounds(int M, int N, int K, Big &&big, Small &&small)
 {
