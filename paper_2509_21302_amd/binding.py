@@ -199,15 +199,19 @@ def _dtype_code(t) -> int:
 
 # The current device's current stream without the two Python objects that torch.cuda.current_stream() makes (a 64 x 128 -> 128 layer 14.5 ->
 # 11.4 us a call, together with the kept workspace size), where this torch has the functions it is made of.
-_RAW_STREAM, _DEVICE = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is None or _device is None:
+    def _raw_stream(device):
+        return torch.cuda.current_stream(device).cuda_stream
+
+    def _device():
+        return None         # the current one
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is not None:
-        return stream.cuda_stream or None
-    if _RAW_STREAM is None or _DEVICE is None:
-        return torch.cuda.current_stream().cuda_stream or None
-    return _RAW_STREAM(_DEVICE()) or None
+    if stream is None:
+        return _raw_stream(_device()) or None
+    return stream.cuda_stream or None
 
 
 def _check(status: int, where: str):
