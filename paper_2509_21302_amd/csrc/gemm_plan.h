@@ -29,6 +29,7 @@ struct GemmPlan {
 //          at K = 512, 6.8 / 6.7 at 768 (but 2045 rows -> 2048 8.4 / 8.7), 7.6 / 7.3 at 1024, 10.5 / 9.8 at 2048.
 //   tail   the token rows that fill whole big rounds in big tiles, the rest in deep ones, in one launch (us, big / small / tail): packed codes
 //          17354 x 4096 -> 1184 87 / 89 / 80, 113324 x 768 -> 672 86 / 81 / 72; int8 rows 34003 x 2048 -> 480 53 / 53 / 43.
+//          Few deep tiles after a whole round of them cost 0.6 of one (affine codes, 4298 x 3584 -> 4864, 304 of them: 82 / 87 / 77).
 // Measured (us, big / small / tail): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1, 32976 x 256 -> 3072 56 / 50 / 55,
 // 32976 x 1024 -> 1024 50 / 40 / 45, 32976 x 4096 -> 1024 137 / 130 / 113; int8 blocks 32976 x 4096 -> 1024 140 / 156 / 118,
 // 20000 x 4096 -> 1024 89 / 92 / 71; just past one round of small tiles (big / small) int8 rows 9591 x 4096 -> 896 43 / 66,
@@ -55,8 +56,9 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
     const int main_tile_rows = (int)std::min<double>(tiles_m, std::floor(tiles(M, 256) / 256.0) * 256.0 / tiles_n);
     if (main_tile_rows > 0 && main_tile_rows < tiles_m && ktiles >= 4) {        // the eight-stage ring needs three, and with few is filled with re-reads
         const int rows_main = main_tile_rows * 256;
-        const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + rounds(tiles(M - rows_main, 128)) * deep_round +
-                                 (affine || dump ? 3.0 : 0.0);
+        const double deep_rounds = tiles(M - rows_main, 128) / 256.0, deep_whole = std::floor(deep_rounds), deep_rest = deep_rounds - deep_whole;
+        const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + (affine || dump ? 3.0 : 0.0) +
+                                 (deep_whole + (deep_rest == 0.0 ? 0.0 : deep_whole > 0.0 ? std::max(deep_rest, 0.6) : 1.0)) * deep_round;
         if (tail_cost < std::min(big_cost, small_cost)) return {GemmPlan::kBigThenDeep, rows_main};
     }
     return {small_cost < big_cost ? GemmPlan::kSmall : GemmPlan::kBig, 0};

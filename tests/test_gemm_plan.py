@@ -60,7 +60,8 @@ def test_deep_ring_needs_a_long_chain(plans, M, N, K, bits, affine, want):
 
 # whole rounds in big tiles and the rest in deep ones, where that measured faster than one configuration for all rows (by 5 to 19 %)
 @pytest.mark.parametrize("M,N,K,bits,affine", [(17354, 1184, 4096, 4, 0), (34003, 480, 2048, 8, 0), (46628, 736, 1024, 8, 0), (49610, 1952, 1024, 4, 0),
-                                               (113324, 672, 768, 4, 0), (90930, 192, 4096, 4, 1)])
+                                               (113324, 672, 768, 4, 0), (90930, 192, 4096, 4, 1),
+                                               (4298, 4864, 3584, 4, 1)])
 def test_rows_are_divided(plans, M, N, K, bits, affine):
     (shape, rows), = plans([(M, N, K, bits, affine, 0)])
     assert shape == "big+deep" and rows % 256 == 0 and 0 < rows < M
