@@ -28,11 +28,13 @@
 // are dealt to the waves in turn (piece n to wave n % 4), so any tile whose rows are multiples of 128 divides.
 //
 // Tiles: 256 x 256 per block, one block per compute unit, four waves of 128 x 128 (256 accumulator registers each): the least
-// operand traffic per MFMA that the register file allows; 128 x 128 blocks, two per compute unit, for problems of less than a round.
+// operand traffic per MFMA that the register file allows; 192 x 256 where that fills the last round better; 128 x 128 blocks, two per
+// compute unit, for problems of less than a round or so, and a kernel without shared stages for few tiles (gemm_plan.h has the rule).
 // (256 x 128 blocks, two per compute unit, so that one block's epilogue runs under the other's K loop, were built and measured:
 // the K loop is not limited by the matrix pipes but by what feeds them, and 1.5 times the LDS traffic per MFMA ate the overlap.)
 // The epilogue: accumulators from AGPRs, scale + bias, bf16, rows through a wave-private LDS tile, non-temporal 128-byte line
 // stores.
+#include "gemm_plan.h"
 #include "qvggt_common.h"
 
 #include <algorithm>
@@ -76,7 +78,7 @@ struct E2m3Cfg {
     static constexpr int EP_BYTES = NW * 32 * EP_PITCH;
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + 2 * SC_BYTES + EP_BYTES;
     static_assert(TN % 2 == 0, "the epilogue handles channel sub-tiles in pairs");
-    static_assert(BM % 128 == 0 && BN % 128 == 0, "tiles are whole 128-row blocks of the operand format");
+    static_assert(BM % 64 == 0 && BN % 128 == 0, "tiles are whole 1 KiB pieces of the operand format (64 rows are three), channel tiles whole blocks");
     static_assert(STAGES >= 3, "ring needs one stage being read, one landed, one in flight");
 };
 
@@ -112,14 +114,26 @@ __device__ inline void e_wait_vmcnt()
 
 }  // namespace
 
+// Which tiles of an XCD's range are neighbours: those of one row of tokens, unless the weights are the larger operand and more than its L2 of
+// 4 MiB holds with anything else.  Then those of one column: the XCD reads its share of the weights once and all tokens, instead of all
+// weights.  us at K = 4096, channels first / tokens first: 85 x 4096 -> 4096 9.3 / 6.2 (32 x 64 tiles), 374 -> 3072 16.0 / 11.7 (64 x 64),
+// 1374 -> 4096 24.0 / 20.7 (128 x 128); 1374 x 1024 -> 3072, whose weights fit, 8.8 / 9.0.
+__host__ __device__ inline bool e2m3_tokens_first(int tiles_m, int tiles_n, int N, int K)
+{
+    return tiles_m < tiles_n && (long long)N * K > (4 << 20);
+}
+
 // SHIFTED: sum_j (u_tj - zp_t) qw_oj = sum_j (u_tj - 7.5) qw_oj + (7.5 - zp_t) * wsum_o: the first sum is what the MFMAs give (multiples
-// of 0.5 below 2^23: exact), the second term is added in the epilogue (exact as well)
-template <int TM, int TN, int WM, int WN, int STAGES, int MINB, bool DEBUG, bool SHIFTED = false>
+// of 0.5 below 2^23: exact), the second term is added in the epilogue (exact as well).
+// STREAM_Y: Y goes past the caches (e2m3_streams_y); TOKENS_FIRST: the order of the tiles (e2m3_tokens_first).  Template arguments, because the
+// kernel that asks at run time is slower where the answer is the usual one: both kinds of store in it cost 137400 x 1024 -> 4096 8 %, the second
+// order 1374 x 1024 -> 3072 2 %.
+template <int TM, int TN, int WM, int WN, int STAGES, int MINB, bool DEBUG, bool SHIFTED, bool STREAM_Y, bool TOKENS_FIRST>
 __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per_eu(WM * WN * MINB / 4, WM * WN * MINB / 4))) void e2m3_gemm_kernel(
     const uint8_t *__restrict__ Xf, const float *__restrict__ sx, const uint8_t *__restrict__ Wf,
     const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int N, int K,
     uint16_t *__restrict__ Y, int32_t *__restrict__ acc_debug, int tiles_m, int tiles_n,
-    const float *__restrict__ xzero = nullptr, const float *__restrict__ wsum = nullptr)
+    const float *__restrict__ xzero, const float *__restrict__ wsum)
 {
     using C = E2m3Cfg<TM, TN, WM, WN, STAGES, SHIFTED>;
     constexpr int NM = C::NM, NF = C::NF, LPW = C::LPW;
@@ -133,7 +147,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
     const int units = K >> 6;                                   // even: K is a multiple of 128
     const int ntiles = tiles_m * tiles_n;
 
-    // tile assignment: XCD x (blocks are dealt round-robin to the 8 XCDs) owns a contiguous tile range, channel tiles fastest
+    // tile assignment: XCD x (blocks are dealt round-robin to the 8 XCDs) owns a contiguous tile range
+    auto tile_position = [&](int t, int &tm, int &tn) {
+        if constexpr (TOKENS_FIRST) { tn = t / tiles_m; tm = t % tiles_m; }
+        else { tm = t / tiles_n; tn = t % tiles_n; }
+    };
     const int per_xcd = (ntiles + 7) >> 3;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
     const int tile_end = min((xcd + 1) * per_xcd, ntiles);
@@ -149,15 +167,19 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
     const uint8_t *src[LPW];                                    // wave-uniform: unit 0 of this wave's pieces of the tile under the load cursor
     int ld_tile = first_tile, ld_unit = 0, ld_stage = 0;
     auto set_tile_pointers = [&](int t) {
-        const int tm = t / tiles_n, tn = t % tiles_n;
+        int tm, tn;
+        tile_position(t, tm, tn);
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
             const int n = i * C::NW + wave;
             const bool is_x = n < C::XT;
             const int m = is_x ? n : n - C::XT;
-            // a block past the operand's end: re-read the last one (results unused)
-            const int blk = min((is_x ? tm * (C::BM / RB) : tn * (C::BN / RB)) + m / RB_PIECES, (is_x ? xblocks : wblocks) - 1);
-            src[i] = (is_x ? Xf : Wf) + (size_t)blk * units * RB_BYTES + (m % RB_PIECES) * 1024;
+            // block and piece in it (a 192-row tile starts in the middle of every other block); past the operand's end: the last block again,
+            // results unused
+            const int first = is_x ? tm * C::XT : tn * (C::NT - C::XT);
+            const int blk = C::BM % RB == 0 ? (is_x ? tm * (C::BM / RB) : tn * (C::BN / RB)) + m / RB_PIECES : (first + m) / RB_PIECES;
+            const int piece = C::BM % RB == 0 ? m % RB_PIECES : (first + m) % RB_PIECES;
+            src[i] = (is_x ? Xf : Wf) + (size_t)min(blk, (is_x ? xblocks : wblocks) - 1) * units * RB_BYTES + piece * 1024;
         }
     };
     auto issue_transfer = [&](auto i_c) {
@@ -182,7 +204,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
         advance_cursor();
     };
     auto issue_scales = [&](int t, int sb) {
-        const int tm = t / tiles_n, tn = t % tiles_n;
+        int tm, tn;
+        tile_position(t, tm, tn);
         const uint32_t dst = lds0 + STAGES * C::STAGE_BYTES + sb * C::SC_BYTES;
 #pragma unroll
         for (int g = 0; g < C::SC_GROUPS; ++g) {
@@ -303,7 +326,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
         unit(I1{}, BF{});              // its LDS reads fetch the first fragments of the block's next tile: they live through the epilogue
 
         // ---- epilogue.  32x32 result layout: lane l holds column (l % 32) = token and rows 8*(r/4) + 4*(l/32) + r%4 = channels
-        const int tm = tile / tiles_n, tn = tile % tiles_n;
+        int tm, tn;
+        tile_position(tile, tm, tn);
         const int row0 = tm * C::BM + wm * TM * 32, col0 = tn * C::BN + wn * TN * 32;
         const uint8_t *sc = sc_all + sb * C::SC_BYTES;
         const float *scx = reinterpret_cast<const float *>(sc);
@@ -373,13 +397,18 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
                     v4i rowv[4];
 #pragma unroll
                     for (int it = 0; it < 4; ++it) rowv[it] = *reinterpret_cast<const v4i *>(ep + (it * 8 + rd_row) * C::EP_PITCH + rd_col * 16);
+                    auto store = [&](int it) {
+                        v4i *const dst = reinterpret_cast<v4i *>(yp + (size_t)it * 8 * N);
+                        if constexpr (STREAM_Y) __builtin_nontemporal_store(rowv[it], dst);
+                        else *dst = rowv[it];
+                    };
                     if (rows_left - i * 32 >= 32 && cols_left - jp * 64 >= 64) {
 #pragma unroll
-                        for (int it = 0; it < 4; ++it) __builtin_nontemporal_store(rowv[it], reinterpret_cast<v4i *>(yp + (size_t)it * 8 * N));
+                        for (int it = 0; it < 4; ++it) store(it);
                     } else {
 #pragma unroll
                         for (int it = 0; it < 4; ++it)
-                            if (col_ok && rd_row < rows_left - (i * 32 + it * 8)) __builtin_nontemporal_store(rowv[it], reinterpret_cast<v4i *>(yp + (size_t)it * 8 * N));
+                            if (col_ok && rd_row < rows_left - (i * 32 + it * 8)) store(it);
                     }
                     yp += (size_t)32 * N;
                     __builtin_amdgcn_sched_barrier(0);
@@ -389,6 +418,145 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
         sb ^= 1;
     }
     e_wait_vmcnt<0>();      // transfers issued past the last tile must not outlive the block's LDS allocation
+}
+
+// The same product for few tiles.  A 128 x 128 tile that is alone on its compute unit walks along K at some 190 ns per unit, however deep
+// its ring: a barrier, the LDS reads behind it and four MFMAs, one after the other (64 units of K = 4096: 13 us for any 1 to 1000 rows).  Here
+// the KW waves of a block divide K among themselves instead of the tile: wave w takes units w, w + KW, ..., its fragments come from
+// memory straight into registers, DEPTH units ahead, with no LDS, no barrier and no other wave in the loop, and the partial sums meet in
+// LDS at the end.  They are integers (multiples of 1/2 when SHIFTED) below 2^24, so their sum is the same whatever the order: Y is what
+// the other kernels give, bit for bit.  Price: a fragment is loaded for one tile only, 64 bytes per clock and compute unit, so it loses to the
+// shared LDS stages as soon as the chip is full.  us, 128 x 128 tiles / this one: 64 x 4096 -> 1024 13.3 / 5.2, 500 x 4096 -> 1024 13.2 / 6.4,
+// 1374 x 4096 -> 1024 13.7 / 12.0, 500 x 2048 -> 2048 9.0 / 6.1, 1000 x 1024 -> 1024 6.8 / 5.0 (what the rule in gemm_plan.h picks).
+template <int TM, int TN, int KW>
+struct E2m3FewCfg {
+    static constexpr int THREADS = KW * 64, BM = TM * 32, BN = TN * 32, NF = TM + TN;
+    static constexpr int GROUPS = TM * TN * 4;              // of four accumulator registers of a lane
+    static constexpr int PITCH = 64 * 16 + 128;             // bytes of a group and a gap: neighbouring groups start in different halves of the banks
+    static constexpr int LDS_BYTES = KW * GROUPS * PITCH;
+    static constexpr int OCTS = BN / 8, ITEMS = BM * OCTS;  // runs of eight channels of a token
+    static_assert(RB % BM == 0 && RB % BN == 0, "a tile lies in one block of the operand format");
+    static_assert(THREADS % OCTS == 0, "a thread's runs are the same channels of different tokens");
+};
+
+template <int TM, int TN, int KW, int DEPTH, bool SHIFTED>
+__global__ __launch_bounds__(KW * 64, 1) void e2m3_gemm_few_kernel(
+    const uint8_t *__restrict__ Xf, const float *__restrict__ sx, const uint8_t *__restrict__ Wf, const float *__restrict__ sw,
+    const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ Y, int32_t *__restrict__ acc_debug, int tiles_m, int tiles_n,
+    const float *__restrict__ xzero, const float *__restrict__ wsum)
+{
+    using C = E2m3FewCfg<TM, TN, KW>;
+    constexpr int NF = C::NF;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int units = K >> 6, ntiles = tiles_m * tiles_n;
+    const int per_xcd = (ntiles + 7) >> 3;
+    const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= ntiles) return;
+    const bool tokens_first = e2m3_tokens_first(tiles_m, tiles_n, N, K);
+    const int fast = tokens_first ? tiles_m : tiles_n, outer = tile / fast, inner = tile - outer * fast;
+    const int tm = tokens_first ? inner : outer, tn = tokens_first ? outer : inner;
+
+    const int frow = lane & 31, fhalf = lane >> 5;
+    const int row0 = tm * C::BM, col0 = tn * C::BN;
+    const uint8_t *xb = Xf + (size_t)(row0 / RB) * units * RB_BYTES + (row0 % RB) * U_BYTES + (size_t)(frow * U_BYTES + fhalf * 16);
+    const uint8_t *wb = Wf + (size_t)(col0 / RB) * units * RB_BYTES + (col0 % RB) * U_BYTES + (size_t)(frow * U_BYTES + fhalf * 16);
+    const int hi = 32 - fhalf * 8;                          // from the lane's first 16 bytes to its last 8
+    // fragments as in the kernel above: W sub-tiles, then X sub-tiles
+    v8i F[DEPTH][NF];
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) { F[d][f][6] = 0; F[d][f][7] = 0; }
+    auto load = [&](auto d_c, int u) {
+        constexpr int d = decltype(d_c)::value;
+        const size_t off = (size_t)min(u, units - 1) * RB_BYTES;      // past the end: the last unit again (not used)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const uint8_t *p = (f < TN ? wb + f * 32 * U_BYTES : xb + (f - TN) * 32 * U_BYTES) + off;
+            const v4i v = *reinterpret_cast<const v4i *>(p);
+            const int2 w = *reinterpret_cast<const int2 *>(p + hi);
+            F[d][f][0] = v[0]; F[d][f][1] = v[1]; F[d][f][2] = v[2]; F[d][f][3] = v[3]; F[d][f][4] = w.x; F[d][f][5] = w.y;
+        }
+    };
+    e_static_for<DEPTH>([&](auto d_c) { load(d_c, wave + decltype(d_c)::value * KW); });
+    // what the epilogue needs, asked for before the products: behind the barrier the loads would cost a memory round trip (1 to 3 us of a call)
+    constexpr int IT = (C::ITEMS + C::THREADS - 1) / C::THREADS;
+    const int oct = tid % C::OCTS, t0 = tid / C::OCTS, n = col0 + oct * 8;
+    const int nc = min(n, N - 8);
+    const float4 sw0 = *reinterpret_cast<const float4 *>(sw + nc), sw1 = *reinterpret_cast<const float4 *>(sw + nc + 4);
+    uint4 bw = make_uint4(0u, 0u, 0u, 0u);
+    if (bias != nullptr) bw = *reinterpret_cast<const uint4 *>(bias + nc);
+    float4 ws0, ws1;
+    if constexpr (SHIFTED) { ws0 = *reinterpret_cast<const float4 *>(wsum + nc); ws1 = *reinterpret_cast<const float4 *>(wsum + nc + 4); }
+    float st[IT], zt[SHIFTED ? IT : 1];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int m = min(row0 + t0 + k * (C::THREADS / C::OCTS), M - 1);
+        st[k] = sx[m];
+        if constexpr (SHIFTED) zt[k] = 7.5f - xzero[m];
+    }
+    v16f acc[TN][TM];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.0f;
+    for (int u0 = wave; u0 < units; u0 += DEPTH * KW) {       // every condition is the same for the whole wave
+        e_static_for<DEPTH>([&](auto d_c) {
+            constexpr int d = decltype(d_c)::value;
+            if (u0 + d * KW < units) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        acc[j][i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[d][j], F[d][TN + i], acc[j][i], 2, 2, 0, UNIT_SCALE_ONE, 0, UNIT_SCALE_ONE);
+            }
+            if (u0 + DEPTH * KW < units) load(d_c, u0 + (d + DEPTH) * KW);
+        });
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4 *>(smem + (wave * C::GROUPS + (j * TM + i) * 4 + q) * C::PITCH + lane * 16) =
+                    make_float4(acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]);
+    __syncthreads();
+    // 32x32 result layout as above: group q of a sub-tile holds channels 8 q .. 8 q + 3 in lanes 0 .. 31 and 8 q + 4 .. 8 q + 7 in lanes 32 .. 63
+    const float swv[8] = {sw0.x, sw0.y, sw0.z, sw0.w, sw1.x, sw1.y, sw1.z, sw1.w};
+    const uint32_t bwv[4] = {bw.x, bw.y, bw.z, bw.w};
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int t = t0 + k * (C::THREADS / C::OCTS), m = row0 + t;
+        if ((C::ITEMS % C::THREADS != 0 && t >= C::BM) || m >= M || n >= N) continue;
+        const uint8_t *p = smem + ((oct / 4) * TM * 4 + (t / 32) * 4 + oct % 4) * C::PITCH + (t % 32) * 16;
+        float a[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[e] = 0.0f;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) {
+            const float4 lo = *reinterpret_cast<const float4 *>(p + w * C::GROUPS * C::PITCH), h = *reinterpret_cast<const float4 *>(p + w * C::GROUPS * C::PITCH + 512);
+            a[0] += lo.x; a[1] += lo.y; a[2] += lo.z; a[3] += lo.w; a[4] += h.x; a[5] += h.y; a[6] += h.z; a[7] += h.w;
+        }
+        if (acc_debug != nullptr) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc_debug[(size_t)m * N + n + e] = (int)a[e];
+        }
+        if constexpr (SHIFTED) {
+            const float wsv[8] = {ws0.x, ws0.y, ws0.z, ws0.w, ws1.x, ws1.y, ws1.z, ws1.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[e] = fmaf(zt[k], wsv[e], a[e]);
+        }
+        uint32_t out[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            out[e] = pack_bf16x2(fmaf(a[2 * e], swv[2 * e] * st[k], __uint_as_float(bwv[e] << 16)), fmaf(a[2 * e + 1], swv[2 * e + 1] * st[k], __uint_as_float(bwv[e] & 0xFFFF0000u)));
+        *reinterpret_cast<uint4 *>(Y + (size_t)m * N + n) = make_uint4(out[0], out[1], out[2], out[3]);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -434,108 +602,130 @@ hipError_t run_codes_to_e2m3(const uint8_t *packed, int rows, int K, uint8_t *ou
 }
 
 // every instantiation launched below, with the dynamic LDS it needs
-#define QVGGT_E2M3_KERNELS(TM, TN, WM, WN, ST, MB)                                                                                  \
-    {reinterpret_cast<const void *>(e2m3_gemm_kernel<TM, TN, WM, WN, ST, MB, false, false>), E2m3Cfg<TM, TN, WM, WN, ST, false>::LDS_BYTES}, \
-    {reinterpret_cast<const void *>(e2m3_gemm_kernel<TM, TN, WM, WN, ST, MB, true, false>), E2m3Cfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
-    {reinterpret_cast<const void *>(e2m3_gemm_kernel<TM, TN, WM, WN, ST, MB, false, true>), E2m3Cfg<TM, TN, WM, WN, ST, true>::LDS_BYTES}
-static const LdsKernel e2m3_lds_kernel_list[] = {QVGGT_E2M3_KERNELS(4, 4, 2, 2, 5, 1), QVGGT_E2M3_KERNELS(2, 2, 2, 2, 4, 2)};
+#define QVGGT_E2M3_KERNEL(TM, TN, WM, WN, ST, MB, DEBUG, SHIFTED, STREAM_Y, TOKENS_FIRST) \
+    {reinterpret_cast<const void *>(e2m3_gemm_kernel<TM, TN, WM, WN, ST, MB, DEBUG, SHIFTED, STREAM_Y, TOKENS_FIRST>), E2m3Cfg<TM, TN, WM, WN, ST, SHIFTED>::LDS_BYTES}
+#define QVGGT_E2M3_KERNELS(TM, TN, WM, WN, ST, MB)                                                                            \
+    QVGGT_E2M3_KERNEL(TM, TN, WM, WN, ST, MB, false, false, true, false), QVGGT_E2M3_KERNEL(TM, TN, WM, WN, ST, MB, true, false, true, false), \
+    QVGGT_E2M3_KERNEL(TM, TN, WM, WN, ST, MB, false, true, true, false)
+#define QVGGT_E2M3_VARIANT(TM, TN, WM, WN, ST, MB, STREAM_Y, TOKENS_FIRST) \
+    QVGGT_E2M3_KERNEL(TM, TN, WM, WN, ST, MB, false, false, STREAM_Y, TOKENS_FIRST), QVGGT_E2M3_KERNEL(TM, TN, WM, WN, ST, MB, false, true, STREAM_Y, TOKENS_FIRST)
+#define QVGGT_E2M3_FEW_KERNELS(TM, TN, KW, DEPTH)                                                                                   \
+    {reinterpret_cast<const void *>(e2m3_gemm_few_kernel<TM, TN, KW, DEPTH, false>), E2m3FewCfg<TM, TN, KW>::LDS_BYTES}, \
+    {reinterpret_cast<const void *>(e2m3_gemm_few_kernel<TM, TN, KW, DEPTH, true>), E2m3FewCfg<TM, TN, KW>::LDS_BYTES}
+static const LdsKernel e2m3_lds_kernel_list[] = {QVGGT_E2M3_KERNELS(4, 4, 2, 2, 5, 1), QVGGT_E2M3_KERNELS(3, 4, 2, 2, 5, 1),
+                                                 QVGGT_E2M3_KERNELS(2, 2, 2, 2, 4, 2), QVGGT_E2M3_VARIANT(4, 4, 2, 2, 5, 1, false, false),
+                                                 QVGGT_E2M3_VARIANT(3, 4, 2, 2, 5, 1, false, false), QVGGT_E2M3_VARIANT(2, 2, 2, 2, 4, 2, true, true),
+                                                 QVGGT_E2M3_FEW_KERNELS(2, 2, 4, 4),
+                                                 QVGGT_E2M3_FEW_KERNELS(1, 2, 4, 4), QVGGT_E2M3_FEW_KERNELS(1, 1, 8, 2)};
+#undef QVGGT_E2M3_KERNEL
 #undef QVGGT_E2M3_KERNELS
+#undef QVGGT_E2M3_VARIANT
+#undef QVGGT_E2M3_FEW_KERNELS
 static const LdsKernels e2m3_lds_kernels(e2m3_lds_kernel_list);
 
-template <int TM, int TN, int WM, int WN, int STAGES, int MINB, bool SHIFTED = false>
-static hipError_t launch_e2m3(const uint8_t *Xf, const float *sx, const uint8_t *Wf, const float *sw, const void *bias,
-                              int M, int N, int K, void *Y, int32_t *acc_debug, hipStream_t stream,
-                              const float *xzero = nullptr, const float *wsum = nullptr)
+namespace {
+
+// A product's operands and result; xzero and wsum only with SHIFTED codes.
+struct E2m3Problem {
+    const uint8_t *Xf;
+    const float *sx;
+    const uint8_t *Wf;
+    const float *sw;
+    const uint16_t *bias;
+    int M, N, K;
+    uint16_t *Y;
+    int32_t *acc_debug;
+    const float *xzero, *wsum;
+
+    // token rows row0 .. row0 + rows - 1; row0 is a multiple of 128, i.e. whole blocks of the operand format
+    E2m3Problem part(int row0, int rows) const
+    {
+        E2m3Problem p = *this;
+        p.Xf += (size_t)row0 * ((size_t)K / 4 * 3);
+        p.sx += row0;
+        p.M = rows;
+        p.Y += (size_t)row0 * N;
+        if (acc_debug != nullptr) p.acc_debug += (size_t)row0 * N;
+        if (xzero != nullptr) p.xzero += row0;
+        return p;
+    }
+};
+
+template <int TM, int TN, int WM, int WN, int STAGES, int MINB, bool SHIFTED>
+hipError_t launch_e2m3(const E2m3Problem &p, hipStream_t stream)
 {
     using C = E2m3Cfg<TM, TN, WM, WN, STAGES, SHIFTED>;
-    const bool debug = acc_debug != nullptr;
-    auto kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, false, SHIFTED>;
-    if constexpr (!SHIFTED) {
-        if (debug) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, true, false>;
+    const int tiles_m = (p.M + C::BM - 1) / C::BM, tiles_n = (p.N + C::BN - 1) / C::BN;
+    auto kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, false, SHIFTED, true, false>;
+    if constexpr (C::BM > 128) {
+        if (!e2m3_streams_y(p.M, p.N)) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, false, SHIFTED, false, false>;
     } else {
-        if (debug) return hipErrorInvalidValue;      // the corrected sum is never an integer register: no dump
+        if (e2m3_tokens_first(tiles_m, tiles_n, p.N, p.K)) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, false, SHIFTED, true, true>;
     }
-    hipError_t e = prepare_device();                 // the kernel's dynamic-LDS limit on this device (see e2m3_lds_kernels above)
-    if (e != hipSuccess) return e;
-    const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
+    if constexpr (!SHIFTED) {
+        if (p.acc_debug != nullptr) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, true, false, true, false>;
+    } else {
+        if (p.acc_debug != nullptr) return hipErrorInvalidValue;      // the corrected sum is never an integer register: no dump
+    }
     const int ntiles = tiles_m * tiles_n;
     int grid = 256 * MINB;
     if (grid > (ntiles + 7) / 8 * 8) grid = (ntiles + 7) / 8 * 8;
-    kern<<<grid, C::THREADS, C::LDS_BYTES, stream>>>(Xf, sx, Wf, sw, reinterpret_cast<const uint16_t *>(bias), M, N, K,
-                                                     reinterpret_cast<uint16_t *>(Y), acc_debug, tiles_m, tiles_n, xzero, wsum);
+    kern<<<grid, C::THREADS, C::LDS_BYTES, stream>>>(p.Xf, p.sx, p.Wf, p.sw, p.bias, p.M, p.N, p.K, p.Y, p.acc_debug, tiles_m, tiles_n, p.xzero, p.wsum);
     return hipGetLastError();
 }
 
-// Which tile shape runs where.  Both configurations work in rounds (256 big tiles, or 512 small ones: two blocks per compute
-// unit), and a last round that is mostly empty costs as much as a full one.  A round of small tiles does half the work of a round
-// of big ones and measured 0.50 - 0.54 of its duration at K = 1024 and 0.6 - 0.75 at K = 4096.  Three plans are priced in
-// hundredths of a big round: everything big, everything small, or the token rows that fill whole big rounds through the big kernel
-// and the rest through the small one in a second launch on the same stream (rows are independent; the two launches write disjoint
-// rows of Y, and row offsets that are multiples of 256 are whole 128-row blocks of the operand format).  The split has to win by
-// 3 % to be taken.  Measured: 32976 x 4096 -> 1024 (2.02 big rounds) 85.5 -> 78.3 us; at K = 1024 the same token count is left as it
-// was (a split that ignored the launch cost made 32976 x 1024 -> 1024 11 % slower), and so is 137400 x 4096 -> 1024 (8.4 rounds).
-// Counting whole rounds overstates small tiles just past one (K = 1024, 2048 tiles 29.9 us, 2064 31.3; K = 4096, 512 tiles 24.1, 528 32.3), as
-// the int8-instruction kernel's plan, which prices the last round by its tiles, does not.  It matters little here: with the codes of real rows,
-// 4093 to 65533 rows -> 1024, the plan is within 3 % of the best at K = 2048 and 4096; at K = 1024 it gives away 8 to 10 % at 12285 and 65533
-// rows (14.4 us for 13.3, 62 for 56) and at most 6 % elsewhere.
-template <class Big, class Small>
-static hipError_t e2m3_by_rounds(int M, int N, int K, Big &&big, Small &&small)
+template <int TM, int TN, int KW, int DEPTH, bool SHIFTED>
+hipError_t launch_e2m3_few(const E2m3Problem &p, hipStream_t stream)
 {
-    const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
-    // the second launch costs about 6 us whatever the shape; a big round takes about 4.7 + 6.7 K / 1024 us (11 us at K = 1024, 31 at 4096)
-    const long long small_unit = (K <= 2048 ? 55 : 70), launch_cost = 600000 / (4700 + 6700LL * K / 1024);
-    const long long big_tiles = (long long)tiles_m * tiles_n;
-    const long long big_cost = (big_tiles + 255) / 256 * 100;
-    const long long small_cost = (((long long)((M + 127) / 128) * ((N + 127) / 128) + 511) / 512) * small_unit;
-    const long long whole_cost = small_cost < big_cost ? small_cost : big_cost;
-    const int main_tile_rows = (int)std::min<long long>(tiles_m, big_tiles / 256 * 256 / tiles_n);
-    if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
-        const int rows_main = main_tile_rows * 256, rows_rem = M - rows_main;
-        const long long main_cost = ((long long)main_tile_rows * tiles_n + 255) / 256 * 100;
-        const long long rem_cost = (((long long)((rows_rem + 127) / 128) * ((N + 127) / 128) + 511) / 512) * small_unit;
-        if ((main_cost + rem_cost + launch_cost) * 100 < whole_cost * 97) {
-            const hipError_t e = big(0, rows_main);
-            if (e != hipSuccess) return e;
-            return small(rows_main, rows_rem);
-        }
-    }
-    return small_cost < big_cost ? small(0, M) : big(0, M);
+    using C = E2m3FewCfg<TM, TN, KW>;
+    if (SHIFTED && p.acc_debug != nullptr) return hipErrorInvalidValue;
+    const int tiles_m = (p.M + C::BM - 1) / C::BM, tiles_n = (p.N + C::BN - 1) / C::BN;
+    e2m3_gemm_few_kernel<TM, TN, KW, DEPTH, SHIFTED><<<(tiles_m * tiles_n + 7) / 8 * 8, C::THREADS, C::LDS_BYTES, stream>>>(
+        p.Xf, p.sx, p.Wf, p.sw, p.bias, p.M, p.N, p.K, p.Y, p.acc_debug, tiles_m, tiles_n, p.xzero, p.wsum);
+    return hipGetLastError();
 }
+
+template <bool SHIFTED>
+hipError_t launch_e2m3_shape(E2m3Plan::Shape shape, const E2m3Problem &p, hipStream_t stream)
+{
+    switch (shape) {
+        case E2m3Plan::k256: return launch_e2m3<4, 4, 2, 2, 5, 1, SHIFTED>(p, stream);
+        case E2m3Plan::k192: return launch_e2m3<3, 4, 2, 2, 5, 1, SHIFTED>(p, stream);
+        case E2m3Plan::k128: return launch_e2m3<2, 2, 2, 2, 4, 2, SHIFTED>(p, stream);
+        case E2m3Plan::k64: return launch_e2m3_few<2, 2, 4, 4, SHIFTED>(p, stream);
+        case E2m3Plan::k32x64: return launch_e2m3_few<1, 2, 4, 4, SHIFTED>(p, stream);
+        case E2m3Plan::k32: return launch_e2m3_few<1, 1, 8, 2, SHIFTED>(p, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <bool SHIFTED>
+hipError_t run_e2m3(const E2m3Problem &p, hipStream_t stream)
+{
+    if (p.M <= 0) return hipSuccess;
+    hipError_t e = prepare_device();                 // the kernels' dynamic-LDS limits on this device (see e2m3_lds_kernels above)
+    if (e != hipSuccess) return e;
+    const E2m3Plan plan = e2m3_gemm_plan(p.M, p.N, p.K);
+    if (plan.rows_main == p.M) return launch_e2m3_shape<SHIFTED>(plan.shape, p, stream);
+    e = launch_e2m3_shape<SHIFTED>(plan.shape, p.part(0, plan.rows_main), stream);
+    if (e != hipSuccess) return e;
+    return launch_e2m3_shape<SHIFTED>(plan.rest, p.part(plan.rows_main, p.M - plan.rows_main), stream);
+}
+
+}  // namespace
 
 // E2M3 blocks of both operands -> Y.
 hipError_t run_e2m3_gemm(const uint8_t *Xf, const float *sx, const uint8_t *Wf, const float *sw, const void *bias, int M, int N,
                          int K, void *Y, int32_t *acc_debug, hipStream_t stream)
 {
-    if (M <= 0) return hipSuccess;
-    const size_t KB = (size_t)K / 4 * 3;                  // bytes per row: row0 below is a multiple of 256, i.e. whole 128-row blocks
-    auto big = [&](int row0, int rows) {
-        return launch_e2m3<4, 4, 2, 2, 5, 1>(Xf + (size_t)row0 * KB, sx + row0, Wf, sw, bias, rows, N, K,
-                                             static_cast<uint16_t *>(Y) + (size_t)row0 * N,
-                                             acc_debug ? acc_debug + (size_t)row0 * N : nullptr, stream);
-    };
-    auto small = [&](int row0, int rows) {
-        return launch_e2m3<2, 2, 2, 2, 4, 2>(Xf + (size_t)row0 * KB, sx + row0, Wf, sw, bias, rows, N, K,
-                                             static_cast<uint16_t *>(Y) + (size_t)row0 * N,
-                                             acc_debug ? acc_debug + (size_t)row0 * N : nullptr, stream);
-    };
-    return e2m3_by_rounds(M, N, K, big, small);
+    return run_e2m3<false>({Xf, sx, Wf, sw, static_cast<const uint16_t *>(bias), M, N, K, static_cast<uint16_t *>(Y), acc_debug, nullptr, nullptr}, stream);
 }
 
 // Activations as u - 7.5 with a zero point per token (xzero), weights as before, wsum their code sums per channel.
 hipError_t run_e2m3_gemm_shifted(const uint8_t *Xf, const float *sx, const float *xzero, const uint8_t *Wf, const float *sw,
                                  const float *wsum, const void *bias, int M, int N, int K, void *Y, hipStream_t stream)
 {
-    if (M <= 0) return hipSuccess;
-    const size_t KB = (size_t)K / 4 * 3;
-    auto big = [&](int row0, int rows) {
-        return launch_e2m3<4, 4, 2, 2, 5, 1, true>(Xf + (size_t)row0 * KB, sx + row0, Wf, sw, bias, rows, N, K,
-                                                   static_cast<uint16_t *>(Y) + (size_t)row0 * N, nullptr, stream, xzero + row0, wsum);
-    };
-    auto small = [&](int row0, int rows) {
-        return launch_e2m3<2, 2, 2, 2, 4, 2, true>(Xf + (size_t)row0 * KB, sx + row0, Wf, sw, bias, rows, N, K,
-                                                   static_cast<uint16_t *>(Y) + (size_t)row0 * N, nullptr, stream, xzero + row0, wsum);
-    };
-    return e2m3_by_rounds(M, N, K, big, small);
+    return run_e2m3<true>({Xf, sx, Wf, sw, static_cast<const uint16_t *>(bias), M, N, K, static_cast<uint16_t *>(Y), nullptr, xzero, wsum}, stream);
 }
 
 }  // namespace qvggt

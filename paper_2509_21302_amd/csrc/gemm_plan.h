@@ -64,4 +64,81 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
     return {small_cost < big_cost ? GemmPlan::kSmall : GemmPlan::kBig, 0};
 }
 
+// Which tile shape of the E2M3 GEMM runs where.
+struct E2m3Plan {
+    enum Shape { k256, k192, k128, k64, k32x64, k32 } shape;
+    int rows_main;      // token rows of `shape`: all of them, or whole 256-row tiles that fill whole rounds
+    Shape rest;         // what takes the others, in a second launch
+};
+
+// Rows of Y that are whole 128-byte lines (N a multiple of 64) go past the caches.  Others are written in pieces of lines, which the memory
+// takes badly one by one: while Y fits the memory-side cache (256 MB), the 256- and 192-row tiles leave them there to be put together.  us at
+// K = 1024, past the caches / through them, 256-row tiles: 2000 x 3056 (12 MB) 13.5 / 14.5, 4000 (24) 19.9 / 16.7, 10992 (67) 54 / 41, 34000 (208)
+// 121 / 96, 50000 (306) 169 / 163, 192-row tiles 159 / 176.  The 128-row tiles, two blocks to a compute unit, do not gain (35.0 / 33.8, 91 / 90,
+// 136 / 191), nor do whole lines (10992 x 4096 40.5 / 43.9, 1374 x 3072 12.6 / 13.8).
+inline bool e2m3_streams_y(int M, int N)
+{
+    const double bytes = 2.0 * M * N;
+    return N % 64 == 0 || bytes < 20e6 || bytes > 210e6;
+}
+
+// The plan that this model prices lowest, in microseconds, fitted to 550 random problems of 16 to 137400 rows and all sizes of K that were
+// measured in every shape on two cards (as graph nodes, codes of a normal distribution): within 3 to 7 % of the time (rms), the choice 0.7 %
+// slower than the best on geometric average.  The last three shapes are priced 4 % above what they took, the 128s' last word where it is close.
+//   256, 192   tokens x 256 channels per block, one per compute unit: whole rounds of 256 tiles, and the tiles themselves (power).  192 rows
+//              where they waste less of the last round: 32976 x 4096 -> 1024 (2.02 rounds of 256) 77.3 us in 256s and a rest, 71.7 in 192s;
+//              10992 x 4096 -> 1024 28.3 / 26.5; the LDS traffic per MFMA is a sixth more: 87025 x 1024 -> 3072 192 / 210.
+//   128        128 x 128, two blocks per compute unit: by number beyond the first block, at least 0.3 of a round for a last one.
+//   64, 32x64, 32   tokens x channels, K divided among the block's waves (e2m3_gemm_few_kernel): for problems whose 128 x 128 tiles would walk along
+//              K alone on their compute units (64 x 4096 -> 1024 13.3 us in 128s, 7.5 / 6.1 / 5.2 in these; 500 x 4096 -> 1024 13.2, 7.6 / 6.4 / 7.6;
+//              1000 x 1024 -> 1024 6.7, 5.0 / 5.0 / 6.1; 1374 x 1024 -> 3072 8.9, 11.2 / 11.3 / 15.4).
+inline double e2m3_shape_cost(E2m3Plan::Shape shape, int M, int N, int K)
+{
+    auto tiles = [&](int m, int n) { return (double)((M + m - 1) / m) * ((N + n - 1) / n) / 256.0; };        // per compute unit
+    const double k = K / 1024.0, pieces = N % 64 ? 1.0 : 0.0;
+    switch (shape) {
+        case E2m3Plan::k256: {
+            const double t = tiles(256, 256);
+            return 5.3 - 0.7 * k + std::ceil(t) * (3.4 + 4.85 * k) + t * (1.6 + 2.1 * k + 1.2 * pieces);
+        }
+        case E2m3Plan::k192: {
+            const double t = tiles(192, 256);
+            return 5.2 - 0.65 * k + std::ceil(t) * (2.5 + 4.25 * k) + t * (1.55 + 1.4 * k + 0.7 * pieces);
+        }
+        case E2m3Plan::k128: {
+            const double t = tiles(128, 128), rounds = t / 2.0, whole = std::floor(rounds), rest = rounds - whole;
+            const double priced = whole > 0.0 && rest > 0.0 ? whole + std::max(rest, 0.3) : rounds;
+            return 5.05 + 2.2 * k + std::min(t, 1.0) * (1.2 + 0.6 * k) + std::max(priced - 0.5, 0.0) * std::max(2.1 + 4.95 * k, 3.4 + 1.8 * pieces);
+        }
+        case E2m3Plan::k64: return 4.85 + 0.93 * k + (std::ceil(tiles(64, 64)) - 1.0) * (0.95 + 1.1 * k);
+        case E2m3Plan::k32x64: return 4.45 + 0.65 * k + (std::ceil(tiles(32, 64)) - 1.0) * (0.38 + 0.81 * k);
+        case E2m3Plan::k32: return 4.8 + 0.37 * k + (std::ceil(tiles(32, 32)) - 1.0) * (0.38 + 0.52 * k);
+    }
+    return 0.0;
+}
+
+inline E2m3Plan e2m3_gemm_plan(int M, int N, int K)
+{
+    auto cheapest = [&](int rows, double &cost) {
+        E2m3Plan::Shape best = E2m3Plan::k256;
+        cost = e2m3_shape_cost(best, rows, N, K);
+        for (E2m3Plan::Shape s : {E2m3Plan::k192, E2m3Plan::k128, E2m3Plan::k64, E2m3Plan::k32x64, E2m3Plan::k32}) {
+            const double c = e2m3_shape_cost(s, rows, N, K);
+            if (c < cost) { cost = c; best = s; }
+        }
+        return best;
+    };
+    double whole, rest;
+    const E2m3Plan::Shape shape = cheapest(M, whole);
+    // the token rows that fill whole rounds of 256 x 256 tiles, and the others in a launch of their own, if that wins by 3 %
+    const long long tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
+    const long long main_tile_rows = tiles_m * tiles_n / 256 * 256 / tiles_n;
+    if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
+        const int rows_main = (int)main_tile_rows * 256;
+        const E2m3Plan::Shape rest_shape = cheapest(M - rows_main, rest);
+        if (e2m3_shape_cost(E2m3Plan::k256, rows_main, N, K) + rest < 0.97 * whole) return {E2m3Plan::k256, rows_main, rest_shape};
+    }
+    return {shape, M, shape};
+}
+
 }  // namespace qvggt

@@ -116,3 +116,45 @@ def test_gpu_tests_reach_the_plans_they_are_named_for(plans):
             assert rows == ((M + 255) // 256 * tiles_n // 256 * 256 // tiles_n) * 256
     for plan in ("big", "small", "deep", "big+deep"):
         assert any(want == plan for _, _, _, want in ASYM_PLANS) and any(p[4] == plan for p in TILE_PLANS)
+
+
+E2M3_DRIVER = r"""
+#include "gemm_plan.h"
+#include <cstdio>
+int main()
+{
+    int M, N, K;
+    const char *names[] = {"256", "192", "128", "64", "32x64", "32"};
+    while (std::scanf("%d %d %d", &M, &N, &K) == 3) {
+        const qvggt::E2m3Plan p = qvggt::e2m3_gemm_plan(M, N, K);
+        std::printf("%s %s %d\n", names[p.shape], names[p.rest], p.rows_main);
+    }
+}
+"""
+
+
+def test_e2m3_plans(tmp_path):
+    """The GPU test's table reaches the tile shapes it names; every plan of 100000 random problems is one of them, and one that divides the rows
+    gives whole blocks of the operand format to the first launch and leaves some to the second."""
+    from tests.test_gpu_e2m3 import E2M3_PLANS
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text(E2M3_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+
+    def ask(problems):
+        lines = subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
+        return [(lines[i], lines[i + 1], int(lines[i + 2])) for i in range(0, len(lines), 3)]
+    for (M, N, K, want), (shape, rest, rows) in zip(E2M3_PLANS, ask([p[:3] for p in E2M3_PLANS])):
+        assert (shape if rows == M else f"{shape}+{rest}") == want, (M, N, K)
+    rng = random.Random(5)
+    problems = [(int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(4096)))),
+                 rng.choice([128, 256, 512, 768, 1024, 1280, 1792, 2048, 3584, 4096, 6144, 8192])) for _ in range(100000)]
+    divided = 0
+    for (M, N, K), (shape, rest, rows) in zip(problems, ask(problems)):
+        if rows != M:
+            divided += 1
+            assert shape == "256" and rows % 256 == 0 and 0 < rows < M
+    assert divided > 100
+    assert {p[3].split("+")[0] for p in E2M3_PLANS} == {"256", "192", "128", "64", "32x64", "32"}

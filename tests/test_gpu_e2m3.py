@@ -314,3 +314,54 @@ def test_linear_e2m3_few_rows(M, K, N):
     assert torch.equal(Y, G.gpu_linear(G.to_dev(X), pg, None))
     want = oracle.linear(X, oracle.prepare_weights(W, oracle.rotated_col_absmax(X, pre_signs=signs), pre_signs=signs), pre_signs=signs)
     assert G.rel_fro(G.bf16_bits(Y), want.Y) <= G.Y_REL_FRO
+
+
+# Each tile shape of the plan (csrc/gemm_plan.h; tests/test_gemm_plan.py holds the table to it): one row, tile edges and remainders, channels that
+# end inside a tile, K with fewer units than a block has waves, rows of Y that are no whole lines (520, 1040, 3056), weights beyond an L2.
+E2M3_PLANS = [(1, 16, 4096, "32"), (33, 48, 2048, "32"), (33, 48, 8192, "32"), (200, 1040, 4096, "32"), (64, 4096, 4096, "32"),
+              (31, 144, 1024, "32x64"), (97, 2064, 128, "32x64"), (500, 1024, 4096, "32x64"), (300, 384, 256, "32x64"), (385, 3088, 2048, "32x64"),
+              (700, 1040, 2048, "64"), (1374, 1024, 4096, "64"),
+              (1374, 3072, 1024, "128"), (1000, 2064, 1024, "128"), (5500, 3056, 768, "128"), (2000, 4000, 2048, "128"),
+              (10992, 1024, 4096, "192"), (2749, 3104, 1024, "192"), (8300, 1040, 2048, "192"),
+              (13741, 3056, 512, "256"), (10992, 4096, 1024, "256"),
+              (16500, 4096, 1024, "256+32x64"), (16600, 1024, 2048, "256+32")]
+
+
+@pytest.mark.parametrize("M,N,K,plan", E2M3_PLANS)
+def test_e2m3_gemm_in_every_tile_shape(M, N, K, plan):
+    """The integer sums and Y are those of the int8-instruction kernel, bit for bit; nothing past the last row is written."""
+    gen = torch.Generator(device="cpu").manual_seed(M + N + K)
+    qx = torch.randint(-7, 8, (M, K), generator=gen, dtype=torch.int8).numpy()
+    qw = torch.randint(-7, 8, (N, K), generator=gen, dtype=torch.int8).numpy()
+    rng = np.random.default_rng(M + K)
+    dx, dw = G.to_dev(np.exp(rng.uniform(-3, 1, M)).astype(np.float32)), G.to_dev(np.exp(rng.uniform(-8, -4, N)).astype(np.float32))
+    bias = G.to_dev(f32_to_bf16_bits((rng.standard_normal(N) * 0.02).astype(np.float32)))
+    (Xq, Xf), (Wq, Wf) = _e2m3(qx), _e2m3(qw)
+    whole = torch.full((M + 3, N), 7.0, dtype=torch.bfloat16, device=G.DEV)
+    acc = torch.full((M, N), 12345, dtype=torch.int32, device=G.DEV)
+    G.q.qvggt_e2m3_gemm(Xf, dx, Wf, dw, bias, M, N, K, whole[:M], acc)
+    Y8, acc8 = torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV), torch.empty_like(acc)
+    G.q.qvggt_w4a4_gemm(Xq, dx, Wq, dw, bias, M, N, K, Y8, acc8)
+    assert torch.equal(acc, acc8)
+    assert torch.equal(whole[:M].view(torch.int16), Y8.view(torch.int16)) and (whole[M:] == 7.0).all().item()
+    G.q.qvggt_e2m3_gemm(Xf, dx, Wf, dw, None, M, N, K, whole[:M])           # without bias and without the dump: the kernels that calls run
+    G.q.qvggt_w4a4_gemm(Xq, dx, Wq, dw, None, M, N, K, Y8)
+    assert torch.equal(whole[:M].view(torch.int16), Y8.view(torch.int16)) and (whole[M:] == 7.0).all().item()
+
+
+@pytest.mark.parametrize("M,N,K,plan", [p for p in E2M3_PLANS if p[2] in (1024, 2048, 4096) and p[0] < 12000])
+def test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan):
+    """Affine codes through the same tile shapes: Y of the int8-instruction kernel on the same codes, bit for bit."""
+    rng = np.random.default_rng(M + N)
+    X = G.to_dev(_heavy_bf16(M, K, M + K))
+    signs, inv = G.to_dev((rng.integers(0, 2, K) * 2 - 1).astype(np.int8)), G.to_dev(np.exp(rng.uniform(-1, 1, K)).astype(np.float32))
+    Wq, Wf = _e2m3(rng.integers(-7, 8, (N, K)).astype(np.int8))
+    dw, wsum = G.to_dev(np.exp(rng.uniform(-8, -4, N)).astype(np.float32)), G.gpu_code_sums(Wq, N, K)
+    bias = G.to_dev(f32_to_bf16_bits((rng.standard_normal(N) * 0.02).astype(np.float32)))
+    Xq, sx, zx = G.gpu_rsq_asym(X, signs, inv)
+    Xf = torch.full((G.q.qvggt_e2m3_bytes(M, K),), 0xA5, dtype=torch.uint8, device=G.DEV)
+    G.q.qvggt_rotate_smooth_quant_asym_e2m3(X, signs, inv, Xf, sx, zx)
+    whole, Y8 = torch.full((M + 3, N), 7.0, dtype=torch.bfloat16, device=G.DEV), torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV)
+    G.q.qvggt_e2m3_gemm_shifted(Xf, sx, zx, Wf, dw, wsum, bias, M, N, K, whole[:M])
+    G.q.qvggt_w4a4_gemm_asym(Xq, sx, zx, Wq, dw, wsum, bias, M, N, K, Y8)
+    assert torch.equal(whole[:M].view(torch.int16), Y8.view(torch.int16)) and (whole[M:] == 7.0).all().item()
