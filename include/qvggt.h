@@ -104,6 +104,21 @@ int qvggt_prep_weights(const void *W, int w_dtype, int N, int K, const float *ac
                        float *inv_smooth, void *stream);
 
 /*
+ * The same for a layer whose codes are kept in both forms, in two calls and three launches (bf16 W [N, K] and X_cal [M, K], M >= 1, K = 1024,
+ * 2048 or 4096; QVGGT_ERR_SHAPE otherwise): qvggt_rotated_col_absmax of X_cal and of W, then qvggt_prep_weights (int8_codes = 0, bits = 4) or
+ * qvggt_prep_weights_i8 (int8_codes = 1, bits 4..8) into Wq, w_scale and inv_smooth, and Wq's codes as E2M3 blocks resp. int8 blocks into
+ * Wblocks (qvggt_e2m3_bytes / qvggt_i8b_bytes of N rows; its padding rows are not written).  n_unrepresentable: as in qvggt_codes_to_e2m3, but set
+ * and not added to (int8_codes = 1: may be NULL, not written).  The same outputs, bit for bit.  workspace: qvggt_layer_workspace_bytes(M, N, K)
+ * bytes, written by the first call and read by the second, which takes the same M, N and K.
+ */
+size_t qvggt_layer_workspace_bytes(int M, int N, int K);
+int qvggt_layer_statistics(const void *W, const void *X_cal, int M, int N, int K, const int8_t *signs, void *workspace,
+                           size_t workspace_bytes, void *stream);
+int qvggt_layer_codes(const void *W, int M, int N, int K, const int8_t *signs, float alpha, int bits, int int8_codes, void *Wq,
+                      void *Wblocks, float *w_scale, float *inv_smooth, uint32_t *n_unrepresentable, void *workspace,
+                      size_t workspace_bytes, void *stream);
+
+/*
  * Offline half with calibrated parameters handed in (appendix, implementation details: the channel-wise factor and the
  * quantization steps are learnable during calibration; this is what deploys the learned values, the activation side being
  * qvggt_rotate_smooth_quant_static):

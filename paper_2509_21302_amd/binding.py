@@ -33,6 +33,7 @@ EXPORTS = [
     "qvggt_workspace_bytes_i8", "qvggt_layout_int8",
     "qvggt_nfds_workspace_bytes", "qvggt_nfds_moments", "qvggt_nfds_frame_correlation", "qvggt_nfds_scores",
     "qvggt_nfds_keep_lowest", "qvggt_nfds_kmeans_step",
+    "qvggt_layer_workspace_bytes", "qvggt_layer_statistics", "qvggt_layer_codes",
     "qvggt_rotate_rows", "qvggt_calib_workspace_bytes", "qvggt_calib_loss_grad", "qvggt_calib_descent_step",
 ]
 
@@ -133,6 +134,12 @@ def load_library() -> C.CDLL:
     lib.qvggt_linear.argtypes = [vp, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.qvggt_prep_weights_given.restype = i
     lib.qvggt_prep_weights_given.argtypes = [vp, i, i, i, vp, vp, vp, i, vp, vp, vp, vp]
+    lib.qvggt_layer_workspace_bytes.restype = sz
+    lib.qvggt_layer_workspace_bytes.argtypes = [i, i, i]
+    lib.qvggt_layer_statistics.restype = i
+    lib.qvggt_layer_statistics.argtypes = [vp, vp, i, i, i, vp, vp, sz, vp]
+    lib.qvggt_layer_codes.restype = i
+    lib.qvggt_layer_codes.argtypes = [vp, i, i, i, vp, f, i, i, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.qvggt_prep_weights_i8.restype = i
     lib.qvggt_prep_weights_i8.argtypes = [vp, i, i, i, vp, vp, f, i, vp, vp, vp, vp]
     lib.qvggt_rotate_smooth_quant_i8.restype = i
@@ -447,6 +454,31 @@ def qvggt_prep_weights_given(W, c_hat, signs, w_step, bits, Wq, w_scale, inv_smo
     _check(load_library().qvggt_prep_weights_given(_ptr(W), _dtype_code(W), N, K, _ptr(c_hat), _ptr(signs), _ptr(w_step), int(bits),
                                                    _ptr(Wq), _ptr(w_scale), _ptr(inv_smooth), _stream(stream)),
            "qvggt_prep_weights_given")
+
+
+def qvggt_layer_workspace_bytes(M: int, N: int, K: int) -> int:
+    return int(load_library().qvggt_layer_workspace_bytes(M, N, K))
+
+
+def _bf16_rows(t):
+    if t.dtype != torch.bfloat16:
+        raise ValueError(f"unsupported dtype {t.dtype}: bf16")
+    return t.shape
+
+
+def qvggt_layer_statistics(W, X_cal, signs, workspace, stream=None):
+    (N, K), (M, K_cal) = _bf16_rows(W), _bf16_rows(X_cal)
+    if K != K_cal:
+        raise ValueError("weight and calibration rows of different lengths")
+    _check(load_library().qvggt_layer_statistics(_ptr(W), _ptr(X_cal), M, N, K, _ptr(signs), _ptr(workspace), workspace.numel(),
+                                                 _stream(stream)), "qvggt_layer_statistics")
+
+
+def qvggt_layer_codes(W, M, signs, alpha, bits, int8_codes, Wq, Wblocks, w_scale, inv_smooth, n_unrepresentable, workspace, stream=None):
+    N, K = _bf16_rows(W)
+    _check(load_library().qvggt_layer_codes(_ptr(W), M, N, K, _ptr(signs), float(alpha), int(bits), int(int8_codes), _ptr(Wq), _ptr(Wblocks),
+                                            _ptr(w_scale), _ptr(inv_smooth), _ptr(n_unrepresentable), _ptr(workspace), workspace.numel(),
+                                            _stream(stream)), "qvggt_layer_codes")
 
 
 def qvggt_prep_weights_i8(W, act_absmax_rot, signs, alpha, bits, Wq, w_scale, inv_smooth, stream=None):

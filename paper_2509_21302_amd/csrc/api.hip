@@ -111,6 +111,10 @@ hipError_t run_calib_loss_grad(const float *R, const float *V, const float *y_re
                                const float *w_step, const float *x_step, int T, int N, int K, int bits, float *loss, float *grad_c,
                                float *grad_w_step, float *grad_x_step, void *workspace, hipStream_t stream);
 hipError_t run_descent_step(float *theta, const float *grad, int n, float lr, float floor_, hipStream_t stream);
+size_t layer_workspace_bytes(int M, int N, int K);
+hipError_t run_layer_statistics(const void *W, const void *X_cal, int M, int N, int K, const int8_t *signs, void *workspace, hipStream_t stream);
+hipError_t run_layer_codes(const void *W, int M, int N, int K, const int8_t *signs, float alpha, int bits, uint8_t *Wq, uint8_t *Wblocks, float *w_scale,
+                           float *inv_smooth, unsigned int *minus_eights, void *workspace, hipStream_t stream);
 hipError_t run_int8_to_blocks(const int8_t *src, int rows, int K, uint8_t *dst, hipStream_t stream);
 hipError_t run_rotate_quant_i8b_mfma(const void *X, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out,
                                      float *scale, int bits, hipStream_t stream);
@@ -237,6 +241,36 @@ int qvggt_prep_weights_given(const void *W, int w_dtype, int N, int K, const flo
     // the same kernel as qvggt_prep_weights, with the steps given (clamp live) when w_step is not NULL
     return hip_status(qvggt::run_rotate_smooth_quant(W, w_dtype == QVGGT_F32, N, K, signs, inv_smooth, 1, static_cast<uint8_t *>(Wq),
                                                      w_scale, w_step, 1, bits == 4 ? 4 : qvggt::kInt8Container + bits, s));
+}
+
+static bool layer_size(int M, int N, int K) { return M >= 1 && valid_n(N) && (K == 1024 || K == 2048 || K == 4096); }
+
+size_t qvggt_layer_workspace_bytes(int M, int N, int K) { return layer_size(M, N, K) ? qvggt::layer_workspace_bytes(M, N, K) : 0; }
+
+int qvggt_layer_statistics(const void *W, const void *X_cal, int M, int N, int K, const int8_t *signs, void *workspace, size_t workspace_bytes,
+                           void *stream)
+{
+    if (!layer_size(M, N, K)) return QVGGT_ERR_SHAPE;
+    if (!W || !X_cal || !workspace) return QVGGT_ERR_NULL;
+    if (!aligned16(W) || !aligned16(X_cal) || !aligned16(signs) || !aligned16(workspace)) return QVGGT_ERR_ALIGN;
+    if (workspace_bytes < qvggt::layer_workspace_bytes(M, N, K)) return QVGGT_ERR_WORKSPACE;
+    return hip_status(qvggt::run_layer_statistics(W, X_cal, M, N, K, signs, workspace, static_cast<hipStream_t>(stream)));
+}
+
+int qvggt_layer_codes(const void *W, int M, int N, int K, const int8_t *signs, float alpha, int bits, int int8_codes, void *Wq, void *Wblocks,
+                      float *w_scale, float *inv_smooth, uint32_t *n_unrepresentable, void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (!layer_size(M, N, K)) return QVGGT_ERR_SHAPE;
+    if (!valid_wide_bits(bits) || (int8_codes != 0 && int8_codes != 1) || (int8_codes == 0 && bits != 4)) return QVGGT_ERR_ARG;
+    if (!std::isfinite(alpha) || alpha < 0.0f || alpha > 1.0f) return QVGGT_ERR_ARG;
+    if (!W || !Wq || !Wblocks || !w_scale || !inv_smooth || !workspace || (int8_codes == 0 && !n_unrepresentable)) return QVGGT_ERR_NULL;
+    if (!aligned16(W) || !aligned16(signs) || !aligned16(Wq) || !aligned16(Wblocks) || !aligned16(w_scale) || !aligned16(inv_smooth) ||
+        !aligned16(workspace) || (reinterpret_cast<uintptr_t>(n_unrepresentable) & 3u) != 0)
+        return QVGGT_ERR_ALIGN;
+    if (workspace_bytes < qvggt::layer_workspace_bytes(M, N, K)) return QVGGT_ERR_WORKSPACE;
+    return hip_status(qvggt::run_layer_codes(W, M, N, K, signs, alpha, int8_codes ? qvggt::kInt8Container + bits : 4, static_cast<uint8_t *>(Wq),
+                                             static_cast<uint8_t *>(Wblocks), w_scale, inv_smooth, int8_codes ? nullptr : n_unrepresentable,
+                                             workspace, static_cast<hipStream_t>(stream)));
 }
 
 int qvggt_prep_weights_i8(const void *W, int w_dtype, int N, int K, const float *act_absmax_rot, const int8_t *signs,

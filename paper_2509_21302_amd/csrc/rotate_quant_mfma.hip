@@ -113,12 +113,24 @@ __host__ __device__ constexpr int row_of_seg_hi(int seg_hi /* seg >> 2 */)
     }
     return m;
 }
+
+// Arguments of the variants that make a layer
+struct LayerArgs {
+    const uint16_t *X2;             // CB = -1: the second operand and its rows; blocks below blocks1 work on the first
+    int rows2, blocks1;
+    float *parts;                   // CB = -1: [blocks][K] column maxima
+    uint8_t *rows_out;              // BOTH: the codes as rows
+    unsigned int *minus_eights;     // BOTH, CB = 6: number of codes -8 (no E2M3 value; only values that are no numbers give them)
+};
 }  // namespace rq
 
 // CB: bits a stored code occupies: 4 (packed nibbles, codes in [-8, 7]) or 8 (int8, codes in [-qmax - 1, qmax]);
 // CB = 6: 4-bit codes written as E2M3 numbers in the 128-row blocks the 6-bit matrix path reads (dynamic steps only: codes in [-7, 7]);
 // CB = 0 is the statistic mode: nothing is quantized or stored, the kernel leaves max_t |X H / sqrt(K)|[t, j] per column j
 // in col_absmax_bits (the numerator of the smoothing factor, Sec. 3.2), which must be zero on entry
+// CB = -1 is the statistic mode over two operands of the same K in one launch (calibration rows and weight rows): every block leaves the
+// maxima of its rows as one row of la.parts, so that nothing has to be cleared first and nothing is atomic
+// BOTH (CB = 6 and BLK8): the codes also go out as rows, packed nibbles resp. int8, to la.rows_out (the two forms a layer keeps)
 // LN: a LayerNorm of every token (fp32, result rounded to bf16 as a separate normalisation kernel would hand it on) is
 // applied to the loaded values before anything else
 // ASYM: affine codes.  The row's range [min(0, min z), max(0, max z)] takes the 16 codes, the zero point goes to zero[row], and
@@ -127,7 +139,7 @@ __host__ __device__ constexpr int row_of_seg_hi(int seg_hi /* seg >> 2 */)
 // ((r / 128) * (K / 64) + kt) * 8192 + (r % 128) * 64, its 16-byte chunk ch in slot ch ^ ((r % 16) >> 2)
 // GELU: the activation between fc1 and fc2 applied to every loaded value (fp32, result rounded to bf16 as a separate activation
 // kernel would hand it on) before anything else: X is fc1's output as stored, the kernel is fc2's kernel 1
-template <int K, int PF, int OCC, bool STATIC, int CB, bool LN = false, bool ASYM = false, bool BLK8 = false, bool GELU = false, bool LONG = false>
+template <int K, int PF, int OCC, bool STATIC, int CB, bool LN = false, bool ASYM = false, bool BLK8 = false, bool GELU = false, bool LONG = false, bool BOTH = false>
 __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint16_t *__restrict__ X, int rows,
                                                                    const int8_t *__restrict__ signs,
                                                                    const float *__restrict__ mul, int mul_mode,
@@ -137,9 +149,11 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                                                                    float qmax8, unsigned int *__restrict__ col_absmax_bits,
                                                                    LnParams ln = LnParams{nullptr, nullptr, 0.0f, 0},
                                                                    float *__restrict__ zero = nullptr,
-                                                                   const uint16_t *__restrict__ gelu_table = nullptr)
+                                                                   const uint16_t *__restrict__ gelu_table = nullptr,
+                                                                   rq::LayerArgs la = rq::LayerArgs{})
 {
-    constexpr bool STAT = (CB == 0);
+    constexpr bool PAIR = (CB == -1), STAT = (CB == 0) || PAIR;
+    static_assert(!BOTH || ((CB == 6 || BLK8) && !STATIC && !ASYM), "two forms of a layer's weight codes");
     static_assert(!ASYM || ((CB == 4 || CB == 6) && !STATIC), "affine codes: dynamic 4-bit only");
     // CB = 6 with a static step or affine codes: the stored E2M3 number is code + 0.5 resp. u - 7.5 (sixteen half-integers, all
     // representable), and zero[row] receives what the GEMM's correction term needs (8 for a static step: 7.5 - 8 = -0.5)
@@ -176,8 +190,19 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
     const int lane = threadIdx.x & 63, wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 31, g = lane >> 5;
     uint8_t *lds = lds_all + wave_in_block * rq::LDS_PER_WAVE;
-    const int wave = blockIdx.x * rq::WAVES_PER_BLOCK + wave_in_block;
-    const int nwaves = gridDim.x * rq::WAVES_PER_BLOCK;
+    int first_block = 0, nblocks = gridDim.x;
+    if constexpr (PAIR) {
+        if ((int)blockIdx.x < la.blocks1) {
+            nblocks = la.blocks1;
+        } else {
+            first_block = la.blocks1;
+            nblocks -= la.blocks1;
+            X = la.X2;
+            rows = la.rows2;
+        }
+    }
+    const int wave = ((int)blockIdx.x - first_block) * rq::WAVES_PER_BLOCK + wave_in_block;
+    const int nwaves = nblocks * rq::WAVES_PER_BLOCK;
     const int ntiles = (rows + TOK - 1) / TOK;
 
     // ---- per-lane constants -------------------------------------------------------------------
@@ -523,6 +548,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
 #pragma unroll
                 for (int bb = 0; bb < C::NL / 32; ++bb) {
                     v16f ev, od;
+                    uint32_t nib[4] = {0u, 0u, 0u, 0u};     // BOTH: the same codes as nibbles
 #pragma unroll
                     for (int k = 0; k < 16; ++k) {
                         const int h = 8 * bb + k / 2;
@@ -535,8 +561,20 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                             ev[k] = ((__builtin_amdgcn_fmed3f(ze * inv, -8.0f, 7.0f) + rq::MAGIC) - rq::MAGIC) + 0.5f;
                             od[k] = ((__builtin_amdgcn_fmed3f(zo * inv, -8.0f, 7.0f) + rq::MAGIC) - rq::MAGIC) + 0.5f;
                         } else {
-                            ev[k] = fmaf(ze, inv, rq::MAGIC) - rq::MAGIC;
-                            od[k] = fmaf(zo, inv, rq::MAGIC) - rq::MAGIC;
+                            const float ue = fmaf(ze, inv, rq::MAGIC), uo = fmaf(zo, inv, rq::MAGIC);
+                            ev[k] = ue - rq::MAGIC;
+                            od[k] = uo - rq::MAGIC;
+                            if constexpr (BOTH) nib[k / 4] |= ((__float_as_uint(ue) & 15u) | ((__float_as_uint(uo) & 15u) << 4)) << (8 * (k % 4));
+                        }
+                    }
+                    if constexpr (BOTH) {
+                        if (row < rows) {
+                            *reinterpret_cast<uint4 *>(la.rows_out + (size_t)row * (K / 2) + (P0 + 32 * bb) / 2) =
+                                make_uint4(nib[0] ^ 0x88888888u, nib[1] ^ 0x88888888u, nib[2] ^ 0x88888888u, nib[3] ^ 0x88888888u);
+                            int n8 = 0;             // a code -8 is a nibble 0 here
+#pragma unroll
+                            for (int d = 0; d < 4; ++d) n8 += __popc(~(((nib[d] & 0x77777777u) + 0x77777777u) | nib[d] | 0x77777777u));
+                            if (n8 != 0) atomicAdd(la.minus_eights, (unsigned int)n8);
                         }
                     }
                     // The conversion makes several passes over its 32 source registers while it writes its 6 results, so the result
@@ -612,6 +650,14 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                     // the lane's NL bytes are positions P0 .. of the row: chunk P / 16 of K-tile P / 64
                     const int P0 = c * (K / 32) + (REM == 5 ? g * 64 : 0);
                     const int swz = (row & 15) >> 2;
+                    if constexpr (BOTH) {
+                        if (row < rows) {
+#pragma unroll
+                            for (int d4 = 0; d4 < C::NL / 16; ++d4)
+                                *reinterpret_cast<uint4 *>(la.rows_out + (size_t)row * K + P0 + 16 * d4) =
+                                    make_uint4(words[4 * d4], words[4 * d4 + 1], words[4 * d4 + 2], words[4 * d4 + 3]);
+                        }
+                    }
                     if constexpr (REM == 5) {
                         // K = 4096: the lane holds K-tile 2 c + g of this wave's token, 64 bytes; the block's four tokens leave together
                         // (flush area [K-tile][wave][64 bytes]) in runs of 256 bytes, see the 6-bit variant
@@ -705,7 +751,11 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                 atomicMax(&blk[128 * hb + 32 * nt + c], __float_as_uint(cmax[h][nt] * rs));
             }
         __syncthreads();
-        for (int j = threadIdx.x; j < K; j += 256) atomicMax(&col_absmax_bits[j], blk[j]);
+        if constexpr (PAIR) {
+            for (int j = threadIdx.x; j < K; j += 256) la.parts[(size_t)blockIdx.x * K + j] = __uint_as_float(blk[j]);
+        } else {
+            for (int j = threadIdx.x; j < K; j += 256) atomicMax(&col_absmax_bits[j], blk[j]);
+        }
     }
 }
 
@@ -941,6 +991,106 @@ hipError_t run_rotated_col_absmax_mfma(const void *X, int rows, int K, const int
         default: return hipErrorInvalidValue;
     }
 #undef RQS
+    return hipGetLastError();
+}
+
+// ---- Making a layer: statistics of the calibration rows and of the weight rows, the smoothing factor, the weight codes in both forms the layer
+// keeps.  Three launches, where one entry point per step took eight (two clears, two statistics, factor, codes, counter, second form).
+namespace {
+
+// Blocks of the two statistics.  A block has work for TILES tiles per wave, a serial chain of about 1.5 us each, until the chip is full (two
+// blocks per compute unit); every block costs a row of K maxima, written here and read by the next kernel.
+struct LayerBlocks {
+    int x, w;
+};
+LayerBlocks layer_blocks(int M, int N, int K)
+{
+    const int tok = 32 / (K / 128);
+    const int tx = (M + tok - 1) / tok, tw = (N + tok - 1) / tok;
+    const int tiles = std::max(2, (tx + tw + 4 * 512 - 1) / (4 * 512)) * rq::WAVES_PER_BLOCK;
+    return {(tx + tiles - 1) / tiles, (tw + tiles - 1) / tiles};
+}
+
+// 32 columns per block (a cache line of each row of maxima), 32 groups of threads share the rows, so that their loads are in flight together: a_j from the first parts_x rows, w_j from the others, then the factor
+//   inv_smooth[j] = 1 / (sqrt(K) c_j),  c_j = max(a_j, 1e-5)^alpha / max(w_j, 1e-5)^(1 - alpha),  and what the weight rows are multiplied by,
+//   w_mul[j] = 1 / (K inv_smooth[j]) = c_j / sqrt(K).  Also clears the counter that the next kernel adds to.
+__global__ __launch_bounds__(1024) void layer_factor_kernel(const float *__restrict__ parts, int parts_x, int parts_w, int K, float alpha,
+                                                            float *__restrict__ inv_smooth, float *__restrict__ w_mul,
+                                                            unsigned int *__restrict__ counter)
+{
+    __shared__ float red[2][32][32];
+    const int col = threadIdx.x & 31, grp = threadIdx.x >> 5, j = blockIdx.x * 32 + col;
+    if (counter != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;
+    float a = 0.0f, w = 0.0f;
+#pragma unroll 8
+    for (int r = grp; r < parts_x; r += 32) a = fmaxf(a, parts[(size_t)r * K + j]);
+#pragma unroll 8
+    for (int r = parts_x + grp; r < parts_x + parts_w; r += 32) w = fmaxf(w, parts[(size_t)r * K + j]);
+    red[0][grp][col] = a;
+    red[1][grp][col] = w;
+    __syncthreads();
+    if (grp != 0) return;
+#pragma unroll
+    for (int g = 1; g < 32; ++g) { a = fmaxf(a, red[0][g][col]); w = fmaxf(w, red[1][g][col]); }
+    const float floor_ = 1e-5f;
+    a = fmaxf(a, floor_);
+    w = fmaxf(w, floor_);
+    const float c = powf(a, alpha) / powf(w, 1.0f - alpha), inv = 1.0f / (sqrtf((float)K) * c);
+    inv_smooth[j] = inv;
+    w_mul[j] = 1.0f / ((float)K * inv);
+}
+
+}  // namespace
+
+size_t layer_workspace_bytes(int M, int N, int K)
+{
+    const LayerBlocks b = layer_blocks(M, N, K);
+    return (size_t)(b.x + b.w + 1) * K * sizeof(float);
+}
+
+hipError_t run_layer_statistics(const void *W, const void *X_cal, int M, int N, int K, const int8_t *signs, void *workspace, hipStream_t stream)
+{
+    const LayerBlocks b = layer_blocks(M, N, K);
+    const LnParams no_ln{nullptr, nullptr, 0.0f, 0};
+    const rq::LayerArgs la{reinterpret_cast<const uint16_t *>(W), N, b.x, static_cast<float *>(workspace), nullptr, nullptr};
+#define RQP(KK) rotate_quant_mfma_kernel<KK, 1, 2, false, -1><<<b.x + b.w, 256, 0, stream>>>(reinterpret_cast<const uint16_t *>(X_cal), M, signs, nullptr, 0, nullptr, nullptr, nullptr, 0, 0.0f, nullptr, no_ln, nullptr, nullptr, la)
+    switch (K) {
+        case 1024: RQP(1024); break;
+        case 2048: RQP(2048); break;
+        case 4096: RQP(4096); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef RQP
+    return hipGetLastError();
+}
+
+// bits: 4 = nibbles and E2M3 blocks, kInt8Container + b = int8 rows and int8 blocks
+hipError_t run_layer_codes(const void *W, int M, int N, int K, const int8_t *signs, float alpha, int bits, uint8_t *Wq, uint8_t *Wblocks, float *w_scale,
+                           float *inv_smooth, unsigned int *minus_eights, void *workspace, hipStream_t stream)
+{
+    const LayerBlocks b = layer_blocks(M, N, K);
+    float *parts = static_cast<float *>(workspace), *w_mul = parts + (size_t)(b.x + b.w) * K;
+    layer_factor_kernel<<<K / 32, 1024, 0, stream>>>(parts, b.x, b.w, K, alpha, inv_smooth, w_mul, minus_eights);
+    const int tok = 32 / (K / 128), ntiles = (N + tok - 1) / tok;
+    const int blocks = std::min((ntiles + rq::WAVES_PER_BLOCK - 1) / rq::WAVES_PER_BLOCK, 256 * 2);
+    const float qmax8 = (float)((1 << (code_width(bits) - 1)) - 1);
+    const uint16_t *w = reinterpret_cast<const uint16_t *>(W);
+    const LnParams no_ln{nullptr, nullptr, 0.0f, 0};
+    const rq::LayerArgs la{nullptr, 0, 0, nullptr, Wq, minus_eights};
+#define RQL(KK)                                                                                                                          \
+    do {                                                                                                                                 \
+        if (bits == 4)                                                                                                                   \
+            rotate_quant_mfma_kernel<KK, 1, 2, false, 6, false, false, false, false, false, true><<<blocks, 256, 0, stream>>>(w, N, signs, w_mul, 0, Wblocks, w_scale, nullptr, 0, 7.0f, nullptr, no_ln, nullptr, nullptr, la); \
+        else                                                                                                                             \
+            rotate_quant_mfma_kernel<KK, 1, 2, false, 8, false, false, true, false, false, true><<<blocks, 256, 0, stream>>>(w, N, signs, w_mul, 0, Wblocks, w_scale, nullptr, 0, qmax8, nullptr, no_ln, nullptr, nullptr, la); \
+    } while (0)
+    switch (K) {
+        case 1024: RQL(1024); break;
+        case 2048: RQL(2048); break;
+        case 4096: RQL(4096); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef RQL
     return hipGetLastError();
 }
 

@@ -38,31 +38,44 @@ class DsfqLinear:
         self.bits, self.act_bits, self.bias, self.signs = bits, act_bits, bias, signs
         self.packed = bits == 4 and act_bits == 4            # both 4-bit: two codes per byte; otherwise int8 codes
         dev = weight.device
+        # bf16 rows of the sizes with matrix-core kernels keep their codes in a second form, the blocks that the fast GEMMs read (E2M3 numbers
+        # resp. int8), and with a calibration batch are made in three launches; the others one entry point at a time
+        blocks = self.K in (1024, 2048, 4096)
+        fused = (blocks and calibration is not None and weight.dtype == calibration.dtype == torch.bfloat16 and calibration.dim() == 2
+                 and calibration.shape[0] > 0 and calibration.shape[1] == self.K)
         absmax = None
-        if calibration is not None:
+        if fused:
+            rows = calibration.shape[0]
+            scratch = torch.empty(q.qvggt_layer_workspace_bytes(rows, self.N, self.K), dtype=torch.uint8, device=dev)
+            q.qvggt_layer_statistics(weight, calibration, signs, scratch)
+        elif calibration is not None:
             absmax = torch.empty(self.K, dtype=torch.float32, device=dev)
             q.qvggt_rotated_col_absmax(calibration, signs, absmax)
         self.w_scale = torch.empty(self.N, dtype=torch.float32, device=dev)
         self.inv_smooth = torch.empty(self.K, dtype=torch.float32, device=dev)
         if self.packed:
             self.Wq = torch.empty(self.N, self.K // 2, dtype=torch.uint8, device=dev)
-            q.qvggt_prep_weights(weight, absmax, signs, alpha, self.Wq, self.w_scale, self.inv_smooth)
-            # the same codes as E2M3 numbers for the 6-bit floating-point matrix path (bf16 inputs, K = 1024 / 2048 / 4096)
-            self.Wf = None
-            if self.K in (1024, 2048, 4096):
-                self.Wf = torch.empty(q.qvggt_e2m3_bytes(self.N, self.K), dtype=torch.uint8, device=dev)
-                lost = torch.zeros(1, dtype=torch.int32, device=dev)
-                q.qvggt_codes_to_e2m3(self.Wq, self.N, self.K, self.Wf, lost)
-                if int(lost.item()) != 0:        # cannot happen with the absmax steps of qvggt_prep_weights (codes lie in [-7, 7])
-                    raise RuntimeError(f"{int(lost.item())} weight codes -8 have no E2M3 value")
+            self.Wf = torch.empty(q.qvggt_e2m3_bytes(self.N, self.K), dtype=torch.uint8, device=dev) if blocks else None
+            lost = None
+            if fused:
+                lost = torch.empty(1, dtype=torch.int32, device=dev)
+                q.qvggt_layer_codes(weight, rows, signs, alpha, bits, False, self.Wq, self.Wf, self.w_scale, self.inv_smooth, lost, scratch)
+            else:
+                q.qvggt_prep_weights(weight, absmax, signs, alpha, self.Wq, self.w_scale, self.inv_smooth)
+                if blocks:
+                    lost = torch.zeros(1, dtype=torch.int32, device=dev)
+                    q.qvggt_codes_to_e2m3(self.Wq, self.N, self.K, self.Wf, lost)
+            if lost is not None and (n := int(lost.item())) != 0:      # cannot happen with absmax steps of numbers (codes lie in [-7, 7])
+                raise RuntimeError(f"{n} weight codes -8 have no E2M3 value")
         else:
             self.Wq = torch.empty(self.N, self.K, dtype=torch.int8, device=dev)
-            q.qvggt_prep_weights_i8(weight, absmax, signs, alpha, bits, self.Wq, self.w_scale, self.inv_smooth)
-            # the same codes in 128-row blocks for the GEMM with contiguous operand transfers (bf16 inputs, K = 1024 / 2048 / 4096)
-            self.Wb = None
-            if self.K in (1024, 2048, 4096):
-                self.Wb = torch.empty(q.qvggt_i8b_bytes(self.N, self.K), dtype=torch.int8, device=dev)
-                q.qvggt_int8_to_blocks(self.Wq, self.N, self.K, self.Wb)
+            self.Wb = torch.empty(q.qvggt_i8b_bytes(self.N, self.K), dtype=torch.int8, device=dev) if blocks else None
+            if fused:
+                q.qvggt_layer_codes(weight, rows, signs, alpha, bits, True, self.Wq, self.Wb, self.w_scale, self.inv_smooth, None, scratch)
+            else:
+                q.qvggt_prep_weights_i8(weight, absmax, signs, alpha, bits, self.Wq, self.w_scale, self.inv_smooth)
+                if blocks:
+                    q.qvggt_int8_to_blocks(self.Wq, self.N, self.K, self.Wb)
         self._ws = (-1, None)       # rows the workspace is large enough for, the workspace
 
     def _workspace(self, M: int, dev) -> torch.Tensor:
