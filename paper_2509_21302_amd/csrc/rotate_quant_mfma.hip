@@ -995,7 +995,9 @@ hipError_t run_rotated_col_absmax_mfma(const void *X, int rows, int K, const int
 }
 
 // ---- Making a layer: statistics of the calibration rows and of the weight rows, the smoothing factor, the weight codes in both forms the layer
-// keeps.  Three launches, where one entry point per step took eight (two clears, two statistics, factor, codes, counter, second form).
+// keeps.  Three launches, where one entry point per step took eight (two clears, two statistics, factor, codes, counter, second form) and
+// its layer 62 us instead of 43 (1374 x 4096 calibration rows, 1024 weight rows).  Bound by what one wave does in a row: 12 us the statistics (two
+// tiles; one or four per wave within 5 % at K = 4096, 5.7 and 8.1 against 6.3 us at K = 1024), 4 the factor, 7 the codes (one tile).
 namespace {
 
 // Blocks of the two statistics.  A block has work for TILES tiles per wave, a serial chain of about 1.5 us each, until the chip is full (two
@@ -1011,7 +1013,7 @@ LayerBlocks layer_blocks(int M, int N, int K)
     return {(tx + tiles - 1) / tiles, (tw + tiles - 1) / tiles};
 }
 
-// 32 columns per block (a cache line of each row of maxima), 32 groups of threads share the rows, so that their loads are in flight together: a_j from the first parts_x rows, w_j from the others, then the factor
+// 32 columns per block (a cache line of each row of maxima), 32 groups of threads share the rows (64 and 16: the same time): a_j from the first parts_x rows, w_j from the others, then the factor
 //   inv_smooth[j] = 1 / (sqrt(K) c_j),  c_j = max(a_j, 1e-5)^alpha / max(w_j, 1e-5)^(1 - alpha),  and what the weight rows are multiplied by,
 //   w_mul[j] = 1 / (K inv_smooth[j]) = c_j / sqrt(K).  Also clears the counter that the next kernel adds to.
 __global__ __launch_bounds__(1024) void layer_factor_kernel(const float *__restrict__ parts, int parts_x, int parts_w, int K, float alpha,
