@@ -298,6 +298,10 @@ size_t qvggt_workspace_bytes_e2m3(int M, int N, int K);
 int qvggt_linear_e2m3(const void *X, int x_dtype, int M, int N, int K, const int8_t *signs, const float *inv_smooth,
                       const uint8_t *Wf, const float *w_scale, const void *bias, void *Y, void *workspace,
                       size_t workspace_bytes, void *stream);
+/* qvggt_linear_e2m3 for rows of either type and every supported K: the same Y, bit for bit, as qvggt_linear on the Wq that Wf was made of. */
+int qvggt_linear_e2m3_any(const void *X, int x_dtype, int M, int N, int K, const int8_t *signs, const float *inv_smooth,
+                          const uint8_t *Wf, const float *w_scale, const void *bias, void *Y, void *workspace,
+                          size_t workspace_bytes, void *stream);
 int qvggt_codes_to_e2m3(const uint8_t *packed, int rows, int K, uint8_t *out, uint32_t *n_unrepresentable, void *stream);
 
 /*

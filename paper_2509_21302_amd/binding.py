@@ -33,7 +33,7 @@ EXPORTS = [
     "qvggt_workspace_bytes_i8", "qvggt_layout_int8",
     "qvggt_nfds_workspace_bytes", "qvggt_nfds_moments", "qvggt_nfds_frame_correlation", "qvggt_nfds_scores",
     "qvggt_nfds_keep_lowest", "qvggt_nfds_kmeans_step",
-    "qvggt_layer_workspace_bytes", "qvggt_layer_statistics", "qvggt_layer_codes",
+    "qvggt_linear_e2m3_any", "qvggt_layer_workspace_bytes", "qvggt_layer_statistics", "qvggt_layer_codes",
     "qvggt_rotate_rows", "qvggt_calib_workspace_bytes", "qvggt_calib_loss_grad", "qvggt_calib_descent_step",
 ]
 
@@ -118,6 +118,8 @@ def load_library() -> C.CDLL:
     lib.qvggt_gelu_linear_e2m3.argtypes = [vp, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, vp, C.c_size_t, vp]
     lib.qvggt_linear_e2m3.restype = i
     lib.qvggt_linear_e2m3.argtypes = [vp, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, C.c_size_t, vp]
+    lib.qvggt_linear_e2m3_any.restype = i
+    lib.qvggt_linear_e2m3_any.argtypes = [vp, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, C.c_size_t, vp]
     lib.qvggt_own_workspace_bytes.restype = C.c_size_t
     lib.qvggt_own_workspace_bytes.argtypes = []
     lib.qvggt_linear_e2m3_own_workspace.restype = i
@@ -393,6 +395,14 @@ def qvggt_linear_e2m3(X, signs, inv_smooth, Wf, w_scale, bias, Y, workspace, str
     _check(load_library().qvggt_linear_e2m3(_ptr(X), _dtype_code(X), M, N, K, _ptr(signs), _ptr(inv_smooth), _ptr(Wf), _ptr(w_scale),
                                             _ptr(bias), _ptr(Y), _ptr(workspace), workspace.numel() * workspace.element_size(),
                                             _stream(stream)), "qvggt_linear_e2m3")
+
+
+def qvggt_linear_e2m3_any(X, signs, inv_smooth, Wf, w_scale, bias, Y, workspace, stream=None):
+    M, K = X.shape
+    N = Y.shape[1]
+    _check(load_library().qvggt_linear_e2m3_any(_ptr(X), _dtype_code(X), M, N, K, _ptr(signs), _ptr(inv_smooth), _ptr(Wf), _ptr(w_scale),
+                                            _ptr(bias), _ptr(Y), _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                            _stream(stream)), "qvggt_linear_e2m3_any")
 
 
 def qvggt_own_workspace_bytes():

@@ -121,6 +121,8 @@ hipError_t run_rotate_quant_i8b_mfma(const void *X, int rows, int K, const int8_
 hipError_t run_i8b_gemm(const int8_t *Xb, const float *sx, const int8_t *Wb, const float *sw, const void *bias, int M, int N,
                         int K, void *Y, int32_t *acc_debug, hipStream_t stream);
 hipError_t run_codes_to_e2m3(const uint8_t *packed, int rows, int K, uint8_t *out, unsigned int *n_unrepresentable, hipStream_t stream);
+hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
+                                hipStream_t stream);
 hipError_t run_e2m3_gemm(const uint8_t *Xf, const float *sx, const uint8_t *Wf, const float *sw, const void *bias, int M, int N,
                          int K, void *Y, int32_t *acc_debug, hipStream_t stream);
 hipError_t run_layout_int8(const int8_t *src, int rows, int K, int8_t *dst, int to_library, hipStream_t stream);
@@ -594,11 +596,12 @@ size_t qvggt_workspace_bytes_e2m3(int M, int N, int K)
 
 static int linear_e2m3(const void *gelu_table, const void *X, int x_dtype, int M, int N, int K, const int8_t *signs, const float *inv_smooth,
                       const uint8_t *Wf, const float *w_scale, const void *bias, void *Y, void *workspace,
-                      size_t workspace_bytes, void *stream)
+                      size_t workspace_bytes, void *stream, bool any_rows = false)
 {
     if (!valid_dtype(x_dtype)) return QVGGT_ERR_DTYPE;
     if (M < 0 || !valid_n(N) || !valid_k(K)) return QVGGT_ERR_SHAPE;
-    if (!e2m3_direct(x_dtype, K)) return x_dtype == QVGGT_BF16 ? QVGGT_ERR_SHAPE : QVGGT_ERR_DTYPE;
+    const bool direct = e2m3_direct(x_dtype, K);
+    if (!direct && !any_rows) return x_dtype == QVGGT_BF16 ? QVGGT_ERR_SHAPE : QVGGT_ERR_DTYPE;
     if (M == 0) return QVGGT_OK;
     if (!X || !Wf || !w_scale || !Y || !workspace) return QVGGT_ERR_NULL;
     if (!aligned16(X) || !aligned16(Wf) || !aligned16(w_scale) || !aligned16(bias) || !aligned16(Y) ||
@@ -609,7 +612,8 @@ static int linear_e2m3(const void *gelu_table, const void *X, int x_dtype, int M
     float *x_scale = reinterpret_cast<float *>(Xf + round_up(qvggt_e2m3_bytes(M, K), 256));
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = gelu_table ? qvggt::run_gelu_rotate_quant_mfma(X, M, K, signs, inv_smooth, gelu_table, Xf, x_scale, true, s)
-                              : qvggt::run_rotate_quant_e2m3_mfma(X, M, K, signs, inv_smooth, Xf, x_scale, s);
+                   : direct   ? qvggt::run_rotate_quant_e2m3_mfma(X, M, K, signs, inv_smooth, Xf, x_scale, s)
+                              : qvggt::run_rotate_rows_e2m3(X, x_dtype == QVGGT_F32, M, K, signs, inv_smooth, Xf, x_scale, s);
     if (e != hipSuccess) return QVGGT_ERR_HIP;
     return hip_status(qvggt::run_e2m3_gemm(Xf, x_scale, Wf, w_scale, bias, M, N, K, Y, nullptr, s));
 }
@@ -619,6 +623,13 @@ int qvggt_linear_e2m3(const void *X, int x_dtype, int M, int N, int K, const int
                       size_t workspace_bytes, void *stream)
 {
     return linear_e2m3(nullptr, X, x_dtype, M, N, K, signs, inv_smooth, Wf, w_scale, bias, Y, workspace, workspace_bytes, stream);
+}
+
+int qvggt_linear_e2m3_any(const void *X, int x_dtype, int M, int N, int K, const int8_t *signs, const float *inv_smooth,
+                          const uint8_t *Wf, const float *w_scale, const void *bias, void *Y, void *workspace,
+                          size_t workspace_bytes, void *stream)
+{
+    return linear_e2m3(nullptr, X, x_dtype, M, N, K, signs, inv_smooth, Wf, w_scale, bias, Y, workspace, workspace_bytes, stream, true);
 }
 
 size_t qvggt_own_workspace_bytes(void) { return QVGGT_OWN_WORKSPACE_BYTES; }

@@ -72,14 +72,16 @@ struct E2m3Plan {
 };
 
 // Rows of Y that are whole 128-byte lines (N a multiple of 64) go past the caches.  Others are written in pieces of lines, which the memory
-// takes badly one by one: while Y fits the memory-side cache (256 MB), the 256- and 192-row tiles leave them there to be put together.  us at
+// takes badly one by one: while Y fits half the memory-side cache (256 MB; the rows of X go through it too), the 256- and 192-row tiles leave them
+// there to be put together.  us at
 // K = 1024, past the caches / through them, 256-row tiles: 2000 x 3056 (12 MB) 13.5 / 14.5, 4000 (24) 19.9 / 16.7, 10992 (67) 54 / 41, 34000 (208)
 // 121 / 96, 50000 (306) 169 / 163, 192-row tiles 159 / 176.  The 128-row tiles, two blocks to a compute unit, do not gain (35.0 / 33.8, 91 / 90,
 // 136 / 191), nor do whole lines (10992 x 4096 40.5 / 43.9, 1374 x 3072 12.6 / 13.8).
+constexpr double kCachedY = 130e6;       // bytes
 inline bool e2m3_streams_y(int M, int N)
 {
     const double bytes = 2.0 * M * N;
-    return N % 64 == 0 || bytes < 20e6 || bytes > 210e6;
+    return N % 64 == 0 || bytes < 20e6 || bytes > kCachedY;
 }
 
 // The plan that this model prices lowest, in microseconds, fitted to 550 random problems of 16 to 137400 rows and all sizes of K that were
@@ -95,7 +97,7 @@ inline bool e2m3_streams_y(int M, int N)
 inline double e2m3_shape_cost(E2m3Plan::Shape shape, int M, int N, int K)
 {
     auto tiles = [&](int m, int n) { return (double)((M + m - 1) / m) * ((N + n - 1) / n) / 256.0; };        // per compute unit
-    const double k = K / 1024.0, pieces = N % 64 ? 1.0 : 0.0;
+    const double k = K / 1024.0, pieces = N % 64 == 0 ? 0.0 : 2.0 * M * N > kCachedY ? 4.0 : 1.0;
     switch (shape) {
         case E2m3Plan::k256: {
             const double t = tiles(256, 256);
@@ -108,7 +110,7 @@ inline double e2m3_shape_cost(E2m3Plan::Shape shape, int M, int N, int K)
         case E2m3Plan::k128: {
             const double t = tiles(128, 128), rounds = t / 2.0, whole = std::floor(rounds), rest = rounds - whole;
             const double priced = whole > 0.0 && rest > 0.0 ? whole + std::max(rest, 0.3) : rounds;
-            return 5.05 + 2.2 * k + std::min(t, 1.0) * (1.2 + 0.6 * k) + std::max(priced - 0.5, 0.0) * std::max(2.1 + 4.95 * k, 3.4 + 1.8 * pieces);
+            return 5.05 + 2.2 * k + std::min(t, 1.0) * (1.2 + 0.6 * k) + std::max(priced - 0.5, 0.0) * std::max(2.1 + 4.95 * k, 3.4 + std::min(1.8 * pieces, 1.8));
         }
         case E2m3Plan::k64: return 4.85 + 0.93 * k + (std::ceil(tiles(64, 64)) - 1.0) * (0.95 + 1.1 * k);
         case E2m3Plan::k32x64: return 4.45 + 0.65 * k + (std::ceil(tiles(32, 64)) - 1.0) * (0.38 + 0.81 * k);

@@ -18,7 +18,7 @@ enum RowMode { kQuantize = 0, kColAbsMax = 1 };
 
 // mul_mode 0: mul[j] used as given (inv_smooth, or 1/sqrt(K) when mul == nullptr)
 // mul_mode 1: 1 / (K * mul[j])   (weights: c_j / sqrt(K) recovered from inv_smooth)
-// CB: bits a stored code occupies (4: two per byte; 8: one int8 each).  qmax: largest code, 2^(bits-1) - 1.
+// CB: bits a stored code occupies (4: two per byte; 8: one int8 each; 6: 4-bit codes as E2M3 blocks, dynamic steps).  qmax: largest code, 2^(bits-1) - 1.
 // LN: a LayerNorm of the row precedes everything else (quantize mode, K <= 4096: beyond that the row no longer fits the registers)
 // ASYM: affine 4-bit codes over the row's range [min(0, min z), max(0, max z)], zero point to zero[row], nibbles hold u - 8
 template <int K, bool F32, int MODE, int CB, bool LN = false, bool ASYM = false>
@@ -37,10 +37,13 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
     constexpr int WPR = K > 4096 ? 4 : 1, KW = K / WPR;
     constexpr int V = RowMap<KW>::V, C = RowMap<KW>::C, R = RowMap<KW>::R;
     constexpr bool kPermuted = (K == 1024 || K == 2048 || K == 4096) && MODE == kQuantize;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_stage[kPermuted ? 4 * K : 16];
+    constexpr bool E2M3 = (CB == 6);
+    static_assert(!E2M3 || (MODE == kQuantize && !LN && !ASYM), "E2M3 blocks: dynamic 4-bit codes");
+    __shared__ __attribute__((aligned(16))) uint8_t lds_stage[E2M3 ? E2m3Stage<K>::BYTES : kPermuted ? 4 * K : 16];
     const int lane = threadIdx.x & 63;
     const int sub = WPR > 1 ? (int)(threadIdx.x >> 6) : 0, first = sub * KW;       // this wave's part of a row
-    const int wave = WPR > 1 ? (int)blockIdx.x : (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int group = !E2M3 || WPR == 1 || rows > kFewSharedRows ? kE2m3Group : 1;       // rows that leave together
+    const int wave = WPR > 1 ? (int)blockIdx.x * (E2M3 ? group : 1) : (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
     const int nwaves = WPR > 1 ? (int)gridDim.x : (int)gridDim.x * 4;
     __shared__ float4 exchange[WPR > 1 ? K / 4 : 1];
     __shared__ float red[2][4];
@@ -83,9 +86,12 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
     float colmax[MODE == kColAbsMax ? R : 1];
 #pragma unroll
     for (int r = 0; r < (MODE == kColAbsMax ? R : 1); ++r) colmax[r] = 0.0f;
-    for (int row = wave; row < rows; row += nwaves) {
+    // E2M3: a block takes a group of consecutive rows at a time, one per wave or (WPR > 1) one after the other; past the end: the last row, not
+    // written
+    const int last = group - 1;
+    for (int row = wave; (E2M3 ? row & ~last : row) < rows; row += !(E2M3 && WPR > 1) ? nwaves : (row & last) == last ? group * nwaves - last : 1) {
         float x[R];
-        load_row<KW, F32>(X, (size_t)row * WPR + sub, lane, x);
+        load_row<KW, F32>(X, (size_t)(E2M3 ? min(row, rows - 1) : row) * WPR + sub, lane, x);
         if constexpr (LN) {
             static_assert(!LN || WPR == 1, "the normalisation sums over one wave");
             // LayerNorm of the token in fp32 (two passes over the registers), result rounded to the input's type as a separate
@@ -160,7 +166,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
                 delta = live ? amax / qmax : 0.0f;
                 inv = live ? qmax / amax : 0.0f;
             }
-            if (lane == 0 && sub == 0) scale[row] = delta;
+            if (lane == 0 && sub == 0 && (!E2M3 || row < rows)) scale[row] = delta;
             const int q_hi = (int)qmax, q_lo = -q_hi - 1;
             // a step from the row's own maximum bounds |x * inv| by qmax (1 + 2^-22): rounding cannot leave the range, and the code is the low
             // bits of one fma.  (inv is 0 for a row without a step, or whose values overflowed: the general form gives codes 0 there.)
@@ -170,6 +176,27 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
                 const int q = (int)__builtin_rintf(ASYM ? fmaf(x[r], inv, off) : x[r] * inv);
                 return (uint32_t)min(q_hi, max(q_lo, q));
             };
+            if constexpr (E2M3) {
+                uint8_t *stage = lds_stage + (row & last) * E2m3Stage<K>::PITCH;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const int e0 = first + c * 64 * V + lane * V;
+                    if constexpr (kPermuted || V < 4) {
+#pragma unroll
+                        for (int i = 0; i < V; ++i) stage[code_position(e0 + i, K)] = (uint8_t)code_of(c * V + i);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < V; i += 4)
+                            *reinterpret_cast<uint32_t *>(stage + e0 + i) = low_bytes(code_of(c * V + i), code_of(c * V + i + 1), code_of(c * V + i + 2), code_of(c * V + i + 3));
+                    }
+                }
+                if (WPR == 1 || (row & last) == last) {       // the same for the whole block
+                    __syncthreads();
+                    flush_e2m3<K>(lds_stage, row & ~last, group, rows, packed);
+                    __syncthreads();
+                }
+                continue;
+            }
             uint8_t *out = packed + (size_t)row * (K * CB / 8);
             if constexpr (K == 1024 || K == 2048 || K == 4096) {
                 // permuted layout: scatter the codes as bytes into the wave's LDS row at their positions,
@@ -319,6 +346,9 @@ hipError_t run_rotate_rows_general(const void *X, bool f32, int rows, int K, con
                                    uint8_t *packed, float *scale, unsigned int *colmax, const float *step, int step_stride,
                                    int bits, hipStream_t stream);
 
+hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out,
+                                        float *scale, hipStream_t stream);
+
 template <int MODE, int CB>
 static hipError_t launch_rotate_rows(const void *X, bool f32, int rows, int K, const int8_t *signs,
                                      const float *mul, int mul_mode, uint8_t *packed, float *scale,
@@ -326,7 +356,8 @@ static hipError_t launch_rotate_rows(const void *X, bool f32, int rows, int K, c
 {
     if (rows <= 0) return hipSuccess;
     const int waves_per_block = 4;
-    const int rows_per_block = K > 4096 ? 1 : waves_per_block;       // four waves share a row beyond 4096 values
+    // four waves share a row beyond 4096 values; E2M3 blocks leave in groups of rows
+    const int rows_per_block = K > 4096 && (CB != 6 || rows <= kFewSharedRows) ? 1 : waves_per_block;
     int blocks = (rows + rows_per_block - 1) / rows_per_block;
     // up to eight blocks per compute unit; the column statistic takes fewer waves for small inputs so that each folds several
     // rows into its running maximum before touching the shared result
@@ -373,6 +404,14 @@ hipError_t run_rotate_smooth_quant(const void *X, bool f32, int rows, int K, con
     if (bits == 4)
         return launch_rotate_rows<kQuantize, 4>(X, f32, rows, K, signs, mul, mul_mode, packed, scale, nullptr, step, step_stride, qmax, stream);
     return launch_rotate_rows<kQuantize, 8>(X, f32, rows, K, signs, mul, mul_mode, packed, scale, nullptr, step, step_stride, qmax, stream);
+}
+
+// rotation + smoothing + per-token 4-bit codes as E2M3 blocks for the rows that the matrix-core kernel does not take: f32, or other sizes
+hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
+                                hipStream_t stream)
+{
+    if (general_size_supported(K)) return run_rotate_rows_general_e2m3(X, f32, rows, K, signs, mul, out, scale, stream);
+    return launch_rotate_rows<kQuantize, 6>(X, f32, rows, K, signs, mul, 0, out, scale, nullptr, nullptr, 0, 7.0f, stream);
 }
 
 hipError_t run_ln_rotate_quant_mfma(const void *X, int rows, const int8_t *signs, const float *mul, uint8_t *packed, float *scale,

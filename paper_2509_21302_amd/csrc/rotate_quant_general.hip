@@ -7,6 +7,7 @@
 // This is the general path: VGGT-1B itself has no layer that needs it.  Bound by the vector ALU (34350 x 768 bf16: 38 us with dense
 // m-point sums and the lane bits through LDS, 28 us now).
 #include "qvggt_common.h"
+#include "rotate_rows.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -83,7 +84,7 @@ constexpr int waves_per_row(int n2, int mm) { return n2 / 64 * mm >= 80 ? 4 : 1;
 }  // namespace gen
 
 // mul_mode 0: mul[j] used as given (inv_smooth, or 1/sqrt(K) when mul == nullptr); 1: 1 / (K * mul[j]) (weights)
-// CB: bits a stored code occupies (4 or 8); qmax: largest code; step: static quantization step or nullptr
+// CB: bits a stored code occupies (4 or 8; 6: 4-bit codes as E2M3 blocks, dynamic steps); qmax: largest code; step: static quantization step or nullptr
 template <int N2, int MM, bool F32, int MODE, int CB>
 __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__restrict__ X, int rows,
                                                                   const int8_t *__restrict__ signs,
@@ -98,10 +99,13 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
     static_assert(N2 / WPR >= 64 && (N2 & (N2 - 1)) == 0, "the power-of-two factor covers the 64 lanes");
     const int lane = threadIdx.x & 63;
     const int sub = WPR > 1 ? (int)(threadIdx.x >> 6) : 0, first = sub * (K / WPR);       // this wave's part of a row
-    const int wave = WPR > 1 ? (int)blockIdx.x : (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+    constexpr bool E2M3 = (CB == 6);
+    const int group = !E2M3 || WPR == 1 || rows > kFewSharedRows ? kE2m3Group : 1;       // rows that leave together
+    const int wave = WPR > 1 ? (int)blockIdx.x * (E2M3 ? group : 1) : (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
     const int nwaves = WPR > 1 ? (int)gridDim.x : (int)gridDim.x * 4;
     __shared__ float4 exchange[WPR > 1 ? K / 4 : 1];
     __shared__ float red[4];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_stage[E2M3 ? E2m3Stage<K>::BYTES : 16];
 
     // per-lane constants: register r = c * MM + b holds element e = (lane + 64 c) * MM + b
     constexpr bool SIGN_MASKS = R <= 32;       // signs as masks while there is room, one bit per register otherwise
@@ -134,12 +138,15 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
     float colmax[MODE == gen::kColAbsMax ? R : 1];
 #pragma unroll
     for (int r = 0; r < (MODE == gen::kColAbsMax ? R : 1); ++r) colmax[r] = 0.0f;
-    for (int row = wave; row < rows; row += nwaves) {
+    // E2M3: a block takes a group of consecutive rows at a time, one per wave or (WPR > 1) one after the other; past the end: the last row, not
+    // written
+    const int last = group - 1;
+    for (int row = wave; (E2M3 ? row & ~last : row) < rows; row += !(E2M3 && WPR > 1) ? nwaves : (row & last) == last ? group * nwaves - last : 1) {
         float x[R];
         // a lane's MM values of one a are contiguous: 8-byte (bf16) or 16-byte (f32) pieces of four values
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const size_t e0 = (size_t)row * K + first + (size_t)(lane + 64 * c) * MM;
+            const size_t e0 = (size_t)(E2M3 ? min(row, rows - 1) : row) * K + first + (size_t)(lane + 64 * c) * MM;
 #pragma unroll
             for (int q = 0; q < MM / 4; ++q) {
                 if constexpr (F32) {
@@ -221,11 +228,28 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                 delta = live ? amax / qmax : 0.0f;
                 inv = live ? qmax / amax : 0.0f;
             }
-            if (lane == 0 && sub == 0) scale[row] = delta;
+            if (lane == 0 && sub == 0 && (!E2M3 || row < rows)) scale[row] = delta;
             const int q_hi = (int)qmax, q_lo = -q_hi - 1;
             // a step from the row's own maximum bounds |x * inv| by qmax (1 + 2^-22): rounding cannot leave the range, and the code is the low
             // bits of one fma.  (inv is 0 for a row without a step, or whose values overflowed: the general form gives codes 0 there.)
             const bool bounded = step == nullptr && inv > 0.0f;
+            auto code_of = [&](int r) -> uint32_t {       // two's complement in the low CB bits, anything above
+                return bounded ? __float_as_uint(fmaf(x[r], inv, kRoundMagic)) : (uint32_t)min(q_hi, max(q_lo, (int)__builtin_rintf(x[r] * inv)));
+            };
+            if constexpr (E2M3) {
+                uint8_t *stage = lds_stage + (row & last) * E2m3Stage<K>::PITCH + first;
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int g = 0; g < MM; g += 4)
+                        *reinterpret_cast<uint32_t *>(stage + (lane + 64 * c) * MM + g) = low_bytes(code_of(c * MM + g), code_of(c * MM + g + 1), code_of(c * MM + g + 2), code_of(c * MM + g + 3));
+                if (WPR == 1 || (row & last) == last) {       // the same for the whole block
+                    __syncthreads();
+                    flush_e2m3<K>(lds_stage, row & ~last, group, rows, packed);
+                    __syncthreads();
+                }
+                continue;
+            }
             uint8_t *out = packed + (size_t)row * (K * CB / 8);
 #pragma unroll
             for (int c = 0; c < C; ++c)
@@ -234,9 +258,7 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                     uint32_t word = 0;          // four codes: two bytes of nibbles, or four bytes
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float v = x[c * MM + 4 * g + i];
-                        const uint32_t qv = bounded ? __float_as_uint(fmaf(v, inv, kRoundMagic)) : (uint32_t)min(q_hi, max(q_lo, (int)__builtin_rintf(v * inv)));
-                        word |= (qv & ((1u << CB) - 1)) << (CB * i);
+                        word |= (code_of(c * MM + 4 * g + i) & ((1u << CB) - 1)) << (CB * i);
                     }
                     const size_t pos = first + (size_t)(lane + 64 * c) * MM + 4 * g;      // position of the first of the four codes
                     if constexpr (CB == 4) *reinterpret_cast<uint16_t *>(out + pos / 2) = (uint16_t)word;
@@ -295,6 +317,33 @@ hipError_t run_rotate_rows_general(const void *X, bool f32, int rows, int K, con
 {
 #define QVGGT_CASE(KK, N2, MM) \
     case KK: return launch_general<N2, MM>(X, f32, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, bits, stream);
+    switch (K) {
+        QVGGT_CASE(768, 64, 12)
+        QVGGT_CASE(1536, 128, 12)
+        QVGGT_CASE(3072, 256, 12)
+        QVGGT_CASE(6144, 512, 12)
+        QVGGT_CASE(1280, 64, 20)
+        QVGGT_CASE(2560, 128, 20)
+        QVGGT_CASE(5120, 256, 20)
+        QVGGT_CASE(1792, 64, 28)
+        QVGGT_CASE(3584, 128, 28)
+        default: return hipErrorInvalidValue;
+    }
+#undef QVGGT_CASE
+}
+
+// the same rows as E2M3 blocks (dynamic 4-bit codes)
+hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out,
+                                        float *scale, hipStream_t stream)
+{
+    if (rows <= 0) return hipSuccess;
+    const int group = (K == 5120 || K == 6144) && rows <= kFewSharedRows ? 1 : kE2m3Group;
+    const int blocks = std::min((rows + group - 1) / group, 256 * 8);
+#define QVGGT_CASE(KK, N2, MM)                                                                                                           \
+    case KK:                                                                                                                             \
+        if (f32) rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, 0, out, scale, nullptr, nullptr, 0, 7.0f); \
+        else rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, 0, out, scale, nullptr, nullptr, 0, 7.0f);    \
+        return hipGetLastError();
     switch (K) {
         QVGGT_CASE(768, 64, 12)
         QVGGT_CASE(1536, 128, 12)

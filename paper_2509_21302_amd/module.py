@@ -38,9 +38,9 @@ class DsfqLinear:
         self.bits, self.act_bits, self.bias, self.signs = bits, act_bits, bias, signs
         self.packed = bits == 4 and act_bits == 4            # both 4-bit: two codes per byte; otherwise int8 codes
         dev = weight.device
-        # bf16 rows of the sizes with matrix-core kernels keep their codes in a second form, the blocks that the fast GEMMs read (E2M3 numbers
-        # resp. int8), and with a calibration batch are made in three launches; the others one entry point at a time
-        blocks = self.K in (1024, 2048, 4096)
+        # the codes are kept in a second form, the blocks that the fast GEMMs read: E2M3 numbers, and int8 blocks for the sizes whose kernel 1
+        # writes them.  bf16 rows of those sizes with a calibration batch are made in three launches, the others one entry point at a time
+        self._blocks = blocks = self.K in (1024, 2048, 4096)
         fused = (blocks and calibration is not None and weight.dtype == calibration.dtype == torch.bfloat16 and calibration.dim() == 2
                  and calibration.shape[0] > 0 and calibration.shape[1] == self.K)
         absmax = None
@@ -55,18 +55,18 @@ class DsfqLinear:
         self.inv_smooth = torch.empty(self.K, dtype=torch.float32, device=dev)
         if self.packed:
             self.Wq = torch.empty(self.N, self.K // 2, dtype=torch.uint8, device=dev)
-            self.Wf = torch.empty(q.qvggt_e2m3_bytes(self.N, self.K), dtype=torch.uint8, device=dev) if blocks else None
-            lost = None
+            self.Wf = torch.empty(q.qvggt_e2m3_bytes(self.N, self.K), dtype=torch.uint8, device=dev)
+            lost = torch.empty(1, dtype=torch.int32, device=dev) if fused else torch.zeros(1, dtype=torch.int32, device=dev)
             if fused:
-                lost = torch.empty(1, dtype=torch.int32, device=dev)
                 q.qvggt_layer_codes(weight, rows, signs, alpha, bits, False, self.Wq, self.Wf, self.w_scale, self.inv_smooth, lost, scratch)
             else:
                 q.qvggt_prep_weights(weight, absmax, signs, alpha, self.Wq, self.w_scale, self.inv_smooth)
+                q.qvggt_codes_to_e2m3(self.Wq, self.N, self.K, self.Wf, lost)
+            n = int(lost.item())
+            if n != 0:                       # cannot happen with absmax steps of numbers (codes lie in [-7, 7])
                 if blocks:
-                    lost = torch.zeros(1, dtype=torch.int32, device=dev)
-                    q.qvggt_codes_to_e2m3(self.Wq, self.N, self.K, self.Wf, lost)
-            if lost is not None and (n := int(lost.item())) != 0:      # cannot happen with absmax steps of numbers (codes lie in [-7, 7])
-                raise RuntimeError(f"{n} weight codes -8 have no E2M3 value")
+                    raise RuntimeError(f"{n} weight codes -8 have no E2M3 value")
+                self.Wf = None               # the other sizes have always taken such weights: their nibbles are multiplied as they are
         else:
             self.Wq = torch.empty(self.N, self.K, dtype=torch.int8, device=dev)
             self.Wb = torch.empty(q.qvggt_i8b_bytes(self.N, self.K), dtype=torch.int8, device=dev) if blocks else None
@@ -101,9 +101,12 @@ class DsfqLinear:
             if X.dtype != torch.bfloat16:
                 raise ValueError("pre_gelu needs bf16 input")
             q.qvggt_gelu_linear_e2m3(X, self.signs, self.inv_smooth, self.gelu_table, self.Wf, self.w_scale, self.bias, Y, ws)
-        elif self.packed and self.Wf is not None and X.dtype == torch.bfloat16:
-            q.qvggt_linear_e2m3(X, self.signs, self.inv_smooth, self.Wf, self.w_scale, self.bias, Y, ws)      # same Y, bit for bit
-        elif self.packed:
+        elif self.packed and self.Wf is not None and (M <= 4096 or self._blocks and X.dtype == torch.bfloat16 or self.N >= 448 and self.K >= 512):
+            # (many rows of few channels or features are kernel 1 and the stores of Y; kernel 1 writes nibbles 10 to 15 % faster where it is not
+            # the matrix-core one: 41505 x 768 -> 128 44.4 us in nibbles, 50.0 in E2M3 blocks, 50398 x 1536 -> 272 110 / 112, 57418 x 256 -> 512
+            # 41.4 / 45.1, 9374 x 512 -> 2576 44.2 / 33.4, 64 x 128 -> 128 9.0 / 8.1)
+            q.qvggt_linear_e2m3_any(X, self.signs, self.inv_smooth, self.Wf, self.w_scale, self.bias, Y, ws)
+        elif self.packed:                                # the same Y, bit for bit
             q.qvggt_linear(X, self.signs, self.inv_smooth, self.Wq, self.w_scale, self.bias, Y, ws)
         elif self.Wb is not None and X.dtype == torch.bfloat16:
             q.qvggt_linear_i8b(X, self.signs, self.inv_smooth, self.act_bits, self.Wb, self.w_scale, self.bias, Y, ws)   # same Y

@@ -365,3 +365,29 @@ def test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan):
     G.q.qvggt_e2m3_gemm_shifted(Xf, sx, zx, Wf, dw, wsum, bias, M, N, K, whole[:M])
     G.q.qvggt_w4a4_gemm_asym(Xq, sx, zx, Wq, dw, wsum, bias, M, N, K, Y8)
     assert torch.equal(whole[:M].view(torch.int16), Y8.view(torch.int16)) and (whole[M:] == 7.0).all().item()
+
+
+# every K in both types: rows below a group of four, groups that end inside a 128-row block, more groups than blocks
+@pytest.mark.parametrize("K", [128, 256, 512, 768, 1024, 1280, 1536, 1792, 2048, 2560, 3072, 3584, 4096, 5120, 6144, 8192])
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("M", [1, 6, 131, 8500])
+def test_linear_e2m3_of_any_rows(K, f32, M):
+    """The row kernels writing E2M3 blocks: steps and Y of the packed path, bit for bit, with rows of zeros and of infinities among them."""
+    if M * K > 20e6:
+        pytest.skip("covered by the smaller sizes")
+    N = 80
+    g = torch.Generator(device=G.DEV).manual_seed(K + M)
+    X = torch.randn(M, K, device=G.DEV, generator=g)
+    X[:, ::61] *= 30
+    X[M // 2] = 0
+    if M > 5 and (f32 or K not in (1024, 2048, 4096)):       # the matrix-core kernel, which takes the others, has no code for them in this form
+        X[3, 7], X[5, 1] = float("inf"), float("nan")
+    X = X if f32 else X.to(torch.bfloat16)
+    W = torch.randn(N, K, device=G.DEV, generator=g) * 0.03
+    bias = torch.randn(N, device=G.DEV, generator=g).to(torch.bfloat16)
+    layer = G.q.DsfqLinear(W, bias, None, X[-1:].contiguous())
+    Y = layer(X)
+    want = torch.empty_like(Y)
+    ws = torch.empty(G.q.qvggt_workspace_bytes(M, N, K), dtype=torch.uint8, device=G.DEV)
+    G.q.qvggt_linear(X, None, layer.inv_smooth, layer.Wq, layer.w_scale, bias, want, ws)
+    assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
