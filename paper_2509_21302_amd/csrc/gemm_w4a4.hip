@@ -514,6 +514,155 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
                                                            M - rows_main, N, K, Y + (size_t)rows_main * N, nullptr, nullptr, nullptr);
 }
 
+// The same product for few tiles, as e2m3_gemm_few_kernel: the KW waves of a block divide K among themselves instead of the tile (wave w takes
+// K-tiles w, w + KW, ...), fragments come from memory straight into registers, DEPTH K-tiles ahead, and the int32 partial sums meet in LDS at the
+// end.  A tile of the streaming kernel that is alone on its compute unit is a serial chain of transfers, barriers, LDS reads and MFMAs along K.
+template <int TM, int TN, int KW>
+struct FewCfg {
+    static constexpr int THREADS = KW * 64, BM = TM * 32, BN = TN * 32, NF = TM + TN;
+    static constexpr int GROUPS = TM * TN * 4;              // of four accumulator registers of a lane
+    static constexpr int PITCH = 64 * 16 + 128;             // bytes of a group and a gap: neighbouring groups start in different halves of the banks
+    static constexpr int LDS_BYTES = KW * GROUPS * PITCH;
+    static constexpr int OCTS = BN / 8, ITEMS = BM * OCTS;  // runs of eight channels of a token
+    static_assert(128 % BM == 0 && 128 % BN == 0, "a tile lies in one block of the blocked operand format");
+    static_assert(THREADS % OCTS == 0, "a thread's runs are the same channels of different tokens");
+};
+
+template <int TM, int TN, int KW, int DEPTH, int CB, bool ASYM, bool BLK>
+__global__ __launch_bounds__(KW * 64, 1) void w4a4_gemm_few_kernel(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq, const float *__restrict__ sw,
+    const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ Y, int tiles_m, int tiles_n, bool tokens_first,
+    const float *__restrict__ xzero, const float *__restrict__ wsum)
+{
+    using C = FewCfg<TM, TN, KW>;
+    constexpr int NF = C::NF;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row_bytes = CB == 4 ? K / 2 : K, ktiles = row_bytes / KT_BYTES, ntiles = tiles_m * tiles_n;
+    const int per_xcd = (ntiles + 7) >> 3;
+    const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= ntiles) return;
+    const int fast = tokens_first ? tiles_m : tiles_n, outer = tile / fast, inner = tile - outer * fast;
+    const int tm = tokens_first ? inner : outer, tn = tokens_first ? outer : inner;
+    const int row0 = tm * C::BM, col0 = tn * C::BN;
+
+    // fragments: W sub-tiles, then X sub-tiles.  A lane's 16 bytes are chunk 2 p + lane / 32 of its row's 64-byte K-tile (p = 0, 1)
+    const int frow = lane & 31, fhalf = lane >> 5;
+    const uint8_t *src[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const bool is_w = f < TN;
+        const int first = is_w ? col0 + f * 32 : row0 + (f - TN) * 32;
+        if constexpr (BLK) {
+            src[f] = (is_w ? Wq : Xq) + (size_t)(first / 128) * ktiles * 8192 + ((first % 128) + frow) * 64 + ((fhalf ^ ((frow & 15) >> 2)) << 4);
+        } else {                                            // rows past the operand's end: the last one (results unused)
+            src[f] = (is_w ? Wq : Xq) + (size_t)min(first + frow, (is_w ? N : M) - 1) * row_bytes + fhalf * 16;
+        }
+    }
+    // chunk 2 + lane / 32 of a K-tile, from chunk lane / 32: in blocks its slot differs in bit 1 (byte 32), to either side
+    const int pair1 = BLK ? ((((fhalf ^ ((frow & 15) >> 2)) & 2) != 0) ? -32 : 32) : 32;
+    const size_t kt_step = BLK ? 8192 : KT_BYTES;
+    v4i F[DEPTH][NF][2];
+    auto load = [&](auto d_c, int kt) {
+        constexpr int d = decltype(d_c)::value;
+        const size_t off = (size_t)min(kt, ktiles - 1) * kt_step;          // past the end: the last K-tile again (not used)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            F[d][f][0] = *reinterpret_cast<const v4i *>(src[f] + off);
+            F[d][f][1] = *reinterpret_cast<const v4i *>(src[f] + off + pair1);
+        }
+    };
+    static_for<DEPTH>([&](auto d_c) { load(d_c, wave + decltype(d_c)::value * KW); });
+    // what the epilogue needs, asked for before the products
+    constexpr int IT = (C::ITEMS + C::THREADS - 1) / C::THREADS;
+    const int oct = tid % C::OCTS, t0 = tid / C::OCTS, n = col0 + oct * 8;
+    const int nc = min(n, N - 8);
+    const float4 sw0 = *reinterpret_cast<const float4 *>(sw + nc), sw1 = *reinterpret_cast<const float4 *>(sw + nc + 4);
+    uint4 bw = make_uint4(0u, 0u, 0u, 0u);
+    if (bias != nullptr) bw = *reinterpret_cast<const uint4 *>(bias + nc);
+    float4 ws0, ws1;
+    if constexpr (ASYM) { ws0 = *reinterpret_cast<const float4 *>(wsum + nc); ws1 = *reinterpret_cast<const float4 *>(wsum + nc + 4); }
+    float st[IT], zt[ASYM ? IT : 1];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int m = min(row0 + t0 + k * (C::THREADS / C::OCTS), M - 1);
+        st[k] = sx[m] * (CB == 4 ? 1.0f / 256.0f : 1.0f);
+        if constexpr (ASYM) zt[k] = (8.0f - xzero[m]) * (CB == 4 ? 256.0f : 1.0f);
+    }
+    v16i acc[TN][TM];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][i][r] = 0;
+    for (int kt = wave; kt < ktiles; kt += DEPTH * KW) {      // every condition is the same for the whole wave
+        static_for<DEPTH>([&](auto d_c) {
+            constexpr int d = decltype(d_c)::value;
+            if (kt + d * KW < ktiles) {
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    // packed codes: the odd ones of the 32 in the high nibbles as they are, then the even ones moved there
+                    constexpr int PARTS = CB == 4 ? 2 : 1;
+#pragma unroll
+                    for (int e = 0; e < PARTS; ++e) {
+                        v4i op[NF];
+#pragma unroll
+                        for (int f = 0; f < NF; ++f) {
+                            if constexpr (CB == 4) op[f] = (e == 0 ? F[d][f][p] : F[d][f][p] << 4) & (int)0xF0F0F0F0;
+                            else op[f] = F[d][f][p];
+                        }
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int i = 0; i < TM; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(op[j], op[TN + i], acc[j][i], 0, 0, 0);
+                    }
+                }
+            }
+            if (kt + DEPTH * KW < ktiles) load(d_c, kt + (d + DEPTH) * KW);
+        });
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<int4 *>(smem + (wave * C::GROUPS + (j * TM + i) * 4 + q) * C::PITCH + lane * 16) =
+                    make_int4(acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]);
+    __syncthreads();
+    // 32x32 result layout: group q of a sub-tile holds channels 8 q .. 8 q + 3 in lanes 0 .. 31 and 8 q + 4 .. 8 q + 7 in lanes 32 .. 63
+    const float swv[8] = {sw0.x, sw0.y, sw0.z, sw0.w, sw1.x, sw1.y, sw1.z, sw1.w};
+    const uint32_t bwv[4] = {bw.x, bw.y, bw.z, bw.w};
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int t = t0 + k * (C::THREADS / C::OCTS), m = row0 + t;
+        if ((C::ITEMS % C::THREADS != 0 && t >= C::BM) || m >= M || n >= N) continue;
+        const uint8_t *p = smem + ((oct / 4) * TM * 4 + (t / 32) * 4 + oct % 4) * C::PITCH + (t % 32) * 16;
+        int a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int w = 0; w < KW; ++w) {
+            const int4 lo = *reinterpret_cast<const int4 *>(p + w * C::GROUPS * C::PITCH), hi = *reinterpret_cast<const int4 *>(p + w * C::GROUPS * C::PITCH + 512);
+            a[0] += lo.x; a[1] += lo.y; a[2] += lo.z; a[3] += lo.w; a[4] += hi.x; a[5] += hi.y; a[6] += hi.z; a[7] += hi.w;
+        }
+        float fv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) fv[e] = (float)a[e];
+        if constexpr (ASYM) {
+            const float wsv[8] = {ws0.x, ws0.y, ws0.z, ws0.w, ws1.x, ws1.y, ws1.z, ws1.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) fv[e] = fmaf(zt[k], wsv[e], fv[e]);
+        }
+        uint32_t out[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            out[e] = pack_bf16x2(fmaf(fv[2 * e], swv[2 * e] * st[k], __uint_as_float(bwv[e] << 16)),
+                                 fmaf(fv[2 * e + 1], swv[2 * e + 1] * st[k], __uint_as_float(bwv[e] & 0xFFFF0000u)));
+        *reinterpret_cast<uint4 *>(Y + (size_t)m * N + n) = make_uint4(out[0], out[1], out[2], out[3]);
+    }
+}
+
 // every instantiation launched below, with the dynamic LDS it needs: packed codes (plain, accumulator dump, affine), int8 codes
 // row-major and in blocks (plain, accumulator dump)
 #define QVGGT_GEMM_KERNELS(TM, TN, WM, WN, ST, MB)                                                                                        \
@@ -524,13 +673,20 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, true, false, false>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, false, false, true>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, true, false, true>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES}
+#define QVGGT_FEW_KERNELS(TM, TN, KW, D)                                                                                                  \
+    {reinterpret_cast<const void *>(w4a4_gemm_few_kernel<TM, TN, KW, D, 4, false, false>), FewCfg<TM, TN, KW>::LDS_BYTES}, \
+    {reinterpret_cast<const void *>(w4a4_gemm_few_kernel<TM, TN, KW, D, 4, true, false>), FewCfg<TM, TN, KW>::LDS_BYTES},  \
+    {reinterpret_cast<const void *>(w4a4_gemm_few_kernel<TM, TN, KW, D, 8, false, false>), FewCfg<TM, TN, KW>::LDS_BYTES}, \
+    {reinterpret_cast<const void *>(w4a4_gemm_few_kernel<TM, TN, KW, D, 8, false, true>), FewCfg<TM, TN, KW>::LDS_BYTES}
 static constexpr int TAIL_LDS_BYTES = std::max(StreamCfg<4, 4, 2, 2, 4>::LDS_BYTES, StreamCfg<2, 2, 2, 2, 8>::LDS_BYTES);
 static const LdsKernel gemm_lds_kernel_list[] = {QVGGT_GEMM_KERNELS(4, 4, 2, 2, 4, 1), QVGGT_GEMM_KERNELS(2, 2, 2, 2, 3, 2),
                                                  QVGGT_GEMM_KERNELS(2, 2, 2, 2, 8, 1),
+                                                 QVGGT_FEW_KERNELS(2, 2, 4, 2), QVGGT_FEW_KERNELS(1, 2, 4, 2), QVGGT_FEW_KERNELS(1, 1, 8, 2),
                                                  {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<4, false>), TAIL_LDS_BYTES},
                                                  {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, false>), TAIL_LDS_BYTES},
                                                  {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, true>), TAIL_LDS_BYTES}};
 #undef QVGGT_GEMM_KERNELS
+#undef QVGGT_FEW_KERNELS
 static const LdsKernels gemm_lds_kernels(gemm_lds_kernel_list);
 
 template <int TM, int TN, int WM, int WN, int STAGES, int MINB, int CB, bool ASYM = false, bool BLK = false>
@@ -571,6 +727,21 @@ static hipError_t launch_gemm_tail(const uint8_t *Xq, const float *sx, const uin
     return hipGetLastError();
 }
 
+template <int TM, int TN, int KW, int DEPTH, int CB, bool ASYM, bool BLK>
+static hipError_t launch_gemm_few(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw, const void *bias, int M, int N, int K, void *Y,
+                                  hipStream_t stream, const float *xzero, const float *wsum)
+{
+    using C = FewCfg<TM, TN, KW>;
+    hipError_t e = prepare_device();
+    if (e != hipSuccess) return e;
+    const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
+    // neighbouring tiles of an XCD share tokens, or, where the weights are the larger operand and more than its L2 holds with anything else, channels
+    const bool tokens_first = tiles_m < tiles_n && (long long)N * K * CB / 8 > (3 << 20);
+    w4a4_gemm_few_kernel<TM, TN, KW, DEPTH, CB, ASYM, BLK><<<(tiles_m * tiles_n + 7) / 8 * 8, C::THREADS, C::LDS_BYTES, stream>>>(
+        Xq, sx, Wq, sw, reinterpret_cast<const uint16_t *>(bias), M, N, K, reinterpret_cast<uint16_t *>(Y), tiles_m, tiles_n, tokens_first, xzero, wsum);
+    return hipGetLastError();
+}
+
 // The tile shapes that the plan of gemm_plan.h names, over the token rows it gives them.
 template <int CB, bool ASYM = false, bool BLK = false>
 static hipError_t gemm_by_plan(const uint8_t *Xq, const float *sx, const uint8_t *Wq, const float *sw, const void *bias,
@@ -582,6 +753,16 @@ static hipError_t gemm_by_plan(const uint8_t *Xq, const float *sx, const uint8_t
                                                      static_cast<uint16_t *>(Y) + (size_t)(row0) * N,                                    \
                                                      acc_debug ? acc_debug + (size_t)(row0) * N : nullptr, stream,                       \
                                                      ASYM ? xzero + (row0) : nullptr, wsum)
+    if (acc_debug == nullptr) {                      // the dump is for the streaming kernel
+#define QVGGT_FEW(TM, TN, KW, D) return launch_gemm_few<TM, TN, KW, D, CB, ASYM, BLK>(Xq, sx, Wq, sw, bias, M, N, K, Y, stream, xzero, wsum)
+        switch (int8_instruction_few_tiles(M, N, K, CB, BLK)) {
+            case FewTiles::kNone: break;
+            case FewTiles::k64: QVGGT_FEW(2, 2, 4, 2);
+            case FewTiles::k32x64: QVGGT_FEW(1, 2, 4, 2);
+            case FewTiles::k32: QVGGT_FEW(1, 1, 8, 2);
+        }
+#undef QVGGT_FEW
+    }
     const GemmPlan plan = int8_instruction_gemm_plan(M, N, K, CB, ASYM, acc_debug != nullptr);
     switch (plan.shape) {
         case GemmPlan::kBig: return QVGGT_ROWS(4, 4, 4, 1, 0, M);

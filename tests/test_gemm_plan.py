@@ -158,3 +158,36 @@ def test_e2m3_plans(tmp_path):
             assert shape == "256" and rows % 256 == 0 and 0 < rows < M
     assert divided > 100
     assert {p[3].split("+")[0] for p in E2M3_PLANS} == {"256", "192", "128", "64", "32x64", "32"}
+
+
+FEW_DRIVER = r"""
+#include "gemm_plan.h"
+#include <cstdio>
+int main()
+{
+    int M, N, K, bits, blocks;
+    const char *names[] = {"none", "64", "32x64", "32"};
+    while (std::scanf("%d %d %d %d %d", &M, &N, &K, &bits, &blocks) == 5) std::printf("%s\n", names[(int)qvggt::int8_instruction_few_tiles(M, N, K, bits, blocks)]);
+}
+"""
+
+
+def test_few_tiles(tmp_path):
+    """The GPU test's table reaches the shapes it names; no problem of more than 256 tiles of 128 x 128 is one of few."""
+    from tests.test_gpu_gemm import FEW_TILES
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text(FEW_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+
+    def ask(problems):
+        return subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d %d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
+    bits = {"packed": (4, 0), "affine": (4, 0), "int8": (8, 0), "blocks": (8, 1)}
+    for (M, N, K, kind, want), got in zip(FEW_TILES, ask([p[:3] + bits[p[3]] for p in FEW_TILES])):
+        assert got == want, (M, N, K, kind)
+    rng = random.Random(7)
+    problems = [(int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(4096)))), rng.choice([128, 768, 1024, 4096, 8192]),
+                 *rng.choice([(4, 0), (8, 0), (8, 1)])) for _ in range(20000)]
+    for (M, N, *_), got in zip(problems, ask(problems)):
+        assert got == "none" or (M + 127) // 128 * ((N + 127) // 128) <= 256

@@ -215,3 +215,53 @@ def test_tile_plans(M, N, K, kind):
     Yo = oracle.dequant_bias(want, dx[rows], dw)
     ulp_off = np.abs(G.bf16_bits(Y)[rows].astype(np.int32) - Yo.astype(np.int32))
     assert ulp_off.max() <= 1 and (ulp_off != 0).mean() < 5e-3
+
+
+# w4a4_gemm_few_kernel's shapes (csrc/gemm_plan.h; tests/test_gemm_plan.py holds the table to it): one row, tile edges and remainders, channels that end
+# inside a tile, K with fewer K-tiles than a block has waves, weights beyond an L2; and two problems with as few tiles that stay with the deep ring
+FEW_TILES = [(1, 16, 4096, "packed", "32"), (33, 48, 1024, "packed", "32"), (200, 1040, 4096, "packed", "32"), (260, 2064, 1024, "packed", "64"), (97, 2064, 128, "packed", "32x64"), (500, 1040, 2048, "packed", "64"),
+             (1374, 496, 1024, "packed", "64"), (291, 3072, 4096, "packed", "64"), (2048, 2048, 4096, "packed", "none"),
+             (1, 16, 128, "affine", "32x64"), (131, 528, 2048, "affine", "32"), (1374, 496, 1024, "affine", "64"), (187, 2192, 4096, "affine", "32x64"),
+             (361, 96, 4096, "int8", "32"), (29, 4096, 256, "int8", "32"), (434, 1024, 768, "int8", "32x64"), (434, 2064, 512, "int8", "64"), (65, 80, 8192, "int8", "32"),
+             (1012, 336, 4096, "blocks", "32x64"), (40, 944, 4096, "blocks", "32"), (749, 1040, 4096, "blocks", "64"), (533, 1200, 1024, "blocks", "64"), (428, 3280, 1024, "blocks", "none"),
+             (1374, 1024, 4096, "blocks", "none")]
+
+
+@pytest.mark.parametrize("M,N,K,kind,shape", FEW_TILES)
+@pytest.mark.parametrize("with_bias", [True, False])
+def test_few_tiles_are_the_streaming_kernels_bits(M, N, K, kind, shape, with_bias):
+    """Against the accumulator dump's call, which always takes the streaming kernel (whose sums other tests hold to the oracle), resp. for affine
+    codes against the same tokens among more rows than this kernel takes; nothing past the last row is written."""
+    g = torch.Generator(device=G.DEV).manual_seed(M + N + K)
+
+    def rand(lo, hi, *shape):
+        return torch.randint(lo, hi, shape, device=G.DEV, generator=g)
+    sx, sw = torch.rand(M, device=G.DEV, generator=g) + 0.1, torch.rand(N, device=G.DEV, generator=g) * 0.01
+    bias = torch.randn(N, device=G.DEV, generator=g).to(torch.bfloat16) if with_bias else None
+    whole, want = torch.full((M + 3, N), 7.0, dtype=torch.bfloat16, device=G.DEV), torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV)
+    acc = torch.empty(M, N, dtype=torch.int32, device=G.DEV)
+    if kind in ("packed", "affine"):
+        A, W = rand(0, 256, M, K // 2).to(torch.uint8), rand(0, 256, N, K // 2).to(torch.uint8)
+    if kind == "packed":
+        G.q.qvggt_w4a4_gemm(A, sx, W, sw, bias, M, N, K, whole[:M])
+        G.q.qvggt_w4a4_gemm(A, sx, W, sw, bias, M, N, K, want, acc)
+    elif kind == "affine":
+        zero, sums = rand(0, 16, M).float(), G.gpu_code_sums(W, N, K)
+        G.q.qvggt_w4a4_gemm_asym(A, sx, zero, W, sw, sums, bias, M, N, K, whole[:M])
+        many = 128 * 257 // ((N + 127) // 128) + M
+        rep = [torch.cat([v, v[:1].expand(many - M, *v.shape[1:])]).contiguous() for v in (A, sx, zero)]
+        Y = torch.empty(many, N, dtype=torch.bfloat16, device=G.DEV)
+        G.q.qvggt_w4a4_gemm_asym(rep[0], rep[1], rep[2], W, sw, sums, bias, many, N, K, Y)
+        want = Y[:M]
+    else:
+        A, W = rand(-128, 128, M, K).to(torch.int8), rand(-128, 128, N, K).to(torch.int8)
+        call = G.q.qvggt_i8_gemm
+        if kind == "blocks":
+            rows = []
+            for v, n in ((A, M), (W, N)):
+                rows.append(torch.full((G.q.qvggt_i8b_bytes(n, K),), 0x55, dtype=torch.int8, device=G.DEV))
+                G.q.qvggt_int8_to_blocks(v, n, K, rows[-1])
+            (A, W), call = rows, G.q.qvggt_i8b_gemm
+        call(A, sx, W, sw, bias, M, N, K, whole[:M])
+        call(A, sx, W, sw, bias, M, N, K, want, acc)
+    assert torch.equal(whole[:M].view(torch.int16), want.view(torch.int16)) and (whole[M:] == 7.0).all().item()
