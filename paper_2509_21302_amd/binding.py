@@ -13,6 +13,11 @@ from typing import Optional
 
 import torch
 
+try:
+    from . import _call          # DsfqLinear's calls in native code; without it (another torch than it was built for) they go through this module
+except ImportError:
+    _call = None
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 QVGGT_BF16, QVGGT_F32 = 0, 1
 
@@ -36,6 +41,11 @@ EXPORTS = [
     "qvggt_linear_e2m3_any", "qvggt_layer_workspace_bytes", "qvggt_layer_statistics", "qvggt_layer_codes",
     "qvggt_rotate_rows", "qvggt_calib_workspace_bytes", "qvggt_calib_loss_grad", "qvggt_calib_descent_step",
 ]
+
+
+# the entry points that _call.linear knows, in its order
+LINEAR_KINDS = ("qvggt_linear", "qvggt_linear_e2m3_any", "qvggt_gelu_linear_e2m3", "qvggt_linear_i8", "qvggt_linear_i8b")
+PACKED, E2M3, GELU, INT8, INT8_BLOCKS = range(5)
 
 
 class QvggtError(RuntimeError):
@@ -181,6 +191,9 @@ def load_library() -> C.CDLL:
     lib.qvggt_pack_int4.argtypes = [vp, i, i, vp, vp]
     lib.qvggt_unpack_int4.restype = i
     lib.qvggt_unpack_int4.argtypes = [vp, i, i, vp, vp]
+    if _call is not None:
+        for kind, name in enumerate(LINEAR_KINDS):
+            _call.bind(kind, C.cast(getattr(lib, name), C.c_void_p).value)
     _lib = lib
     return lib
 
@@ -226,6 +239,20 @@ def _stream(stream) -> Optional[int]:
 def _check(status: int, where: str):
     if status != 0:
         raise QvggtError(status, where)
+
+
+def native_linear(kind, X, signs, inv_smooth, gelu_table, W, w_scale, bias, out, workspace, N, bits):
+    """The entry point LINEAR_KINDS[kind] with the output allocated (out = None): the output, or None, before anything was launched, for a call
+    that the functions below have to take (or refuse)."""
+    if _call is None:
+        return None
+    load_library()
+    Y = _call.linear(kind, X, signs, inv_smooth, gelu_table, W, w_scale, bias, out, workspace, N, bits)
+    if Y is NotImplemented:
+        return None
+    if type(Y) is int:
+        raise QvggtError(Y, LINEAR_KINDS[kind])
+    return Y
 
 
 # ------------------------------------------------------------------ entry points

@@ -1,9 +1,9 @@
-"""Compile the HIP sources in csrc/ into libqvggt.so (gfx950 only), in-tree.
+"""Compile the HIP sources in csrc/ into libqvggt.so (gfx950 only), and csrc/call.cpp into the Python module _call, in-tree.
 
     python -m paper_2509_21302_amd.build          # build (always recompiles)
 
-Objects and compiler temporaries go to paper_2509_21302_amd/_build/; the shared library is
-written next to this file so that it travels with the source tree.
+Objects and compiler temporaries go to paper_2509_21302_amd/_build/; the shared libraries are
+written next to this file so that they travel with the source tree.
 """
 import os
 import subprocess
@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqvggt.so")
+CALL = os.path.join(HERE, "_call.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["api.hip", "rotate_quant.hip", "rotate_quant_mfma.hip", "gemm_w4a4.hip", "nfds.hip",
            "rotate_quant_general.hip", "gemm_e2m3.hip", "ceilings.hip", "calib.hip"]
@@ -44,10 +45,31 @@ def _compile(src: str, save_temps: bool) -> str:
     return obj
 
 
+def _compile_call() -> None:
+    """csrc/call.cpp against torch's headers (host code)."""
+    import sysconfig
+
+    import torch
+    top = os.path.dirname(torch.__file__)
+    tmp = CALL + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", os.path.join(top, "include"), "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "call.cpp"), "-o", tmp, "-L" + os.path.join(top, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on call.cpp:\n{r.stderr}")
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+    os.replace(tmp, CALL)
+
+
 def build(save_temps: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        call = ex.submit(_compile_call)
         objs = list(ex.map(lambda s: _compile(s, save_temps), SOURCES))
+        call.result()
     tmp = LIB + ".tmp"
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB)

@@ -95,21 +95,32 @@ class DsfqLinear:
     def __call__(self, X: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
         """X: [M, K] bf16 or f32 on the GPU; returns bf16 [M, N] (written into `out` when given)."""
         M = X.shape[0]
-        Y = out if out is not None else torch.empty(M, self.N, dtype=torch.bfloat16, device=X.device)
-        ws = self._workspace(M, X.device)
+        bf16 = X.dtype == torch.bfloat16
         if self.pre_gelu:
-            if X.dtype != torch.bfloat16:
+            if not bf16:
                 raise ValueError("pre_gelu needs bf16 input")
-            q.qvggt_gelu_linear_e2m3(X, self.signs, self.inv_smooth, self.gelu_table, self.Wf, self.w_scale, self.bias, Y, ws)
-        elif self.packed and self.Wf is not None and (M <= 4096 or self._blocks and X.dtype == torch.bfloat16 or self.N >= 448 and self.K >= 512):
+            kind, W, bits = q.GELU, self.Wf, 4
+        elif self.packed and self.Wf is not None and (M <= 4096 or bf16 and self._blocks or self.N >= 448 and self.K >= 512):
             # (many rows of few channels or features are kernel 1 and the stores of Y; kernel 1 writes nibbles 10 to 15 % faster where it is not
             # the matrix-core one: 41505 x 768 -> 128 44.4 us in nibbles, 50.0 in E2M3 blocks, 50398 x 1536 -> 272 110 / 112, 57418 x 256 -> 512
             # 41.4 / 45.1, 9374 x 512 -> 2576 44.2 / 33.4, 64 x 128 -> 128 9.0 / 8.1)
-            q.qvggt_linear_e2m3_any(X, self.signs, self.inv_smooth, self.Wf, self.w_scale, self.bias, Y, ws)
+            kind, W, bits = q.E2M3, self.Wf, 4
         elif self.packed:                                # the same Y, bit for bit
-            q.qvggt_linear(X, self.signs, self.inv_smooth, self.Wq, self.w_scale, self.bias, Y, ws)
-        elif self.Wb is not None and X.dtype == torch.bfloat16:
-            q.qvggt_linear_i8b(X, self.signs, self.inv_smooth, self.act_bits, self.Wb, self.w_scale, self.bias, Y, ws)   # same Y
+            kind, W, bits = q.PACKED, self.Wq, 4
+        elif bf16 and self.Wb is not None:
+            kind, W, bits = q.INT8_BLOCKS, self.Wb, self.act_bits
+        else:                                            # the same Y
+            kind, W, bits = q.INT8, self.Wq, self.act_bits
+        ws = self._workspace(M, X.device)
+        Y = q.native_linear(kind, X, self.signs, self.inv_smooth, self.gelu_table, W, self.w_scale, self.bias, out, ws, self.N, bits)
+        if Y is not None:
+            return Y
+        Y = out if out is not None else torch.empty(M, self.N, dtype=torch.bfloat16, device=X.device)
+        call = getattr(q, q.LINEAR_KINDS[kind])
+        if kind == q.GELU:
+            call(X, self.signs, self.inv_smooth, self.gelu_table, W, self.w_scale, self.bias, Y, ws)
+        elif kind in (q.INT8, q.INT8_BLOCKS):
+            call(X, self.signs, self.inv_smooth, bits, W, self.w_scale, self.bias, Y, ws)
         else:
-            q.qvggt_linear_i8(X, self.signs, self.inv_smooth, self.act_bits, self.Wq, self.w_scale, self.bias, Y, ws)
+            call(X, self.signs, self.inv_smooth, W, self.w_scale, self.bias, Y, ws)
         return Y

@@ -1,0 +1,91 @@
+"""DsfqLinear's calls in native code (csrc/call.cpp): the outputs of the Python path, its errors, and nothing taken that the Python path would not."""
+import threading
+
+import pytest
+import torch
+
+import paper_2509_21302_amd as q
+from paper_2509_21302_amd import binding as B
+
+
+def test_the_module_is_built_and_knows_its_entry_points():
+    assert B._call is not None
+    q.load_library()
+    with pytest.raises(ValueError):
+        B._call.bind(len(B.LINEAR_KINDS), 0)
+    with pytest.raises(TypeError):
+        B._call.linear(0)
+
+
+@pytest.mark.parametrize("X", [torch.zeros(2, 128), torch.zeros(2, 128, dtype=torch.float16), torch.zeros(128), torch.zeros(2, 256)[:, ::2], None, 3])
+def test_what_is_not_an_ordinary_device_tensor_is_left_to_the_python_path(X):
+    w = torch.zeros(128)
+    for kind in range(len(B.LINEAR_KINDS)):
+        assert B.native_linear(kind, X, None, w, None, w, w, None, None, w, 16, 4) is None
+
+
+def _layer(bits, act_bits, pre_gelu, K):
+    g = torch.Generator(device="cuda:0").manual_seed(K + bits)
+    W, X = torch.randn(144, K, device="cuda:0", generator=g) * 0.02, torch.randn(70, K, device="cuda:0", generator=g)
+    bias = torch.randn(144, device="cuda:0", generator=g).to(torch.bfloat16)
+    signs = (torch.randint(0, 2, (K,), device="cuda:0", generator=g, dtype=torch.int8) * 2 - 1).contiguous()
+    return q.DsfqLinear(W.to(torch.bfloat16), bias, signs, X.to(torch.bfloat16), bits=bits, act_bits=act_bits, pre_gelu=pre_gelu), X
+
+
+CASES = [(4, 4, False, 1024, torch.bfloat16), (4, 4, False, 256, torch.float32), (4, 4, True, 1024, torch.bfloat16), (8, 8, False, 1024, torch.bfloat16),
+         (4, 8, False, 1024, torch.float32), (6, 6, False, 768, torch.bfloat16)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,act_bits,pre_gelu,K,dtype", CASES)
+def test_the_same_output_as_the_python_path(monkeypatch, bits, act_bits, pre_gelu, K, dtype):
+    layer, X = _layer(bits, act_bits, pre_gelu, K)
+    X = X.to(dtype)
+    taken = []
+    native = B.native_linear
+    monkeypatch.setattr(B, "native_linear", lambda *a: taken.append(native(*a)) or taken[-1])
+    got = layer(X)
+    out = torch.full((73, 144), 7.0, dtype=torch.bfloat16, device="cuda:0")
+    assert layer(X, out[:70]).data_ptr() == out.data_ptr() and (out[70:] == 7.0).all().item()
+    assert taken[0] is got and taken[1] is not None
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        on_side = layer(X)
+    side.synchronize()
+    monkeypatch.setattr(B, "native_linear", lambda *a: None)
+    want = layer(X)
+    assert got.shape == want.shape and got.dtype == torch.bfloat16 and got.device == want.device
+    for y in (got, out[:70], on_side):
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.gpu
+def test_errors_and_threads():
+    layer, X = _layer(4, 4, False, 1024)
+    X = X.to(torch.bfloat16)
+    with pytest.raises(ValueError, match="contiguous"):
+        layer(torch.cat([X, X], 1)[:, ::2])
+    with pytest.raises(ValueError, match="device tensors"):
+        layer(X.cpu())
+    with pytest.raises(ValueError, match="unsupported dtype"):
+        layer(X.half())
+    with pytest.raises(q.QvggtError, match="QVGGT_ERR_ALIGN"):
+        layer(torch.cat([X, X]).flatten()[1:1 + 1024].view(1, 1024))
+    with pytest.raises(q.QvggtError, match="QVGGT_ERR_SHAPE"):
+        layer(X, torch.empty(70, 17, dtype=torch.bfloat16, device="cuda:0"))
+    assert layer(X[:0]).shape == (0, 144)
+    want = layer(X)
+    layers = [_layer(4, 4, False, 1024)[0] for _ in range(4)]         # a layer's workspace is one call's at a time
+    bad = []
+
+    def work(l):
+        for _ in range(50):
+            if not torch.equal(l(X), want):
+                bad.append(l)
+    threads = [threading.Thread(target=work, args=(l,)) for l in layers]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
