@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "libqvggt.so")
 CALL = os.path.join(HERE, "_call.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["api.hip", "rotate_quant.hip", "rotate_quant_mfma.hip", "gemm_w4a4.hip", "nfds.hip",
-           "rotate_quant_general.hip", "gemm_e2m3.hip", "ceilings.hip", "calib.hip"]
+           "rotate_quant_general.hip", "gemm_e2m3.hip", "linear_small.hip", "ceilings.hip", "calib.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -121,6 +121,9 @@ hipError_t run_rotate_quant_i8b_mfma(const void *X, int rows, int K, const int8_
 hipError_t run_i8b_gemm(const int8_t *Xb, const float *sx, const int8_t *Wb, const float *sw, const void *bias, int M, int N,
                         int K, void *Y, int32_t *acc_debug, hipStream_t stream);
 hipError_t run_codes_to_e2m3(const uint8_t *packed, int rows, int K, uint8_t *out, unsigned int *n_unrepresentable, hipStream_t stream);
+bool linear_small_pays(int M, int N, int K);
+hipError_t run_linear_small(const void *X, bool f32, int M, int N, int K, const int8_t *signs, const float *mul, const uint8_t *Wf, const float *sw,
+                            const void *bias, void *Y, hipStream_t stream);
 hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
                                 hipStream_t stream);
 hipError_t run_e2m3_gemm(const uint8_t *Xf, const float *sx, const uint8_t *Wf, const float *sw, const void *bias, int M, int N,
@@ -611,6 +614,8 @@ static int linear_e2m3(const void *gelu_table, const void *X, int x_dtype, int M
     uint8_t *Xf = static_cast<uint8_t *>(workspace);
     float *x_scale = reinterpret_cast<float *>(Xf + round_up(qvggt_e2m3_bytes(M, K), 256));
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (!direct && qvggt::linear_small_pays(M, N, K))      // one launch, nothing in the workspace
+        return hip_status(qvggt::run_linear_small(X, x_dtype == QVGGT_F32, M, N, K, signs, inv_smooth, Wf, w_scale, bias, Y, s));
     hipError_t e = gelu_table ? qvggt::run_gelu_rotate_quant_mfma(X, M, K, signs, inv_smooth, gelu_table, Xf, x_scale, true, s)
                    : direct   ? qvggt::run_rotate_quant_e2m3_mfma(X, M, K, signs, inv_smooth, Xf, x_scale, s)
                               : qvggt::run_rotate_rows_e2m3(X, x_dtype == QVGGT_F32, M, K, signs, inv_smooth, Xf, x_scale, s);

@@ -207,11 +207,4 @@ struct LdsKernels {
 };
 hipError_t prepare_device(int *device = nullptr);
 
-__device__ inline float wave_max(float v)
-{
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) v = fmaxf(v, __shfl_xor(v, m));
-    return v;
-}
-
 }  // namespace qvggt

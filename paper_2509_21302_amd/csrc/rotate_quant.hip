@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
             // dynamic: the step comes from the row's absmax; static: it is given (per token or one for the tensor)
             float inv, delta, off = 0.0f;
             if constexpr (ASYM) {
-                float hi = wave_max(amax), nlo = wave_max(nmin);
+                float hi = max_over_64_lanes(amax), nlo = max_over_64_lanes(nmin);
                 if constexpr (WPR > 1) { hi = max_over_4_waves(hi, red[0]); nlo = max_over_4_waves(nlo, red[1]); }
                 const float range = hi + nlo;
                 const bool live = range >= 15.0f * kMinStep;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
                 delta = step[(size_t)row * step_stride];
                 inv = delta >= kMinStep ? 1.0f / delta : 0.0f;
             } else {
-                amax = wave_max(amax);
+                amax = max_over_64_lanes(amax);
                 if constexpr (WPR > 1) amax = max_over_4_waves(amax, red[0]);
                 const bool live = amax >= qmax * kMinStep;
                 delta = live ? amax / qmax : 0.0f;

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                 delta = step[(size_t)row * step_stride];
                 inv = delta >= kMinStep ? 1.0f / delta : 0.0f;
             } else {
-                amax = wave_max(amax);
+                amax = max_over_64_lanes(amax);
                 if constexpr (WPR > 1) amax = max_over_4_waves(amax, red);
                 const bool live = amax >= qmax * kMinStep;
                 delta = live ? amax / qmax : 0.0f;

@@ -97,31 +97,36 @@ __device__ inline uint32_t low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_
     return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0C0C0400u), __builtin_amdgcn_perm(b, a, 0x0C0C0400u), 0x05040100u);
 }
 
-// 256 threads write the staged codes (two's complement, in [-7, 7]) of rows row0 .. row0 + group - 1 (a group of four or one), as far as they
-// exist.  Between two barriers.
+// 32 codes (bytes, two's complement, in [-7, 7], 16-byte aligned) as the 24 bytes of an E2M3 blob
+typedef unsigned int e2m3_v6u __attribute__((ext_vector_type(6)));
+__device__ inline e2m3_v6u e2m3_blob(const uint8_t *p)
+{
+    typedef float v16f __attribute__((ext_vector_type(16)));
+    const uint4 lo = *reinterpret_cast<const uint4 *>(p), hi = *reinterpret_cast<const uint4 *>(p + 16);
+    const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    v16f ev, od;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        const uint32_t v = w[d] ^ 0x80808080u;
+        ev[2 * d] = (float)(v & 0xFFu) - 128.0f;
+        od[2 * d] = (float)((v >> 8) & 0xFFu) - 128.0f;
+        ev[2 * d + 1] = (float)((v >> 16) & 0xFFu) - 128.0f;
+        od[2 * d + 1] = (float)(v >> 24) - 128.0f;
+    }
+    e2m3_v6u blob;           // early clobber: the conversion writes results while it still reads its sources (see the matrix-core kernel)
+    asm volatile("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, 1.0" : "=&v"(blob) : "v"(ev), "v"(od));
+    return blob;
+}
+
+// 256 threads write the staged codes of rows row0 .. row0 + group - 1 (a group of four or one), as far as they exist.  Between two barriers.
 template <int K>
 __device__ inline void flush_e2m3(const uint8_t *stage, int row0, int group, int rows, uint8_t *out)
 {
-    typedef float v16f __attribute__((ext_vector_type(16)));
-    typedef unsigned int v6u __attribute__((ext_vector_type(6)));
     uint8_t *block = out + (size_t)(row0 / 128) * (K / 64) * 6144 + (size_t)(row0 % 128) * 48;
     for (int t = threadIdx.x; t < K / 32 * group; t += 256) {          // 32 codes each: unit, row, half
         const int h = t & 1, r = (t >> 1) & (group - 1), unit = (t >> 1) / group;
         if (row0 + r >= rows) continue;
-        const uint8_t *p = stage + r * E2m3Stage<K>::PITCH + 64 * unit + 32 * h;
-        const uint4 lo = *reinterpret_cast<const uint4 *>(p), hi = *reinterpret_cast<const uint4 *>(p + 16);
-        const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        v16f ev, od;
-#pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            const uint32_t v = w[d] ^ 0x80808080u;
-            ev[2 * d] = (float)(v & 0xFFu) - 128.0f;
-            od[2 * d] = (float)((v >> 8) & 0xFFu) - 128.0f;
-            ev[2 * d + 1] = (float)((v >> 16) & 0xFFu) - 128.0f;
-            od[2 * d + 1] = (float)(v >> 24) - 128.0f;
-        }
-        v6u blob;           // early clobber: the conversion writes results while it still reads its sources (see the matrix-core kernel)
-        asm volatile("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, 1.0" : "=&v"(blob) : "v"(ev), "v"(od));
+        const e2m3_v6u blob = e2m3_blob(stage + r * E2m3Stage<K>::PITCH + 64 * unit + 32 * h);
         uint8_t *u = block + (size_t)unit * 6144 + r * 48;
         *reinterpret_cast<uint4 *>(u + h * 16) = make_uint4(blob[0], blob[1], blob[2], blob[3]);
         *reinterpret_cast<uint2 *>(u + 32 + h * 8) = make_uint2(blob[4], blob[5]);

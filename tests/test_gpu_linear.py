@@ -290,3 +290,26 @@ def test_convenience_object_matches_the_entry_points(bits):
     assert torch.equal(Y, by_hand)
     out = torch.empty_like(Y)
     assert layer(G.to_dev(X), out=out) is out and torch.equal(out, Y)
+
+
+# the one-launch layer (csrc/linear_small.hip): 8, 16 and 32 tokens per block, the last size with a block per compute unit and the first beyond, channels that
+# end inside a wave's 32, a block's 256 and past them
+@pytest.mark.parametrize("K,M,N", [(128, 1, 16), (128, 2048, 80), (128, 2049, 256), (128, 4097, 144), (128, 8192, 16), (128, 8193, 16), (256, 7, 272), (256, 700, 1040),
+                                   (256, 1366, 512), (256, 130, 4096), (512, 9, 48), (512, 300, 2064), (512, 512, 1024), (512, 520, 2064), (512, 1033, 528)])
+@pytest.mark.parametrize("f32,with_bias", [(True, True), (False, False)])
+def test_small_layers_in_one_launch_are_the_two_kernels_bits(K, M, N, f32, with_bias):
+    g = torch.Generator(device=G.DEV).manual_seed(K + M + N)
+    X = torch.randn(M, K, device=G.DEV, generator=g)
+    X[:, ::37] *= 30
+    X[M // 2] = 0
+    X = X if f32 else X.to(torch.bfloat16)
+    W = torch.randn(N, K, device=G.DEV, generator=g) * 0.03
+    bias = torch.randn(N, device=G.DEV, generator=g).to(torch.bfloat16) if with_bias else None
+    signs = (torch.randint(0, 2, (K,), device=G.DEV, generator=g, dtype=torch.int8) * 2 - 1).contiguous() if with_bias else None
+    layer = G.q.DsfqLinear(W, bias, signs, X[: 100].contiguous())
+    whole, want = torch.full((M + 3, N), 7.0, dtype=torch.bfloat16, device=G.DEV), torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV)
+    ws = torch.empty(max(G.q.qvggt_workspace_bytes(M, N, K), G.q.qvggt_workspace_bytes_e2m3(M, N, K)), dtype=torch.uint8, device=G.DEV)
+    for inv in (layer.inv_smooth, None):
+        G.q.qvggt_linear_e2m3_any(X, signs, inv, layer.Wf, layer.w_scale, bias, whole[:M], ws)
+        G.q.qvggt_linear(X, signs, inv, layer.Wq, layer.w_scale, bias, want, ws)
+        assert torch.equal(whole[:M].view(torch.int16), want.view(torch.int16)) and (whole[M:] == 7.0).all().item()
