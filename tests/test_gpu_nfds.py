@@ -102,6 +102,21 @@ def test_frame_correlation(samples, frames, tokens, d, dtype):
         assert np.allclose(got[i], want, rtol=RTOL, atol=2e-7), i
 
 
+@pytest.mark.parametrize("samples,frames,shares", [(1, 101, 20), (1, 102, 20), (1, 103, 20), (2, 50, 20), (1, 80, 20), (1, 79, 19), (3, 11, 3), (2, 6, 5)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_frame_correlation_of_grouped_frames(samples, frames, shares, dtype):
+    """Blocks of four frames and of two, with every remainder, at the number of blocks where the one gives way to the other, shares of odd sizes."""
+    count = shares * 1024 * (8 if dtype == torch.bfloat16 else 4) + 8 * 37
+    g = torch.Generator(device=G.DEV).manual_seed(frames)
+    X = torch.randn(samples, frames, count, generator=g, device=G.DEV)
+    X = (X + torch.rand(samples, frames, 1, generator=g, device=G.DEV) * X[:, :1]).to(dtype)
+    c = torch.empty(samples, frames - 1, dtype=torch.float32, device=G.DEV)
+    q.qvggt_nfds_frame_correlation(X, c, _ws(samples * frames, count, X))
+    norm = X.double().square().sum(2).sqrt()
+    want = torch.stack([(X[:, t].double() * X[:, 0].double()).sum(1) / (norm[:, 0] * norm[:, t]) for t in range(1, frames)], 1)
+    assert np.allclose(c.cpu().numpy(), want.cpu().numpy(), rtol=RTOL, atol=2e-7)
+
+
 def test_frame_correlation_on_synthetic_vggt_frames():
     """The recipe's fc1 input (100 frames of 1374 x 1024, special tokens salient) as one sample's feature map."""
     s = synth.layer_spec(3, "fc1")
