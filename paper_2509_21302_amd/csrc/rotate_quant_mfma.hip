@@ -167,6 +167,14 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
     // a unit's (K-tile's) four pieces start FLUSH_PITCH apart: one 16-byte bank group more than they fill, so that the lanes of a
     // write (consecutive units) and of a read spread over the banks
     constexpr int FLUSH_PITCH = (BLK8 ? 256 : 192) + 16;
+    // At K = 2048 a tile's codes leave through the wave's own staging rows, in runs of 96 bytes (int8 blocks: 128) and 3 (4) stores of consecutive lanes;
+    // every lane storing its own 16 and 8 bytes, 6 KiB from its neighbour's, took a line each (a 40000 x 2048 -> 2048 layer 153.8 / 143.2 us, 10992 x
+    // 2048 -> 2048 50.7 / 49.6, int8 blocks 70.8 / 68.0; below 1000 rows the same).  K = 1024 keeps the lanes' own stores: four rows of a unit meet in a
+    // line anyway (10992 x 1024 -> 4096 49.3 / 49.3, 9551 x 1024 -> 1024 23.0 / 23.2, 109386 x 1024 -> 1024 141.3 / 138.8).  Stores past the caches
+    // make this kernel 2 us shorter and the GEMM that reads the codes longer by more: 9493 x 1024 -> 2784 34.9 / 44.8, 5207 x 2048 -> 1040 27.8 / 29.3.
+    constexpr bool TILE_FLUSH = (CB == 6 || BLK8) && REM == 4;
+    constexpr int UNITS = K / 64, ROW_BYTES = BLK8 ? 64 : 48, OUT_PITCH = TOK * ROW_BYTES + 16;
+    static_assert(UNITS * OUT_PITCH <= rq::LDS_PER_WAVE || !TILE_FLUSH, "a tile's codes fit its staging rows");
     // LDS: the waves' staging rows, then the flush area; with the activation table, both inside the table's gap
     constexpr int STAGE0 = GELU ? rq::GELU_HALF_BYTES : 0, STAGE_ALL = rq::WAVES_PER_BLOCK * rq::LDS_PER_WAVE;
     constexpr int FLUSH0 = STAGE0 + STAGE_ALL, LDS_END = FLUSH0 + (BLOCK_FLUSH ? 64 * FLUSH_PITCH : 0);
@@ -595,9 +603,10 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                         }
                         continue;
                     }
-                    if (row < rows) {
-                        const int pb = P0 / 32 + bb;            // blob of the row: unit pb / 2, half pb % 2
-                        uint8_t *u = packed + ((size_t)(row / 128) * (K / 64) + (pb >> 1)) * 6144 + (size_t)(row % 128) * 48;
+                    const int pb = P0 / 32 + bb;                // blob of the row: unit pb / 2, half pb % 2
+                    if (TILE_FLUSH || row < rows) {
+                        uint8_t *u = TILE_FLUSH ? lds + (pb >> 1) * OUT_PITCH + tk * 48
+                                                : packed + ((size_t)(row / 128) * (K / 64) + (pb >> 1)) * 6144 + (size_t)(row % 128) * 48;
                         *reinterpret_cast<uint4 *>(u + (pb & 1) * 16) = make_uint4(blob[0], blob[1], blob[2], blob[3]);
                         *reinterpret_cast<uint2 *>(u + 32 + (pb & 1) * 8) = make_uint2(blob[4], blob[5]);
                     }
@@ -614,7 +623,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                         {
                             // whole runs of 192 bytes, written past the caches: the 422 MB of a 137400-token launch would otherwise sit
                             // there as dirty lines while the GEMM that follows runs (measured: that GEMM 365 -> 312 us, this kernel + 4 us);
-                            // the direct stores of the smaller K stay cached: their pieces are partial lines and their output fits the
+                            // the stores of the smaller K stay cached: their pieces are partial lines and their output fits the
                             // memory-side cache, where the GEMM finds it
                             const uint4 fv = *reinterpret_cast<const uint4 *>(flush_all + unit * FLUSH_PITCH + within * 16);
                             const v4u nv = {fv.x, fv.y, fv.z, fv.w};
@@ -678,12 +687,13 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                             }
                         }
                         __syncthreads();
-                    } else if (row < rows) {
-                        uint8_t *rb = packed + (size_t)(row / 128) * (K / 64) * 8192 + (size_t)(row % 128) * 64;
+                    } else if (TILE_FLUSH || row < rows) {
+                        uint8_t *rb = TILE_FLUSH ? lds + tk * 64 : packed + (size_t)(row / 128) * (K / 64) * 8192 + (size_t)(row % 128) * 64;
+                        constexpr int KT_PITCH = TILE_FLUSH ? OUT_PITCH : 8192;
 #pragma unroll
                         for (int d4 = 0; d4 < C::NL / 16; ++d4) {
                             const int P = P0 + 16 * d4;
-                            *reinterpret_cast<uint4 *>(rb + (size_t)(P / 64) * 8192 + ((((P % 64) / 16) ^ swz) * 16)) =
+                            *reinterpret_cast<uint4 *>(rb + (size_t)(P / 64) * KT_PITCH + ((((P % 64) / 16) ^ swz) * 16)) =
                                 make_uint4(words[4 * d4], words[4 * d4 + 1], words[4 * d4 + 2], words[4 * d4 + 3]);
                         }
                     }
@@ -730,6 +740,20 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                     scale[row] = delta;
                     if constexpr (ASYM) zero[row] = zp;
                 }
+            }
+        }
+        if constexpr (TILE_FLUSH) {
+            // the tile's rows are consecutive ones of a 128-row block: TOK * ROW_BYTES contiguous bytes per unit (K-tile)
+            lanes_exchange_fence();
+            const int row0 = tile * TOK;
+            uint8_t *rb = packed + (size_t)(row0 / 128) * UNITS * (128 * ROW_BYTES) + (size_t)(row0 % 128) * ROW_BYTES;
+            constexpr int CHUNKS = TOK * ROW_BYTES / 16;
+#pragma unroll
+            for (int i = 0; i < UNITS * CHUNKS / 64; ++i) {
+                const int j = i * 64 + lane, unit = j / CHUNKS, within = j % CHUNKS;       // 16-byte chunk j of the tile
+                if (row0 + within / (ROW_BYTES / 16) < rows)
+                    *reinterpret_cast<uint4 *>(rb + (size_t)unit * (128 * ROW_BYTES) + within * 16) =
+                        *reinterpret_cast<const uint4 *>(lds + unit * OUT_PITCH + within * 16);
             }
         }
     }

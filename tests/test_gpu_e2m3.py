@@ -391,3 +391,21 @@ def test_linear_e2m3_of_any_rows(K, f32, M):
     ws = torch.empty(G.q.qvggt_workspace_bytes(M, N, K), dtype=torch.uint8, device=G.DEV)
     G.q.qvggt_linear(X, None, layer.inv_smooth, layer.Wq, layer.w_scale, bias, want, ws)
     assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 9, 127, 128, 129, 385])
+def test_rows_of_2048_leave_through_lds(M):
+    """Two rows a tile: with an odd last row, and on both sides of a 128-row block, the rows' codes reach the GEMM and nothing behind them is written."""
+    K, N = 2048, 48
+    g = torch.Generator(device=G.DEV).manual_seed(M)
+    X = torch.randn(M, K, device=G.DEV, generator=g).to(torch.bfloat16)
+    layer = G.q.DsfqLinear(torch.randn(N, K, device=G.DEV, generator=g) * 0.03, None, None, X[:100].contiguous())
+    need = G.q.qvggt_workspace_bytes_e2m3(M, N, K)
+    ws = torch.full((max(need, G.q.qvggt_workspace_bytes(M, N, K)) + 4096,), 7, dtype=torch.uint8, device=G.DEV)
+    got, want = (torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV) for _ in range(2))
+    G.q.qvggt_linear_e2m3_any(X, None, layer.inv_smooth, layer.Wf, layer.w_scale, None, got, ws[:need])
+    assert (ws[need:] == 7).all().item()
+    blocks = ws[:G.q.qvggt_e2m3_bytes(M, K)].view(-1, K // 64, 128, 48)        # rows past M are not written
+    if M % 128: assert (blocks[M // 128, :, M % 128:] == 7).all().item()
+    G.q.qvggt_linear(X, None, layer.inv_smooth, layer.Wq, layer.w_scale, None, want, ws)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
