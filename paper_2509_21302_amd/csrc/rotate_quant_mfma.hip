@@ -168,8 +168,8 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
     // write (consecutive units) and of a read spread over the banks
     constexpr int FLUSH_PITCH = (BLK8 ? 256 : 192) + 16;
     // At K = 2048 a tile's codes leave through the wave's own staging rows, in runs of 96 bytes (int8 blocks: 128) and 3 (4) stores of consecutive lanes;
-    // every lane storing its own 16 and 8 bytes, 6 KiB from its neighbour's, took a line each (a 40000 x 2048 -> 2048 layer 153.8 / 143.2 us, 10992 x
-    // 2048 -> 2048 50.7 / 49.6, int8 blocks 70.8 / 68.0; below 1000 rows the same).  K = 1024 keeps the lanes' own stores: four rows of a unit meet in a
+    // every lane storing its own 16 and 8 bytes, 6 KiB from its neighbour's, took a line each (a 40000 x 2048 -> 2048 layer 157.1 / 146.2 us, 10992 x
+    // 2048 -> 2048 52.0 / 51.1, int8 blocks 72.1 / 69.8; below 1000 rows the same).  K = 1024 keeps the lanes' own stores: four rows of a unit meet in a
     // line anyway (10992 x 1024 -> 4096 49.3 / 49.3, 9551 x 1024 -> 1024 23.0 / 23.2, 109386 x 1024 -> 1024 141.3 / 138.8).  Stores past the caches
     // make this kernel 2 us shorter and the GEMM that reads the codes longer by more: 9493 x 1024 -> 2784 34.9 / 44.8, 5207 x 2048 -> 1040 27.8 / 29.3.
     constexpr bool TILE_FLUSH = (CB == 6 || BLK8) && REM == 4;
@@ -748,9 +748,13 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
             const int row0 = tile * TOK;
             uint8_t *rb = packed + (size_t)(row0 / 128) * UNITS * (128 * ROW_BYTES) + (size_t)(row0 % 128) * ROW_BYTES;
             constexpr int CHUNKS = TOK * ROW_BYTES / 16;
+            int l = lane;
+            // E2M3: the chunks' places are worked out here; kept across the loop they take registers it has not (12 to 76 bytes spilled; 5207 x 2048 ->
+            // 1040 27.5 / 27.1 us).  The int8 blocks have room for them (10992 x 2048 -> 2048 69.8 kept, 70.9 worked out here).
+            if constexpr (CB == 6) asm volatile("" : "+v"(l));
 #pragma unroll
             for (int i = 0; i < UNITS * CHUNKS / 64; ++i) {
-                const int j = i * 64 + lane, unit = j / CHUNKS, within = j % CHUNKS;       // 16-byte chunk j of the tile
+                const int j = i * 64 + l, unit = j / CHUNKS, within = j % CHUNKS;       // 16-byte chunk j of the tile
                 if (row0 + within / (ROW_BYTES / 16) < rows)
                     *reinterpret_cast<uint4 *>(rb + (size_t)unit * (128 * ROW_BYTES) + within * 16) =
                         *reinterpret_cast<const uint4 *>(lds + unit * OUT_PITCH + within * 16);
