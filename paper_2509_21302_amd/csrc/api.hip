@@ -591,6 +591,12 @@ int qvggt_e2m3_gemm_shifted(const uint8_t *Xf, const float *x_scale, const float
                                                    static_cast<hipStream_t>(stream)));
 }
 
+static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + b_bytes && q < p + a_bytes;
+}
+
 size_t qvggt_workspace_bytes_e2m3(int M, int N, int K)
 {
     if (M < 0 || !valid_n(N) || !valid_k(K)) return 0;
@@ -614,7 +620,9 @@ static int linear_e2m3(const void *gelu_table, const void *X, int x_dtype, int M
     uint8_t *Xf = static_cast<uint8_t *>(workspace);
     float *x_scale = reinterpret_cast<float *>(Xf + round_up(qvggt_e2m3_bytes(M, K), 256));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!direct && qvggt::linear_small_pays(M, N, K))      // one launch, nothing in the workspace
+    // one launch, nothing in the workspace.  Its blocks read token rows for every 256 channels that one of them writes, so a Y in X's memory (a square
+    // layer applied in place) takes the two kernels, of which the first is done with X before the second writes
+    if (!direct && qvggt::linear_small_pays(M, N, K) && !overlap(X, (size_t)M * K * (x_dtype == QVGGT_F32 ? 4 : 2), Y, (size_t)M * N * 2))
         return hip_status(qvggt::run_linear_small(X, x_dtype == QVGGT_F32, M, N, K, signs, inv_smooth, Wf, w_scale, bias, Y, s));
     hipError_t e = gelu_table ? qvggt::run_gelu_rotate_quant_mfma(X, M, K, signs, inv_smooth, gelu_table, Xf, x_scale, true, s)
                    : direct   ? qvggt::run_rotate_quant_e2m3_mfma(X, M, K, signs, inv_smooth, Xf, x_scale, s)

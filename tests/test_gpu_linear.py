@@ -313,3 +313,20 @@ def test_small_layers_in_one_launch_are_the_two_kernels_bits(K, M, N, f32, with_
         G.q.qvggt_linear_e2m3_any(X, signs, inv, layer.Wf, layer.w_scale, bias, whole[:M], ws)
         G.q.qvggt_linear(X, signs, inv, layer.Wq, layer.w_scale, bias, want, ws)
         assert torch.equal(whole[:M].view(torch.int16), want.view(torch.int16)) and (whole[M:] == 7.0).all().item()
+
+
+@pytest.mark.parametrize("K,M,f32", [(512, 40, False), (512, 1000, False), (256, 130, False), (128, 70, True), (512, 33, True)])
+def test_layers_write_into_their_input(K, M, f32):
+    """Y in X's memory, where one launch would have blocks reading token rows that others have written: the output of separate memory."""
+    N = K if not f32 else 2 * K
+    g = torch.Generator(device=G.DEV).manual_seed(K + M)
+    X = torch.randn(M, K, device=G.DEV, generator=g)
+    X = X if f32 else X.to(torch.bfloat16)
+    layer = G.q.DsfqLinear(torch.randn(N, K, device=G.DEV, generator=g) * 0.03, None, None, X[:30].contiguous())
+    want = layer(X.clone())
+    room = torch.zeros(M + 1, N, dtype=torch.bfloat16, device=G.DEV)           # the output ahead of the input by a row, as long as it, behind it by one
+    for x0, y0 in ((1, 0), (0, 0), (0, 1)):
+        x = room[x0:x0 + M].view(X.dtype).view(M, K)
+        x.copy_(X)
+        layer(x, out=room[y0:y0 + M])
+        assert torch.equal(room[y0:y0 + M].view(torch.int16), want.view(torch.int16)), (x0, y0)
