@@ -20,6 +20,7 @@ except ImportError:
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 QVGGT_BF16, QVGGT_F32 = 0, 1
+ERR_SHAPE = 2
 
 EXPORTS = [
     "qvggt_status_string", "qvggt_init", "qvggt_mfma_ceiling", "qvggt_rotated_col_absmax", "qvggt_prep_weights", "qvggt_rotate_smooth_quant",

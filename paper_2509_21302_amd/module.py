@@ -95,6 +95,8 @@ class DsfqLinear:
     def __call__(self, X: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
         """X: [M, K] bf16 or f32 on the GPU; returns bf16 [M, N] (written into `out` when given)."""
         M = X.shape[0]
+        if X.dim() == 2 and X.shape[1] != self.K:        # the entry points take K from X, and E2M3 blocks of another K would be read as this one's
+            raise q.QvggtError(q.ERR_SHAPE, "DsfqLinear")
         bf16 = X.dtype == torch.bfloat16
         if self.pre_gelu:
             if not bf16:

@@ -1,0 +1,41 @@
+"""DsfqLinear's choice of an entry point, and what it refuses before any, without a GPU."""
+import pytest
+import torch
+
+from paper_2509_21302_amd import binding as B
+from paper_2509_21302_amd.module import DsfqLinear
+
+
+@pytest.fixture
+def taken(monkeypatch):
+    """kinds of the calls that reach the library, which does not run"""
+    kinds = []
+
+    def native_linear(kind, X, *a):
+        kinds.append(kind)
+        return torch.empty(X.shape[0], 16, dtype=torch.bfloat16)
+    monkeypatch.setattr(B, "native_linear", native_linear)
+    return kinds
+
+
+def _layer(K, N=16, bits=4, pre_gelu=False, wide=None):
+    layer = DsfqLinear.__new__(DsfqLinear)
+    layer.__dict__.update(N=N, K=K, bits=bits, act_bits=bits, bias=None, signs=None, packed=bits == 4, pre_gelu=pre_gelu, gelu_table=None,
+                          w_scale=None, inv_smooth=None, Wq=torch.empty(0), _blocks=K in (1024, 2048, 4096), _ws=(-1, None))
+    blocks = torch.empty(0) if bits == 4 or K in (1024, 2048, 4096) else None
+    layer.__dict__["Wf" if bits == 4 else "Wb"] = blocks
+    return layer
+
+
+@pytest.mark.parametrize("bits,pre_gelu", [(4, False), (4, True), (8, False)])
+@pytest.mark.parametrize("K,other", [(1024, 512), (1024, 2048), (4096, 1024), (512, 1024), (768, 512)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_rows_of_another_length_are_refused(taken, bits, pre_gelu, K, other, dtype):
+    if pre_gelu and (K not in (1024, 4096) or dtype != torch.bfloat16):
+        pytest.skip("no such layer or input")
+    layer = _layer(K, bits=bits, pre_gelu=pre_gelu)
+    with pytest.raises(B.QvggtError, match="QVGGT_ERR_SHAPE"):
+        layer(torch.zeros(3, other, dtype=dtype))
+    assert not taken
+    layer(torch.zeros(3, K, dtype=dtype))
+    assert len(taken) == 1
