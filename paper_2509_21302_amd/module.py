@@ -40,7 +40,7 @@ class DsfqLinear:
         dev = weight.device
         # the codes are kept in a second form, the blocks that the fast GEMMs read: E2M3 numbers, and int8 blocks for the sizes whose kernel 1
         # writes them.  bf16 rows of those sizes with a calibration batch are made in three launches, the others one entry point at a time
-        self._blocks = blocks = self.K in (1024, 2048, 4096)
+        blocks = self.K in (1024, 2048, 4096)
         fused = (blocks and calibration is not None and weight.dtype == calibration.dtype == torch.bfloat16 and calibration.dim() == 2
                  and calibration.shape[0] > 0 and calibration.shape[1] == self.K)
         absmax = None
@@ -102,7 +102,7 @@ class DsfqLinear:
             if not bf16:
                 raise ValueError("pre_gelu needs bf16 input")
             kind, W, bits = q.GELU, self.Wf, 4
-        elif self.packed and self.Wf is not None and (M <= 4096 or bf16 and self._blocks or self.N >= 448 and self.K >= 512):
+        elif self.packed and self.Wf is not None and (M <= 4096 or bf16 and self.K in (1024, 2048, 4096) or self.N >= 448 and self.K >= 512):
             # (many rows of few channels or features are kernel 1 and the stores of Y; kernel 1 writes nibbles 10 to 15 % faster where it is not
             # the matrix-core one: 41505 x 768 -> 128 44.4 us in nibbles, 50.0 in E2M3 blocks, 50398 x 1536 -> 272 110 / 112, 57418 x 256 -> 512
             # 41.4 / 45.1, 9374 x 512 -> 2576 44.2 / 33.4, 64 x 128 -> 128 9.0 / 8.1)

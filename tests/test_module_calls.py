@@ -21,7 +21,7 @@ def taken(monkeypatch):
 def _layer(K, N=16, bits=4, pre_gelu=False, wide=None):
     layer = DsfqLinear.__new__(DsfqLinear)
     layer.__dict__.update(N=N, K=K, bits=bits, act_bits=bits, bias=None, signs=None, packed=bits == 4, pre_gelu=pre_gelu, gelu_table=None,
-                          w_scale=None, inv_smooth=None, Wq=torch.empty(0), _blocks=K in (1024, 2048, 4096), _ws=(-1, None))
+                          w_scale=None, inv_smooth=None, Wq=torch.empty(0), _ws=(-1, None))
     blocks = torch.empty(0) if bits == 4 or K in (1024, 2048, 4096) else None
     layer.__dict__["Wf" if bits == 4 else "Wb"] = blocks
     return layer
@@ -39,3 +39,14 @@ def test_rows_of_another_length_are_refused(taken, bits, pre_gelu, K, other, dty
     assert not taken
     layer(torch.zeros(3, K, dtype=dtype))
     assert len(taken) == 1
+
+
+def test_a_layer_of_an_earlier_build_is_called_as_before(taken):
+    """A layer that was copied or saved with the attributes it has always had (here without anything newer)."""
+    layer = _layer(1024)
+    assert set(layer.__dict__) == {"N", "K", "bits", "act_bits", "bias", "signs", "packed", "pre_gelu", "gelu_table", "w_scale", "inv_smooth", "Wq", "Wf", "_ws"}
+    layer(torch.zeros(5000, 1024, dtype=torch.bfloat16))
+    old = _layer(768)
+    old.Wf = None                           # sizes that had no second form of the codes
+    old(torch.zeros(5000, 768, dtype=torch.bfloat16))
+    assert taken == [B.E2M3, B.PACKED]
