@@ -50,3 +50,14 @@ def test_a_layer_of_an_earlier_build_is_called_as_before(taken):
     old.Wf = None                           # sizes that had no second form of the codes
     old(torch.zeros(5000, 768, dtype=torch.bfloat16))
     assert taken == [B.E2M3, B.PACKED]
+
+
+@pytest.mark.parametrize("rows,cols,dtype", [(2, 48, torch.bfloat16), (3, 64, torch.bfloat16), (3, 48, torch.uint8), (0, 48, torch.bfloat16)])
+def test_an_output_that_a_call_does_not_fit_is_refused(taken, rows, cols, dtype):
+    layer, X = _layer(1024, N=48), torch.zeros(3, 1024, dtype=torch.bfloat16)
+    with pytest.raises(B.QvggtError, match="QVGGT_ERR_SHAPE"):
+        layer(X, out=torch.empty(rows, cols, dtype=dtype))
+    assert not taken
+    for fits in (torch.empty(3, 48, dtype=torch.bfloat16), torch.empty(5, 16, dtype=torch.bfloat16), torch.empty(3, 48)):
+        layer(X, out=fits)
+    assert len(taken) == 3
