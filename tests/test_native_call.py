@@ -1,4 +1,6 @@
 """DsfqLinear's calls in native code (csrc/call.cpp): the outputs of the Python path, its errors, and nothing taken that the Python path would not."""
+import os
+import subprocess
 import threading
 
 import pytest
@@ -6,6 +8,7 @@ import torch
 
 import paper_2509_21302_amd as q
 from paper_2509_21302_amd import binding as B
+from paper_2509_21302_amd import build
 
 
 def test_the_module_is_built_and_knows_its_entry_points():
@@ -15,6 +18,26 @@ def test_the_module_is_built_and_knows_its_entry_points():
         B._call.bind(len(B.LINEAR_KINDS), 0)
     with pytest.raises(TypeError):
         B._call.linear(0)
+
+
+def test_the_library_is_built_where_the_module_cannot_be(monkeypatch, tmp_path, capsys):
+    """No host compiler: libqvggt.so is linked all the same, and a module of an older source does not stay behind."""
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libqvggt.so"))
+    monkeypatch.setattr(build, "CALL", str(tmp_path / "_call.so"))
+    monkeypatch.setattr(build, "BUILD", str(tmp_path))
+    monkeypatch.setattr(build, "_compile", lambda src, save_temps: src)
+    monkeypatch.setenv("CXX", str(tmp_path / "no-compiler"))
+    (tmp_path / "_call.so").write_text("old")
+    run = subprocess.run
+
+    def link(cmd, **kw):
+        if cmd[0] != build.HIPCC:
+            return run(cmd, **kw)
+        (tmp_path / "libqvggt.so.tmp").write_text("linked")
+    monkeypatch.setattr(build.subprocess, "run", link)
+    build.build()
+    assert (tmp_path / "libqvggt.so").read_text() == "linked" and not os.path.exists(tmp_path / "_call.so")
+    assert "_call.so was not built" in capsys.readouterr().err
 
 
 @pytest.mark.parametrize("X", [torch.zeros(2, 128), torch.zeros(2, 128, dtype=torch.float16), torch.zeros(128), torch.zeros(2, 256)[:, ::2], None, 3])
