@@ -13,8 +13,12 @@ from typing import Optional
 
 import torch
 
+# DsfqLinear's calls in native code.  Without it they go through this module: where it is not built, or was built for another torch, whose objects
+# may be laid out differently even where all its symbols are found
 try:
-    from . import _call          # DsfqLinear's calls in native code; without it (another torch than it was built for) they go through this module
+    from . import _call
+    if getattr(_call, "torch_version", None) != torch.__version__:
+        _call = None
 except ImportError:
     _call = None
 

@@ -8,13 +8,14 @@ written next to this file so that they travel with the source tree.
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqvggt.so")
-CALL = os.path.join(HERE, "_call.so")
+CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))       # another Python does not find it
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["api.hip", "rotate_quant.hip", "rotate_quant_mfma.hip", "gemm_w4a4.hip", "nfds.hip",
            "rotate_quant_general.hip", "gemm_e2m3.hip", "linear_small.hip", "ceilings.hip", "calib.hip"]
@@ -46,13 +47,13 @@ def _compile(src: str, save_temps: bool) -> str:
 
 
 def _compile_call() -> None:
-    """csrc/call.cpp against torch's headers (host code)."""
-    import sysconfig
-
+    """csrc/call.cpp against torch's headers (host code).  It reads torch's objects through inlined accessors, so it is for this torch only and
+    says which that is."""
     import torch
     top = os.path.dirname(torch.__file__)
     tmp = CALL + ".tmp"
     cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           f'-DQVGGT_TORCH_VERSION="{torch.__version__}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", os.path.join(top, "include"), "-isystem", "/opt/rocm/include",
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "call.cpp"), "-o", tmp, "-L" + os.path.join(top, "lib"),
            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]

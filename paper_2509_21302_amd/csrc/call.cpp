@@ -121,4 +121,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, methods, null
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__call() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__call()
+{
+    PyObject *const m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", QVGGT_TORCH_VERSION) != 0) {       // binding.py compares it
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,6 +1,11 @@
 """DsfqLinear's calls in native code (csrc/call.cpp): the outputs of the Python path, its errors, and nothing taken that the Python path would not."""
+import importlib
+import importlib.machinery
+import importlib.util
 import os
+import shutil
 import subprocess
+import sys
 import threading
 
 import pytest
@@ -38,6 +43,19 @@ def test_the_library_is_built_where_the_module_cannot_be(monkeypatch, tmp_path, 
     build.build()
     assert (tmp_path / "libqvggt.so").read_text() == "linked" and not os.path.exists(tmp_path / "_call.so")
     assert "_call.so was not built" in capsys.readouterr().err
+
+
+@pytest.mark.parametrize("built_for,used", [(torch.__version__, True), ("1.0.0", False), (None, False)])
+def test_a_module_of_another_torch_is_not_used(monkeypatch, tmp_path, built_for, used):
+    shutil.copy(B.__file__, tmp_path / "binding.py")
+    (tmp_path / "__init__.py").write_text("")
+    (tmp_path / "_call.py").write_text("" if built_for is None else f"torch_version = {built_for!r}")
+    name = f"another_build_{used}_{built_for is None}"
+    spec = importlib.util.spec_from_file_location(name, tmp_path / "__init__.py", submodule_search_locations=[str(tmp_path)])
+    monkeypatch.setitem(sys.modules, name, importlib.util.module_from_spec(spec))
+    binding = importlib.import_module(name + ".binding")
+    assert (binding._call is not None) == used
+    assert build.CALL.endswith(importlib.machinery.EXTENSION_SUFFIXES[0]) and B._call.__file__ == build.CALL
 
 
 @pytest.mark.parametrize("X", [torch.zeros(2, 128), torch.zeros(2, 128, dtype=torch.float16), torch.zeros(128), torch.zeros(2, 256)[:, ::2], None, 3])
