@@ -1,11 +1,14 @@
 // What DsfqLinear does on the host between two launches, in native code: the checks of a call's tensors, the output's allocation, the current
 // stream, the call of the C entry point with the interpreter's lock released.  The same as the Python functions of binding.py do one by one
-// (64 x 128 -> 128 in f32: 11.5 us a call with them, 8.9 this way, of which 7.2 are the two launches).
+// (a call of two launches, 64 x 128 -> 128 in f32 when it was one: 11.5 us with them, 8.9 this way, of which 7.2 are the launches).
 //
 // linear(kind, X, signs, inv_smooth, gelu_table, W, w_scale, bias, out, workspace, N, bits)
 //   -> the output, or the entry point's status where it is not 0, or NotImplemented, before anything is launched, where a call is not an ordinary
-//      one (a tensor subclass or wrapper, another device, type, shape or layout): the caller's Python path takes it then, with its errors.
+//      one: an argument that is no plain contiguous GPU tensor (a subclass, a wrapper, a view that is not contiguous), an X that is not
+//      two-dimensional bf16 or f32, an output that cannot be allocated.  The caller's Python path takes it then, with its errors.  As there, types
+//      of the other operands and which GPU holds what are the caller's to get right.
 // bind(kind, address): the C entry point of a kind.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
@@ -49,6 +52,7 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t n)
         PyErr_SetString(PyExc_TypeError, "linear takes 12 arguments");
         return nullptr;
     }
+    bool launched = false;
     try {
         const long kind = PyLong_AsLong(args[0]), N_layer = PyLong_AsLong(args[10]), bits = PyLong_AsLong(args[11]);
         if (PyErr_Occurred()) return nullptr;
@@ -78,6 +82,7 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t n)
         const int dtype = type == at::kFloat;                       // QVGGT_BF16 = 0, QVGGT_F32 = 1
         void *stream = reinterpret_cast<void *>(c10::hip::getCurrentHIPStream(c10::hip::current_device()).stream());
         int status;
+        launched = true;
         Py_BEGIN_ALLOW_THREADS
         switch (kind) {
             case kGelu: status = reinterpret_cast<GeluFn>(entry[kind])(x, dtype, M, N, K, signs, inv, table, W, w_scale, bias, y, w, w_bytes, stream); break;
@@ -90,8 +95,11 @@ PyObject *linear(PyObject *, PyObject *const *args, Py_ssize_t n)
         if (args[8] == Py_None) return THPVariable_Wrap(std::move(made));
         Py_INCREF(args[8]);
         return args[8];
-    } catch (const std::exception &e) {                             // torch's own errors, the allocator's among them
-        if (dynamic_cast<const c10::OutOfMemoryError *>(&e) != nullptr) Py_RETURN_NOTIMPLEMENTED;      // torch.empty raises it as Python knows it
+    } catch (python_error &e) {                                     // raised in Python: a dispatch mode that sees the allocation
+        e.restore();
+        return nullptr;
+    } catch (const std::exception &e) {
+        if (!launched) Py_RETURN_NOTIMPLEMENTED;                    // torch's own errors, the allocator's among them: torch.empty raises them as Python knows them
         PyErr_SetString(PyExc_RuntimeError, e.what());
         return nullptr;
     }

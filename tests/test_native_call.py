@@ -130,3 +130,28 @@ def test_errors_and_threads():
     for t in threads:
         t.join()
     assert not bad
+
+
+@pytest.mark.gpu
+def test_an_error_of_the_allocation_is_raised_as_it_is():
+    """What a dispatch mode raises where it sees the output's allocation, and the allocator's own error, keep their types."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Refused(Exception):
+        pass
+
+    class NoAllocation(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            if "empty" in func.__name__:
+                raise Refused(func.__name__)
+            return func(*args, **(kwargs or {}))
+    layer, X = _layer(4, 4, False, 1024)
+    X = X.to(torch.bfloat16)
+    want = layer(X)
+    with NoAllocation(), pytest.raises(Refused):
+        layer(X)
+    layer.N = 1 << 42
+    with pytest.raises(torch.OutOfMemoryError):
+        layer(X)
+    layer.N = 144
+    assert torch.equal(layer(X), want)
