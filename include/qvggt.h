@@ -104,7 +104,15 @@ int qvggt_prep_weights(const void *W, int w_dtype, int N, int K, const float *ac
                        float *inv_smooth, void *stream);
 
 /*
- * The same for a layer whose codes are kept in both forms, in two calls and three launches (bf16 W [N, K] and X_cal [M, K], M >= 1, K = 1024,
+ * qvggt_prep_weights that leaves Wq's codes as E2M3 blocks as well, in the same number of launches (K other than 1024, 2048 and 4096, which are
+ * QVGGT_ERR_SHAPE).  Wf: qvggt_e2m3_bytes(N, K) bytes, padding rows not written: what qvggt_codes_to_e2m3 makes of Wq.  There is nothing to count: at
+ * these sizes no weights, numbers or not, have a code -8 (a row whose largest value is infinite, or that has no number in it, has codes 0).
+ */
+int qvggt_prep_weights_e2m3(const void *W, int w_dtype, int N, int K, const float *act_absmax_rot, const int8_t *signs, float alpha,
+                            uint8_t *Wq, uint8_t *Wf, float *w_scale, float *inv_smooth, void *stream);
+
+/*
+ * qvggt_prep_weights for a layer whose codes are kept in both forms, in two calls and three launches (bf16 W [N, K] and X_cal [M, K], M >= 1, K = 1024,
  * 2048 or 4096; QVGGT_ERR_SHAPE otherwise): qvggt_rotated_col_absmax of X_cal and of W, then qvggt_prep_weights (int8_codes = 0, bits = 4) or
  * qvggt_prep_weights_i8 (int8_codes = 1, bits 4..8) into Wq, w_scale and inv_smooth, and Wq's codes as E2M3 blocks resp. int8 blocks into
  * Wblocks (qvggt_e2m3_bytes / qvggt_i8b_bytes of N rows; its padding rows are not written).  n_unrepresentable: as in qvggt_codes_to_e2m3, but set

@@ -27,7 +27,7 @@ QVGGT_BF16, QVGGT_F32 = 0, 1
 ERR_SHAPE = 2
 
 EXPORTS = [
-    "qvggt_status_string", "qvggt_init", "qvggt_mfma_ceiling", "qvggt_rotated_col_absmax", "qvggt_prep_weights", "qvggt_rotate_smooth_quant",
+    "qvggt_status_string", "qvggt_init", "qvggt_mfma_ceiling", "qvggt_rotated_col_absmax", "qvggt_prep_weights", "qvggt_prep_weights_e2m3", "qvggt_rotate_smooth_quant",
     "qvggt_rotate_smooth_quant_static", "qvggt_layernorm_rotate_smooth_quant",
     "qvggt_rotate_smooth_quant_asym", "qvggt_weight_code_sums", "qvggt_w4a4_gemm_asym",
     "qvggt_e2m3_bytes", "qvggt_codes_to_e2m3", "qvggt_e2m3_gemm",
@@ -149,6 +149,8 @@ def load_library() -> C.CDLL:
     lib.qvggt_w4a4_gemm.argtypes = [vp, vp, vp, vp, vp, i, i, i, vp, vp, vp]
     lib.qvggt_linear.restype = i
     lib.qvggt_linear.argtypes = [vp, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+    lib.qvggt_prep_weights_e2m3.restype = i
+    lib.qvggt_prep_weights_e2m3.argtypes = [vp, i, i, i, vp, vp, f, vp, vp, vp, vp, vp]
     lib.qvggt_prep_weights_given.restype = i
     lib.qvggt_prep_weights_given.argtypes = [vp, i, i, i, vp, vp, vp, i, vp, vp, vp, vp]
     lib.qvggt_layer_workspace_bytes.restype = sz
@@ -496,6 +498,12 @@ def qvggt_prep_weights_given(W, c_hat, signs, w_step, bits, Wq, w_scale, inv_smo
     _check(load_library().qvggt_prep_weights_given(_ptr(W), _dtype_code(W), N, K, _ptr(c_hat), _ptr(signs), _ptr(w_step), int(bits),
                                                    _ptr(Wq), _ptr(w_scale), _ptr(inv_smooth), _stream(stream)),
            "qvggt_prep_weights_given")
+
+
+def qvggt_prep_weights_e2m3(W, act_absmax_rot, signs, alpha, Wq, Wf, w_scale, inv_smooth, stream=None):
+    N, K = W.shape
+    _check(load_library().qvggt_prep_weights_e2m3(_ptr(W), _dtype_code(W), N, K, _ptr(act_absmax_rot), _ptr(signs), float(alpha), _ptr(Wq), _ptr(Wf),
+                                                  _ptr(w_scale), _ptr(inv_smooth), _stream(stream)), "qvggt_prep_weights_e2m3")
 
 
 def qvggt_layer_workspace_bytes(M: int, N: int, K: int) -> int:

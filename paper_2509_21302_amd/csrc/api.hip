@@ -124,8 +124,8 @@ hipError_t run_codes_to_e2m3(const uint8_t *packed, int rows, int K, uint8_t *ou
 bool linear_small_pays(int M, int N, int K);
 hipError_t run_linear_small(const void *X, bool f32, int M, int N, int K, const int8_t *signs, const float *mul, const uint8_t *Wf, const float *sw,
                             const void *bias, void *Y, hipStream_t stream);
-hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
-                                hipStream_t stream);
+hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
+                                float *scale, uint8_t *rows_out, hipStream_t stream);
 hipError_t run_e2m3_gemm(const uint8_t *Xf, const float *sx, const uint8_t *Wf, const float *sw, const void *bias, int M, int N,
                          int K, void *Y, int32_t *acc_debug, hipStream_t stream);
 hipError_t run_layout_int8(const int8_t *src, int rows, int K, int8_t *dst, int to_library, hipStream_t stream);
@@ -155,9 +155,10 @@ int hip_status(hipError_t e) { return e == hipSuccess ? QVGGT_OK : QVGGT_ERR_HIP
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 bool valid_wide_bits(int bits) { return bits >= 4 && bits <= 8; }
 
-// offline half for either storage: bits == 4 writes packed nibbles, kInt8Container + b int8 codes of width b
+// offline half for either storage: bits == 4 writes packed nibbles, kInt8Container + b int8 codes of width b; Wf: the nibbles' codes as E2M3 blocks
+// too, or nullptr
 int prep_weights(const void *W, int w_dtype, int N, int K, const float *act_absmax_rot, const int8_t *signs, float alpha,
-                 int bits, void *Wq, float *w_scale, float *inv_smooth, void *stream)
+                 int bits, void *Wq, float *w_scale, float *inv_smooth, void *stream, uint8_t *Wf = nullptr)
 {
     if (!valid_dtype(w_dtype)) return QVGGT_ERR_DTYPE;
     if (!valid_n(N) || !valid_k(K)) return QVGGT_ERR_SHAPE;
@@ -179,6 +180,8 @@ int prep_weights(const void *W, int w_dtype, int N, int K, const float *act_absm
     }
     if (e != hipSuccess) return QVGGT_ERR_HIP;
     // rows of W go through the same rotate / scale / quantize kernel, with c_j / sqrt(K) as the multiplier
+    if (Wf != nullptr)
+        return hip_status(qvggt::run_rotate_rows_e2m3(W, f32, N, K, signs, inv_smooth, 1, Wf, w_scale, static_cast<uint8_t *>(Wq), s));
     return hip_status(qvggt::run_rotate_smooth_quant(W, f32, N, K, signs, inv_smooth, 1, static_cast<uint8_t *>(Wq), w_scale,
                                                      nullptr, 0, bits, s));
 }
@@ -227,6 +230,16 @@ int qvggt_prep_weights(const void *W, int w_dtype, int N, int K, const float *ac
                        float alpha, uint8_t *Wq, float *w_scale, float *inv_smooth, void *stream)
 {
     return prep_weights(W, w_dtype, N, K, act_absmax_rot, signs, alpha, 4, Wq, w_scale, inv_smooth, stream);
+}
+
+int qvggt_prep_weights_e2m3(const void *W, int w_dtype, int N, int K, const float *act_absmax_rot, const int8_t *signs, float alpha, uint8_t *Wq,
+                            uint8_t *Wf, float *w_scale, float *inv_smooth, void *stream)
+{
+    if (!valid_dtype(w_dtype)) return QVGGT_ERR_DTYPE;
+    if (!valid_n(N) || !valid_k(K) || K == 1024 || K == 2048 || K == 4096) return QVGGT_ERR_SHAPE;
+    if (!Wf) return QVGGT_ERR_NULL;
+    if (!aligned16(Wf)) return QVGGT_ERR_ALIGN;
+    return prep_weights(W, w_dtype, N, K, act_absmax_rot, signs, alpha, 4, Wq, w_scale, inv_smooth, stream, Wf);
 }
 
 int qvggt_prep_weights_given(const void *W, int w_dtype, int N, int K, const float *c_hat, const int8_t *signs, const float *w_step,
@@ -626,7 +639,7 @@ static int linear_e2m3(const void *gelu_table, const void *X, int x_dtype, int M
         return hip_status(qvggt::run_linear_small(X, x_dtype == QVGGT_F32, M, N, K, signs, inv_smooth, Wf, w_scale, bias, Y, s));
     hipError_t e = gelu_table ? qvggt::run_gelu_rotate_quant_mfma(X, M, K, signs, inv_smooth, gelu_table, Xf, x_scale, true, s)
                    : direct   ? qvggt::run_rotate_quant_e2m3_mfma(X, M, K, signs, inv_smooth, Xf, x_scale, s)
-                              : qvggt::run_rotate_rows_e2m3(X, x_dtype == QVGGT_F32, M, K, signs, inv_smooth, Xf, x_scale, s);
+                              : qvggt::run_rotate_rows_e2m3(X, x_dtype == QVGGT_F32, M, K, signs, inv_smooth, 0, Xf, x_scale, nullptr, s);
     if (e != hipSuccess) return QVGGT_ERR_HIP;
     return hip_status(qvggt::run_e2m3_gemm(Xf, x_scale, Wf, w_scale, bias, M, N, K, Y, nullptr, s));
 }

@@ -21,7 +21,8 @@ enum RowMode { kQuantize = 0, kColAbsMax = 1 };
 // CB: bits a stored code occupies (4: two per byte; 8: one int8 each; 6: 4-bit codes as E2M3 blocks, dynamic steps).  qmax: largest code, 2^(bits-1) - 1.
 // LN: a LayerNorm of the row precedes everything else (quantize mode, K <= 4096: beyond that the row no longer fits the registers)
 // ASYM: affine 4-bit codes over the row's range [min(0, min z), max(0, max z)], zero point to zero[row], nibbles hold u - 8
-template <int K, bool F32, int MODE, int CB, bool LN = false, bool ASYM = false>
+// BOTH (CB = 6): the codes also go out as rows of packed nibbles, to rows_out (the two forms a layer keeps)
+template <int K, bool F32, int MODE, int CB, bool LN = false, bool ASYM = false, bool BOTH = false>
 __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict__ X, int rows,
                                                           const int8_t *__restrict__ signs,
                                                           const float *__restrict__ mul, int mul_mode,
@@ -29,7 +30,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
                                                           float *__restrict__ scale,
                                                           unsigned int *__restrict__ col_absmax_bits,
                                                           const float *__restrict__ step, int step_stride, float qmax,
-                                                          LnParams ln, float *__restrict__ zero = nullptr)
+                                                          LnParams ln, float *__restrict__ zero = nullptr, uint8_t *__restrict__ rows_out = nullptr)
 {
     // waves per row: one, or the four of a block where a row would take 128 registers of a lane (two copies of it with the multipliers:
     // one wave per SIMD).  A wave then has K / 4 consecutive elements, and two butterflies go over the wave number.
@@ -39,6 +40,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
     constexpr bool kPermuted = (K == 1024 || K == 2048 || K == 4096) && MODE == kQuantize;
     constexpr bool E2M3 = (CB == 6);
     static_assert(!E2M3 || (MODE == kQuantize && !LN && !ASYM), "E2M3 blocks: dynamic 4-bit codes");
+    static_assert(!BOTH || E2M3, "two forms of a layer's weight codes");
     __shared__ __attribute__((aligned(16))) uint8_t lds_stage[E2M3 ? E2m3Stage<K>::BYTES : kPermuted ? 4 * K : 16];
     const int lane = threadIdx.x & 63;
     const int sub = WPR > 1 ? (int)(threadIdx.x >> 6) : 0, first = sub * KW;       // this wave's part of a row
@@ -192,7 +194,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const void *__restrict
                 }
                 if (WPR == 1 || (row & last) == last) {       // the same for the whole block
                     __syncthreads();
-                    flush_e2m3<K>(lds_stage, row & ~last, group, rows, packed);
+                    flush_e2m3<K, BOTH>(lds_stage, row & ~last, group, rows, packed, rows_out);
                     __syncthreads();
                 }
                 continue;
@@ -346,13 +348,15 @@ hipError_t run_rotate_rows_general(const void *X, bool f32, int rows, int K, con
                                    uint8_t *packed, float *scale, unsigned int *colmax, const float *step, int step_stride,
                                    int bits, hipStream_t stream);
 
-hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out,
-                                        float *scale, hipStream_t stream);
+hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
+                                        float *scale, uint8_t *rows_out, hipStream_t stream);
 
+// rows_out (CB = 6): the packed rows, or nullptr
 template <int MODE, int CB>
 static hipError_t launch_rotate_rows(const void *X, bool f32, int rows, int K, const int8_t *signs,
                                      const float *mul, int mul_mode, uint8_t *packed, float *scale,
-                                     unsigned int *colmax, const float *step, int step_stride, float qmax, hipStream_t stream)
+                                     unsigned int *colmax, const float *step, int step_stride, float qmax, hipStream_t stream,
+                                     uint8_t *rows_out = nullptr)
 {
     if (rows <= 0) return hipSuccess;
     const int waves_per_block = 4;
@@ -370,6 +374,23 @@ static hipError_t launch_rotate_rows(const void *X, bool f32, int rows, int K, c
         if (f32) rotate_rows_kernel<KK, true, MODE, CB><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, qmax, LnParams{nullptr, nullptr, 0.0f, 0}); \
         else rotate_rows_kernel<KK, false, MODE, CB><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, qmax, LnParams{nullptr, nullptr, 0.0f, 0});    \
         break;
+    if constexpr (CB == 6) {
+        if (rows_out != nullptr) {
+#define QVGGT_LAUNCH_BOTH(KK)                                                                                \
+    case KK:                                                                                                 \
+        if (f32) rotate_rows_kernel<KK, true, MODE, CB, false, false, true><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, qmax, LnParams{nullptr, nullptr, 0.0f, 0}, nullptr, rows_out); \
+        else rotate_rows_kernel<KK, false, MODE, CB, false, false, true><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, qmax, LnParams{nullptr, nullptr, 0.0f, 0}, nullptr, rows_out);    \
+        return hipGetLastError();
+            switch (K) {
+                QVGGT_LAUNCH_BOTH(128)
+                QVGGT_LAUNCH_BOTH(256)
+                QVGGT_LAUNCH_BOTH(512)
+                QVGGT_LAUNCH_BOTH(8192)
+                default: return hipErrorInvalidValue;
+            }
+#undef QVGGT_LAUNCH_BOTH
+        }
+    }
     switch (K) {
         QVGGT_LAUNCH(128)
         QVGGT_LAUNCH(256)
@@ -406,12 +427,13 @@ hipError_t run_rotate_smooth_quant(const void *X, bool f32, int rows, int K, con
     return launch_rotate_rows<kQuantize, 8>(X, f32, rows, K, signs, mul, mul_mode, packed, scale, nullptr, step, step_stride, qmax, stream);
 }
 
-// rotation + smoothing + per-token 4-bit codes as E2M3 blocks for the rows that the matrix-core kernel does not take: f32, or other sizes
-hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
-                                hipStream_t stream)
+// rotation + smoothing + per-row 4-bit codes as E2M3 blocks for the rows that the matrix-core kernel does not take: f32, or other sizes.
+// rows_out: the same codes as packed rows, or nullptr (K other than 1024, 2048 and 4096)
+hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
+                                float *scale, uint8_t *rows_out, hipStream_t stream)
 {
-    if (general_size_supported(K)) return run_rotate_rows_general_e2m3(X, f32, rows, K, signs, mul, out, scale, stream);
-    return launch_rotate_rows<kQuantize, 6>(X, f32, rows, K, signs, mul, 0, out, scale, nullptr, nullptr, 0, 7.0f, stream);
+    if (general_size_supported(K)) return run_rotate_rows_general_e2m3(X, f32, rows, K, signs, mul, mul_mode, out, scale, rows_out, stream);
+    return launch_rotate_rows<kQuantize, 6>(X, f32, rows, K, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f, stream, rows_out);
 }
 
 hipError_t run_ln_rotate_quant_mfma(const void *X, int rows, const int8_t *signs, const float *mul, uint8_t *packed, float *scale,

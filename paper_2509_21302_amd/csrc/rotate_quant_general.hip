@@ -85,13 +85,15 @@ constexpr int waves_per_row(int n2, int mm) { return n2 / 64 * mm >= 80 ? 4 : 1;
 
 // mul_mode 0: mul[j] used as given (inv_smooth, or 1/sqrt(K) when mul == nullptr); 1: 1 / (K * mul[j]) (weights)
 // CB: bits a stored code occupies (4 or 8; 6: 4-bit codes as E2M3 blocks, dynamic steps); qmax: largest code; step: static quantization step or nullptr
-template <int N2, int MM, bool F32, int MODE, int CB>
+// BOTH (CB = 6): the codes also go out as rows of packed nibbles, to rows_out
+template <int N2, int MM, bool F32, int MODE, int CB, bool BOTH = false>
 __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__restrict__ X, int rows,
                                                                   const int8_t *__restrict__ signs,
                                                                   const float *__restrict__ mul, int mul_mode,
                                                                   uint8_t *__restrict__ packed, float *__restrict__ scale,
                                                                   unsigned int *__restrict__ col_absmax_bits,
-                                                                  const float *__restrict__ step, int step_stride, float qmax)
+                                                                  const float *__restrict__ step, int step_stride, float qmax,
+                                                                  uint8_t *__restrict__ rows_out = nullptr)
 {
     // waves per row: one, or the four of a block where a row would take 80 registers of a lane or more (see gen::waves_per_row).  A wave then
     // has N2 / 4 consecutive values of a, and two butterflies go over the wave number.
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(256) void rotate_rows_general_kernel(const void *__
                         *reinterpret_cast<uint32_t *>(stage + (lane + 64 * c) * MM + g) = low_bytes(code_of(c * MM + g), code_of(c * MM + g + 1), code_of(c * MM + g + 2), code_of(c * MM + g + 3));
                 if (WPR == 1 || (row & last) == last) {       // the same for the whole block
                     __syncthreads();
-                    flush_e2m3<K>(lds_stage, row & ~last, group, rows, packed);
+                    flush_e2m3<K, BOTH>(lds_stage, row & ~last, group, rows, packed, rows_out);
                     __syncthreads();
                 }
                 continue;
@@ -332,17 +334,19 @@ hipError_t run_rotate_rows_general(const void *X, bool f32, int rows, int K, con
 #undef QVGGT_CASE
 }
 
-// the same rows as E2M3 blocks (dynamic 4-bit codes)
-hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out,
-                                        float *scale, hipStream_t stream)
+// the same rows as E2M3 blocks (dynamic 4-bit codes); rows_out: as packed rows too, or nullptr
+hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
+                                        float *scale, uint8_t *rows_out, hipStream_t stream)
 {
     if (rows <= 0) return hipSuccess;
     const int group = (K == 5120 || K == 6144) && rows <= kFewSharedRows ? 1 : kE2m3Group;
     const int blocks = std::min((rows + group - 1) / group, 256 * 8);
 #define QVGGT_CASE(KK, N2, MM)                                                                                                           \
     case KK:                                                                                                                             \
-        if (f32) rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, 0, out, scale, nullptr, nullptr, 0, 7.0f); \
-        else rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, 0, out, scale, nullptr, nullptr, 0, 7.0f);    \
+        if (rows_out != nullptr && f32) rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6, true><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f, rows_out); \
+        else if (rows_out != nullptr) rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6, true><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f, rows_out);   \
+        else if (f32) rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f); \
+        else rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f);    \
         return hipGetLastError();
     switch (K) {
         QVGGT_CASE(768, 64, 12)

@@ -118,15 +118,29 @@ __device__ inline e2m3_v6u e2m3_blob(const uint8_t *p)
     return blob;
 }
 
-// 256 threads write the staged codes of rows row0 .. row0 + group - 1 (a group of four or one), as far as they exist.  Between two barriers.
-template <int K>
-__device__ inline void flush_e2m3(const uint8_t *stage, int row0, int group, int rows, uint8_t *out)
+// 32 codes (bytes, two's complement) as the 16 bytes of packed nibbles
+__device__ inline uint4 packed_codes(const uint8_t *p)
+{
+    const uint4 lo = *reinterpret_cast<const uint4 *>(p), hi = *reinterpret_cast<const uint4 *>(p + 16);
+    auto nibbles = [](uint32_t a, uint32_t b) {
+        const uint32_t x = (a & 0x0F0F0F0Fu) | (a & 0x0F0F0F0Fu) >> 4, y = (b & 0x0F0F0F0Fu) | (b & 0x0F0F0F0Fu) >> 4;      // pairs in bytes 0 and 2
+        return __builtin_amdgcn_perm(y, x, 0x06040200u);
+    };
+    return make_uint4(nibbles(lo.x, lo.y), nibbles(lo.z, lo.w), nibbles(hi.x, hi.y), nibbles(hi.z, hi.w));
+}
+
+// 256 threads write the staged codes of rows row0 .. row0 + group - 1 (a group of four or one), as far as they exist; BOTH: to packed rows as well.
+// Between two barriers.
+template <int K, bool BOTH>
+__device__ inline void flush_e2m3(const uint8_t *stage, int row0, int group, int rows, uint8_t *out, uint8_t *rows_out)
 {
     uint8_t *block = out + (size_t)(row0 / 128) * (K / 64) * 6144 + (size_t)(row0 % 128) * 48;
     for (int t = threadIdx.x; t < K / 32 * group; t += 256) {          // 32 codes each: unit, row, half
         const int h = t & 1, r = (t >> 1) & (group - 1), unit = (t >> 1) / group;
         if (row0 + r >= rows) continue;
-        const e2m3_v6u blob = e2m3_blob(stage + r * E2m3Stage<K>::PITCH + 64 * unit + 32 * h);
+        const uint8_t *codes = stage + r * E2m3Stage<K>::PITCH + 64 * unit + 32 * h;
+        if constexpr (BOTH) *reinterpret_cast<uint4 *>(rows_out + (size_t)(row0 + r) * (K / 2) + 32 * unit + 16 * h) = packed_codes(codes);
+        const e2m3_v6u blob = e2m3_blob(codes);
         uint8_t *u = block + (size_t)unit * 6144 + r * 48;
         *reinterpret_cast<uint4 *>(u + h * 16) = make_uint4(blob[0], blob[1], blob[2], blob[3]);
         *reinterpret_cast<uint2 *>(u + 32 + h * 8) = make_uint2(blob[4], blob[5]);

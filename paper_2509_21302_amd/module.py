@@ -56,17 +56,18 @@ class DsfqLinear:
         if self.packed:
             self.Wq = torch.empty(self.N, self.K // 2, dtype=torch.uint8, device=dev)
             self.Wf = torch.empty(q.qvggt_e2m3_bytes(self.N, self.K), dtype=torch.uint8, device=dev)
-            lost = torch.empty(1, dtype=torch.int32, device=dev) if fused else torch.zeros(1, dtype=torch.int32, device=dev)
-            if fused:
-                q.qvggt_layer_codes(weight, rows, signs, alpha, bits, False, self.Wq, self.Wf, self.w_scale, self.inv_smooth, lost, scratch)
+            if not blocks:                   # nothing to count there, and nothing to wait for
+                q.qvggt_prep_weights_e2m3(weight, absmax, signs, alpha, self.Wq, self.Wf, self.w_scale, self.inv_smooth)
             else:
-                q.qvggt_prep_weights(weight, absmax, signs, alpha, self.Wq, self.w_scale, self.inv_smooth)
-                q.qvggt_codes_to_e2m3(self.Wq, self.N, self.K, self.Wf, lost)
-            n = int(lost.item())
-            if n != 0:                       # cannot happen with absmax steps of numbers (codes lie in [-7, 7])
-                if blocks:
+                lost = torch.empty(1, dtype=torch.int32, device=dev) if fused else torch.zeros(1, dtype=torch.int32, device=dev)
+                if fused:
+                    q.qvggt_layer_codes(weight, rows, signs, alpha, bits, False, self.Wq, self.Wf, self.w_scale, self.inv_smooth, lost, scratch)
+                else:
+                    q.qvggt_prep_weights(weight, absmax, signs, alpha, self.Wq, self.w_scale, self.inv_smooth)
+                    q.qvggt_codes_to_e2m3(self.Wq, self.N, self.K, self.Wf, lost)
+                n = int(lost.item())
+                if n != 0:                   # cannot happen with absmax steps of numbers (codes lie in [-7, 7])
                     raise RuntimeError(f"{n} weight codes -8 have no E2M3 value")
-                self.Wf = None               # the other sizes have always taken such weights: their nibbles are multiplied as they are
         else:
             self.Wq = torch.empty(self.N, self.K, dtype=torch.int8, device=dev)
             self.Wb = torch.empty(q.qvggt_i8b_bytes(self.N, self.K), dtype=torch.int8, device=dev) if blocks else None

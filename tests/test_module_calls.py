@@ -61,3 +61,18 @@ def test_an_output_that_a_call_does_not_fit_is_refused(taken, rows, cols, dtype)
     for fits in (torch.empty(3, 48, dtype=torch.bfloat16), torch.empty(5, 16, dtype=torch.bfloat16), torch.empty(3, 48)):
         layer(X, out=fits)
     assert len(taken) == 3
+
+
+@pytest.mark.parametrize("K", [128, 768, 5120, 8192])
+@pytest.mark.parametrize("calibrated", [True, False])
+def test_a_layer_of_other_sizes_is_made_without_waiting(monkeypatch, K, calibrated):
+    """Sizes that have no fused making: one call writes both forms of the codes, and nothing is read back from the device."""
+    calls = []
+    for name in B.EXPORTS:
+        if hasattr(B, name) and "bytes" not in name:
+            monkeypatch.setattr(B, name, lambda *a, name=name: calls.append(name))
+    monkeypatch.setattr(torch.Tensor, "item", lambda self: pytest.fail("the host waits for the device"))
+    W = torch.zeros(32, K)
+    layer = DsfqLinear(W, calibration=W if calibrated else None)
+    assert calls == ["qvggt_rotated_col_absmax"] * calibrated + ["qvggt_prep_weights_e2m3"]
+    assert layer.Wf.numel() == B.qvggt_e2m3_bytes(32, K) and layer.Wq.shape == (32, K // 2)
