@@ -1,5 +1,5 @@
-// Which tile configuration of the int8-instruction GEMM runs where: a function of the problem's sizes alone, on the host and without HIP,
-// so that it can be looked at without a GPU.
+// Which tile configuration of the two GEMMs (int8 instructions, E2M3) runs where: a function of the problem's sizes alone, on the host and
+// without HIP, so that it can be looked at without a GPU.
 #pragma once
 
 #include <algorithm>
@@ -121,12 +121,17 @@ inline bool e2m3_streams_y(int M, int N)
 }
 
 // The plan that this model prices lowest, in microseconds, fitted to 550 random problems of 16 to 137400 rows and all sizes of K that were
-// measured in every shape on two cards (as graph nodes, codes of a normal distribution): within 3 to 7 % of the time (rms), the choice 0.7 %
-// slower than the best on geometric average.  The last three shapes are priced 4 % above what they took, the 128s' last word where it is close.
+// measured in every shape on two cards (as graph nodes, codes of a normal distribution): within 3 to 7 % of the time (rms).  The last three shapes are
+// priced 4 % above what they took, the 128s' last word where it is close.  Measured as calls run it, behind kernel 1 and with codes of heavy-tailed
+// rows, on 1940 problems: the choice is 1 % slower than the best on geometric average.  The 128s' round is priced by those measurements where the rows of
+// Y are whole lines; as the fit had it, 2.1 + 4.95 k, it put 256s and 192s where 128s are the faster: with kernel 1, 6715 x 1024 -> 3072 27.4 / 24.9,
+// 12759 -> 3072 52.1 / 48.3, 13091 -> 4096 62.6 / 56.0, 26106 -> 2048 74.1 / 65.7, 50838 -> 1024 85.7 / 73.9.
 //   256, 192   tokens x 256 channels per block, one per compute unit: whole rounds of 256 tiles, and the tiles themselves (power).  192 rows
-//              where they waste less of the last round: 32976 x 4096 -> 1024 (2.02 rounds of 256) 77.3 us in 256s and a rest, 71.7 in 192s;
-//              10992 x 4096 -> 1024 28.3 / 26.5; the LDS traffic per MFMA is a sixth more: 87025 x 1024 -> 3072 192 / 210.
-//   128        128 x 128, two blocks per compute unit: by number beyond the first block, at least 0.3 of a round for a last one.
+//              where they waste less of the last round: with kernel 1, 21984 x 4096 -> 1024 112.8 us in 256s, 103.8 in 192s, 10992 -> 1024 57.7 /
+//              53.9; the LDS traffic per MFMA is a sixth more: 97554 x 1024 -> 1024 122 / 131.
+//   256 and a rest   32976 x 4096 -> 1024 (2.02 rounds of 256) 157.5 us in 256s, 151.9 in 192s, 142.1 as 32768 rows in 256s and 208 in 32s.
+//   128        128 x 128, two blocks per compute unit: by number beyond the first block, at least 0.3 of a round for a last one, 0.7 where some
+//              units have two blocks in it: 10992 x 1024 -> 2048 (2.69 rounds) 35.0 in 128s, 33.9 in 192s.
 //   64, 32x64, 32   tokens x channels, K divided among the block's waves (e2m3_gemm_few_kernel): for problems whose 128 x 128 tiles would walk along
 //              K alone on their compute units (64 x 4096 -> 1024 13.3 us in 128s, 7.5 / 6.1 / 5.2 in these; 500 x 4096 -> 1024 13.2, 7.6 / 6.4 / 7.6;
 //              1000 x 1024 -> 1024 6.7, 5.0 / 5.0 / 6.1; 1374 x 1024 -> 3072 8.9, 11.2 / 11.3 / 15.4).
@@ -145,8 +150,9 @@ inline double e2m3_shape_cost(E2m3Plan::Shape shape, int M, int N, int K)
         }
         case E2m3Plan::k128: {
             const double t = tiles(128, 128), rounds = t / 2.0, whole = std::floor(rounds), rest = rounds - whole;
-            const double priced = whole > 0.0 && rest > 0.0 ? whole + std::max(rest, 0.3) : rounds;
-            return 5.05 + 2.2 * k + std::min(t, 1.0) * (1.2 + 0.6 * k) + std::max(priced - 0.5, 0.0) * std::max(2.1 + 4.95 * k, 3.4 + std::min(1.8 * pieces, 1.8));
+            const double priced = whole > 0.0 && rest > 0.0 ? whole + std::max(rest, rest > 0.5 && pieces == 0.0 ? 0.7 : 0.3) : rounds;
+            const double round = pieces == 0.0 ? 1.5 + 5.05 * k : 2.1 + 4.95 * k;
+            return 5.05 + 2.2 * k + std::min(t, 1.0) * (1.2 + 0.6 * k) + std::max(priced - 0.5, 0.0) * std::max(round, 3.4 + std::min(1.8 * pieces, 1.8));
         }
         case E2m3Plan::k64: return 4.85 + 0.93 * k + (std::ceil(tiles(64, 64)) - 1.0) * (0.95 + 1.1 * k);
         case E2m3Plan::k32x64: return 4.45 + 0.65 * k + (std::ceil(tiles(32, 64)) - 1.0) * (0.38 + 0.81 * k);

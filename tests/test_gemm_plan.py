@@ -191,3 +191,17 @@ def test_few_tiles(tmp_path):
                  *rng.choice([(4, 0), (8, 0), (8, 1)])) for _ in range(20000)]
     for (M, N, *_), got in zip(problems, ask(problems)):
         assert got == "none" or (M + 127) // 128 * ((N + 127) // 128) <= 256
+
+
+# problems whose shapes were measured far enough apart to say which it has to be (with kernel 1, us, the shape that a wrong price takes / this one):
+# 27.4 / 24.9, 62.6 / 56.0, 112.5 / 103.6, 73.6 / 69.8; 128s 97.6 / 192s 81.9; 192s 151.9 / 256s and a rest 142.1
+@pytest.mark.parametrize("M,N,K,plan", [(6715, 3072, 1024, "128"), (13091, 4096, 1024, "128"), (50838, 1024, 1024, "128"),
+                                        (10992, 1024, 4096, "192"), (21984, 1024, 4096, "192"), (32976, 1024, 4096, "256+32")])
+def test_e2m3_plan_where_the_shapes_differ(tmp_path, M, N, K, plan):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text(E2M3_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+    shape, rest, rows = subprocess.run([tmp_path / "d"], input=f"{M} {N} {K}", capture_output=True, text=True, check=True).stdout.split()
+    assert (shape if int(rows) == M else f"{shape}+{rest}") == plan
