@@ -759,6 +759,7 @@ __global__ __launch_bounds__(256, OCC) void rotate_quant_mfma_kernel(const uint1
                     *reinterpret_cast<uint4 *>(rb + (size_t)unit * (128 * ROW_BYTES) + within * 16) =
                         *reinterpret_cast<const uint4 *>(lds + unit * OUT_PITCH + within * 16);
             }
+            lanes_exchange_fence();     // the next tile is staged where other lanes' chunks were read
         }
     }
     if constexpr (STAT) {

@@ -101,6 +101,25 @@ def test_rotate_quant_i8b_equals_the_row_major_kernel(K, rows, bits):
     assert torch.equal(sx, sxb) and torch.equal(got, want)
 
 
+@pytest.mark.parametrize("rows", [1, 3, 127, 129, 385, 4097])
+def test_rows_of_2048_leave_as_int8_blocks(rows):
+    """Two rows a tile, four 16-byte chunks a row: with an odd last row, on both sides of a 128-row block and with several tiles per wave, the codes are the
+    row-major kernel's, and rows behind them are not written."""
+    K = 2048
+    g = torch.Generator(device=G.DEV).manual_seed(rows)
+    X = torch.randn(rows, K, device=G.DEV, generator=g).to(torch.bfloat16)
+    inv = torch.rand(K, device=G.DEV, generator=g) + 0.5
+    Xq, sx = G.gpu_rsq_i8(X, None, inv, 8)
+    want = torch.full((G.q.qvggt_i8b_bytes(rows, K),), 0x5A, dtype=torch.uint8, device=G.DEV).view(torch.int8)
+    G.q.qvggt_int8_to_blocks(Xq, rows, K, want)
+    got, sxb = torch.full_like(want, 0x5A), torch.empty_like(sx)
+    G.q.qvggt_rotate_smooth_quant_i8b(X, None, inv, 8, got, sxb)
+    blocks = [b.view(-1, K // 64, 128, 64) for b in (got, want)]
+    r = torch.arange(rows, device=G.DEV)
+    assert torch.equal(sx, sxb) and torch.equal(*[b[r // 128, :, r % 128] for b in blocks])
+    if rows % 128: assert (blocks[0][rows // 128, :, rows % 128:] == 0x5A).all().item()
+
+
 @pytest.mark.parametrize("name,M,bits", [("fc1", 3000, 8), ("fc2", 700, 8), ("fc1", 130, 6)])
 def test_linear_i8b(name, M, bits):
     s = synth.layer_spec(5, name)
