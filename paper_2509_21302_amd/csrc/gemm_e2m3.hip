@@ -114,17 +114,6 @@ __device__ inline void e_wait_vmcnt()
 
 }  // namespace
 
-// Which tiles of an XCD's range are neighbours: those of one row of tokens, unless the weights are the larger operand and more than its L2 of
-// 4 MiB holds with anything else.  Then those of one column: the XCD reads its share of the weights once and all tokens, instead of all
-// weights.  us at K = 4096, channels first / tokens first: 85 x 4096 -> 4096 9.3 / 6.2 (32 x 64 tiles), 374 -> 3072 16.0 / 11.7 (64 x 64),
-// 1374 -> 4096 24.0 / 20.7 (128 x 128); 1374 x 1024 -> 3072, whose weights fit, 8.8 / 9.0.  128 x 128 tiles that have a compute unit each only at
-// K = 4096: with shorter K it costs them (with kernel 1: 670 x 2048 -> 3072 14.5 / 15.1, 1000 -> 3328 15.0 / 15.8, 1374 -> 2624 15.4 / 16.6; with more
-// tiles 1182 -> 3840 19.6 / 18.8, 1374 -> 3696 20.0 / 19.7).
-__host__ __device__ inline bool e2m3_tokens_first(int tiles_m, int tiles_n, int N, int K)
-{
-    return tiles_m < tiles_n && (long long)N * K > (4 << 20);
-}
-
 // SHIFTED: sum_j (u_tj - zp_t) qw_oj = sum_j (u_tj - 7.5) qw_oj + (7.5 - zp_t) * wsum_o: the first sum is what the MFMAs give (multiples
 // of 0.5 below 2^23: exact), the second term is added in the epilogue (exact as well).
 // STREAM_Y: Y goes past the caches (e2m3_streams_y); TOKENS_FIRST: the order of the tiles (e2m3_tokens_first).  Template arguments, because the
@@ -662,7 +651,7 @@ hipError_t launch_e2m3(const E2m3Problem &p, hipStream_t stream)
     if constexpr (C::BM > 128) {
         if (!e2m3_streams_y(p.M, p.N)) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, false, SHIFTED, false, false>;
     } else {
-        if (e2m3_tokens_first(tiles_m, tiles_n, p.N, p.K) && (p.K >= 4096 || tiles_m * tiles_n > 256)) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, false, SHIFTED, true, true>;
+        if (e2m3_128_tokens_first(tiles_m, tiles_n, p.N, p.K)) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, false, SHIFTED, true, true>;
     }
     if constexpr (!SHIFTED) {
         if (p.acc_debug != nullptr) kern = e2m3_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, true, false, true, false>;

@@ -120,6 +120,21 @@ inline bool e2m3_streams_y(int M, int N)
     return N % 64 == 0 || bytes < 20e6 || bytes > kCachedY;
 }
 
+// Which tiles of an XCD's range are neighbours: those of one row of tokens, unless the weights are the larger operand and more than its L2 of
+// 4 MiB holds with anything else.  Then those of one column: the XCD reads its share of the weights once and all tokens, instead of all
+// weights.  us at K = 4096, channels first / tokens first: 85 x 4096 -> 4096 9.3 / 6.2 (32 x 64 tiles), 374 -> 3072 16.0 / 11.7 (64 x 64),
+// 1374 -> 4096 24.0 / 20.7 (128 x 128); 1374 x 1024 -> 3072, whose weights fit, 8.8 / 9.0.  128 x 128 tiles that have a compute unit each only at
+// K = 4096: with shorter K it costs them (with kernel 1: 670 x 2048 -> 3072 14.5 / 15.1, 1000 -> 3328 15.0 / 15.8, 1374 -> 2624 15.4 / 16.6; with more
+// tiles 1182 -> 3840 19.6 / 18.8, 1374 -> 3696 20.0 / 19.7).
+constexpr bool e2m3_tokens_first(int tiles_m, int tiles_n, int N, int K)
+{
+    return tiles_m < tiles_n && (long long)N * K > (4 << 20);
+}
+constexpr bool e2m3_128_tokens_first(int tiles_m, int tiles_n, int N, int K)
+{
+    return e2m3_tokens_first(tiles_m, tiles_n, N, K) && (K >= 4096 || tiles_m * tiles_n > 256);
+}
+
 // The plan that this model prices lowest, in microseconds, fitted to 550 random problems of 16 to 137400 rows and all sizes of K that were
 // measured in every shape on two cards (as graph nodes, codes of a normal distribution): within 3 to 7 % of the time (rms).  The last three shapes are
 // priced 4 % above what they took, the 128s' last word where it is close.  Measured as calls run it, behind kernel 1 and with codes of heavy-tailed

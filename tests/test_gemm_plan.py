@@ -205,3 +205,46 @@ def test_e2m3_plan_where_the_shapes_differ(tmp_path, M, N, K, plan):
     subprocess.run([gxx, "-std=c++17", "-O1", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
     shape, rest, rows = subprocess.run([tmp_path / "d"], input=f"{M} {N} {K}", capture_output=True, text=True, check=True).stdout.split()
     assert (shape if int(rows) == M else f"{shape}+{rest}") == plan
+
+
+VARIANT_DRIVER = r"""
+#include "gemm_plan.h"
+#include <cstdio>
+int main()
+{
+    int M, N, K;
+    const char *names[] = {"256", "192", "128", "64", "32x64", "32"};
+    while (std::scanf("%d %d %d", &M, &N, &K) == 3) {
+        const qvggt::E2m3Plan p = qvggt::e2m3_gemm_plan(M, N, K);
+        std::printf("%s %d %d %d\n", names[p.shape], p.rows_main, qvggt::e2m3_streams_y(p.rows_main, N),
+                    qvggt::e2m3_128_tokens_first((p.rows_main + 127) / 128, (N + 127) / 128, N, K));
+    }
+}
+"""
+
+
+def test_gpu_tests_reach_every_variant_of_the_e2m3_tiles(tmp_path):
+    """Plain codes and shifted ones (which are not dumped): both kinds of store of the 256- and 192-row tiles, both orders of the 128-row ones, and
+    a divided plan."""
+    from tests.test_gpu_e2m3 import CACHED_PLANS, E2M3_PLANS
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text(VARIANT_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+
+    def variants(problems):
+        lines = subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d" % p[:3] for p in problems), capture_output=True, text=True, check=True).stdout.split()
+        found = set()
+        for p, shape, rows, streams, tokens in zip(problems, lines[::4], lines[1::4], lines[2::4], lines[3::4]):
+            assert shape == p[3].split("+")[0], p
+            if shape in ("256", "192"):
+                found.add((shape, "streams" if streams == "1" else "caches"))
+            elif shape == "128":
+                found.add((shape, "tokens first" if tokens == "1" else "channels first"))
+            if int(rows) != p[0]:
+                found.add("divided")
+        return found
+    every = {("256", "streams"), ("256", "caches"), ("192", "streams"), ("192", "caches"), ("128", "channels first"), ("128", "tokens first"), "divided"}
+    shifted = [p for p in E2M3_PLANS if p[2] in (1024, 2048, 4096) and p[0] < 12000 or "+" in p[3]]
+    assert variants(E2M3_PLANS + CACHED_PLANS) == every and variants(shifted + CACHED_PLANS) == every

@@ -367,6 +367,52 @@ def test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan):
     assert torch.equal(whole[:M].view(torch.int16), Y8.view(torch.int16)) and (whole[M:] == 7.0).all().item()
 
 
+# the 256- and 192-row tiles with Y through the caches: Y of 20 to 130 MB, rows that are no whole lines
+CACHED_PLANS = [(10992, 3056, 1024, "192"), (9000, 1200, 2048, "192"), (9000, 1552, 2048, "256"), (10992, 1040, 4096, "256")]
+
+
+@pytest.mark.parametrize("M,N,K,plan", CACHED_PLANS)
+def test_e2m3_gemm_with_y_through_the_caches(M, N, K, plan):
+    test_e2m3_gemm_in_every_tile_shape(M, N, K, plan)
+    test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan)
+
+
+@pytest.mark.parametrize("M,N,K,plan", [p for p in E2M3_PLANS if "+" in p[3]])
+def test_e2m3_gemm_shifted_in_divided_plans(M, N, K, plan):
+    """The rest's zero points are those of its own rows."""
+    test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan)
+
+
+# The row kernels writing E2M3 blocks, by the entry point itself (a layer takes nibbles at many of these sizes): more groups of rows than blocks, four
+# waves per row with groups of four rows (K = 5120, 6144, 8192 beyond 4096 rows), and channels enough that small K are not one launch
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("K,M,N", [(K, M, 80) for K in (768, 1280, 1536, 1792, 2560, 3072, 3584, 5120, 6144, 8192) for M in (5, 4097, 8503)] +
+                         [(K, M, N) for K in (128, 256, 512) for M, N in ((131, 13328), (6, 65552), (8503, 80))] + [(K, 8503, 80) for K in (1024, 2048, 4096)])
+def test_row_kernels_write_the_packed_paths_codes(K, M, N, f32):
+    if not f32 and K in (1024, 2048, 4096):
+        pytest.skip("the matrix-core kernel")
+    g = torch.Generator(device=G.DEV).manual_seed(K + M)
+    X = torch.randn(M, K, device=G.DEV, generator=g)
+    X[:, ::61] *= 30
+    X[M // 2], X[M - 1, 7], X[M - 2, 1] = 0, float("inf"), float("nan")
+    X = X if f32 else X.to(torch.bfloat16)
+    inv, signs = torch.rand(K, device=G.DEV, generator=g) + 0.5, (torch.randint(0, 2, (K,), device=G.DEV, generator=g, dtype=torch.int8) * 2 - 1).contiguous()
+    Wq = torch.randint(0, 7, (N, K // 2), device=G.DEV, generator=g, dtype=torch.uint8) * 17          # codes 0 .. 6
+    Wf, lost = torch.empty(G.q.qvggt_e2m3_bytes(N, K), dtype=torch.uint8, device=G.DEV), torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    G.q.qvggt_codes_to_e2m3(Wq, N, K, Wf, lost)
+    sw = torch.rand(N, device=G.DEV, generator=g) * 0.01
+    need = G.q.qvggt_workspace_bytes_e2m3(M, N, K)
+    ws = torch.full((need + 4096,), 7, dtype=torch.uint8, device=G.DEV)
+    whole, want = torch.full((M + 3, N), 7.0, dtype=torch.bfloat16, device=G.DEV), torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV)
+    G.q.qvggt_linear_e2m3_any(X, signs, inv, Wf, sw, None, whole[:M], ws[:need])
+    assert (ws[need:] == 7).all().item() and (whole[M:] == 7.0).all().item()
+    blocks = ws[:G.q.qvggt_e2m3_bytes(M, K)].view(-1, K // 64, 128, 48)
+    assert (blocks[0, :, 0] != 7).any().item(), "not the two kernels"
+    if M % 128: assert (blocks[M // 128, :, M % 128:] == 7).all().item()
+    G.q.qvggt_linear(X, signs, inv, Wq, sw, None, want, torch.empty(G.q.qvggt_workspace_bytes(M, N, K), dtype=torch.uint8, device=G.DEV))
+    assert torch.equal(whole[:M].view(torch.int16), want.view(torch.int16))
+
+
 # every K in both types: rows below a group of four, groups that end inside a 128-row block, more groups than blocks
 @pytest.mark.parametrize("K", [128, 256, 512, 768, 1024, 1280, 1536, 1792, 2048, 2560, 3072, 3584, 4096, 5120, 6144, 8192])
 @pytest.mark.parametrize("f32", [True, False])

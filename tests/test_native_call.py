@@ -155,3 +155,32 @@ def test_an_error_of_the_allocation_is_raised_as_it_is():
         layer(X)
     layer.N = 144
     assert torch.equal(layer(X), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", ["float16", "one dimension", "three dimensions", "not contiguous", "subclass", "conjugate", "host bias", "strided bias", "host workspace",
+                                   "strided output", "output of one dimension", "meta"])
+def test_what_is_not_an_ordinary_tensor_on_the_device_is_left_to_the_python_path(which):
+    """Each differs in one thing from arguments that are taken."""
+    class Other(torch.Tensor):
+        pass
+    dev = "cuda:0"
+    layer, X = _layer(4, 4, False, 1024)
+    args = dict(X=X.to(torch.bfloat16), bias=layer.bias, out=torch.zeros(70, 144, dtype=torch.bfloat16, device=dev), ws=layer._workspace(70, X.device))
+
+    def call():
+        return B.native_linear(B.E2M3, args["X"], layer.signs, layer.inv_smooth, None, layer.Wf, layer.w_scale, args["bias"], args["out"], args["ws"], 144, 4)
+    want = call()
+    assert want is args["out"]
+    want = want.clone()
+    name, value = {"float16": ("X", X.half()), "one dimension": ("X", args["X"].flatten()), "three dimensions": ("X", args["X"][None]),
+                   "not contiguous": ("X", torch.cat([args["X"]] * 2, 1)[:, ::2]), "subclass": ("X", args["X"].as_subclass(Other)),
+                   "conjugate": ("X", torch.zeros(70, 1024, dtype=torch.complex64, device=dev).conj()), "host bias": ("bias", layer.bias.cpu()),
+                   "strided bias": ("bias", torch.cat([layer.bias] * 2)[::2]), "host workspace": ("ws", args["ws"].cpu()),
+                   "strided output": ("out", torch.zeros(144, 70, dtype=torch.bfloat16, device=dev).t()),
+                   "output of one dimension": ("out", torch.zeros(70 * 144, dtype=torch.bfloat16, device=dev)),
+                   "meta": ("X", args["X"].to("meta"))}[which]
+    kept, args[name] = args[name], value
+    assert call() is None
+    args[name] = kept
+    assert torch.equal(call().view(torch.int16), want.view(torch.int16))
