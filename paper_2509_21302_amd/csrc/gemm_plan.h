@@ -139,7 +139,7 @@ constexpr bool e2m3_128_tokens_first(int tiles_m, int tiles_n, int N, int K)
 // measured in every shape on two cards (as graph nodes, codes of a normal distribution): within 3 to 7 % of the time (rms).  The last three shapes are
 // priced 4 % above what they took, the 128s' last word where it is close.  Measured as calls run it, behind kernel 1 and with codes of heavy-tailed
 // rows, on 1940 problems: the choice is 1 % slower than the best on geometric average.  The 128s' round is priced by those measurements where the rows of
-// Y are whole lines; as the fit had it, 2.1 + 4.95 k, it put 256s and 192s where 128s are the faster: with kernel 1, 6715 x 1024 -> 3072 27.4 / 24.9,
+// Y are whole lines and K >= 1024 (K = 512 and 768 take the same time by either price: 10992 x 768 -> 3072 39.6 in 192s, 40.0 in 128s); as the fit had it, 2.1 + 4.95 k, it put 256s and 192s where 128s are the faster: with kernel 1, 6715 x 1024 -> 3072 27.4 / 24.9,
 // 12759 -> 3072 52.1 / 48.3, 13091 -> 4096 62.6 / 56.0, 26106 -> 2048 74.1 / 65.7, 50838 -> 1024 85.7 / 73.9.
 //   256, 192   tokens x 256 channels per block, one per compute unit: whole rounds of 256 tiles, and the tiles themselves (power).  192 rows
 //              where they waste less of the last round: with kernel 1, 21984 x 4096 -> 1024 112.8 us in 256s, 103.8 in 192s, 10992 -> 1024 57.7 /
@@ -165,8 +165,9 @@ inline double e2m3_shape_cost(E2m3Plan::Shape shape, int M, int N, int K)
         }
         case E2m3Plan::k128: {
             const double t = tiles(128, 128), rounds = t / 2.0, whole = std::floor(rounds), rest = rounds - whole;
-            const double priced = whole > 0.0 && rest > 0.0 ? whole + std::max(rest, rest > 0.5 && pieces == 0.0 ? 0.7 : 0.3) : rounds;
-            const double round = pieces == 0.0 ? 1.5 + 5.05 * k : 2.1 + 4.95 * k;
+            const bool in_calls = pieces == 0.0 && K >= 1024;
+            const double priced = whole > 0.0 && rest > 0.0 ? whole + std::max(rest, in_calls && rest > 0.5 ? 0.7 : 0.3) : rounds;
+            const double round = in_calls ? 1.5 + 5.05 * k : 2.1 + 4.95 * k;
             return 5.05 + 2.2 * k + std::min(t, 1.0) * (1.2 + 0.6 * k) + std::max(priced - 0.5, 0.0) * std::max(round, 3.4 + std::min(1.8 * pieces, 1.8));
         }
         case E2m3Plan::k64: return 4.85 + 0.93 * k + (std::ceil(tiles(64, 64)) - 1.0) * (0.95 + 1.1 * k);

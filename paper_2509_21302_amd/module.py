@@ -95,8 +95,8 @@ class DsfqLinear:
 
     def __call__(self, X: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
         """X: [M, K] bf16 or f32 on the GPU; returns bf16 [M, N] (written into `out` when given)."""
-        M = X.shape[0]
-        if X.dim() == 2 and X.shape[1] != self.K:        # the entry points take K from X, and E2M3 blocks of another K would be read as this one's
+        M, K = X.shape
+        if K != self.K:                                  # the entry points take K from X, and E2M3 blocks of another K would be read as this one's
             raise q.QvggtError(q.ERR_SHAPE, "DsfqLinear")
         if out is not None and out.dim() == 2 and (out.shape[1] > self.N or out.numel() * out.element_size() < 2 * M * out.shape[1]):
             raise q.QvggtError(q.ERR_SHAPE, "DsfqLinear: out")     # written, or weights read, past their end
