@@ -463,7 +463,8 @@ int qvggt_nfds_kmeans_step(const float *c, int n, int dim, int K, const float *c
  *   bias bf16 [N] or NULL, c_hat f32 [K] and w_step f32 [N] positive, x_step f32 [1] or NULL, bits in 4..8.  Outputs f32: loss [1],
  *   grad_c [K], grad_w_step [N], grad_x_step [1] (given exactly when x_step is: QVGGT_ERR_NULL otherwise).  T, N >= 1, K a
  *   multiple of 4 up to 8192 (QVGGT_ERR_SHAPE).  workspace: qvggt_calib_workspace_bytes(T, N, K) bytes (0 for an invalid shape),
- *   16-byte aligned.  fp32 arithmetic, sums in a fixed order (the same call gives the same bits).
+ *   16-byte aligned.  The size is for a static step too, whose derivative reads [T, K] floats more (where tokens outnumber channels they decide:
+ *   121 MB at T = 2748, N = 64, K = 4096), and belongs to this version of the library: ask for it, do not keep it.  fp32 arithmetic, sums in a fixed order (the same call gives the same bits).
  * qvggt_calib_descent_step:  theta[i] <- max(theta[i] - lr * grad[i], floor), floor > 0 keeping factors and steps positive
  *   (plain gradient descent with the paper's learning rates; which optimiser the paper's pipeline runs it does not say).
  * The refined values are deployed by qvggt_prep_weights_given (c_hat, w_step) and qvggt_rotate_smooth_quant_static (x_step).

@@ -23,7 +23,7 @@ SOURCES = ["api.hip", "rotate_quant.hip", "rotate_quant_mfma.hip", "gemm_w4a4.hi
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-    # no packed-fp32 instructions: some of their forms are unreliable on the test machines
+    # no packed-fp32 instructions: some of their forms are unreliable on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", INCLUDE, "-Wall", "-Wno-unused-function",
     # the global -> LDS transfer wrappers name M0 (a register the compiler reserves) as clobbered, which it reports for every use

@@ -558,7 +558,9 @@ static CalibPlan calib_plan(int T, int N, int K)
 }
 
 // workspace: codes of both operands [Tp + Np, Kp] bf16, their steps [Tp + Np], what the products are multiplied by (up to [2 Tp + Np, Kp]), E
-// [Tp, Np], partial sums: 52 of the 53 MB that are asked for at 1374 x 1024 -> 3072.  The size has always covered fp32 copies of both operands,
+// [Tp, Np], partial sums: 52 of the 53 MB that are asked for at 1374 x 1024 -> 3072.  Tp x Kp of them are a static step's alone; with z in place of both
+// of its planes and the quotients taken again in the products, 2748 x 4096 -> 64 asks for 93 MB and not 121, and takes 141 us and not 129
+// (1374 x 1024 -> 3072 138 and not 120).  The size has always covered fp32 copies of both operands,
 // both products and E, the ABI's tests hold it to that, and it stays where the own need is less.
 size_t calib_workspace_bytes(int T, int N, int K)
 {

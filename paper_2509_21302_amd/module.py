@@ -18,6 +18,10 @@ class DsfqLinear:
 
     weight: [N, K] bf16 or f32 device tensor; bias: [N] bf16 device tensor or None; signs: int8 [K] of +-1 or None;
     calibration: [M_cal, K] activations for the smoothing statistic, or None for rotation only (c = 1).
+
+    The weight codes are kept in two forms (1.25 bytes a weight in the 4-bit setting).  A layer keeps one workspace, into which a call's first kernel
+    writes what its second reads: calls of one layer follow each other on one stream, from one thread at a time; several streams or threads
+    take a layer each.
     """
 
     def __init__(self, weight: torch.Tensor, bias: Optional[torch.Tensor] = None, signs: Optional[torch.Tensor] = None,
@@ -80,7 +84,7 @@ class DsfqLinear:
         self._ws = (-1, None)       # rows the workspace is large enough for, the workspace
 
     def _workspace(self, M: int, dev) -> torch.Tensor:
-        rows, ws = self._ws         # read and replaced as a pair: several threads may be here
+        rows, ws = self._ws         # read and replaced as a pair: a thread that comes at a bad moment is given one that is large enough
         if M <= rows and ws.device == dev:       # what M rows need grows with M
             return ws
         need = q.qvggt_workspace_bytes(M, self.N, self.K) if self.packed else q.qvggt_workspace_bytes_i8(M, self.N, self.K)
@@ -107,8 +111,9 @@ class DsfqLinear:
             kind, W, bits = q.GELU, self.Wf, 4
         elif self.packed and self.Wf is not None and (M <= 4096 or bf16 and self.K in (1024, 2048, 4096) or self.N >= 448 and self.K >= 512):
             # (many rows of few channels or features are kernel 1 and the stores of Y; kernel 1 writes nibbles 10 to 15 % faster where it is not
-            # the matrix-core one: 41505 x 768 -> 128 44.4 us in nibbles, 50.0 in E2M3 blocks, 50398 x 1536 -> 272 110 / 112, 57418 x 256 -> 512
-            # 41.4 / 45.1, 9374 x 512 -> 2576 44.2 / 33.4, 64 x 128 -> 128 9.0 / 8.1)
+            # the matrix-core one.  Kernels alone, nibbles / E2M3 blocks: 41505 x 768 -> 128 40.4 us / 45.2, 99022 x 1792 -> 320 238 / 257, 105364 x 256 -> 48
+            # 41.1 / 55.3; 10992 x 768 -> 3072 43.5 / 38.3, 64 x 128 -> 128 5.2 / 3.5.  Over 320 random sizes the rule is 1.2 % above the better of
+            # the two; most of that is many rows of K = 128 and 256 with many channels, which stay with nibbles: 7662 x 256 -> 3632 35.6 / 24.0)
             kind, W, bits = q.E2M3, self.Wf, 4
         elif self.packed:                                # the same Y, bit for bit
             kind, W, bits = q.PACKED, self.Wq, 4
