@@ -243,6 +243,12 @@ def _stream(stream) -> Optional[int]:
     return stream.cuda_stream or None
 
 
+def _written(t):
+    """What torch's own writes into a tensor do and a kernel's do not: its version moves on (DsfqLinear looks at its packed codes')."""
+    if not t.is_inference():
+        torch.autograd.graph.increment_version(t)
+
+
 def _check(status: int, where: str):
     if status != 0:
         raise QvggtError(status, where)
@@ -253,7 +259,8 @@ def native_linear(kind, X, signs, inv_smooth, gelu_table, W, w_scale, bias, out,
     that the functions below have to take (or refuse)."""
     if _call is None:
         return None
-    load_library()
+    if _lib is None:
+        load_library()
     Y = _call.linear(kind, X, signs, inv_smooth, gelu_table, W, w_scale, bias, out, workspace, N, bits)
     if Y is NotImplemented:
         return None
@@ -286,6 +293,7 @@ def qvggt_prep_weights(W, act_absmax_rot, signs, alpha, Wq, w_scale, inv_smooth,
     _check(load_library().qvggt_prep_weights(_ptr(W), _dtype_code(W), N, K, _ptr(act_absmax_rot), _ptr(signs),
                                              float(alpha), _ptr(Wq), _ptr(w_scale), _ptr(inv_smooth),
                                              _stream(stream)), "qvggt_prep_weights")
+    _written(Wq)
 
 
 def qvggt_rotate_smooth_quant(X, signs, inv_smooth, Xq, x_scale, stream=None):
@@ -485,6 +493,7 @@ def qvggt_linear(X, signs, inv_smooth, Wq, w_scale, bias, Y, workspace, stream=N
 def qvggt_pack_int4(codes, packed, stream=None):
     rows, K = codes.shape
     _check(load_library().qvggt_pack_int4(_ptr(codes), rows, K, _ptr(packed), _stream(stream)), "qvggt_pack_int4")
+    _written(packed)
 
 
 def qvggt_unpack_int4(packed, codes, stream=None):
@@ -498,6 +507,7 @@ def qvggt_prep_weights_given(W, c_hat, signs, w_step, bits, Wq, w_scale, inv_smo
     _check(load_library().qvggt_prep_weights_given(_ptr(W), _dtype_code(W), N, K, _ptr(c_hat), _ptr(signs), _ptr(w_step), int(bits),
                                                    _ptr(Wq), _ptr(w_scale), _ptr(inv_smooth), _stream(stream)),
            "qvggt_prep_weights_given")
+    _written(Wq)
 
 
 def qvggt_prep_weights_e2m3(W, act_absmax_rot, signs, alpha, Wq, Wf, w_scale, inv_smooth, stream=None):

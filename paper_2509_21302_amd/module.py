@@ -6,6 +6,7 @@ method happens here.  `bits` = 4 uses the packed 4-bit path, 5..8 the int8-code 
 """
 from __future__ import annotations
 
+import contextlib
 from typing import Optional
 
 import torch
@@ -19,7 +20,9 @@ class DsfqLinear:
     weight: [N, K] bf16 or f32 device tensor; bias: [N] bf16 device tensor or None; signs: int8 [K] of +-1 or None;
     calibration: [M_cal, K] activations for the smoothing statistic, or None for rotation only (c = 1).
 
-    The weight codes are kept in two forms (1.25 bytes a weight in the 4-bit setting).  A layer keeps one workspace, into which a call's first kernel
+    The weight codes are kept in two forms (1.25 bytes a weight in the 4-bit setting): Wq, and the blocks Wf or Wb that bf16 rows of K = 1024, 2048 and
+    4096 are multiplied with.  Other rows of a 4-bit layer take Wf only while Wq is the tensor, and as it was, when Wf was made of it; other codes
+    assigned to Wq or written into it are the ones that count.  A layer keeps one workspace, into which a call's first kernel
     writes what its second reads: calls of one layer follow each other on one stream, from one thread at a time; several streams or threads
     take a layer each.
     """
@@ -58,7 +61,8 @@ class DsfqLinear:
         self.w_scale = torch.empty(self.N, dtype=torch.float32, device=dev)
         self.inv_smooth = torch.empty(self.K, dtype=torch.float32, device=dev)
         if self.packed:
-            self.Wq = torch.empty(self.N, self.K // 2, dtype=torch.uint8, device=dev)
+            with torch.inference_mode(False) if torch.is_inference_mode_enabled() else contextlib.nullcontext():       # versions are counted
+                self.Wq = torch.empty(self.N, self.K // 2, dtype=torch.uint8, device=dev)
             self.Wf = torch.empty(q.qvggt_e2m3_bytes(self.N, self.K), dtype=torch.uint8, device=dev)
             if not blocks:                   # nothing to count there, and nothing to wait for
                 q.qvggt_prep_weights_e2m3(weight, absmax, signs, alpha, self.Wq, self.Wf, self.w_scale, self.inv_smooth)
@@ -81,7 +85,26 @@ class DsfqLinear:
                 q.qvggt_prep_weights_i8(weight, absmax, signs, alpha, bits, self.Wq, self.w_scale, self.inv_smooth)
                 if blocks:
                     q.qvggt_int8_to_blocks(self.Wq, self.N, self.K, self.Wb)
+        if self.packed:
+            self._blocks_of = (self.Wq, self.Wq._version)
         self._ws = (-1, None)       # rows the workspace is large enough for, the workspace
+
+    _blocks_of = None               # the packed codes that Wf was made of, and their version (layers of earlier builds: not known)
+
+    def _blocks_hold(self) -> bool:
+        made = self._blocks_of
+        return made is not None and made[0] is self.Wq and made[1] == self.Wq._version
+
+    def __getstate__(self):         # a copy's tensors count their versions anew
+        state = dict(self.__dict__)
+        if "_blocks_of" in state:
+            state["_blocks_of"] = self._blocks_hold()
+        return state
+
+    def __setstate__(self, state):
+        self.__dict__.update(state)
+        if "_blocks_of" in state:
+            self._blocks_of = (self.Wq, self.Wq._version) if state["_blocks_of"] else None
 
     def _workspace(self, M: int, dev) -> torch.Tensor:
         rows, ws = self._ws         # read and replaced as a pair: a thread that comes at a bad moment is given one that is large enough
@@ -109,7 +132,7 @@ class DsfqLinear:
             if not bf16:
                 raise ValueError("pre_gelu needs bf16 input")
             kind, W, bits = q.GELU, self.Wf, 4
-        elif self.packed and self.Wf is not None and (M <= 4096 or bf16 and self.K in (1024, 2048, 4096) or self.N >= 448 and self.K >= 512):
+        elif self.packed and self.Wf is not None and (bf16 and self.K in (1024, 2048, 4096) or (M <= 4096 or self.N >= 448 and self.K >= 512) and self._blocks_hold()):
             # (many rows of few channels or features are kernel 1 and the stores of Y; kernel 1 writes nibbles 10 to 15 % faster where it is not
             # the matrix-core one.  Kernels alone, nibbles / E2M3 blocks: 41505 x 768 -> 128 40.4 us / 45.2, 99022 x 1792 -> 320 238 / 257, 105364 x 256 -> 48
             # 41.1 / 55.3; 10992 x 768 -> 3072 43.5 / 38.3, 64 x 128 -> 128 5.2 / 3.5.  Over 320 random sizes the rule is 1.2 % above the better of
@@ -121,7 +144,9 @@ class DsfqLinear:
             kind, W, bits = q.INT8_BLOCKS, self.Wb, self.act_bits
         else:                                            # the same Y
             kind, W, bits = q.INT8, self.Wq, self.act_bits
-        ws = self._workspace(M, X.device)
+        rows, ws = self._ws         # as _workspace does
+        if M > rows or ws.get_device() != X.get_device():
+            ws = self._workspace(M, X.device)
         Y = q.native_linear(kind, X, self.signs, self.inv_smooth, self.gelu_table, W, self.w_scale, self.bias, out, ws, self.N, bits)
         if Y is not None:
             return Y

@@ -77,3 +77,18 @@ def test_deployed_layer_with_given_parameters():
     Y = torch.empty(s.M, s.N, dtype=torch.bfloat16, device=G.DEV)
     G.q.qvggt_w4a4_gemm(Xq, sx, Wq, sw, G.to_dev(bias), s.M, s.N, s.K, Y)
     assert G.rel_fro(G.bf16_bits(Y), want) <= G.Y_REL_FRO
+
+
+@pytest.mark.parametrize("K,f32", [(768, False), (128, True), (1024, True)])
+def test_given_parameters_written_into_a_layer(K, f32):
+    """The calls of a layer whose codes, steps and factor have been overwritten by qvggt_prep_weights_given: the product with what is there now."""
+    g = torch.Generator(device=G.DEV).manual_seed(K)
+    W, X = torch.randn(48, K, device=G.DEV, generator=g) * 0.02, torch.randn(70, K, device=G.DEV, generator=g)
+    X = X if f32 else X.to(torch.bfloat16)
+    layer = G.q.DsfqLinear(W, None, None, X)
+    first = layer(X)
+    c_hat = torch.rand(K, device=G.DEV, generator=g) + 0.5
+    G.q.qvggt_prep_weights_given(W, c_hat, None, layer.w_scale * 0.7, 4, layer.Wq, layer.w_scale, layer.inv_smooth)       # clamp live: codes -8 too
+    want, ws = torch.empty_like(first), torch.empty(G.q.qvggt_workspace_bytes(70, 48, K), dtype=torch.uint8, device=G.DEV)
+    G.q.qvggt_linear(X, None, layer.inv_smooth, layer.Wq, layer.w_scale, None, want, ws)
+    assert torch.equal(layer(X).view(torch.int16), want.view(torch.int16)) and not torch.equal(first, want)

@@ -1,4 +1,7 @@
 """DsfqLinear's choice of an entry point, and what it refuses before any, without a GPU."""
+import copy
+import pickle
+
 import pytest
 import torch
 
@@ -76,3 +79,47 @@ def test_a_layer_of_other_sizes_is_made_without_waiting(monkeypatch, K, calibrat
     layer = DsfqLinear(W, calibration=W if calibrated else None)
     assert calls == ["qvggt_rotated_col_absmax"] * calibrated + ["qvggt_prep_weights_e2m3"]
     assert layer.Wf.numel() == B.qvggt_e2m3_bytes(32, K) and layer.Wq.shape == (32, K // 2)
+
+
+@pytest.fixture
+def made(monkeypatch, taken):
+    """Layers of the constructor, whose kernels do not run."""
+    for name in B.EXPORTS:
+        if hasattr(B, name) and "bytes" not in name:
+            monkeypatch.setattr(B, name, lambda *a: None)
+    monkeypatch.setattr(torch.Tensor, "item", lambda self: 0)
+    return lambda K: DsfqLinear(torch.zeros(32, K), calibration=torch.zeros(4, K))
+
+
+def _assign(layer):
+    layer.Wq = layer.Wq.clone()
+
+
+@pytest.mark.parametrize("K", [128, 768, 1024, 8192])
+@pytest.mark.parametrize("write", [_assign, lambda l: l.Wq.fill_(1), lambda l: l.Wq[3:5].copy_(l.Wq[:2]), lambda l: B._written(l.Wq)])
+@pytest.mark.parametrize("inference", [False, True])
+def test_other_packed_codes_are_the_ones_that_count(taken, made, K, write, inference):
+    """f32 rows, and bf16 rows of other sizes, as long as there was one form of the codes: what is in Wq is what they are multiplied with."""
+    X = torch.zeros(3, K)
+    with torch.inference_mode(inference):
+        layer = made(K)
+        layer(X)
+        write(layer)
+        layer(X)
+        for again in (copy.copy(layer), copy.deepcopy(layer), pickle.loads(pickle.dumps(layer))):
+            again(X)
+    assert taken == [B.E2M3] + [B.PACKED] * 4
+
+
+@pytest.mark.parametrize("K", [128, 768, 1024])
+@pytest.mark.parametrize("again", [copy.copy, copy.deepcopy, lambda l: pickle.loads(pickle.dumps(l)), lambda l: copy.deepcopy(copy.deepcopy(l))])
+def test_copies_of_a_layer_keep_both_forms(taken, made, K, again):
+    """Whatever versions the copy's tensors count, and those of the layer it is a copy of."""
+    X, layer = torch.zeros(3, K), made(K)
+    B._written(layer.Wq)
+    layer._blocks_of = (layer.Wq, layer.Wq._version)               # as where the codes were made by a call that counts
+    twin = again(layer)
+    twin(X)
+    twin.Wq.zero_()
+    twin(X)
+    assert taken == [B.E2M3, B.PACKED]
