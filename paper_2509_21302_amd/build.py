@@ -18,7 +18,7 @@ LIB = os.path.join(HERE, "libqvggt.so")
 CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))       # another Python does not find it
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["api.hip", "rotate_quant.hip", "rotate_quant_mfma.hip", "gemm_w4a4.hip", "nfds.hip",
-           "rotate_quant_general.hip", "gemm_e2m3.hip", "linear_small.hip", "ceilings.hip", "calib.hip"]
+           "rotate_quant_general.hip", "gemm_e2m3.hip", "gemm_e2m3_resident.hip", "linear_small.hip", "ceilings.hip", "calib.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -29,12 +29,15 @@ FLAGS = [
     # the global -> LDS transfer wrappers name M0 (a register the compiler reserves) as clobbered, which it reports for every use
     "-Wno-inline-asm",
 ]
-
+FLAGS_OF = {
+    # results of the matrix instructions in ordinary registers, where the epilogue reads them without a copy
+    "gemm_e2m3_resident.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+}
 
 
 def _compile(src: str, save_temps: bool) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *FLAGS_OF.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
     if save_temps:
         cmd.append("-save-temps=obj")
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -29,35 +29,21 @@
 //
 // Tiles: 256 x 256 per block, one block per compute unit, four waves of 128 x 128 (256 accumulator registers each): the least
 // operand traffic per MFMA that the register file allows; 192 x 256 where that fills the last round better; 128 x 128 blocks, two per
-// compute unit, for problems of less than a round or so, and a kernel without shared stages for few tiles (gemm_plan.h has the rule).
+// compute unit, for problems of less than a round or so, and a kernel without shared stages for few tiles (gemm_plan.h has the rule).  Enough
+// tokens of K up to 2048 go to gemm_e2m3_resident.hip instead: what runs here of a size are few tokens, long K and the accumulator dump.
 // (256 x 128 blocks, two per compute unit, so that one block's epilogue runs under the other's K loop, were built and measured:
 // the K loop is not limited by the matrix pipes but by what feeds them, and 1.5 times the LDS traffic per MFMA ate the overlap.)
 // The epilogue: accumulators from AGPRs, scale + bias, bf16, rows through a wave-private LDS tile, non-temporal 128-byte line
 // stores.
+#include "e2m3.h"
 #include "gemm_plan.h"
-#include "qvggt_common.h"
 
 #include <algorithm>
 #include <cstdlib>
-#include <type_traits>
-#include <utility>
 
 namespace qvggt {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-
 namespace {
-
-constexpr int U_BYTES = 48;        // bytes per row per unit: 64 codes of 6 bits
-constexpr int RB = 128;            // rows per block of the operand format
-constexpr int RB_BYTES = RB * U_BYTES;   // one unit of one block: 6 KiB contiguous
-constexpr int RB_PIECES = RB_BYTES / 1024;
-// Scale operands of the matrix builtin.  Constant zeros make the compiler emit the instruction form without block scales
-// (v_mfma_f32_32x32x64_f8f6f4: products as they are), one instruction per MFMA instead of two; 0x7F7F7F7F (E8M0 exponent 127 = 2^0
-// in every byte) is the explicit unit scale and gives the same sums.
-constexpr int UNIT_SCALE_ONE = 0;
 
 // SHIFTED: the activation codes are stored 7.5 below an unsigned code u in [0, 15] (all sixteen half-integers -7.5 .. 7.5 are E2M3
 // numbers), with a zero point per token; the per-tile scale area then also carries the zero points and the weights' code sums
@@ -81,36 +67,6 @@ struct E2m3Cfg {
     static_assert(BM % 64 == 0 && BN % 128 == 0, "tiles are whole 1 KiB pieces of the operand format (64 rows are three), channel tiles whole blocks");
     static_assert(STAGES >= 3, "ring needs one stage being read, one landed, one in flight");
 };
-
-// Global memory -> LDS, 16 bytes per lane: lane l reads base + lane_off and writes LDS address lds_base + 16 * l.  M0 carries the
-// LDS base; each transfer sets it itself and says so, so nothing depends on what the compiler does with that register elsewhere.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ inline void e_dma16(uint32_t lane_off, const void *base, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-// 4 bytes per lane: lane l writes lds_base + 4 * l
-__device__ inline void e_dma4(const void *src, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-template <class F, int... Is>
-__device__ inline void e_static_for_impl(F &&f, std::integer_sequence<int, Is...>)
-{
-    (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ inline void e_static_for(F &&f)
-{
-    e_static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-template <int N>
-__device__ inline void e_wait_vmcnt()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 
 }  // namespace
 
@@ -616,32 +572,6 @@ static const LdsKernels e2m3_lds_kernels(e2m3_lds_kernel_list);
 
 namespace {
 
-// A product's operands and result; xzero and wsum only with SHIFTED codes.
-struct E2m3Problem {
-    const uint8_t *Xf;
-    const float *sx;
-    const uint8_t *Wf;
-    const float *sw;
-    const uint16_t *bias;
-    int M, N, K;
-    uint16_t *Y;
-    int32_t *acc_debug;
-    const float *xzero, *wsum;
-
-    // token rows row0 .. row0 + rows - 1; row0 is a multiple of 128, i.e. whole blocks of the operand format
-    E2m3Problem part(int row0, int rows) const
-    {
-        E2m3Problem p = *this;
-        p.Xf += (size_t)row0 * ((size_t)K / 4 * 3);
-        p.sx += row0;
-        p.M = rows;
-        p.Y += (size_t)row0 * N;
-        if (acc_debug != nullptr) p.acc_debug += (size_t)row0 * N;
-        if (xzero != nullptr) p.xzero += row0;
-        return p;
-    }
-};
-
 template <int TM, int TN, int WM, int WN, int STAGES, int MINB, bool SHIFTED>
 hipError_t launch_e2m3(const E2m3Problem &p, hipStream_t stream)
 {
@@ -696,6 +626,7 @@ hipError_t run_e2m3(const E2m3Problem &p, hipStream_t stream)
     if (p.M <= 0) return hipSuccess;
     hipError_t e = prepare_device();                 // the kernels' dynamic-LDS limits on this device (see e2m3_lds_kernels above)
     if (e != hipSuccess) return e;
+    if (p.acc_debug == nullptr && e2m3_resident(p.M, p.N, p.K, SHIFTED)) return run_e2m3_resident<SHIFTED>(p, stream);
     const E2m3Plan plan = e2m3_gemm_plan(p.M, p.N, p.K);
     if (plan.rows_main == p.M) return launch_e2m3_shape<SHIFTED>(plan.shape, p, stream);
     e = launch_e2m3_shape<SHIFTED>(plan.shape, p.part(0, plan.rows_main), stream);

@@ -177,7 +177,7 @@ inline double e2m3_shape_cost(E2m3Plan::Shape shape, int M, int N, int K)
     return 0.0;
 }
 
-inline E2m3Plan e2m3_gemm_plan(int M, int N, int K)
+inline E2m3Plan e2m3_gemm_plan(int M, int N, int K, double *cost = nullptr)
 {
     auto cheapest = [&](int rows, double &cost) {
         E2m3Plan::Shape best = E2m3Plan::k256;
@@ -196,9 +196,44 @@ inline E2m3Plan e2m3_gemm_plan(int M, int N, int K)
     if (main_tile_rows > 0 && main_tile_rows < tiles_m) {
         const int rows_main = (int)main_tile_rows * 256;
         const E2m3Plan::Shape rest_shape = cheapest(M - rows_main, rest);
-        if (e2m3_shape_cost(E2m3Plan::k256, rows_main, N, K) + rest < 0.97 * whole) return {E2m3Plan::k256, rows_main, rest_shape};
+        const double divided = e2m3_shape_cost(E2m3Plan::k256, rows_main, N, K) + rest;
+        if (divided < 0.97 * whole) {
+            if (cost != nullptr) *cost = divided;
+            return {E2m3Plan::k256, rows_main, rest_shape};
+        }
     }
+    if (cost != nullptr) *cost = whole;
     return {shape, M, shape};
+}
+
+// The kernel with the weights in registers (gemm_e2m3_resident.hip): 256 channels per block, the tokens in as many ranges of steps of 32 as fill the
+// chip.  K where 64 channels of a wave fit beside two sets of results; affine codes are written for K = 1024 and 2048 only.  (K = 128 and 256 have few
+// products per result: 40000 x 128 -> 2048 33.2 us in 256-row tiles, 31.8 in this one, 10992 x 256 -> 1024 8.1 / 8.9.)
+constexpr bool e2m3_resident_k(int K, bool shifted)
+{
+    return K == 1024 || K == 2048 || (!shifted && (K == 512 || K == 768 || K == 1280 || K == 1536 || K == 1792));
+}
+inline int e2m3_resident_groups(int N) { return (N + 255) / 256; }
+inline int e2m3_resident_ranges(int M, int N) { return std::max(1, std::min(256 / e2m3_resident_groups(N), (M + 31) / 32)); }
+
+// Its price in microseconds, to be compared with the tiles'.  Loading the weights into the registers costs 5.3 + 2.4 k before the first product, a
+// step of a block 0.735 k, and writing Y 0.112 per megabyte on top of that.  Fitted to 660 random problems of 200 to 137400 rows, all seven K, timed
+// with kernel 1 in front beside the tiles' plan: within 4 % of a call's time (rms).  The choice is 1.05 times faster than the tiles alone on geometric
+// average over them, 0.15 % slower than the better of the two, 3 % slower than the tiles at worst (one of 660 by more than 2 %).  us of the GEMM,
+// tiles / this one: 137400 x 1024 -> 4096 385 / 321, 32976 x 2048 -> 4096 161 / 128, 10992 x 1024 -> 4096 38.9 / 29.2, 10992 x 768 -> 3072 25.8 / 21.1,
+// 4096 x 1024 -> 4096 15.9 / 15.6, 2048 x 1024 -> 4096 9.5 / 10.7, 1374 x 2048 -> 4096 12.0 / 15.6.
+inline double e2m3_resident_cost(int M, int N, int K)
+{
+    const double k = K / 1024.0;
+    const int steps = (M + 31) / 32, ranges = e2m3_resident_ranges(M, N);
+    return 1.015 * (5.3 + 2.4 * k + 0.735 * k * ((steps + ranges - 1) / ranges) + 0.112e-6 * 2.0 * M * N);
+}
+inline bool e2m3_resident(int M, int N, int K, bool shifted)
+{
+    if (!e2m3_resident_k(K, shifted)) return false;
+    double tiles;
+    e2m3_gemm_plan(M, N, K, &tiles);
+    return e2m3_resident_cost(M, N, K) < tiles;
 }
 
 }  // namespace qvggt

@@ -248,3 +248,40 @@ def test_gpu_tests_reach_every_variant_of_the_e2m3_tiles(tmp_path):
     every = {("256", "streams"), ("256", "caches"), ("192", "streams"), ("192", "caches"), ("128", "channels first"), ("128", "tokens first"), "divided"}
     shifted = [p for p in E2M3_PLANS if p[2] in (1024, 2048, 4096) and p[0] < 12000 or "+" in p[3]]
     assert variants(E2M3_PLANS + CACHED_PLANS) == every and variants(shifted + CACHED_PLANS) == every
+
+
+RESIDENT_DRIVER = r"""
+#include "gemm_plan.h"
+#include <cstdio>
+int main()
+{
+    int M, N, K, shifted;
+    while (std::scanf("%d %d %d %d", &M, &N, &K, &shifted) == 4)
+        std::printf("%d %d\n", qvggt::e2m3_resident(M, N, K, shifted != 0), qvggt::e2m3_resident_groups(N) * qvggt::e2m3_resident_ranges(M, N));
+}
+"""
+
+
+def test_resident_weights(tmp_path):
+    """The GPU test's table reaches the kernel with every K it takes; no other K does, nor affine codes with those that kernel 1 does not write; the
+    blocks of a launch have a compute unit each unless there are more groups of channels than that."""
+    from tests.test_gpu_e2m3 import RESIDENT
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text(RESIDENT_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+
+    def ask(problems):
+        out = subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
+        return [(int(out[i]), int(out[i + 1])) for i in range(0, len(out), 2)]
+    problems = [(*p, 0) for p in RESIDENT] + [(*p, 1) for p in RESIDENT if p[2] in (1024, 2048)]
+    for p, (resident, _) in zip(problems, ask(problems)):
+        assert resident, p
+    assert {p[2] for p in RESIDENT} == {512, 768, 1024, 1280, 1536, 1792, 2048}
+    rng = random.Random(9)
+    problems = [(int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(8192)))),
+                 rng.choice([128, 256, 512, 768, 1024, 1280, 1536, 1792, 2048, 2560, 3584, 4096, 6144, 8192]), rng.randrange(2)) for _ in range(20000)]
+    for (M, N, K, shifted), (resident, blocks) in zip(problems, ask(problems)):
+        assert not resident or K in ((1024, 2048) if shifted else (512, 768, 1024, 1280, 1536, 1792, 2048))
+        assert blocks <= max(256, (N + 255) // 256)

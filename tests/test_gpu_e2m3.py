@@ -383,6 +383,20 @@ def test_e2m3_gemm_shifted_in_divided_plans(M, N, K, plan):
     test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan)
 
 
+# The kernel with the weights in registers (tests/test_gemm_plan.py holds these to the rule): every K, last steps of 1 to 31 tokens, last waves of 16, 32
+# and 48 channels and waves without any, ranges of unequal length, more groups of channels than compute units, Y through the caches (3056)
+RESIDENT = [(3001, 3088, 512), (40, 66064, 512), (2017, 4112, 768), (5001, 3312, 768), (2015, 4112, 1024), (10992, 3056, 1024), (10990, 1040, 1024),
+            (4005, 4112, 1280), (5001, 3104, 1536), (4997, 4112, 1792), (4005, 4112, 2048), (5000, 3120, 2048)]
+
+
+@pytest.mark.parametrize("M,N,K", RESIDENT)
+def test_e2m3_gemm_with_resident_weights(M, N, K):
+    """As above: the dump comes from the tiles, the Y without it from this kernel."""
+    test_e2m3_gemm_in_every_tile_shape(M, N, K, "")
+    if K in (1024, 2048):
+        test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, "")
+
+
 # The row kernels writing E2M3 blocks, by the entry point itself (a layer takes nibbles at many of these sizes): more groups of rows than blocks, four
 # waves per row with groups of four rows (K = 5120, 6144, 8192 beyond 4096 rows), and channels enough that small K are not one launch
 @pytest.mark.parametrize("f32", [True, False])
