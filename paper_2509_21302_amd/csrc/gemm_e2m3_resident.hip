@@ -38,13 +38,13 @@ __device__ inline void store4(void *base, uint32_t lane_off, uint32_t v)
 template <int AT>
 __device__ inline void dma16_at(uint32_t lane_off, const void *base, uint32_t lds_base)
 {
-    asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base), "n"(AT) : "memory", "m0", "scc");
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base), "n"(AT) : "memory", "m0", "scc");
 }
 
 // 4 bytes per lane
 __device__ inline void dma4(uint32_t lane_off, const void *base, uint32_t lds_base)
 {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 
 // as the matrix builtin takes an operand, of whose eight registers E2M3 numbers fill six
