@@ -77,8 +77,4 @@ struct E2m3Problem {
     }
 };
 
-// The product with the weights resident in registers (gemm_e2m3_resident.hip), for the problems that the plan gives it.
-template <bool SHIFTED>
-hipError_t run_e2m3_resident(const E2m3Problem &p, hipStream_t stream);
-
 }  // namespace qvggt

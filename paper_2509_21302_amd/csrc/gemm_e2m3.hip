@@ -30,13 +30,14 @@
 // Tiles: 256 x 256 per block, one block per compute unit, four waves of 128 x 128 (256 accumulator registers each): the least
 // operand traffic per MFMA that the register file allows; 192 x 256 where that fills the last round better; 128 x 128 blocks, two per
 // compute unit, for problems of less than a round or so, and a kernel without shared stages for few tiles (gemm_plan.h has the rule).  Enough
-// tokens of K up to 2048 go to gemm_e2m3_resident.hip instead: what runs here of a size are few tokens, long K and the accumulator dump.
+// tokens of K up to 2048 go to gemm_resident.hip instead: what runs here of a size are few tokens, long K and the accumulator dump.
 // (256 x 128 blocks, two per compute unit, so that one block's epilogue runs under the other's K loop, were built and measured:
 // the K loop is not limited by the matrix pipes but by what feeds them, and 1.5 times the LDS traffic per MFMA ate the overlap.)
 // The epilogue: accumulators from AGPRs, scale + bias, bf16, rows through a wave-private LDS tile, non-temporal 128-byte line
 // stores.
 #include "e2m3.h"
 #include "gemm_plan.h"
+#include "resident.h"
 
 #include <algorithm>
 #include <cstdlib>
@@ -626,7 +627,9 @@ hipError_t run_e2m3(const E2m3Problem &p, hipStream_t stream)
     if (p.M <= 0) return hipSuccess;
     hipError_t e = prepare_device();                 // the kernels' dynamic-LDS limits on this device (see e2m3_lds_kernels above)
     if (e != hipSuccess) return e;
-    if (p.acc_debug == nullptr && e2m3_resident(p.M, p.N, p.K, SHIFTED)) return run_e2m3_resident<SHIFTED>(p, stream);
+    if (p.acc_debug == nullptr && e2m3_resident(p.M, p.N, p.K, SHIFTED)) {
+        return run_e2m3_resident<SHIFTED>({p.Xf, p.sx, p.Wf, p.sw, p.bias, p.M, p.N, p.K, p.Y, p.xzero, p.wsum}, stream);
+    }
     const E2m3Plan plan = e2m3_gemm_plan(p.M, p.N, p.K);
     if (plan.rows_main == p.M) return launch_e2m3_shape<SHIFTED>(plan.shape, p, stream);
     e = launch_e2m3_shape<SHIFTED>(plan.shape, p.part(0, plan.rows_main), stream);

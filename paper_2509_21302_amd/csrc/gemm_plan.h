@@ -35,7 +35,7 @@ struct GemmPlan {
 // 20000 x 4096 -> 1024 89 / 92 / 71; just past one round of small tiles (big / small) int8 rows 9591 x 4096 -> 896 43 / 66,
 // int8 blocks 22039 x 4096 -> 304 45 / 62, 2247 x 2048 -> 4256 27 / 36, packed codes 39144 x 5120 -> 160 48 / 55.
 // affine and dump: affine activation codes, the accumulator dump (their two tile loops do not fit the registers together: two launches).
-inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, bool affine, bool dump)
+inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, bool affine, bool dump, double *cost = nullptr)
 {
     auto tiles = [&](int rows, int size) { return (double)((rows + size - 1) / size) * ((N + size - 1) / size); };
     auto rounds = [](double t) { return std::ceil(t / 256.0); };
@@ -48,7 +48,10 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
 
     const double small_tiles = tiles(M, 128);
     const bool long_chain = !packed ? ktiles >= 16 : affine ? ktiles >= 8 : ktiles >= 28 && ktiles + small_tiles / 8.0 >= 40.0;
-    if (small_tiles <= 256.0 && long_chain) return {GemmPlan::kDeep, 0};
+    if (small_tiles <= 256.0 && long_chain) {
+        if (cost != nullptr) *cost = deep_round;
+        return {GemmPlan::kDeep, 0};
+    }
     const double big_cost = rounds(tiles(M, 256)) * big_round;
     const double small_rounds = small_tiles / 512.0, whole = std::floor(small_rounds), rest = small_rounds - whole;
     const double small_cost = (whole + (whole > 0.0 && rest > 0.0 ? std::max(rest, LAST_ROUND) : rest)) * small_share * big_round + 3.0;
@@ -59,8 +62,12 @@ inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, b
         const double deep_rounds = tiles(M - rows_main, 128) / 256.0, deep_whole = std::floor(deep_rounds), deep_rest = deep_rounds - deep_whole;
         const double tail_cost = rounds((double)main_tile_rows * tiles_n) * big_round + (affine || dump ? 3.0 : 0.0) +
                                  (deep_whole + (deep_rest == 0.0 ? 0.0 : deep_whole > 0.0 ? std::max(deep_rest, 0.6) : 1.0)) * deep_round;
-        if (tail_cost < std::min(big_cost, small_cost)) return {GemmPlan::kBigThenDeep, rows_main};
+        if (tail_cost < std::min(big_cost, small_cost)) {
+            if (cost != nullptr) *cost = tail_cost;
+            return {GemmPlan::kBigThenDeep, rows_main};
+        }
     }
+    if (cost != nullptr) *cost = std::min(small_cost, big_cost);
     return {small_cost < big_cost ? GemmPlan::kSmall : GemmPlan::kBig, 0};
 }
 
@@ -206,15 +213,15 @@ inline E2m3Plan e2m3_gemm_plan(int M, int N, int K, double *cost = nullptr)
     return {shape, M, shape};
 }
 
-// The kernel with the weights in registers (gemm_e2m3_resident.hip): 256 channels per block, the tokens in as many ranges of steps of 32 as fill the
+// The kernel with the weights in registers (gemm_resident.hip): 256 channels per block, the tokens in as many ranges of steps of 32 as fill the
 // chip.  K where 64 channels of a wave fit beside two sets of results; affine codes are written for K = 1024 and 2048 only.  (K = 128 and 256 have few
 // products per result: 40000 x 128 -> 2048 33.2 us in 256-row tiles, 31.8 in this one, 10992 x 256 -> 1024 8.1 / 8.9.)
 constexpr bool e2m3_resident_k(int K, bool shifted)
 {
     return K == 1024 || K == 2048 || (!shifted && (K == 512 || K == 768 || K == 1280 || K == 1536 || K == 1792));
 }
-inline int e2m3_resident_groups(int N) { return (N + 255) / 256; }
-inline int e2m3_resident_ranges(int M, int N) { return std::max(1, std::min(256 / e2m3_resident_groups(N), (M + 31) / 32)); }
+inline int resident_groups(int N) { return (N + 255) / 256; }
+inline int resident_ranges(int M, int N) { return std::max(1, std::min(256 / resident_groups(N), (M + 31) / 32)); }
 
 // Its price in microseconds, to be compared with the tiles'.  Loading the weights into the registers costs 5.3 + 2.4 k before the first product, a
 // step of a block 0.735 k, and writing Y 0.112 per megabyte on top of that.  Fitted to 660 random problems of 200 to 137400 rows, all seven K, timed
@@ -225,7 +232,7 @@ inline int e2m3_resident_ranges(int M, int N) { return std::max(1, std::min(256 
 inline double e2m3_resident_cost(int M, int N, int K)
 {
     const double k = K / 1024.0;
-    const int steps = (M + 31) / 32, ranges = e2m3_resident_ranges(M, N);
+    const int steps = (M + 31) / 32, ranges = resident_ranges(M, N);
     return 1.015 * (5.3 + 2.4 * k + 0.735 * k * ((steps + ranges - 1) / ranges) + 0.112e-6 * 2.0 * M * N);
 }
 inline bool e2m3_resident(int M, int N, int K, bool shifted)
@@ -234,6 +241,24 @@ inline bool e2m3_resident(int M, int N, int K, bool shifted)
     double tiles;
     e2m3_gemm_plan(M, N, K, &tiles);
     return e2m3_resident_cost(M, N, K) < tiles;
+}
+
+// int8 blocks with the weights in registers: K = 1024, whose 256 channels take half of them (blocks come with K = 1024, 2048 and 4096; at 2048 they would
+// take all).  Few tiles stay with the kernels made for them: alone, those take less than the 8 us that this one needs to begin.  So do few tokens, whose
+// time is the weights' (40 x 66064 19.8 / 23.4, 300 x 66064 53.2 / 47.6).  The others by price
+// in microseconds, fitted to 234 random problems of 100 to 137400 rows (its own within 5 %, rms; 256s cost 4 us more where the rows of Y
+// are no whole lines).  As calls run it, behind kernel 1, the choice is 1.13 times faster than the tiles on the 80 of them that it gives to this kernel,
+// 0.1 % slower than the better of the two over all, 7 % slower than the tiles at worst (3 of 234 by more than 2 %).  us of the GEMM, tiles / this
+// one: 137400 x 4096 637 / 527, 32976 x 4096 153 / 125, 32976 x 1024 41.1 / 36.5, 10992 x 3072 40.9 / 36.7, 2748 x 1024 7.4 / 10.4.
+inline bool i8b_resident(int M, int N, int K)
+{
+    if (K != 1024 || M < 256 || int8_instruction_few_tiles(M, N, K, 8, true) != FewTiles::kNone) return false;
+    double tiles;
+    const GemmPlan plan = int8_instruction_gemm_plan(M, N, K, 8, false, false, &tiles);
+    if (plan.shape == GemmPlan::kDeep) return false;
+    if (plan.shape == GemmPlan::kBig && N % 64 != 0) tiles += 4.0;
+    const int steps = (M + 31) / 32, ranges = resident_ranges(M, N);
+    return 1.03 * (7.4 + 0.89 * ((steps + ranges - 1) / ranges) + 0.236e-6 * 2.0 * M * N) < tiles;
 }
 
 }  // namespace qvggt

@@ -1,30 +1,34 @@
-// Online kernel 2 on the 6-bit floating-point matrix path with the weights resident in registers, for K up to 2048 and enough tokens
-// (e2m3_resident in gemm_plan.h).  Sums, results and operand format are those of gemm_e2m3.hip, bit for bit.
+// Online kernel 2 with the weights resident in registers, for K that they have room for and enough tokens (e2m3_resident and i8b_resident in
+// gemm_plan.h): E2M3 codes on the 6-bit floating-point matrix path, int8 codes on the int8 one.  Sums, results and operand formats are those of
+// gemm_e2m3.hip and gemm_w4a4.hip, bit for bit.
 //
-// A wave keeps 64 channels of all K (12 registers a lane per 64 codes: 192 at K = 1024, 384 at 2048) and the tokens go past it, 32 at a time: a step is
-// K / 32 MFMAs into 32 accumulator registers, and because that is all that a step's results take, there is a second set: the results of one step are
-// scaled and stored between the MFMAs of the next.  That is what the 256 x 256 tiles cannot do, whose accumulators fill half the registers:
-// the matrix pipes idle in their epilogue, two fifths of a tile at K = 1024.  The tokens are also the only operand that moves (24 KiB per
-// step of a block at K = 1024, where the tiles move 24 KiB per 64 codes of K), and a step is fine enough that the last round of a launch wastes
-// little: the tokens are divided evenly, to 32.
+// A wave keeps 64 channels of all K (E2M3: 12 registers a lane per 64 codes, 192 at K = 1024, 384 at 2048; int8: 256 at 1024) and the tokens go past it,
+// 32 at a time: a step is K / 32 (int8 K / 16) MFMAs into 32 accumulator registers, and because that is all that a step's results take, there is a
+// second set: the results of one step are scaled and stored between the MFMAs of the next.  That is what the 256 x 256 tiles cannot do, whose
+// accumulators fill half the registers: the matrix pipes idle in their epilogue, two fifths of a tile at K = 1024 (int8: a third).  The tokens are also the only
+// operand that moves (E2M3: 24 KiB per step of a block at K = 1024, where the tiles move 24 KiB per 64 codes of K), and a step is fine enough that
+// the last round of a launch wastes little: the tokens are divided evenly, to 32.
 //
 // Four waves of 64 channels per block, one block per compute unit, one wave per SIMD.  Tokens go from memory straight into an LDS ring
-// (global_load_lds_dwordx4); each wave reads a fragment for two MFMAs: 117 bytes of LDS traffic per cycle at the matrix rate, 144 in the tiles.  The
-// tokens are the MFMA's row operand, so that a lane holds one channel of each set and neighbouring channels of two sets are a dword of Y: no
+// (global_load_lds_dwordx4); each wave reads a fragment for two MFMAs: 117 bytes of LDS traffic per cycle at the matrix rate, 144 in the tiles (int8: 80).
+// The tokens are the MFMA's row operand, so that a lane holds one channel of each set and neighbouring channels of two sets are a dword of Y: no
 // transposition, a store instruction writes two whole lines.
 //
 // What bounds it: the board's power.  137400 x 1024 -> 4096: 321 us (tiles 385), with all codes zero 233, without the stores 239, without stores and
-// transfers 214, which is the register-only rate of the instruction (5.4 PFLOP/s); the stores alone take 181.  At 8 frames (10992 x 1024 -> 4096, 29 us, tiles
+// transfers 214, which is the register-only rate of the instruction (5.4 PFLOP/s); the stores alone take 181.  int8 codes: 527 us (tiles 637), codes
+// of a sixteenth of the size 482 (548), all zero 328 (409); the register-only rate would be 340.  At 8 frames (10992 x 1024 -> 4096, 29 us, tiles
 // 39) 6 us are the launch and the weights' way into the registers.  Tried and not better: pairs of dwords per store (two swaps more: 1 % slower),
 // fragments read 4 to 7 units ahead instead of 3, stores of wider scope, a wait that counts the stores as well.
 #include "e2m3.h"
 #include "gemm_plan.h"
+#include "resident.h"
 
 namespace qvggt {
 
 namespace {
 
 typedef int v6i __attribute__((ext_vector_type(6)));
+typedef int v16i __attribute__((ext_vector_type(16)));
 
 // 4 bytes per lane to base + lane_off, past the caches or through them
 template <bool STREAM>
@@ -47,38 +51,64 @@ __device__ inline void dma4(uint32_t lane_off, const void *base, uint32_t lds_ba
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 
-// as the matrix builtin takes an operand, of whose eight registers E2M3 numbers fill six
-__device__ inline v8i wide(v6i v) { return __builtin_shufflevector(v, v, 0, 1, 2, 3, 4, 5, -1, -1); }
+// An operand format: a unit is what one MFMA takes of a row's codes, a K-tile of the format holds TILE_UNITS of them.
+struct E2m3Codes {
+    typedef v6i Weights;                                               // a lane's share of a unit
+    typedef v8i Fragment;                                              // as the matrix builtin takes it: E2M3 numbers fill six of the eight registers
+    typedef v16f Sums;
+    static constexpr int TILE_UNITS = 1, ROW_BYTES = U_BYTES, WREGS = 6;
+    static __device__ inline Sums multiply(Fragment f, Weights w, Sums s)
+    {
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f, __builtin_shufflevector(w, w, 0, 1, 2, 3, 4, 5, -1, -1), s, 2, 2, 0, UNIT_SCALE_ONE, 0, UNIT_SCALE_ONE);
+    }
+    static __device__ inline uint32_t first(int r, int h) { return r * U_BYTES + h * 16; }        // a lane's 16 bytes of unit 0 (its other 8 are at 32 + 8 h of the row)
+};
+// "int8 blocks": K-tiles of 64 bytes a row, two units of 32 codes, four 16-byte chunks whose places are swizzled with bits 2 and 3 of the row
+struct Int8Codes {
+    typedef v4i Weights;
+    typedef v4i Fragment;
+    typedef v16i Sums;
+    static constexpr int TILE_UNITS = 2, ROW_BYTES = 64, WREGS = 4;
+    static __device__ inline Sums multiply(Fragment f, Weights w, Sums s) { return __builtin_amdgcn_mfma_i32_32x32x32_i8(f, w, s, 0, 0, 0); }
+    static __device__ inline uint32_t first(int r, int h) { return r * 64 + ((h ^ (r >> 2 & 3)) << 4); }      // unit 1: bit 5 the other way
+};
 
 // Pins values to one half of the register file at this point (accumulator and ordinary registers: the matrix instructions read either).
-__device__ inline void keep_in_accumulators(v6i &a, v6i &b) { asm volatile("" : "+a"(a), "+a"(b)); }
-__device__ inline void keep_in_registers(v6i &a, v6i &b) { asm volatile("" : "+v"(a), "+v"(b)); }
+template <class V>
+__device__ inline void keep_in_accumulators(V &a, V &b) { asm volatile("" : "+a"(a), "+a"(b)); }
+template <class V>
+__device__ inline void keep_in_registers(V &a, V &b) { asm volatile("" : "+v"(a), "+v"(b)); }
 __device__ inline void keep_in_registers(float2 &a) { asm volatile("" : "+v"(a.x), "+v"(a.y)); }
 
-// UNITS of 64 codes per ring stage, PARTS stages per step of 32 tokens: K = 64 * UNITS * PARTS
-template <int UNITS, int PARTS>
+// UNITS per ring stage, PARTS stages per step of 32 tokens: K = 64 * UNITS * PARTS (E2M3), 32 * UNITS * PARTS (int8)
+template <class CODES, int UNITS, int PARTS>
 struct ResidentCfg {
     static constexpr int NW = 4, THREADS = NW * 64;
-    static constexpr int STAGE_BYTES = UNITS * 32 * U_BYTES;
-    static constexpr int STAGES = UNITS <= 16 ? 6 : 5;
+    static constexpr int TILES = UNITS / CODES::TILE_UNITS, TILE_BYTES = 32 * CODES::ROW_BYTES;        // K-tiles of a stage, 32 rows of one
+    static constexpr int RB_TILE = RB * CODES::ROW_BYTES;              // K-tile of a block of the operand format
+    static constexpr int STAGE_BYTES = TILES * TILE_BYTES;
+    static constexpr int STAGES = CODES::TILE_UNITS > 1 ? 8 : UNITS <= 16 ? 6 : 5;
     static constexpr int NT = STAGE_BYTES / 1024;                      // 1 KiB pieces of a stage
     static constexpr int LPW = (NT + NW - 1) / NW, LPW_MIN = NT / NW;  // pieces per wave
     static constexpr int SLOTS = 8, SLOT_BYTES = 512;                  // per step 32 token scales and (SHIFTED) 32 zero points, each twice
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + SLOTS * SLOT_BYTES;
-    static_assert(STAGE_BYTES % 1024 == 0 && LDS_BYTES <= 160 * 1024, "whole pieces; one block per compute unit");
+    static_assert(UNITS % CODES::TILE_UNITS == 0 && STAGE_BYTES % 1024 == 0 && LDS_BYTES <= 160 * 1024, "whole K-tiles and pieces; one block per compute unit");
+    // while stage q runs, the scales of stage q - 1 + STAGES arrive and those of the step before q's are read
+    static_assert((STAGES - 2 + PARTS) / PARTS + 1 < SLOTS, "scales in use are not overwritten");
 };
 
 }  // namespace
 
-template <int UNITS, int PARTS, bool SHIFTED, bool STREAM_Y>
-__global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void e2m3_gemm_resident_kernel(
-    const uint8_t *__restrict__ Xf, const float *__restrict__ sx, const uint8_t *__restrict__ Wf, const float *__restrict__ sw,
+template <class CODES, int UNITS, int PARTS, bool SHIFTED, bool STREAM_Y>
+__global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void resident_gemm_kernel(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq, const float *__restrict__ sw,
     const uint16_t *__restrict__ bias, int M, int N, uint16_t *__restrict__ Y, const float *__restrict__ xzero, const float *__restrict__ wsum,
     int groups, int ranges)
 {
-    using C = ResidentCfg<UNITS, PARTS>;
-    constexpr int ST = C::STAGES, LPW = C::LPW, ALL = UNITS * PARTS;
-    constexpr bool TIGHT = ALL > 28;                                   // short of registers: scalar arithmetic for some addresses, scales at the last moment
+    using C = ResidentCfg<CODES, UNITS, PARTS>;
+    constexpr int ST = C::STAGES, LPW = C::LPW, ALL = UNITS * PARTS, TU = CODES::TILE_UNITS, ALL_TILES = ALL / TU;
+    constexpr int WREGS = 2 * CODES::WREGS;                            // registers of a unit's weights
+    constexpr bool TIGHT = ALL * WREGS > 336;                          // short of registers: scalar arithmetic for some addresses, scales at the last moment
     constexpr int R = UNITS % 4 == 0 ? 4 : 7, D = TIGHT && SHIFTED ? 2 : 3;                           // fragment buffers, units of look-ahead
     static_assert(UNITS % R == 0, "fragment buffers repeat with the stage");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -95,21 +125,23 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     const int step0 = (int)((long long)range * steps / ranges), step1 = (int)((long long)(range + 1) * steps / ranges);
     if (step0 >= step1) return;
 
-    // ---- tokens -> LDS.  A stage holds UNITS units of 32 rows, 1.5 KiB each, contiguous in memory and in the stage
-    constexpr int NOFF = TIGHT ? 3 : LPW;                   // a wave's piece i + 3 is its piece i of 8 units later
+    // ---- tokens -> LDS.  A stage holds K-tiles of 32 rows (E2M3 1.5 KiB, int8 2 KiB), each contiguous in memory and in the stage
+    constexpr int WHOLE = CODES::ROW_BYTES == 48 ? 3 : 1, WHOLE_TILES = WHOLE * C::NW * 1024 / C::TILE_BYTES;
+    constexpr int NOFF = TIGHT || TU > 1 ? WHOLE : LPW;     // a wave's piece i + WHOLE is its piece i of WHOLE_TILES K-tiles later
+    static_assert(WHOLE * C::NW * 1024 % C::TILE_BYTES == 0, "pieces repeat with whole K-tiles");
     uint32_t off[NOFF];
 #pragma unroll
     for (int i = 0; i < NOFF; ++i) {
         const int q = (i * C::NW + wave) * 64 + lane;                  // 16-byte chunk of the stage
-        off[i] = (uint32_t)(q / 96) * RB_BYTES + (uint32_t)(q % 96) * 16;
+        off[i] = (uint32_t)(q / (C::TILE_BYTES / 16)) * C::RB_TILE + (uint32_t)(q % (C::TILE_BYTES / 16)) * 16;
     }
     int ld_step = step0, ld_part = 0, ld_slot = 0;
     const uint32_t dst0 = lds0 + wave * 1024;
     uint32_t ld_dst = dst0;                                            // this wave's first piece of the ring stage to fill
-    const uint8_t *ld_base = Xf + (size_t)(step0 >> 2) * ALL * RB_BYTES + (step0 & 3) * (32 * U_BYTES);
+    const uint8_t *ld_base = Xq + (size_t)(step0 >> 2) * ALL_TILES * C::RB_TILE + (step0 & 3) * C::TILE_BYTES;
     auto issue_piece = [&](auto i_c) {
         constexpr int i = decltype(i_c)::value;
-        const uint8_t *base = ld_base + i / NOFF * 8 * RB_BYTES;
+        const uint8_t *base = ld_base + i / NOFF * WHOLE_TILES * C::RB_TILE;
         if constexpr ((i + 1) * C::NW <= C::NT) dma16_at<i * C::NW * 1024>(off[i % NOFF], base, ld_dst);
         else if (i * C::NW + wave < C::NT) dma16_at<i * C::NW * 1024>(off[i % NOFF], base, ld_dst);       // wave-uniform
     };
@@ -122,13 +154,13 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     };
     auto advance = [&]() {
         ld_dst = ld_dst == dst0 + (ST - 1) * C::STAGE_BYTES ? dst0 : ld_dst + C::STAGE_BYTES;
-        if (PARTS > 1 && ++ld_part < PARTS) { ld_base += UNITS * RB_BYTES; return; }
+        if (PARTS > 1 && ++ld_part < PARTS) { ld_base += C::TILES * C::RB_TILE; return; }
         ld_part = 0;
-        ld_base -= (PARTS - 1) * UNITS * RB_BYTES;
+        ld_base -= (PARTS - 1) * C::TILES * C::RB_TILE;
         ld_slot = (ld_slot + 1) & (C::SLOTS - 1);
         if (ld_step < step1 - 1) {                                     // past the last step: it again (never used)
             ++ld_step;
-            ld_base += (ld_step & 3) != 0 ? 32 * U_BYTES : ALL * RB_BYTES - 3 * 32 * U_BYTES;
+            ld_base += (ld_step & 3) != 0 ? C::TILE_BYTES : ALL_TILES * C::RB_TILE - 3 * C::TILE_BYTES;
         }
     };
     auto issue_stage = [&]() {
@@ -154,36 +186,41 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
         bv = make_float2(__uint_as_float(b << 16), __uint_as_float(b & 0xFFFF0000u));
     }
     if constexpr (SHIFTED) wsv = *reinterpret_cast<const float2 *>(wsum + chan);
-    v6i W[2][ALL];
+    typename CODES::Weights W[2][ALL];
     if (!idle) {
-        const uint8_t *p[2];
+        const uint8_t *p[2][TU];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int r = ch0 + (32 * j + 2 * (c & 15) + (c >> 4)) % chans;
-            p[j] = Wf + (size_t)(r / RB) * ALL * RB_BYTES + (r % RB) * U_BYTES + h * 16;
+#pragma unroll
+            for (int t = 0; t < TU; ++t) p[j][t] = Wq + (size_t)(r / RB) * ALL_TILES * C::RB_TILE + (CODES::first(r % RB, h) ^ t << 5);
         }
         auto load = [&](auto u_c) {
             constexpr int u = decltype(u_c)::value;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const v4i lo = *reinterpret_cast<const v4i *>(p[j] + u * RB_BYTES);
-                const int2 hi = *reinterpret_cast<const int2 *>(p[j] + u * RB_BYTES + 32 - h * 8);
-                W[j][u] = v6i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y};
+                const v4i lo = *reinterpret_cast<const v4i *>(p[j][u % TU] + u / TU * C::RB_TILE);
+                if constexpr (CODES::WREGS == 6) {
+                    const int2 hi = *reinterpret_cast<const int2 *>(p[j][0] + u * C::RB_TILE + 32 - h * 8);
+                    W[j][u] = v6i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y};
+                } else {
+                    W[j][u] = lo;
+                }
             }
         };
-        constexpr int AHEAD = ALL > 28 ? 8 : ALL < 14 ? ALL : 14;                     // 56 loads in flight; 32 where the registers do not hold more
+        constexpr int AHEAD = TU * (TIGHT ? 8 : ALL_TILES < 14 ? ALL_TILES : 14);     // 56 loads in flight; 32 where the registers do not hold more
         e_static_for<AHEAD>(load);
         e_static_for<ALL>([&](auto u_c) {
             constexpr int u = decltype(u_c)::value;
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < 6; ++e) {
+            for (int e = 0; e < CODES::WREGS; ++e) {
                 const auto s = __builtin_amdgcn_permlane16_swap((uint32_t)W[0][u][e], (uint32_t)W[1][u][e], false, false);
                 W[0][u][e] = (int)s[0];
                 W[1][u][e] = (int)s[1];
             }
             // where they stay; without a word the compiler moves some of them about in the loop (60 moves a step, 5 % of the kernel)
-            if constexpr (u < 21) keep_in_accumulators(W[0][u], W[1][u]);
+            if constexpr ((u + 1) * WREGS <= 252) keep_in_accumulators(W[0][u], W[1][u]);
             else keep_in_registers(W[0][u], W[1][u]);
             if constexpr (u + AHEAD < ALL) load(std::integral_constant<int, u + AHEAD>{});
         });
@@ -208,23 +245,27 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     }
 
     // ---- fragments of the tokens
-    v8i F[R];
+    typename CODES::Fragment F[R];
+    if constexpr (TU == 1) {
 #pragma unroll
-    for (int f = 0; f < R; ++f) { F[f][6] = 0; F[f][7] = 0; }
-    const uint32_t frag = c * U_BYTES + h * 16, h8 = h * 8;
+        for (int f = 0; f < R; ++f) { F[f][6] = 0; F[f][7] = 0; }
+    }
+    const uint32_t frag = CODES::first(c, h), h8 = h * 8;
     auto read_lo = [&](auto f_c, int u, const uint8_t *stage) {
         constexpr int f = decltype(f_c)::value;
-        const v4i v = *reinterpret_cast<const v4i *>(stage + u * (32 * U_BYTES));
+        const v4i v = *reinterpret_cast<const v4i *>(stage + (frag ^ u % TU << 5) + u / TU * C::TILE_BYTES);
         F[f][0] = v[0]; F[f][1] = v[1]; F[f][2] = v[2]; F[f][3] = v[3];
     };
     auto read_hi = [&](auto f_c, int u, const uint8_t *stage) {
-        constexpr int f = decltype(f_c)::value;
-        const int2 v = *reinterpret_cast<const int2 *>(stage + 32 - h8 + u * (32 * U_BYTES));
-        F[f][4] = v.x; F[f][5] = v.y;
+        if constexpr (CODES::WREGS == 6) {
+            constexpr int f = decltype(f_c)::value;
+            const int2 v = *reinterpret_cast<const int2 *>(stage + frag + 32 - h8 + u * C::TILE_BYTES);
+            F[f][4] = v.x; F[f][5] = v.y;
+        }
     };
 
     // ---- results: register r of an accumulator is token 8 (r / 4) + 4 h + r % 4 of the step
-    v16f acc[2][2];
+    typename CODES::Sums acc[2][2];
     float4 st[4], zt[SHIFTED ? 4 : 1];
     int cs = 0, slot = 0;                                              // ring stage being multiplied (its LDS offset), scales of the step whose results leave
     const uint32_t row_bytes = (uint32_t)N * 2;
@@ -241,7 +282,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     auto result = [&](auto b_c, int r) {
         constexpr int b = decltype(b_c)::value;
         const float s = (&st[r / 4].x)[r % 4];
-        float a0 = acc[b][0][r], a1 = acc[b][1][r];
+        float a0 = (float)acc[b][0][r], a1 = (float)acc[b][1][r];
         if constexpr (SHIFTED) {
             const float z = 7.5f - (&zt[r / 4].x)[r % 4];
             a0 = fmaf(z, wsv.x, a0);
@@ -258,15 +299,14 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
         e_wait_vmcnt<(ST - 3) * C::LPW_MIN>();
         __syncthreads();
         const int ns = cs == (ST - 1) * C::STAGE_BYTES ? 0 : cs + C::STAGE_BYTES;
-        const uint8_t *from = smem + cs + frag;
-        const v16f zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        const uint8_t *from = smem + cs;
+        const typename CODES::Sums zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         if constexpr (!FIRST && part == 0) read_scales(0);
         e_static_for<2 * UNITS>([&](auto t_c) {
             constexpr int t = decltype(t_c)::value, u = t / 2, j = t % 2, un = u + D;
-            acc[b][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[u % R], wide(W[j][part * UNITS + u]), part == 0 && u == 0 ? zero : acc[b][j], 2, 2, 0,
-                                                                        UNIT_SCALE_ONE, 0, UNIT_SCALE_ONE);
+            acc[b][j] = CODES::multiply(F[u % R], W[j][part * UNITS + u], part == 0 && u == 0 ? zero : acc[b][j]);
             using FB = std::integral_constant<int, un % R>;
-            if constexpr (un == UNITS && j == 0) from = smem + ns + frag;
+            if constexpr (un == UNITS && j == 0) from = smem + ns;
             if constexpr (j == 0) read_lo(FB{}, un % UNITS, from);
             else read_hi(FB{}, un % UNITS, from);
             if constexpr (t == 0) issue_scales();
@@ -308,8 +348,8 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     using I1 = std::integral_constant<int, 1>;
 
     e_static_for<D>([&](auto u_c) {
-        read_lo(u_c, decltype(u_c)::value, smem + frag);
-        read_hi(u_c, decltype(u_c)::value, smem + frag);
+        read_lo(u_c, decltype(u_c)::value, smem);
+        read_hi(u_c, decltype(u_c)::value, smem);
     });
     step(I0{}, std::true_type{});
     int left = step1 - step0 - 1;
@@ -326,49 +366,59 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     e_wait_vmcnt<0>();      // transfers issued past the last step must not outlive the block's LDS allocation
 }
 
-#define QVGGT_RESIDENT(UNITS, PARTS, SHIFTED)                                                                                     \
-    {reinterpret_cast<const void *>(e2m3_gemm_resident_kernel<UNITS, PARTS, SHIFTED, true>), ResidentCfg<UNITS, PARTS>::LDS_BYTES}, \
-    {reinterpret_cast<const void *>(e2m3_gemm_resident_kernel<UNITS, PARTS, SHIFTED, false>), ResidentCfg<UNITS, PARTS>::LDS_BYTES}
-static const LdsKernel resident_lds_kernel_list[] = {QVGGT_RESIDENT(8, 1, false), QVGGT_RESIDENT(12, 1, false), QVGGT_RESIDENT(20, 1, false), QVGGT_RESIDENT(14, 2, false),
-                                                     QVGGT_RESIDENT(16, 1, false), QVGGT_RESIDENT(12, 2, false), QVGGT_RESIDENT(16, 2, false),
-                                                     QVGGT_RESIDENT(16, 1, true), QVGGT_RESIDENT(16, 2, true)};
+#define QVGGT_RESIDENT(CODES, UNITS, PARTS, SHIFTED)                                                                                                       \
+    {reinterpret_cast<const void *>(resident_gemm_kernel<CODES, UNITS, PARTS, SHIFTED, true>), ResidentCfg<CODES, UNITS, PARTS>::LDS_BYTES}, \
+    {reinterpret_cast<const void *>(resident_gemm_kernel<CODES, UNITS, PARTS, SHIFTED, false>), ResidentCfg<CODES, UNITS, PARTS>::LDS_BYTES}
+static const LdsKernel resident_lds_kernel_list[] = {
+    QVGGT_RESIDENT(E2m3Codes, 8, 1, false), QVGGT_RESIDENT(E2m3Codes, 12, 1, false), QVGGT_RESIDENT(E2m3Codes, 20, 1, false), QVGGT_RESIDENT(E2m3Codes, 14, 2, false),
+    QVGGT_RESIDENT(E2m3Codes, 16, 1, false), QVGGT_RESIDENT(E2m3Codes, 12, 2, false), QVGGT_RESIDENT(E2m3Codes, 16, 2, false),
+    QVGGT_RESIDENT(E2m3Codes, 16, 1, true), QVGGT_RESIDENT(E2m3Codes, 16, 2, true), QVGGT_RESIDENT(Int8Codes, 16, 2, false)};
 #undef QVGGT_RESIDENT
 static const LdsKernels resident_lds_kernels(resident_lds_kernel_list);
 
 namespace {
 
-template <int UNITS, int PARTS, bool SHIFTED>
-hipError_t launch_resident(const E2m3Problem &p, hipStream_t stream)
+template <class CODES, int UNITS, int PARTS, bool SHIFTED>
+hipError_t launch_resident(const ResidentProblem &p, hipStream_t stream)
 {
-    using C = ResidentCfg<UNITS, PARTS>;
-    const auto kern = e2m3_streams_y(p.M, p.N) ? e2m3_gemm_resident_kernel<UNITS, PARTS, SHIFTED, true> : e2m3_gemm_resident_kernel<UNITS, PARTS, SHIFTED, false>;
-    const int groups = e2m3_resident_groups(p.N), ranges = e2m3_resident_ranges(p.M, p.N);
-    kern<<<(groups * ranges + 7) / 8 * 8, C::THREADS, C::LDS_BYTES, stream>>>(p.Xf, p.sx, p.Wf, p.sw, p.bias, p.M, p.N, p.Y, p.xzero, p.wsum, groups, ranges);
+    using C = ResidentCfg<CODES, UNITS, PARTS>;
+    const auto kern = e2m3_streams_y(p.M, p.N) ? resident_gemm_kernel<CODES, UNITS, PARTS, SHIFTED, true> : resident_gemm_kernel<CODES, UNITS, PARTS, SHIFTED, false>;
+    const int groups = resident_groups(p.N), ranges = resident_ranges(p.M, p.N);
+    kern<<<(groups * ranges + 7) / 8 * 8, C::THREADS, C::LDS_BYTES, stream>>>(p.Xq, p.sx, p.Wq, p.sw, p.bias, p.M, p.N, p.Y, p.xzero, p.wsum, groups, ranges);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// The sizes of K are those of e2m3_resident_k; SHIFTED codes come with K = 1024 and 2048 only.
+// E2M3 blocks: the sizes of K are those of e2m3_resident_k; SHIFTED codes come with K = 1024 and 2048 only.
 template <bool SHIFTED>
-hipError_t run_e2m3_resident(const E2m3Problem &p, hipStream_t stream)
+hipError_t run_e2m3_resident(const ResidentProblem &p, hipStream_t stream)
 {
     switch (p.K) {
-        case 1024: return launch_resident<16, 1, SHIFTED>(p, stream);
-        case 2048: return launch_resident<16, 2, SHIFTED>(p, stream);
+        case 1024: return launch_resident<E2m3Codes, 16, 1, SHIFTED>(p, stream);
+        case 2048: return launch_resident<E2m3Codes, 16, 2, SHIFTED>(p, stream);
     }
     if constexpr (!SHIFTED) {
         switch (p.K) {
-            case 512: return launch_resident<8, 1, false>(p, stream);
-            case 768: return launch_resident<12, 1, false>(p, stream);
-            case 1280: return launch_resident<20, 1, false>(p, stream);
-            case 1536: return launch_resident<12, 2, false>(p, stream);
-            case 1792: return launch_resident<14, 2, false>(p, stream);
+            case 512: return launch_resident<E2m3Codes, 8, 1, false>(p, stream);
+            case 768: return launch_resident<E2m3Codes, 12, 1, false>(p, stream);
+            case 1280: return launch_resident<E2m3Codes, 20, 1, false>(p, stream);
+            case 1536: return launch_resident<E2m3Codes, 12, 2, false>(p, stream);
+            case 1792: return launch_resident<E2m3Codes, 14, 2, false>(p, stream);
         }
     }
     return hipErrorInvalidValue;
 }
-template hipError_t run_e2m3_resident<false>(const E2m3Problem &, hipStream_t);
-template hipError_t run_e2m3_resident<true>(const E2m3Problem &, hipStream_t);
+template hipError_t run_e2m3_resident<false>(const ResidentProblem &, hipStream_t);
+template hipError_t run_e2m3_resident<true>(const ResidentProblem &, hipStream_t);
+
+// int8 blocks, K = 1024
+hipError_t run_i8b_resident(const ResidentProblem &p, hipStream_t stream)
+{
+    if (p.K != 1024) return hipErrorInvalidValue;
+    hipError_t e = prepare_device();
+    if (e != hipSuccess) return e;
+    return launch_resident<Int8Codes, 16, 2, false>(p, stream);
+}
 
 }  // namespace qvggt

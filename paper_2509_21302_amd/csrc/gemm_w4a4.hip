@@ -40,6 +40,7 @@
 // work runs in the shadow of the matrix pipe.
 #include "gemm_plan.h"
 #include "qvggt_common.h"
+#include "resident.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -808,8 +809,10 @@ hipError_t run_i8b_gemm(const int8_t *Xb, const float *sx, const int8_t *Wb, con
                         int K, void *Y, int32_t *acc_debug, hipStream_t stream)
 {
     if (M <= 0) return hipSuccess;
-    return gemm_by_plan<8, false, true>(reinterpret_cast<const uint8_t *>(Xb), sx, reinterpret_cast<const uint8_t *>(Wb), sw, bias,
-                                          M, N, K, Y, acc_debug, stream);
+    const uint8_t *xq = reinterpret_cast<const uint8_t *>(Xb), *wq = reinterpret_cast<const uint8_t *>(Wb);
+    if (acc_debug == nullptr && i8b_resident(M, N, K))
+        return run_i8b_resident({xq, sx, wq, sw, static_cast<const uint16_t *>(bias), M, N, K, static_cast<uint16_t *>(Y), nullptr, nullptr}, stream);
+    return gemm_by_plan<8, false, true>(xq, sx, wq, sw, bias, M, N, K, Y, acc_debug, stream);
 }
 
 }  // namespace qvggt

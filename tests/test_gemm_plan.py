@@ -257,7 +257,7 @@ int main()
 {
     int M, N, K, shifted;
     while (std::scanf("%d %d %d %d", &M, &N, &K, &shifted) == 4)
-        std::printf("%d %d\n", qvggt::e2m3_resident(M, N, K, shifted != 0), qvggt::e2m3_resident_groups(N) * qvggt::e2m3_resident_ranges(M, N));
+        std::printf("%d %d %d\n", qvggt::e2m3_resident(M, N, K, shifted != 0), qvggt::resident_groups(N) * qvggt::resident_ranges(M, N), qvggt::i8b_resident(M, N, K));
 }
 """
 
@@ -266,6 +266,7 @@ def test_resident_weights(tmp_path):
     """The GPU test's table reaches the kernel with every K it takes; no other K does, nor affine codes with those that kernel 1 does not write; the
     blocks of a launch have a compute unit each unless there are more groups of channels than that."""
     from tests.test_gpu_e2m3 import RESIDENT
+    from tests.test_gpu_int8_blocks import RESIDENT as INT8
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no host C++ compiler")
@@ -274,14 +275,16 @@ def test_resident_weights(tmp_path):
 
     def ask(problems):
         out = subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
-        return [(int(out[i]), int(out[i + 1])) for i in range(0, len(out), 2)]
+        return [(int(out[i]), int(out[i + 1]), int(out[i + 2])) for i in range(0, len(out), 3)]
     problems = [(*p, 0) for p in RESIDENT] + [(*p, 1) for p in RESIDENT if p[2] in (1024, 2048)]
-    for p, (resident, _) in zip(problems, ask(problems)):
+    for p, (resident, _, _) in zip(problems, ask(problems)):
         assert resident, p
     assert {p[2] for p in RESIDENT} == {512, 768, 1024, 1280, 1536, 1792, 2048}
+    assert all(int8 for _, _, int8 in ask([(*p, 1024, 0) for p in INT8]))
     rng = random.Random(9)
     problems = [(int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(8192)))),
                  rng.choice([128, 256, 512, 768, 1024, 1280, 1536, 1792, 2048, 2560, 3584, 4096, 6144, 8192]), rng.randrange(2)) for _ in range(20000)]
-    for (M, N, K, shifted), (resident, blocks) in zip(problems, ask(problems)):
+    for (M, N, K, shifted), (resident, blocks, int8) in zip(problems, ask(problems)):
         assert not resident or K in ((1024, 2048) if shifted else (512, 768, 1024, 1280, 1536, 1792, 2048))
+        assert not int8 or K == 1024
         assert blocks <= max(256, (N + 255) // 256)

@@ -82,6 +82,33 @@ def test_i8b_gemm_both_tile_shapes(M, N, K):
     assert np.array_equal(acc[torch.from_numpy(rows).to(G.DEV)].cpu().numpy(), oracle.int_gemm(qx[rows], qw))
 
 
+# The kernel with the weights in registers (tests/test_gemm_plan.py holds these to the rule): last steps of 1 to 31 tokens, ranges of unequal length, last
+# waves of 16 and 48 channels and waves without any, more groups of channels than compute units, Y past the caches and through them (3056)
+RESIDENT = [(2017, 4112), (10993, 3056), (8223, 3120), (20995, 1040), (300, 66064)]
+
+
+@pytest.mark.parametrize("M,N", RESIDENT)
+@pytest.mark.parametrize("with_bias", [True, False])
+def test_i8b_gemm_with_resident_weights(M, N, with_bias):
+    """Every row equals the row-major kernel's, all 256 codes and sums beyond 2^24 among them."""
+    K = 1024
+    g = torch.Generator(device=G.DEV).manual_seed(M + N)
+    Xl = torch.randint(-128, 128, (M, K), generator=g, device=G.DEV, dtype=torch.int8)
+    Wl = torch.randint(-128, 128, (N, K), generator=g, device=G.DEV, dtype=torch.int8)
+    Xl[:: 37] = -128
+    Wl[:: 19] = -128
+    Xb, Wb = (torch.full((G.q.qvggt_i8b_bytes(c.shape[0], K),), 0x5A, dtype=torch.int8, device=G.DEV) for c in (Xl, Wl))
+    G.q.qvggt_int8_to_blocks(Xl, M, K, Xb)
+    G.q.qvggt_int8_to_blocks(Wl, N, K, Wb)
+    dx, dw = torch.rand(M, device=G.DEV, generator=g) + 0.1, torch.rand(N, device=G.DEV, generator=g) * 1e-3
+    bias = torch.randn(N, device=G.DEV, generator=g).to(torch.bfloat16) if with_bias else None
+    Y = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device=G.DEV)
+    want = Y.clone()
+    G.q.qvggt_i8b_gemm(Xb, dx, Wb, dw, bias, M, N, K, Y, None)
+    G.q.qvggt_i8_gemm(Xl, dx, Wl, dw, bias, M, N, K, want, None)
+    assert torch.equal(Y, want)              # the row behind the last one is not written
+
+
 @pytest.mark.parametrize("K,rows", [(1024, 1031), (2048, 300), (4096, 203)])
 @pytest.mark.parametrize("bits", [8, 6])
 def test_rotate_quant_i8b_equals_the_row_major_kernel(K, rows, bits):
