@@ -4,8 +4,9 @@
 // adds and subtracts.  Element e = a * m + b (a < 2^n, b < m); a wavefront owns a row, lane l holds the m values of every
 // a = l + 64 * c: the m-point transform is inside a lane, the six low bits of a go through cross-lane exchanges, the
 // remaining bits are register-to-register butterflies.  Codes are written in natural order (element e -> position e).
-// This is the general path: VGGT-1B itself has no layer that needs it.  Bound by the vector ALU (34350 x 768 bf16: 38 us with dense
+// This is the general path: VGGT-1B itself has no layer that needs it, and many bf16 rows are quantized in rotate_quant_paley.hip.  Bound by the vector ALU (34350 x 768 bf16: 38 us with dense
 // m-point sums and the lane bits through LDS, 28 us now).
+#include "paley.h"
 #include "qvggt_common.h"
 #include "rotate_rows.h"
 
@@ -16,36 +17,6 @@
 namespace qvggt {
 
 namespace gen {
-
-// ---- Paley's matrices, entry (r, c) in {+1, -1}, from the squares of GF(q) found by enumeration
-template <int Q>
-constexpr bool is_square_mod(int x)
-{
-    x %= Q;
-    if (x < 0) x += Q;
-    for (int k = 1; k < Q; ++k)
-        if ((k * k) % Q == x) return true;
-    return false;
-}
-
-template <int MM>
-constexpr int paley_entry(int r, int c)
-{
-    static_assert(MM == 12 || MM == 20 || MM == 28, "Paley matrices of order 12, 20 and 28");
-    if constexpr (MM == 28) {
-        // type II, q = 13: symmetric conference matrix of order 14 blown up by 2 x 2 blocks
-        const int i = r / 2, j = c / 2, u = r % 2, v = c % 2;
-        if (i == j) return (u == 0 && v == 0) ? 1 : -1;                       // the zero diagonal becomes [[1, -1], [-1, -1]]
-        const int cc = (i == 0 || j == 0) ? 1 : (is_square_mod<13>(i - j) ? 1 : -1);
-        return (u == 1 && v == 1) ? -cc : cc;                                 // +-1 becomes +-[[1, 1], [1, -1]]
-    } else {
-        // type I, q = MM - 1: identity plus the skew matrix bordered by +1 (first row) and -1 (first column)
-        if (r == c) return 1;
-        if (r == 0) return 1;
-        if (c == 0) return -1;
-        return is_square_mod<MM - 1>(r - c) ? 1 : -1;
-    }
-}
 
 // Inputs 4 g .. 4 g + 3 of output c, up to the sign of the first: which of the sums x0 +- x1 +- (x2 +- x3) they make (bit 0: x1 subtracted,
 // bit 1: x3 against x2, bit 2: x2 against x0)

@@ -325,6 +325,44 @@ def test_rotate_quant_sizes_with_a_paley_factor(K, dtype):
         G.check_scales(sx.cpu().numpy(), dx, f"K={K} bits={bits}")
 
 
+@pytest.mark.parametrize("K", [768, 1536, 3072, 6144, 2560, 5120])
+@pytest.mark.parametrize("rows", [4095, 6149])
+def test_many_rows_with_a_paley_factor(K, rows):
+    """Enough bf16 rows for the matrix-core kernel, the last tiles partial: rows of the first, middle and last tiles against the oracle, as packed and
+    int8 codes and with a given step (E2M3: the packed codes, in test_gpu_e2m3.py); rows without a code range among them, whose neighbours in a tile are not touched by them."""
+    rng = np.random.default_rng(K + rows)
+    X = synth.f32_to_bf16_bits(rng.standard_t(3, (rows, K)).astype(np.float32) * (1.0 + np.arange(rows) % 5)[:, None].astype(np.float32))
+    bad = {1: 0x0000, 6: 0x7FC0, 11: 0x7F80, rows - 2: 0x7F61}                  # zeros, a NaN, an infinity, values that overflow in the transform
+    for r, v in bad.items():
+        X[r] = 0 if v == 0 else X[r]
+        X[r, K // 2 :: 3] = v
+    near = np.concatenate([np.arange(16), np.arange(rows // 2, rows // 2 + 8), np.arange(rows - 9, rows)])
+    good = np.setdiff1d(near, list(bad))
+    signs = (rng.integers(0, 2, K) * 2 - 1).astype(np.int8)
+    inv = (1.0 / (np.sqrt(K) * np.exp(rng.uniform(-1, 1, K)))).astype(np.float32)
+    c_hat = 1.0 / (inv.astype(np.float64) * np.sqrt(K))
+    Xd, sg, iv = G.to_dev(X), G.to_dev(signs), G.to_dev(inv)
+    for bits in (4, 8):
+        dx, qx, Z = oracle.rotate_smooth_quant(X[good], c_hat, pre_signs=signs, bits=bits)
+        if bits == 4:
+            Xq, sx = G.gpu_rsq(Xd, sg, iv)
+            codes = G.gpu_unpack(Xq, K)
+            step = np.full(rows, np.median(dx) * 0.6, dtype=np.float32)
+            given, _ = G.gpu_rsq_static(Xd, sg, iv, G.to_dev(step), 1)
+            G.check_codes(G.gpu_unpack(given, K)[good], oracle.quantize_rows_static(Z, step[good].astype(np.float64), 4), f"K={K} given step")
+        else:
+            Xq, sx = G.gpu_rsq_i8(Xd, sg, iv, bits)
+            codes = G.gpu_layout_int8(Xq, 0).cpu().numpy()
+        G.check_codes(codes[good], qx, f"K={K} bits={bits}")
+        G.check_scales(sx.cpu().numpy()[good], dx, f"K={K} bits={bits}")
+        assert not codes[list(bad)].any()
+    # without signs and multipliers: the plain transform
+    dx, qx, _ = oracle.rotate_smooth_quant(X[good], np.ones(K))
+    Xq, sx = G.gpu_rsq(Xd, None, None)
+    G.check_codes(G.gpu_unpack(Xq, K)[good], qx, f"K={K} plain")
+    G.check_scales(sx.cpu().numpy()[good], dx, f"K={K} plain")
+
+
 @pytest.mark.parametrize("K,N", [(768, 256), (2560, 144), (3584, 512), (5120, 144), (6144, 80), (8192, 48)])
 def test_linear_end_to_end_with_a_paley_factor(K, N):
     """Whole path (statistic, weight preparation, rotate-quantize, integer GEMM, epilogue) on a size 2^n * m, and on the sizes whose rows,
