@@ -353,7 +353,7 @@ hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K
 int paley_matrix_core_rows(int K);
 hipError_t run_rotate_quant_paley(const void *X, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
                                   const float *step, int step_stride, int form, float qmax, hipStream_t stream);
-// Many activation rows (mul_mode 0) with a Paley factor.  fp32 values are no exact operands of the matrix instruction, and weights, as many rows as a layer
+// Many activation rows (mul_mode 0) with a Paley factor, or of 8192 values.  fp32 values are no exact operands of the matrix instruction, and weights, as many rows as a layer
 // has channels, keep one kernel whatever their number, so that all forms of their codes are the same.
 static bool paley_on_matrix_cores(bool f32, int rows, int K, int mul_mode) { return !f32 && mul_mode == 0 && rows >= paley_matrix_core_rows(K); }
 

@@ -1,7 +1,8 @@
-// Kernel 1 on the matrix cores for many bf16 rows of K = 2^n * m values, m = 12 or 20 (a Paley factor).  Few rows, fp32 ones, weights, the column
-// statistic and the other sizes are in rotate_quant_general.hip.
+// Kernel 1 on the matrix cores for many bf16 rows of K = 2^n * m values, m = 12 or 20 (a Paley factor), and of K = 8192 (H_16 in its
+// place).  Few rows, fp32 ones, weights, the column
+// statistic and the other sizes are in rotate_quant_general.hip, resp. rotate_quant.hip.
 //
-// H_K = H_{K / S} (x) (H_8 (x) H_m), S = 8 m = 96 or 160.  A row is a (K / S) x S matrix of segments; its product with the right factor is taken
+// H_K = H_{K / S} (x) (H_8 (x) H_m), S = 8 m = 96, 160 or 128.  A row is a (K / S) x S matrix of segments; its product with the right factor is taken
 // on the matrix cores: the inputs and the +-1 entries are exact bf16 operands, the sums accumulate in fp32, and S is whole in 32-column
 // tiles where m itself would leave lanes idle.  The left factor is 3 to 6 butterfly stages between the accumulator registers, as in
 // rotate_quant_mfma.hip, whose order of MFMA rows this kernel has.
@@ -9,7 +10,7 @@
 // Order of the contraction: a k-step of 16 is four values of b (4 q ..) for four values of the segment's three-bit index a (bit 2: the step,
 // bit 1: the lane half, bit 0: the operand's two pieces of 8 bytes); a column tile is four outputs b' (4 nt ..) for all eight a'.  The operand
 // of the +-1 entries then depends on the step only through q, and through the sign of bit 2 of a' (one xor): m^2 / 16 fragments instead of twice as many,
-// in registers for m = 12 (36; at K = 6144 there is no room), in LDS otherwise (25 KiB).
+// in registers for m = 12 (36; at K = 6144 there is no room), in LDS otherwise (25 KiB, m = 16: 16).
 //
 // Codes are in natural order (element e at position e).  A lane's results are one column of all segments; its codes go to LDS one by one, where the row's
 // input was, and leave from there in whole units (E2M3: staged as bf16 numbers, which a conversion takes 32 at a time; converting staged bytes
@@ -48,8 +49,8 @@ struct Cfg {
     static constexpr int WAVE_LDS = 32 * RT * PITCH;
     // What a wave has no registers for beside another on its SIMD is in LDS, and where two blocks do not fit there a block has eight waves
     static constexpr bool SHARED = HB == 64 || (MM == 20 && HB >= 16);
-    static constexpr int WAVES = SHARED ? 8 : 4;
-    static constexpr int BLOCKS_PER_CU = SHARED ? 1 : 2;
+    static constexpr int WAVES = SHARED && MM != 16 ? 8 : 4;          // eight waves' rows of 8192 values are 136 KiB and the tables 48
+    static constexpr int BLOCKS_PER_CU = SHARED ? 1 : 2, WAVES_PER_SIMD = WAVES * BLOCKS_PER_CU / 4;
     static constexpr bool TABLES_IN_LDS = MM != 12 || SHARED;         // the +-1 fragments and the multipliers
     static constexpr int FRAGMENTS_AT = WAVES * WAVE_LDS, MULTIPLIERS_AT = FRAGMENTS_AT + (TABLES_IN_LDS ? NT * NT * 1024 : 0);
     static constexpr int LDS_BYTES = MULTIPLIERS_AT + (TABLES_IN_LDS ? K * 4 : 0);
@@ -63,7 +64,8 @@ constexpr uint32_t neg_row(int b)
 {
     uint32_t m = 0;
     for (int c = 0; c < MM; ++c)
-        if (gen::paley_entry<MM>(b, c) < 0) m |= 1u << c;
+        if constexpr (MM == 16) m |= (uint32_t)(__builtin_popcount(b & c) & 1) << c;      // the power of two: H_16
+        else m |= (gen::paley_entry<MM>(b, c) < 0 ? 1u : 0u) << c;
     return m;
 }
 template <int MM>
@@ -87,7 +89,7 @@ __device__ inline int segment_of_row(int m)
 
 // CB: 4 packed nibbles, 8 int8 rows, 6 E2M3 blocks.  mul, step and qmax as rotate_rows_general_kernel.
 template <int MM, int HB, int CB>
-__global__ __launch_bounds__((pal::Cfg<MM, HB>::WAVES * 64), 2) void rotate_quant_paley_kernel(
+__global__ __launch_bounds__((pal::Cfg<MM, HB>::WAVES * 64), (pal::Cfg<MM, HB>::WAVES_PER_SIMD)) void rotate_quant_paley_kernel(
     const uint16_t *__restrict__ X, int rows, const int8_t *__restrict__ signs, const float *__restrict__ mul,
     uint8_t *__restrict__ out, float *__restrict__ scale, const float *__restrict__ step, int step_stride, float qmax)
 {
@@ -411,7 +413,7 @@ static hipError_t launch_paley(const void *X, int rows, const int8_t *signs, con
     return hipGetLastError();
 }
 
-// From how many bf16 activation rows this kernel is the faster one.  A wave has 3072 to 6144 values of its own, the general kernel's a quarter of that or
+// From how many bf16 activation rows this kernel is the faster one.  A wave has 3072 to 8192 values of its own, the general kernel's a quarter of that or
 // less, so that few rows are better off there (16 rows with 512 channels: K = 2560 11.2 us there, 12.7 here, 5120 11.1 / 15.6, 6144 12.2 / 17.4).  us
 // there / here, the layer with 512 channels, E2M3 codes and in brackets int8 rows:
 //    768   1374  9.1 /  9.4           4097 12.6 / 12.2 (14.7 / 14.7)    24000  34.2 /  31.0  (35.1 /  35.4)
@@ -420,6 +422,7 @@ static hipError_t launch_paley(const void *X, int rows, const int8_t *signs, con
 //   6144   2300 42.7 / 42.8 (51.9 / 53.3)  4097 65.2 / 49.7 (61.6 / 55.2)    24000 254.2 / 148.8 (248.9 / 170.3)
 //   2560   1374 16.3 / 16.7 (25.0 / 25.6)  4097 26.5 / 23.4 (31.8 / 30.3)    24000  84.4 /  63.2  (92.3 /  75.6)
 //   5120   2300 33.8 / 35.2 (47.8 / 48.0)  4097 49.7 / 41.4 (56.3 / 49.7)    24000 187.8 / 123.7 (219.7 / 141.1)
+//   8192   2300 52.1 / 51.9 (61.7 / 62.1)  4097 81.5 / 70.3 (80.6 / 75.9)    24000 342.6 / 255.8 (373.9 / 266.2)   (there: rotate_rows_kernel)
 // One rule for all forms, which hold the same codes.  Sizes that begin a round of tiles lose by it: 5000 x 2560 28.4 / 28.8 (33.6 / 35.1), int8 rows
 // 10992 x 1536 34.0 / 35.6, 16384 x 768 27.0 / 27.8.  Not here: K = 1280 (16384 rows 26.9 / 25.0, with 2748 14.8 / 15.3 and as int8 rows behind up to
 // 8192), and m = 28, whose fragments and rows leave room for one wave per SIMD (16384 x 3584 82 / 60, but 2748 31.8 / 32.5 and 16 13.6 / 15.6; 8192 x 1792
@@ -433,6 +436,7 @@ int paley_matrix_core_rows(int K)
         case 6144: return 2700;
         case 2560: return 2000;
         case 5120: return 2500;
+        case 8192: return 2400;
         default: return INT_MAX;
     }
 }
@@ -452,6 +456,7 @@ hipError_t run_rotate_quant_paley(const void *X, int rows, int K, const int8_t *
         QVGGT_CASE(6144, 12, 64)
         QVGGT_CASE(2560, 20, 16)
         QVGGT_CASE(5120, 20, 32)
+        QVGGT_CASE(8192, 16, 64)
         default: return hipErrorInvalidValue;
     }
 #undef QVGGT_CASE

@@ -325,10 +325,10 @@ def test_rotate_quant_sizes_with_a_paley_factor(K, dtype):
         G.check_scales(sx.cpu().numpy(), dx, f"K={K} bits={bits}")
 
 
-@pytest.mark.parametrize("K", [768, 1536, 3072, 6144, 2560, 5120])
+@pytest.mark.parametrize("K", [768, 1536, 3072, 6144, 2560, 5120, 8192])
 @pytest.mark.parametrize("rows", [4095, 6149])
 def test_many_rows_with_a_paley_factor(K, rows):
-    """Enough bf16 rows for the matrix-core kernel, the last tiles partial: rows of the first, middle and last tiles against the oracle, as packed and
+    """Enough bf16 rows for the matrix-core kernel (which has K = 8192 too), the last tiles partial: rows of the first, middle and last tiles against the oracle, as packed and
     int8 codes and with a given step (E2M3: the packed codes, in test_gpu_e2m3.py); rows without a code range among them, whose neighbours in a tile are not touched by them."""
     rng = np.random.default_rng(K + rows)
     X = synth.f32_to_bf16_bits(rng.standard_t(3, (rows, K)).astype(np.float32) * (1.0 + np.arange(rows) % 5)[:, None].astype(np.float32))
