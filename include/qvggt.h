@@ -25,6 +25,7 @@
  *     m = 20: 1280, 2560, 5120; m = 28: 1792, 3584 (type I from GF(11), GF(19), type II from GF(13));
  *     N (output features) a multiple of 16; M (tokens) any value >= 0 (M == 0 is a no-op).
  *     All device pointers must be 16-byte aligned.  Inputs must be finite.
+ *   - A token's codes and step depend on its own row (and the parameters) only: the same bits whatever M and whichever rows it is passed with.
  *   - Return value: QVGGT_OK or an error code; arguments are validated on the host
  *     before anything is launched, so a failed call has touched no output.
  *   - Packed 4-bit buffers (Xq, Wq) hold two's-complement codes, two per byte, rows of K/2

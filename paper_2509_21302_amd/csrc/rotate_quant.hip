@@ -350,12 +350,12 @@ hipError_t run_rotate_rows_general(const void *X, bool f32, int rows, int K, con
 
 hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
                                         float *scale, uint8_t *rows_out, hipStream_t stream);
-int paley_matrix_core_rows(int K);
+bool paley_size(int K);
 hipError_t run_rotate_quant_paley(const void *X, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
                                   const float *step, int step_stride, int form, float qmax, hipStream_t stream);
-// Many activation rows (mul_mode 0) with a Paley factor, or of 8192 values.  fp32 values are no exact operands of the matrix instruction, and weights, as many rows as a layer
-// has channels, keep one kernel whatever their number, so that all forms of their codes are the same.
-static bool paley_on_matrix_cores(bool f32, int rows, int K, int mul_mode) { return !f32 && mul_mode == 0 && rows >= paley_matrix_core_rows(K); }
+// Activation rows (mul_mode 0) with a Paley factor, or of 8192 values, whatever their number: the general kernel sums in another order, and a row's codes do not
+// depend on how many rows come with it.  fp32 values are no exact operands of the matrix instruction; weights keep the codes they have had.
+static bool paley_on_matrix_cores(bool f32, int K, int mul_mode) { return !f32 && mul_mode == 0 && paley_size(K); }
 
 // rows_out (CB = 6): the packed rows, or nullptr
 template <int MODE, int CB>
@@ -423,7 +423,7 @@ hipError_t run_rotate_smooth_quant(const void *X, bool f32, int rows, int K, con
                                    const float *step, int step_stride, int bits, hipStream_t stream)
 {
     const float qmax = (float)((1 << (code_width(bits) - 1)) - 1);
-    if (paley_on_matrix_cores(f32, rows, K, mul_mode))
+    if (paley_on_matrix_cores(f32, K, mul_mode))
         return run_rotate_quant_paley(X, rows, K, signs, mul, packed, scale, step, step_stride, bits == 4 ? 4 : 8, qmax, stream);
     if (general_size_supported(K))
         return run_rotate_rows_general(X, f32, rows, K, signs, mul, mul_mode, packed, scale, nullptr, step, step_stride, bits, stream);
@@ -440,7 +440,7 @@ hipError_t run_rotate_smooth_quant(const void *X, bool f32, int rows, int K, con
 hipError_t run_rotate_rows_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
                                 float *scale, uint8_t *rows_out, hipStream_t stream)
 {
-    if (rows_out == nullptr && paley_on_matrix_cores(f32, rows, K, mul_mode))
+    if (rows_out == nullptr && paley_on_matrix_cores(f32, K, mul_mode))
         return run_rotate_quant_paley(X, rows, K, signs, mul, out, scale, nullptr, 0, 6, 7.0f, stream);
     if (general_size_supported(K)) return run_rotate_rows_general_e2m3(X, f32, rows, K, signs, mul, mul_mode, out, scale, rows_out, stream);
     return launch_rotate_rows<kQuantize, 6>(X, f32, rows, K, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f, stream, rows_out);

@@ -4,8 +4,8 @@
 // adds and subtracts.  Element e = a * m + b (a < 2^n, b < m); a wavefront owns a row, lane l holds the m values of every
 // a = l + 64 * c: the m-point transform is inside a lane, the six low bits of a go through cross-lane exchanges, the
 // remaining bits are register-to-register butterflies.  Codes are written in natural order (element e -> position e).
-// This is the general path: VGGT-1B itself has no layer that needs it, and many bf16 rows are quantized in rotate_quant_paley.hip.  Bound by the vector ALU (34350 x 768 bf16: 38 us with dense
-// m-point sums and the lane bits through LDS, 28 us now).
+// This is the general path: VGGT-1B itself has no layer that needs it, and bf16 activations of m = 12, and m = 20 but for K = 1280, are quantized in
+// rotate_quant_paley.hip.  Bound by the vector ALU (34350 x 768 bf16: 38 us with dense m-point sums and the lane bits through LDS, 28 us now).
 #include "paley.h"
 #include "qvggt_common.h"
 #include "rotate_rows.h"

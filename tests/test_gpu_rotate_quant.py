@@ -328,8 +328,9 @@ def test_rotate_quant_sizes_with_a_paley_factor(K, dtype):
 @pytest.mark.parametrize("K", [768, 1536, 3072, 6144, 2560, 5120, 8192])
 @pytest.mark.parametrize("rows", [4095, 6149])
 def test_many_rows_with_a_paley_factor(K, rows):
-    """Enough bf16 rows for the matrix-core kernel (which has K = 8192 too), the last tiles partial: rows of the first, middle and last tiles against the oracle, as packed and
-    int8 codes and with a given step (E2M3: the packed codes, in test_gpu_e2m3.py); rows without a code range among them, whose neighbours in a tile are not touched by them."""
+    """The matrix-core kernel with a column tile per wave (which has K = 8192 too), the last tiles partial: rows of the first, middle and last tiles against the oracle, as
+    packed and int8 codes and with a given step (E2M3: the packed codes, in test_gpu_e2m3.py); rows without a code range among them, whose neighbours in a tile are not
+    touched by them."""
     rng = np.random.default_rng(K + rows)
     X = synth.f32_to_bf16_bits(rng.standard_t(3, (rows, K)).astype(np.float32) * (1.0 + np.arange(rows) % 5)[:, None].astype(np.float32))
     bad = {1: 0x0000, 6: 0x7FC0, 11: 0x7F80, rows - 2: 0x7F61}                  # zeros, a NaN, an infinity, values that overflow in the transform
@@ -361,6 +362,76 @@ def test_many_rows_with_a_paley_factor(K, rows):
     Xq, sx = G.gpu_rsq(Xd, None, None)
     G.check_codes(G.gpu_unpack(Xq, K)[good], qx, f"K={K} plain")
     G.check_scales(sx.cpu().numpy()[good], dx, f"K={K} plain")
+
+
+def _device_rows(rows, K, seed):
+    """Rows of different sizes, a few large channels; +-1 signs and multipliers: on the device."""
+    gen = torch.Generator(device=G.DEV).manual_seed(seed)
+    X = torch.randn(rows, K, generator=gen, device=G.DEV)
+    X[:, ::61] *= 20.0
+    X = X.mul_(1.0 + (torch.arange(rows, device=G.DEV) % 5)[:, None])
+    signs = (torch.randint(0, 2, (K,), generator=gen, device=G.DEV, dtype=torch.int8) * 2 - 1).contiguous()
+    inv = torch.exp(torch.rand(K, generator=gen, device=G.DEV) * 2 - 1) / K ** 0.5
+    return X, signs, inv
+
+
+@pytest.mark.parametrize("K", [128, 256, 512, 1024, 2048, 4096, 8192] + GENERAL_K)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_rows_codes_do_not_depend_on_the_rows_that_come_with_it(K, dtype):
+    """The codes and steps of a batch are those of its parts, from one row to more than any rule on the number of rows: packed and int8 rows, and E2M3
+    blocks by the Y of a layer (the products are exact)."""
+    rows, N = 20483, 48
+    X, signs, inv = _device_rows(rows, K, K)
+    X = X if dtype == "f32" else X.to(torch.bfloat16)
+    layer = G.q.DsfqLinear(torch.randn(N, K, device=G.DEV, generator=torch.Generator(device=G.DEV).manual_seed(K)), None, signs, X[:64].contiguous())
+    ws = torch.empty(max(G.q.qvggt_workspace_bytes(rows, N, K), G.q.qvggt_workspace_bytes_e2m3(rows, N, K)), dtype=torch.uint8, device=G.DEV)
+
+    def run(x):
+        Y = torch.empty(x.shape[0], N, dtype=torch.bfloat16, device=G.DEV)
+        G.q.qvggt_linear_e2m3_any(x, signs, layer.inv_smooth, layer.Wf, layer.w_scale, None, Y, ws)
+        return [*G.gpu_rsq(x, signs, inv), *G.gpu_rsq_i8(x, signs, inv, 8), Y.view(torch.int16)]
+    cuts = [0, 1, 6, 706, 3789, 9482, rows]
+    parts = [run(X[a:b].contiguous()) for a, b in zip(cuts, cuts[1:])]
+    for whole, *pieces in zip(run(X), *parts):
+        assert torch.equal(whole, torch.cat(pieces))
+
+
+@pytest.mark.parametrize("K", [768, 1536, 3072, 6144, 2560, 5120, 8192])
+def test_several_tiles_per_wave_with_a_paley_factor(K):
+    """Rows of the first, second and last tiles of a wave, and of the partial one at the end, against the oracle: packed and int8 codes, a given step per
+    token and one for all.  Rows without a code range are those of the general kernel, which has the same values as f32."""
+    rows = 24003
+    X, signs, inv = _device_rows(rows, K, K + 1)
+    X = X.to(torch.bfloat16)
+    bad = {9: 0.0, 8201: 0.0, 16393: float("nan"), 20001: float("inf"), rows - 2: float("-inf")}
+    for r, v in bad.items():
+        X[r] = 0.0 if v == 0.0 else X[r]
+        X[r, K // 2 :: 3] = v
+    near = np.concatenate([np.arange(12), np.arange(8188, 8206), np.arange(16380, 16396), np.arange(rows - 9, rows)])
+    good = np.setdiff1d(near, list(bad))
+    Xg, inv_h, signs_h = G.bf16_bits(X)[good], inv.cpu().numpy(), signs.cpu().numpy()
+    c_hat = 1.0 / (inv_h.astype(np.float64) * np.sqrt(K))
+    special = X[list(bad)].float().contiguous()
+    for bits in (4, 8):
+        dx, qx, Z = oracle.rotate_smooth_quant(Xg, c_hat, pre_signs=signs_h, bits=bits)
+        if bits == 4:
+            Xq, sx = G.gpu_rsq(X, signs, inv)
+            codes = G.gpu_unpack(Xq, K)
+        else:
+            Xq, sx = G.gpu_rsq_i8(X, signs, inv, bits)
+            codes = G.gpu_layout_int8(Xq, 0).cpu().numpy()
+        G.check_codes(codes[good], qx, f"K={K} bits={bits}")
+        G.check_scales(sx.cpu().numpy()[good], dx, f"K={K} bits={bits}")
+        assert not codes[list(bad)].any()
+    step = float(np.median(dx) * 127 / 7 * 0.6)
+    for per_token in (1, 0):
+        steps = torch.full((rows if per_token else 1,), step, device=G.DEV)
+        given, sx = G.gpu_rsq_static(X, signs, inv, steps, per_token)
+        given = G.gpu_unpack(given, K)
+        G.check_codes(given[good], oracle.quantize_rows_static(Z, np.full(len(good), np.float32(step), dtype=np.float64), 4), f"K={K} given step {per_token}")
+        assert torch.equal(sx, torch.full_like(sx, step))
+        want = G.gpu_unpack(G.gpu_rsq_static(special, signs, inv, steps[: len(bad)], per_token)[0], K)
+        assert np.array_equal(given[list(bad)], want)
 
 
 @pytest.mark.parametrize("K,N", [(768, 256), (2560, 144), (3584, 512), (5120, 144), (6144, 80), (8192, 48)])
