@@ -116,6 +116,8 @@ def test_gpu_tests_reach_the_plans_they_are_named_for(plans):
             assert rows == ((M + 255) // 256 * tiles_n // 256 * 256 // tiles_n) * 256
     for plan in ("big", "small", "deep", "big+deep"):
         assert any(want == plan for _, _, _, want in ASYM_PLANS) and any(p[4] == plan for p in TILE_PLANS)
+        assert any(p[4] == plan and p[3] == "blocks" and p[2] != 1024 for p in TILE_PLANS)       # K = 1024: registers hold the weights, but for the dump
+    assert {p[3] for p in BOTH_TILE_SHAPES if p[2] != 1024} == {p[3] for p in BOTH_TILE_SHAPES}
 
 
 E2M3_DRIVER = r"""
@@ -216,38 +218,43 @@ int main()
     const char *names[] = {"256", "192", "128", "64", "32x64", "32"};
     while (std::scanf("%d %d %d", &M, &N, &K) == 3) {
         const qvggt::E2m3Plan p = qvggt::e2m3_gemm_plan(M, N, K);
-        std::printf("%s %d %d %d\n", names[p.shape], p.rows_main, qvggt::e2m3_streams_y(p.rows_main, N),
-                    qvggt::e2m3_128_tokens_first((p.rows_main + 127) / 128, (N + 127) / 128, N, K));
+        std::printf("%s %d %d %d %d %d\n", names[p.shape], p.rows_main, qvggt::e2m3_streams_y(p.rows_main, N),
+                    qvggt::e2m3_128_tokens_first((p.rows_main + 127) / 128, (N + 127) / 128, N, K), qvggt::e2m3_resident(M, N, K, false),
+                    qvggt::e2m3_resident(M, N, K, true));
     }
 }
 """
 
 
 def test_gpu_tests_reach_every_variant_of_the_e2m3_tiles(tmp_path):
-    """Plain codes and shifted ones (which are not dumped): both kinds of store of the 256- and 192-row tiles, both orders of the 128-row ones, and
-    a divided plan."""
-    from tests.test_gpu_e2m3 import CACHED_PLANS, E2M3_PLANS
+    """Plain codes and shifted ones, as calls run them (without the dump, whose kernels are others): both kinds of store of the 256- and 192-row tiles, both
+    orders of the 128-row ones, and a divided plan with either store.  What the kernel with the weights in registers takes does not count."""
+    from tests.test_gpu_e2m3 import CACHED_PLANS, CALL_PLANS, E2M3_PLANS
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no host C++ compiler")
     (tmp_path / "d.cpp").write_text(VARIANT_DRIVER)
     subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
 
-    def variants(problems):
+    def variants(problems, affine):
         lines = subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d" % p[:3] for p in problems), capture_output=True, text=True, check=True).stdout.split()
         found = set()
-        for p, shape, rows, streams, tokens in zip(problems, lines[::4], lines[1::4], lines[2::4], lines[3::4]):
-            assert shape == p[3].split("+")[0], p
+        for p, shape, rows, streams, tokens, *resident in zip(problems, *(lines[i::6] for i in range(6))):
+            assert shape == p[3].split("+")[0] and (int(rows) != p[0]) == ("+" in p[3]), p
+            if resident[affine] == "1":
+                assert p not in CALL_PLANS
+                continue
             if shape in ("256", "192"):
                 found.add((shape, "streams" if streams == "1" else "caches"))
             elif shape == "128":
                 found.add((shape, "tokens first" if tokens == "1" else "channels first"))
             if int(rows) != p[0]:
-                found.add("divided")
+                found.add(("divided", "streams" if streams == "1" else "caches"))
         return found
-    every = {("256", "streams"), ("256", "caches"), ("192", "streams"), ("192", "caches"), ("128", "channels first"), ("128", "tokens first"), "divided"}
+    every = {("256", "streams"), ("256", "caches"), ("192", "streams"), ("192", "caches"), ("128", "channels first"), ("128", "tokens first"),
+             ("divided", "streams"), ("divided", "caches")}
     shifted = [p for p in E2M3_PLANS if p[2] in (1024, 2048, 4096) and p[0] < 12000 or "+" in p[3]]
-    assert variants(E2M3_PLANS + CACHED_PLANS) == every and variants(shifted + CACHED_PLANS) == every
+    assert variants(E2M3_PLANS + CACHED_PLANS + CALL_PLANS, False) == every and variants(shifted + CACHED_PLANS + CALL_PLANS, True) == every
 
 
 RESIDENT_DRIVER = r"""
@@ -266,6 +273,7 @@ def test_resident_weights(tmp_path):
     """The GPU test's table reaches the kernel with every K it takes; no other K does, nor affine codes with those that kernel 1 does not write; the
     blocks of a launch have a compute unit each unless there are more groups of channels than that."""
     from tests.test_gpu_e2m3 import RESIDENT
+    from tests.test_gpu_large_offsets import M_BIG
     from tests.test_gpu_int8_blocks import RESIDENT as INT8
     gxx = shutil.which("g++")
     if gxx is None:
@@ -281,6 +289,7 @@ def test_resident_weights(tmp_path):
         assert resident, p
     assert {p[2] for p in RESIDENT} == {512, 768, 1024, 1280, 1536, 1792, 2048}
     assert all(int8 for _, _, int8 in ask([(*p, 1024, 0) for p in INT8]))
+    assert M_BIG * 4096 > 1 << 31 and ask([(M_BIG, 4096, 512, 0)])[0][0] and ask([(M_BIG, 4096, 1024, 0)])[0][2]
     rng = random.Random(9)
     problems = [(int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(8192)))),
                  rng.choice([128, 256, 512, 768, 1024, 1280, 1536, 1792, 2048, 2560, 3584, 4096, 6144, 8192]), rng.randrange(2)) for _ in range(20000)]

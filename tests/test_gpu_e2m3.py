@@ -377,9 +377,19 @@ def test_e2m3_gemm_with_y_through_the_caches(M, N, K, plan):
     test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan)
 
 
-@pytest.mark.parametrize("M,N,K,plan", [p for p in E2M3_PLANS if "+" in p[3]])
+# Several of the tables above run in tiles only with the dump (the kernel with the weights in registers has them otherwise, and all affine ones): these do
+# in every call.  256-row tiles alone and with a rest, stores past the caches and through them
+CALL_PLANS = [(16355, 528, 4096, "256"), (21794, 576, 4096, "256+32"), (16392, 784, 4096, "256+32"), (10863, 2960, 4096, "256+32x64")]
+
+
+@pytest.mark.parametrize("M,N,K,plan", CALL_PLANS)
+def test_e2m3_gemm_in_the_tiles_that_calls_run(M, N, K, plan):
+    test_e2m3_gemm_in_every_tile_shape(M, N, K, plan)
+
+
+@pytest.mark.parametrize("M,N,K,plan", [p for p in E2M3_PLANS if "+" in p[3]] + CALL_PLANS)
 def test_e2m3_gemm_shifted_in_divided_plans(M, N, K, plan):
-    """The rest's zero points are those of its own rows."""
+    """The rest's zero points are those of its own rows (CALL_PLANS)."""
     test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan)
 
 

@@ -54,7 +54,7 @@ def test_i8b_gemm_bit_exact(M, N, K):
     assert torch.equal(Y, Y8)
 
 
-# tests/test_gemm_plan.py holds the plan to what this table says of each problem
+# tests/test_gemm_plan.py holds the plan to what this table says of each problem (K = 1024: in tiles with the dump only)
 BOTH_TILE_SHAPES = [(66000, 512, 256, "small"), (33000, 1024, 512, "small"), (17000, 4096, 1024, "big+deep"), (8400, 2000, 4096, "big+deep")]
 
 
