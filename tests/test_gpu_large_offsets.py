@@ -84,3 +84,37 @@ def test_gemm_output_past_2_31_elements(path):
     ref = (torch.from_numpy(qx).to(G.DEV).float() @ torch.from_numpy(qw).to(G.DEV).float().T)
     assert torch.equal(acc, ref.to(torch.int32))
     assert not torch.isnan(Y[-1].float()).any().item() and not torch.isnan(Y[SEAM].float()).any().item()
+
+
+@pytest.mark.parametrize("path,K", [("e2m3", 512), ("int8", 1024)])
+def test_gemm_with_resident_weights_past_2_31_output_elements(path, K):
+    """The kernel that keeps the weights in registers (tests/test_gemm_plan.py holds these sizes to it): every element of Y is the row-major kernel's."""
+    q, N, lim = G.q, 4096, 7 if path == "e2m3" else 127
+    gen = torch.Generator(device=G.DEV).manual_seed(K)
+    qx, qw = (torch.randint(-lim, lim + 1, (n, K), generator=gen, device=G.DEV, dtype=torch.int8) for n in (M_BIG, N))
+    sx, sw = torch.rand(M_BIG, device=G.DEV, generator=gen) + 0.1, torch.rand(N, device=G.DEV, generator=gen) * 1e-3
+    bias = torch.randn(N, device=G.DEV, generator=gen).to(torch.bfloat16)
+    Y = torch.full((M_BIG, N), float("nan"), dtype=torch.bfloat16, device=G.DEV)
+    want = torch.full_like(Y, float("nan"))
+    if path == "e2m3":
+        Xq, Wq = (torch.empty(n, K // 2, dtype=torch.uint8, device=G.DEV) for n in (M_BIG, N))
+        Xf, Wf = (torch.empty(q.qvggt_e2m3_bytes(n, K), dtype=torch.uint8, device=G.DEV) for n in (M_BIG, N))
+        for codes, packed, blocks in ((qx, Xq, Xf), (qw, Wq, Wf)):
+            q.qvggt_pack_int4(codes, packed)
+            G.codes_to_e2m3(packed, codes.shape[0], K, blocks)
+        q.qvggt_e2m3_gemm(Xf, sx, Wf, sw, bias, M_BIG, N, K, Y)
+        q.qvggt_w4a4_gemm(Xq, sx, Wq, sw, bias, M_BIG, N, K, want)
+    else:
+        Xl, Wl = G.gpu_layout_int8(qx, 1), G.gpu_layout_int8(qw, 1)
+        Xb, Wb = (torch.empty(q.qvggt_i8b_bytes(n, K), dtype=torch.int8, device=G.DEV) for n in (M_BIG, N))
+        q.qvggt_int8_to_blocks(Xl, M_BIG, K, Xb)
+        q.qvggt_int8_to_blocks(Wl, N, K, Wb)
+        q.qvggt_i8b_gemm(Xb, sx, Wb, sw, bias, M_BIG, N, K, Y, None)
+        q.qvggt_i8_gemm(Xl, sx, Wl, sw, bias, M_BIG, N, K, want, None)
+    for r in range(0, M_BIG, 60000):
+        assert torch.equal(Y[r:r + 60000].view(torch.int16), want[r:r + 60000].view(torch.int16))
+    rows = torch.from_numpy(_rows()).to(G.DEV)
+    acc = oracle.int_gemm(qx[rows].cpu().numpy(), qw.cpu().numpy())
+    Yo = oracle.dequant_bias(acc, sx[rows].cpu().numpy(), sw.cpu().numpy(), oracle.to_f64(G.bf16_bits(bias)))
+    ulp_off = np.abs(G.bf16_bits(Y[rows]).astype(np.int32) - Yo.astype(np.int32))
+    assert ulp_off.max() <= 1 and (ulp_off != 0).mean() < 5e-3
