@@ -2,6 +2,10 @@
 #pragma once
 
 namespace qvggt {
+
+// Sizes whose bf16 activation rows are quantized in rotate_quant_paley.hip
+constexpr bool paley_size(int K) { return K == 768 || K == 1536 || K == 3072 || K == 6144 || K == 2560 || K == 5120 || K == 8192; }
+
 namespace gen {
 
 // entry (r, c) in {+1, -1}, from the squares of GF(q) found by enumeration

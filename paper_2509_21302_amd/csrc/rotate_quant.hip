@@ -9,6 +9,7 @@
 // per load instruction).  The transform is one butterfly per index bit (the Hadamard matrix
 // is a Kronecker power of H_2, paper Sec. 3.2): bits inside i and c are register-to-register,
 // the six lane bits go through cross-lane exchanges.
+#include "paley.h"
 #include "qvggt_common.h"
 #include "rotate_rows.h"
 
@@ -350,7 +351,6 @@ hipError_t run_rotate_rows_general(const void *X, bool f32, int rows, int K, con
 
 hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
                                         float *scale, uint8_t *rows_out, hipStream_t stream);
-bool paley_size(int K);
 hipError_t run_rotate_quant_paley(const void *X, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,
                                   const float *step, int step_stride, int form, float qmax, hipStream_t stream);
 // Activation rows (mul_mode 0) with a Paley factor, or of 8192 values, whatever their number: the general kernel sums in another order, and a row's codes do not
@@ -378,6 +378,7 @@ static hipError_t launch_rotate_rows(const void *X, bool f32, int rows, int K, c
 #define QVGGT_LAUNCH(KK)                                                                                     \
     case KK:                                                                                                 \
         if (f32) rotate_rows_kernel<KK, true, MODE, CB><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, qmax, LnParams{nullptr, nullptr, 0.0f, 0}); \
+        else if constexpr (CB == 6 && paley_size(KK)) return hipErrorInvalidValue;      /* bf16 activations: rotate_quant_paley.hip */     \
         else rotate_rows_kernel<KK, false, MODE, CB><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, packed, scale, colmax, step, step_stride, qmax, LnParams{nullptr, nullptr, 0.0f, 0});    \
         break;
     if constexpr (CB == 6) {

@@ -305,20 +305,29 @@ hipError_t run_rotate_rows_general(const void *X, bool f32, int rows, int K, con
 #undef QVGGT_CASE
 }
 
+template <int N2, int MM>
+static hipError_t launch_general_e2m3(const void *X, bool f32, int rows, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out, float *scale,
+                                      uint8_t *rows_out, hipStream_t stream)
+{
+    if (rows <= 0) return hipSuccess;
+    const int group = gen::waves_per_row(N2, MM) > 1 && rows <= kFewSharedRows ? 1 : kE2m3Group;
+    const int blocks = std::min((rows + group - 1) / group, 256 * 8);
+    auto launch = [&](auto kernel) {
+        kernel<<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f, rows_out);
+        return hipGetLastError();
+    };
+    if (rows_out != nullptr) return launch(f32 ? rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6, true> : rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6, true>);
+    if (f32) return launch(rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6>);
+    if constexpr (paley_size(N2 * MM)) return hipErrorInvalidValue;               // bf16 activations: rotate_quant_paley.hip
+    else return launch(rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6>);
+}
+
 // the same rows as E2M3 blocks (dynamic 4-bit codes); rows_out: as packed rows too, or nullptr
 hipError_t run_rotate_rows_general_e2m3(const void *X, bool f32, int rows, int K, const int8_t *signs, const float *mul, int mul_mode, uint8_t *out,
                                         float *scale, uint8_t *rows_out, hipStream_t stream)
 {
-    if (rows <= 0) return hipSuccess;
-    const int group = (K == 5120 || K == 6144) && rows <= kFewSharedRows ? 1 : kE2m3Group;
-    const int blocks = std::min((rows + group - 1) / group, 256 * 8);
-#define QVGGT_CASE(KK, N2, MM)                                                                                                           \
-    case KK:                                                                                                                             \
-        if (rows_out != nullptr && f32) rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6, true><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f, rows_out); \
-        else if (rows_out != nullptr) rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6, true><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f, rows_out);   \
-        else if (f32) rotate_rows_general_kernel<N2, MM, true, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f); \
-        else rotate_rows_general_kernel<N2, MM, false, gen::kQuantize, 6><<<blocks, 256, 0, stream>>>(X, rows, signs, mul, mul_mode, out, scale, nullptr, nullptr, 0, 7.0f);    \
-        return hipGetLastError();
+#define QVGGT_CASE(KK, N2, MM) \
+    case KK: return launch_general_e2m3<N2, MM>(X, f32, rows, signs, mul, mul_mode, out, scale, rows_out, stream);
     switch (K) {
         QVGGT_CASE(768, 64, 12)
         QVGGT_CASE(1536, 128, 12)

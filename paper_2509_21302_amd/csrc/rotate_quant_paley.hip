@@ -636,8 +636,6 @@ static hipError_t launch_paley(const void *X, int rows, const int8_t *signs, con
                   std::min(tiles, 256 * C::COLUMN_BLOCKS_PER_CU), C::NT * 64);
 }
 
-bool paley_size(int K) { return K == 768 || K == 1536 || K == 3072 || K == 6144 || K == 2560 || K == 5120 || K == 8192; }
-
 // bf16 rows of a size that paley_size() has.  form: 4 packed nibbles, 8 int8 rows, 6 E2M3 blocks (dynamic steps).  mul: inv_smooth or
 // nullptr (1 / sqrt(K)); qmax: largest code; step: given steps or nullptr.
 hipError_t run_rotate_quant_paley(const void *X, int rows, int K, const int8_t *signs, const float *mul, uint8_t *out, float *scale,

@@ -408,7 +408,7 @@ def test_e2m3_gemm_with_resident_weights(M, N, K):
 
 
 # The row kernels writing E2M3 blocks, by the entry point itself (a layer takes nibbles at many of these sizes): more groups of rows than blocks, four
-# waves per row with groups of four rows (K = 5120, 6144, 8192 beyond 4096 rows), and channels enough that small K are not one launch
+# waves per row with groups of four rows (K = 5120, 6144, 8192 beyond 4096 f32 rows), and channels enough that small K are not one launch
 @pytest.mark.parametrize("f32", [True, False])
 @pytest.mark.parametrize("K,M,N", [(K, M, 80) for K in (768, 1280, 1536, 1792, 2560, 3072, 3584, 5120, 6144, 8192) for M in (5, 4097, 8503)] +
                          [(K, M, N) for K in (128, 256, 512) for M, N in ((131, 13328), (6, 65552), (8503, 80))] + [(K, 8503, 80) for K in (1024, 2048, 4096)])
@@ -435,6 +435,29 @@ def test_row_kernels_write_the_packed_paths_codes(K, M, N, f32):
     if M % 128: assert (blocks[M // 128, :, M % 128:] == 7).all().item()
     G.q.qvggt_linear(X, signs, inv, Wq, sw, None, want, torch.empty(G.q.qvggt_workspace_bytes(M, N, K), dtype=torch.uint8, device=G.DEV))
     assert torch.equal(whole[:M].view(torch.int16), want.view(torch.int16))
+
+
+# Weights of more than 4096 channels: groups of four rows where four waves share one (K = 5120, 6144, 8192)
+@pytest.mark.parametrize("K,N", [(768, 272), (768, 4112), (5120, 272), (5120, 4112), (6144, 4112), (8192, 272), (8192, 4112)])
+@pytest.mark.parametrize("f32", [True, False])
+def test_weights_in_both_forms_are_those_of_either(K, N, f32):
+    """One kernel writes the packed rows and the blocks: the packed rows' kernel's, and the converter's of them; padding rows are not written."""
+    g = torch.Generator(device=G.DEV).manual_seed(K + N)
+    W = torch.randn(N, K, device=G.DEV, generator=g) * 0.03
+    W = W if f32 else W.to(torch.bfloat16)
+    signs = (torch.randint(0, 2, (K,), device=G.DEV, generator=g, dtype=torch.int8) * 2 - 1).contiguous()
+    absmax = torch.rand(K, device=G.DEV, generator=g) + 0.5
+    Wq, want_q = (torch.empty(N, K // 2, dtype=torch.uint8, device=G.DEV) for _ in range(2))
+    Wf, want_f = (torch.full((G.q.qvggt_e2m3_bytes(N, K),), 0xFF, dtype=torch.uint8, device=G.DEV) for _ in range(2))
+    sw, want_sw = (torch.empty(N, dtype=torch.float32, device=G.DEV) for _ in range(2))
+    inv, want_inv = (torch.empty(K, dtype=torch.float32, device=G.DEV) for _ in range(2))
+    G.q.qvggt_prep_weights_e2m3(W, absmax, signs, 0.5, Wq, Wf, sw, inv)
+    G.q.qvggt_prep_weights(W, absmax, signs, 0.5, want_q, want_sw, want_inv)
+    G.codes_to_e2m3(want_q, N, K, want_f)
+    assert torch.equal(Wq, want_q) and torch.equal(sw, want_sw) and torch.equal(inv, want_inv)
+    rows = torch.arange((N + 127) // 128 * 128, device=G.DEV).view(-1, 1, 128, 1) < N
+    got, want = (f.view(-1, K // 64, 128, 48) for f in (Wf, want_f))
+    assert torch.equal(got.where(rows, 0), want.where(rows, 0)) and (got.where(~rows, 0xFF) == 0xFF).all().item()
 
 
 # every K in both types: rows below a group of four, groups that end inside a 128-row block, more groups than blocks
