@@ -225,8 +225,10 @@ inline int resident_ranges(int M, int N) { return std::max(1, std::min(256 / res
 
 // Its price in microseconds, to be compared with the tiles'.  Loading the weights into the registers costs 5.3 + 2.4 k before the first product, a
 // step of a block 0.735 k, and writing Y 0.112 per megabyte on top of that.  Fitted to 660 random problems of 200 to 137400 rows, all seven K, timed
-// with kernel 1 in front beside the tiles' plan: within 4 % of a call's time (rms).  The choice is 1.05 times faster than the tiles alone on geometric
-// average over them, 0.15 % slower than the better of the two, 3 % slower than the tiles at worst (one of 660 by more than 2 %).  us of the GEMM,
+// with kernel 1 in front beside the tiles' plan: within 4 % of a call's time (rms).  The tiles' price is too high where the rows of Y are 64-byte pieces
+// but no whole lines (N = 32 mod 64: 13740 x 1280 -> 800 23.2 / 26.2, 37024 -> 224 27.6 / 29.6), hence the 1.06.  On other 3000 problems, with kernel 1 (K = 1024,
+// 2048) or a copy of the codes in front, the 1560 that come to this kernel are 1.20 times faster than in tiles on geometric average; 25 of them are
+// slower by more than 2 %, 11 of these with 272 to 368 channels and tens of thousands of tokens (90762 x 1792 -> 352 81.3 / 95.0).  us of the GEMM,
 // tiles / this one: 137400 x 1024 -> 4096 385 / 321, 32976 x 2048 -> 4096 161 / 128, 10992 x 1024 -> 4096 38.9 / 29.2, 10992 x 768 -> 3072 25.8 / 21.1,
 // 4096 x 1024 -> 4096 15.9 / 15.6, 2048 x 1024 -> 4096 9.5 / 10.7, 1374 x 2048 -> 4096 12.0 / 15.6.
 inline double e2m3_resident_cost(int M, int N, int K)
@@ -240,15 +242,16 @@ inline bool e2m3_resident(int M, int N, int K, bool shifted)
     if (!e2m3_resident_k(K, shifted)) return false;
     double tiles;
     e2m3_gemm_plan(M, N, K, &tiles);
-    return e2m3_resident_cost(M, N, K) < tiles;
+    return e2m3_resident_cost(M, N, K) * (N % 64 == 32 ? 1.06 : 1.0) < tiles;
 }
 
 // int8 blocks with the weights in registers: K = 1024, whose 256 channels take half of them (blocks come with K = 1024, 2048 and 4096; at 2048 they would
 // take all).  Few tiles stay with the kernels made for them: alone, those take less than the 8 us that this one needs to begin.  So do few tokens, whose
 // time is the weights' (40 x 66064 19.8 / 23.4, 300 x 66064 53.2 / 47.6).  The others by price
-// in microseconds, fitted to 234 random problems of 100 to 137400 rows (its own within 5 %, rms; 256s cost 4 us more where the rows of Y
-// are no whole lines).  As calls run it, behind kernel 1, the choice is 1.13 times faster than the tiles on the 80 of them that it gives to this kernel,
-// 0.1 % slower than the better of the two over all, 7 % slower than the tiles at worst (3 of 234 by more than 2 %).  us of the GEMM, tiles / this
+// in microseconds, fitted to 234 random problems of 100 to 137400 rows (its own within 5 %, rms).  256s cost 4 us more where the rows of Y are 32-byte
+// pieces of lines, 1 where they are 64-byte ones (at 4 there too, one round of them with N = 32 mod 64 came here and lost: 2796 x 4576 23.6 / 27.5,
+// 5567 x 2080 25.4 / 28.1, 10392 x 992 30.0 / 30.8).  As calls run it, behind kernel 1, the 1620 of 3000 other problems that it gives to this kernel are
+// 1.18 times faster than in tiles on geometric average; 13 are slower by more than 2 %, by 6 % at worst.  us of the GEMM, tiles / this
 // one: 137400 x 4096 637 / 527, 32976 x 4096 153 / 125, 32976 x 1024 41.1 / 36.5, 10992 x 3072 40.9 / 36.7, 2748 x 1024 7.4 / 10.4.
 inline bool i8b_resident(int M, int N, int K)
 {
@@ -256,7 +259,7 @@ inline bool i8b_resident(int M, int N, int K)
     double tiles;
     const GemmPlan plan = int8_instruction_gemm_plan(M, N, K, 8, false, false, &tiles);
     if (plan.shape == GemmPlan::kDeep) return false;
-    if (plan.shape == GemmPlan::kBig && N % 64 != 0) tiles += 4.0;
+    if (plan.shape == GemmPlan::kBig) tiles += N % 32 != 0 ? 4.0 : N % 64 != 0 ? 1.0 : 0.0;
     const int steps = (M + 31) / 32, ranges = resident_ranges(M, N);
     return 1.03 * (7.4 + 0.89 * ((steps + ranges - 1) / ranges) + 0.236e-6 * 2.0 * M * N) < tiles;
 }

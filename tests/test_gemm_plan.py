@@ -269,6 +269,23 @@ int main()
 """
 
 
+# problems that one kernel had measured far enough ahead to say which it has to be (us in front of a copy of the codes or behind kernel 1, tiles / weights in
+# registers), most of them with rows of Y in 64-byte pieces
+@pytest.mark.parametrize("M,N,K,int8,resident", [
+    (2796, 4576, 1024, True, False), (3383, 3680, 1024, True, False), (5567, 2080, 1024, True, False), (6278, 1888, 1024, True, False), (9968, 1248, 1024, True, False),
+    (23358, 1360, 1024, True, True), (117758, 3648, 1024, True, True), (10993, 3056, 1024, True, True),      # 63.1 / 57.3, 529 / 453
+    (13740, 800, 1280, False, False), (13119, 1056, 1280, False, False), (37024, 224, 1280, False, False),   # 23.2 / 26.2, 25.4 / 27.4, 27.6 / 29.6
+    (10992, 4096, 1024, False, True), (32976, 4096, 2048, False, True), (10992, 3072, 768, False, True)])
+def test_resident_weights_where_the_kernels_differ(tmp_path, M, N, K, int8, resident):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text(RESIDENT_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+    out = subprocess.run([tmp_path / "d"], input=f"{M} {N} {K} 0", capture_output=True, text=True, check=True).stdout.split()
+    assert int(out[2 if int8 else 0]) == resident
+
+
 def test_resident_weights(tmp_path):
     """The GPU test's table reaches the kernel with every K it takes; no other K does, nor affine codes with those that kernel 1 does not write; the
     blocks of a launch have a compute unit each unless there are more groups of channels than that."""
