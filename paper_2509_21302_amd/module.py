@@ -14,6 +14,9 @@ import torch
 from . import binding as q
 
 
+_MATRIX_CORE_ROWS = (768, 1536, 3072, 6144, 2560, 5120, 8192)      # beside 1024, 2048 and 4096: sizes whose bf16 rows kernel 1 takes through the matrix cores
+
+
 class DsfqLinear:
     """Y = X W^T + b with W and X quantized as in Sec. 3.2 (rotation, smoothing, per-channel / per-token codes).
 
@@ -132,11 +135,13 @@ class DsfqLinear:
             if not bf16:
                 raise ValueError("pre_gelu needs bf16 input")
             kind, W, bits = q.GELU, self.Wf, 4
-        elif self.packed and self.Wf is not None and (bf16 and self.K in (1024, 2048, 4096) or (M <= 4096 or self.N >= 448 and self.K >= 512) and self._blocks_hold()):
-            # (many rows of few channels or features are kernel 1 and the stores of Y; kernel 1 writes nibbles 10 to 15 % faster where it is not
-            # the matrix-core one.  Kernels alone, nibbles / E2M3 blocks: 41505 x 768 -> 128 40.4 us / 45.2, 99022 x 1792 -> 320 238 / 257, 105364 x 256 -> 48
-            # 41.1 / 55.3; 10992 x 768 -> 3072 43.5 / 38.3, 64 x 128 -> 128 5.2 / 3.5.  Over 320 random sizes the rule is 1.2 % above the better of
-            # the two; most of that is many rows of K = 128 and 256 with many channels, which stay with nibbles: 7662 x 256 -> 3632 35.6 / 24.0)
+        elif self.packed and self.Wf is not None and (bf16 and self.K in (1024, 2048, 4096) or
+                                                      (M <= 4096 or self.K >= 512 and self.N >= (128 if bf16 and self.K in _MATRIX_CORE_ROWS else 448)) and self._blocks_hold()):
+            # (many rows of few channels or features are kernel 1 and the stores of Y; kernel 1 writes nibbles faster, by up to 15 % where it is not on
+            # the matrix cores.  us of both kernels, nibbles / E2M3 blocks: f32 41505 x 768 -> 128 43.6 / 48.0, 20000 x 4096 -> 320 133 / 146, bf16 105364 x 256 -> 48
+            # 41.4 / 55.6, 99022 x 1792 -> 320 240 / 242; 41505 x 768 -> 128 36.8 / 34.1, 20000 x 8192 -> 320 187 / 186, 24000 x 6144 -> 128 120 / 127; 10992 x 768 ->
+            # 3072 44.2 / 32.5, f32 64 x 128 -> 128 5.2 / 3.4.  Over 3000 random sizes of more than 4096 rows the rule is 1.3 % above the better of the two;
+            # most of that is K = 128 and 256 with many channels, which stay with nibbles: 7662 x 256 -> 3632 35.7 / 24.4)
             kind, W, bits = q.E2M3, self.Wf, 4
         elif self.packed:                                # the same Y, bit for bit
             kind, W, bits = q.PACKED, self.Wq, 4

@@ -88,7 +88,15 @@ def made(monkeypatch, taken):
         if hasattr(B, name) and "bytes" not in name:
             monkeypatch.setattr(B, name, lambda *a: None)
     monkeypatch.setattr(torch.Tensor, "item", lambda self: 0)
-    return lambda K: DsfqLinear(torch.zeros(32, K), calibration=torch.zeros(4, K))
+    return lambda K, N=32: DsfqLinear(torch.zeros(N, K), calibration=torch.zeros(4, K))
+
+
+@pytest.mark.parametrize("K,N,dtype,rows,kind", [(768, 128, torch.bfloat16, 4097, B.E2M3), (8192, 320, torch.bfloat16, 4097, B.E2M3), (768, 112, torch.bfloat16, 4097, B.PACKED),
+                                                 (768, 112, torch.bfloat16, 4096, B.E2M3), (768, 432, torch.float32, 4097, B.PACKED), (1792, 432, torch.bfloat16, 4097, B.PACKED),
+                                                 (1792, 448, torch.bfloat16, 4097, B.E2M3), (256, 4096, torch.bfloat16, 4097, B.PACKED), (4096, 320, torch.float32, 4097, B.PACKED)])
+def test_many_rows_take_the_form_that_was_measured_faster(taken, made, K, N, dtype, rows, kind):
+    made(K, N)(torch.zeros(rows, K, dtype=dtype))
+    assert taken == [kind]
 
 
 def _assign(layer):
