@@ -1,5 +1,6 @@
-// What the E2M3 GEMM kernels share: the operand format's sizes, the transfers from global memory into LDS, a product's arguments.
+// What the E2M3 GEMM kernels share: the operand format's sizes, a product's arguments.
 #pragma once
+#include "lds_transfer.h"
 #include "qvggt_common.h"
 
 #include <type_traits>
@@ -20,21 +21,6 @@ constexpr int RB_PIECES = RB_BYTES / 1024;
 // in every byte) is the explicit unit scale and gives the same sums.
 constexpr int UNIT_SCALE_ONE = 0;
 
-// Global memory -> LDS, 16 bytes per lane: lane l reads base + lane_off and writes LDS address lds_base + 16 * l.  M0 carries the
-// LDS base; each transfer sets it itself and says so, so nothing depends on what the compiler does with that register elsewhere.  A transfer wants
-// one wait state behind a scalar write of M0, which the compiler does not put inside an asm block (0.1 % of a GEMM's time).
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ inline void e_dma16(uint32_t lane_off, const void *base, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-// 4 bytes per lane: lane l writes lds_base + 4 * l
-__device__ inline void e_dma4(const void *src, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
 template <class F, int... Is>
 __device__ inline void e_static_for_impl(F &&f, std::integer_sequence<int, Is...>)
 {

@@ -134,9 +134,9 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
         constexpr int i = decltype(i_c)::value;
         const uint32_t dst = lds0 + ld_stage * C::STAGE_BYTES + (i * C::NW + wave) * 1024;
         if constexpr ((i + 1) * C::NW <= C::NT) {
-            e_dma16(lane_off, src[i] + (size_t)ld_unit * RB_BYTES, dst);
+            dma16(lane_off, src[i] + (size_t)ld_unit * RB_BYTES, dst);
         } else {
-            if (i * C::NW + wave < C::NT) e_dma16(lane_off, src[i] + (size_t)ld_unit * RB_BYTES, dst);     // wave-uniform
+            if (i * C::NW + wave < C::NT) dma16(lane_off, src[i] + (size_t)ld_unit * RB_BYTES, dst);     // wave-uniform
         }
     };
     auto advance_cursor = [&]() {
@@ -159,22 +159,22 @@ __global__ __launch_bounds__(WM * WN * 64, MINB) __attribute__((amdgpu_waves_per
         for (int g = 0; g < C::SC_GROUPS; ++g) {
             if (g % C::NW != wave) continue;
             if (g < C::BM / 64) {
-                e_dma4(sx + min(tm * C::BM + g * 64 + lane, M - 1), dst + g * 256);
+                dma4(sx + min(tm * C::BM + g * 64 + lane, M - 1), dst + g * 256);
             } else if (g < C::BM / 64 + C::BN / 64) {
                 const int h = g - C::BM / 64;
-                e_dma4(sw + min(tn * C::BN + h * 64 + lane, N - 1), dst + C::BM * 4 + h * 256);
+                dma4(sw + min(tn * C::BN + h * 64 + lane, N - 1), dst + C::BM * 4 + h * 256);
             } else if (g < C::SC_SYM_GROUPS) {
                 if (bias != nullptr) {
                     const int h = g - C::BM / 64 - C::BN / 64;      // 64 dwords = 128 bf16 values
-                    e_dma4(reinterpret_cast<const uint32_t *>(bias) + min(tn * (C::BN / 2) + h * 64 + lane, N / 2 - 1),
+                    dma4(reinterpret_cast<const uint32_t *>(bias) + min(tn * (C::BN / 2) + h * 64 + lane, N / 2 - 1),
                            dst + C::BM * 4 + C::BN * 4 + h * 256);
                 }
             } else if (g < C::SC_SYM_GROUPS + C::BM / 64) {
                 const int h = g - C::SC_SYM_GROUPS;
-                e_dma4(xzero + min(tm * C::BM + h * 64 + lane, M - 1), dst + C::SC_SYM_BYTES + h * 256);
+                dma4(xzero + min(tm * C::BM + h * 64 + lane, M - 1), dst + C::SC_SYM_BYTES + h * 256);
             } else {
                 const int h = g - C::SC_SYM_GROUPS - C::BM / 64;
-                e_dma4(wsum + min(tn * C::BN + h * 64 + lane, N - 1), dst + C::SC_SYM_BYTES + C::BM * 4 + h * 256);
+                dma4(wsum + min(tn * C::BN + h * 64 + lane, N - 1), dst + C::SC_SYM_BYTES + C::BM * 4 + h * 256);
             }
         }
     };

@@ -38,19 +38,6 @@ __device__ inline void store4(void *base, uint32_t lane_off, uint32_t v)
     else asm volatile("global_store_dword %0, %1, %2" ::"v"(lane_off), "v"(v), "s"(base) : "memory");
 }
 
-// e_dma16 to lds_base + AT
-template <int AT>
-__device__ inline void dma16_at(uint32_t lane_off, const void *base, uint32_t lds_base)
-{
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base), "n"(AT) : "memory", "m0", "scc");
-}
-
-// 4 bytes per lane
-__device__ inline void dma4(uint32_t lane_off, const void *base, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-
 // An operand format: a unit is what one MFMA takes of a row's codes, a K-tile of the format holds TILE_UNITS of them.
 struct E2m3Codes {
     typedef v6i Weights;                                               // a lane's share of a unit

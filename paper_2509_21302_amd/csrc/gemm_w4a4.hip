@@ -39,6 +39,7 @@
 // piece per MFMA, fenced so that the compiler keeps the interleave: the vector ALU and LDS
 // work runs in the shadow of the matrix pipe.
 #include "gemm_plan.h"
+#include "lds_transfer.h"
 #include "qvggt_common.h"
 #include "resident.h"
 
@@ -89,22 +90,6 @@ struct StreamCfg {
         (dst)[(k) + 1] = (int)((p_ << 4) & 0xF0F0F0F0u);               \
     } while (0)
 
-// M0 carries the LDS base of these transfers.  Every transfer sets it itself and names it as clobbered, so nothing depends on what
-// the compiler does with that register between two of them; the s_nop is the wait state that a transfer wants behind a scalar write of M0.
-// 4 bytes per lane from global memory to LDS: lane l writes lds_base + 4 * l
-__device__ inline void dma4(const void *src, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_base) : "memory", "m0");
-}
-// 16 bytes per lane: lane l writes lds_base + OFF + 16 * l.  The instruction offset of such a transfer moves the LDS address and
-// the global address alike: with one LDS base, transfers to different places of a stage differ only in OFF (the lane's global
-// offset is pre-compensated by -OFF).  The global address is a wave-uniform 64-bit base (scalar registers) plus a 32-bit offset
-// per lane: moving along K only touches the scalar base, no vector ALU work.
-template <int OFF>
-__device__ inline void dma16(uint32_t lane_off, const void *base, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(lane_off), "s"(base), "s"(lds_base), "n"(OFF) : "memory", "m0");
-}
 // a pointer that is the same in all lanes, in scalar registers (the transfers' base operand has to be; the compiler does not always see it)
 __device__ inline const uint8_t *scalar_pointer(const uint8_t *p)
 {
