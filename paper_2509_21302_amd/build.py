@@ -18,7 +18,8 @@ LIB = os.path.join(HERE, "libqvggt.so")
 CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))       # another Python does not find it
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["api.hip", "rotate_quant.hip", "rotate_quant_mfma.hip", "gemm_w4a4.hip", "nfds.hip",
-           "rotate_quant_general.hip", "rotate_quant_paley.hip", "gemm_e2m3.hip", "gemm_resident.hip", "linear_small.hip", "ceilings.hip", "calib.hip"]
+           "rotate_quant_general.hip", "rotate_quant_paley.hip", "gemm_e2m3.hip", "gemm_resident.hip",
+           "gemm_resident_1280_2048.hip", "gemm_resident_1536_1792.hip", "gemm_resident_affine.hip", "linear_small.hip", "ceilings.hip", "calib.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -29,10 +30,8 @@ FLAGS = [
     # the global -> LDS transfer wrappers name M0 (a register the compiler reserves) as clobbered, which it reports for every use
     "-Wno-inline-asm",
 ]
-FLAGS_OF = {
-    # results of the matrix instructions in ordinary registers, where the epilogue reads them without a copy
-    "gemm_resident.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-}
+# results of the matrix instructions in ordinary registers, where the epilogue reads them without a copy
+FLAGS_OF = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for s in SOURCES if s.startswith("gemm_resident")}
 
 
 def _compile(src: str, save_temps: bool) -> str:

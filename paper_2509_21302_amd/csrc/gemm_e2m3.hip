@@ -30,7 +30,7 @@
 // Tiles: 256 x 256 per block, one block per compute unit, four waves of 128 x 128 (256 accumulator registers each): the least
 // operand traffic per MFMA that the register file allows; 192 x 256 where that fills the last round better; 128 x 128 blocks, two per
 // compute unit, for problems of less than a round or so, and a kernel without shared stages for few tiles (gemm_plan.h has the rule).  Enough
-// tokens of K up to 2048 go to gemm_resident.hip instead: what runs here of a size are few tokens, long K and the accumulator dump.
+// tokens of K up to 2048 go to gemm_resident.h instead: what runs here of a size are few tokens, long K and the accumulator dump.
 // (256 x 128 blocks, two per compute unit, so that one block's epilogue runs under the other's K loop, were built and measured:
 // the K loop is not limited by the matrix pipes but by what feeds them, and 1.5 times the LDS traffic per MFMA ate the overlap.)
 // The epilogue: accumulators from AGPRs, scale + bias, bf16, rows through a wave-private LDS tile, non-temporal 128-byte line

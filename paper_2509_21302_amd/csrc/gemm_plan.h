@@ -213,7 +213,7 @@ inline E2m3Plan e2m3_gemm_plan(int M, int N, int K, double *cost = nullptr)
     return {shape, M, shape};
 }
 
-// The kernel with the weights in registers (gemm_resident.hip): 256 channels per block, the tokens in as many ranges of steps of 32 as fill the
+// The kernel with the weights in registers (gemm_resident.h): 256 channels per block, the tokens in as many ranges of steps of 32 as fill the
 // chip.  K where 64 channels of a wave fit beside two sets of results; affine codes are written for K = 1024 and 2048 only.  (K = 128 and 256 have few
 // products per result: 40000 x 128 -> 2048 33.2 us in 256-row tiles, 31.8 in this one, 10992 x 256 -> 1024 8.1 / 8.9.)
 constexpr bool e2m3_resident_k(int K, bool shifted)

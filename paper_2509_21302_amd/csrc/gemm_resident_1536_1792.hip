@@ -1,0 +1,11 @@
+// The products with resident weights (gemm_resident.h) of K = 1536 and 1792.
+#include "gemm_resident.h"
+
+namespace qvggt {
+
+template hipError_t launch_resident<E2m3Codes, 12, 2, false>(const ResidentProblem &, hipStream_t);
+template hipError_t launch_resident<E2m3Codes, 14, 2, false>(const ResidentProblem &, hipStream_t);
+static const LdsKernel resident_lds_kernel_list[] = {QVGGT_RESIDENT(E2m3Codes, 12, 2, false), QVGGT_RESIDENT(E2m3Codes, 14, 2, false)};
+static const LdsKernels resident_lds_kernels(resident_lds_kernel_list);
+
+}  // namespace qvggt

@@ -1,4 +1,4 @@
-// The products with the weights resident in registers (gemm_resident.hip), for the problems that the rules of gemm_plan.h give them.
+// The products with the weights resident in registers (gemm_resident.h), for the problems that the rules of gemm_plan.h give them.
 #pragma once
 #include "qvggt_common.h"
 
