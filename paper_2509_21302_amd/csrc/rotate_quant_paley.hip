@@ -20,11 +20,12 @@
 // input was, and leave from there in whole units (E2M3: staged as bf16 numbers, which a conversion takes 32 at a time; converting staged bytes
 // took 5 vector instructions a code instead of 2) or 16-byte pieces of a row.
 //
-// Whole tiles are bound by the vector ALU (12 to 14 instructions a value) up to K = 1536 and by it and memory beyond: 16384 rows to E2M3, us of the general
-// kernel / this one, K = 768 18.0 / 14.8 (2.3 TB/s), 1536 29.5 / 23.9, 3072 69.0 / 36.1 (3.8 TB/s), 6144 148 / 82, 2560 51.9 / 32.6, 5120 110 / 66.8.  Two
-// waves per SIMD, for which some variants spill registers outside the products: 8 to 12 of 256 at K = 6144, up to 4 at 1536, 3072 and 5120; m = 20 and
-// K = 6144 with one wave per SIMD took 41.0, 76.7 and 87.1.
-// Column tiles are bound by latency (three barriers a tile) where there are few rows, by the fragments' way out of LDS where there are many.  us of a layer
+// Whole tiles are bound by the vector ALU (12 to 14 instructions a value; busy 47 % of the clocks at 24000 x 3072 and x 5120) up to K = 1536 and by it and
+// memory beyond: 16384 rows to E2M3, us of the general kernel / this one, K = 768 18.0 / 14.8 (2.3 TB/s), 1536 29.5 / 23.9, 3072 69.0 / 36.1 (3.8 TB/s),
+// 6144 148 / 82, 2560 51.9 / 32.6, 5120 110 / 66.8.  Two waves per SIMD, for which some variants spill registers: 9 to 11 of 256 at K = 6144, up to 4 at 1536,
+// 3072 and 5120; m = 20 and K = 6144 with one wave per SIMD took 41.0, 76.7 and 87.1.
+// Column tiles are bound by latency, three barriers a tile with 1.5 to 1.7 waves per SIMD: 7000 x 5120 39 us (3.2 TB/s), vector ALU busy 40 %, LDS 23 %;
+// 10992 x 768 10.3 us (2.3 TB/s), 29 % and 10 %; only at K = 8192 is LDS near half (16384 rows 129 us, 47 %, more than half of it bank conflicts).  us of a layer
 // with 512 channels, the general kernel (K = 8192: rotate_rows_kernel) in front / this one, 16 rows and 4097: K = 768 6.9 / 6.9 and 12.7 / 11.8, 1536 8.4 /
 // 7.2 and 18.8 / 16.8, 3072 12.1 / 8.1 and 34.4 / 25.7, 6144 12.0 / 11.1 and 65.8 / 43.0, 2560 11.2 / 8.3 and 27.3 / 25.0, 5120 10.9 / 9.8 and 50.5 / 39.4,
 // 8192 14.3 / 12.7 and 82.2 / 56.6; as packed or int8 rows up to 1024 rows of 768 values take 0.1 to 0.3 longer than there (7.0 / 7.2, 8.6 / 8.8).
