@@ -396,6 +396,42 @@ def test_a_rows_codes_do_not_depend_on_the_rows_that_come_with_it(K, dtype):
         assert torch.equal(whole, torch.cat(pieces))
 
 
+@pytest.mark.parametrize("K", [1024, 2048, 4096])
+def test_fused_forms_of_a_row_do_not_depend_on_the_rows_that_come_with_it(K):
+    """The same of bf16 rows with a LayerNorm or a GELU in front, of affine codes, and of both kinds of blocks (parts of whole 128-row blocks)."""
+    q, rows = G.q, 20483
+    X, signs, inv = _device_rows(rows, K, K + 2)
+    X = X.to(torch.bfloat16)
+    gamma, beta, table = torch.rand(K, device=G.DEV) + 0.5, torch.rand(K, device=G.DEV) - 0.5, G.gelu_table()
+
+    def packed(n):
+        return torch.empty(n, K // 2, dtype=torch.uint8, device=G.DEV)
+
+    def e2m3(n):
+        return torch.full((q.qvggt_e2m3_bytes(n, K),), 0x5A, dtype=torch.uint8, device=G.DEV)
+
+    def i8b(n):
+        return torch.full((q.qvggt_i8b_bytes(n, K),), 0x5A, dtype=torch.int8, device=G.DEV)
+    forms = [(e2m3, lambda x, out, s, z: q.qvggt_rotate_smooth_quant_e2m3(x, signs, inv, out, s)),
+             (i8b, lambda x, out, s, z: q.qvggt_rotate_smooth_quant_i8b(x, signs, inv, 8, out, s)),
+             (packed, lambda x, out, s, z: q.qvggt_rotate_smooth_quant_asym(x, signs, inv, out, s, z)),
+             (e2m3, lambda x, out, s, z: q.qvggt_rotate_smooth_quant_asym_e2m3(x, signs, inv, out, s, z)),
+             (packed, lambda x, out, s, z: q.qvggt_layernorm_rotate_smooth_quant(x, gamma, beta, 1e-5, signs, inv, out, s)),
+             (packed, lambda x, out, s, z: q.qvggt_gelu_rotate_smooth_quant(x, signs, inv, table, out, s)),
+             (e2m3, lambda x, out, s, z: q.qvggt_gelu_rotate_smooth_quant_e2m3(x, signs, inv, table, out, s))]
+    if K == 1024:
+        forms.append((e2m3, lambda x, out, s, z: q.qvggt_layernorm_rotate_smooth_quant_e2m3(x, gamma, beta, 1e-5, signs, inv, out, s)))
+    for form, (new, run) in enumerate(forms):
+        def result(x):
+            out, step, zero = new(x.shape[0]), torch.empty(x.shape[0], device=G.DEV), torch.zeros(x.shape[0], device=G.DEV)
+            run(x, out, step, zero)
+            return out, step, zero
+        cuts = [0, 128, 768, 3840, 9472, rows]
+        parts = [result(X[a:b]) for a, b in zip(cuts, cuts[1:])]
+        for whole, *pieces in zip(result(X), *parts):
+            assert torch.equal(whole, torch.cat(pieces)), form
+
+
 @pytest.mark.parametrize("K", [768, 1536, 3072, 6144, 2560, 5120, 8192])
 def test_several_tiles_per_wave_with_a_paley_factor(K):
     """Rows of the first, second and last tiles of a wave, and of the partial one at the end, against the oracle: packed and int8 codes, a given step per
