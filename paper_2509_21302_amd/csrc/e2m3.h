@@ -10,6 +10,7 @@ namespace qvggt {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int U_BYTES = 48;        // bytes per row per unit: 64 codes of 6 bits
@@ -22,12 +23,12 @@ constexpr int RB_PIECES = RB_BYTES / 1024;
 constexpr int UNIT_SCALE_ONE = 0;
 
 template <class F, int... Is>
-__device__ inline void e_static_for_impl(F &&f, std::integer_sequence<int, Is...>)
+__device__ __attribute__((always_inline)) inline void e_static_for_impl(F &&f, std::integer_sequence<int, Is...>)
 {
     (f(std::integral_constant<int, Is>{}), ...);
 }
 template <int N, class F>
-__device__ inline void e_static_for(F &&f)
+__device__ __attribute__((always_inline)) inline void e_static_for(F &&f)
 {
     e_static_for_impl(f, std::make_integer_sequence<int, N>{});
 }

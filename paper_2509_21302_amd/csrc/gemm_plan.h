@@ -220,8 +220,19 @@ constexpr bool e2m3_resident_k(int K, bool shifted)
 {
     return K == 1024 || K == 2048 || (!shifted && (K == 512 || K == 768 || K == 1280 || K == 1536 || K == 1792));
 }
-inline int resident_groups(int N) { return (N + 255) / 256; }
-inline int resident_ranges(int M, int N) { return std::max(1, std::min(256 / resident_groups(N), (M + 31) / 32)); }
+// CT: a wave has 16 CT channels (a block four times that) and 128 / CT tokens a step
+inline int resident_groups(int N, int CT = 4) { return (N + 64 * CT - 1) / (64 * CT); }
+inline int resident_ranges(int M, int N, int CT = 4) { return std::max(1, std::min(256 / resident_groups(N, CT), (M + 128 / CT - 1) / (128 / CT))); }
+
+// K = 1024, E2M3, no zero points: 128 channels a wave instead of 64 halve what a product reads from LDS and what comes from memory, and take 3 us more
+// to load.  us, 64 / 128 channels: 4096 channels, 10992 tokens (22 steps of a block) 30.1 / 28.3, 24576 (48) 58.3 / 53.1, 65536 (128) 137 / 127; 3072, 16384 (25)
+// 29.9 / 31.5, 24576 (37) 42.5 / 41.2, 65536 (98) 105 / 97; 2048, 32976 (33) 37.2 / 38.4, 65536 (64) 70.2 / 65.7; 1536, 65536 (49) 53.3 / 56.2; 1040, where the
+// wider groups leave a third of the chip idle, 44.9 / 48.3.  At K = 768 and 512, which were built as well, equal or slower up to 65536 tokens.
+inline bool resident_wide(int M, int N)
+{
+    auto steps = [&](int CT) { const int s = (M + 128 / CT - 1) / (128 / CT), r = resident_ranges(M, N, CT); return (s + r - 1) / r; };
+    return N >= 2048 && N <= 8192 && steps(8) >= 36 && steps(8) <= steps(4);
+}
 
 // Its price in microseconds, to be compared with the tiles'.  Loading the weights into the registers costs 5.3 + 2.4 k before the first product, a
 // step of a block 0.735 k, and writing Y 0.112 per megabyte on top of that.  Fitted to 660 random problems of 200 to 137400 rows, all seven K, timed

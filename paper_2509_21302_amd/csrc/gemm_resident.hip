@@ -7,7 +7,8 @@ static const LdsKernel resident_lds_kernel_list[] = {
     QVGGT_RESIDENT(E2m3Codes, 8, 1, false), QVGGT_RESIDENT(E2m3Codes, 12, 1, false), QVGGT_RESIDENT(E2m3Codes, 16, 1, false), QVGGT_RESIDENT(Int8Codes, 16, 2, false)};
 static const LdsKernels resident_lds_kernels(resident_lds_kernel_list);
 
-// elsewhere: gemm_resident_1280_2048.hip, gemm_resident_1536_1792.hip, gemm_resident_affine.hip
+// elsewhere: gemm_resident_1024_wide.hip, gemm_resident_1280_2048.hip, gemm_resident_1536_1792.hip, gemm_resident_affine.hip
+extern template hipError_t launch_resident_tiles<E2m3Codes, 16, 1, 8, false>(const ResidentProblem &, hipStream_t);
 extern template hipError_t launch_resident<E2m3Codes, 20, 1, false>(const ResidentProblem &, hipStream_t);
 extern template hipError_t launch_resident<E2m3Codes, 16, 2, false>(const ResidentProblem &, hipStream_t);
 extern template hipError_t launch_resident<E2m3Codes, 12, 2, false>(const ResidentProblem &, hipStream_t);
@@ -20,7 +21,11 @@ template <bool SHIFTED>
 hipError_t run_e2m3_resident(const ResidentProblem &p, hipStream_t stream)
 {
     switch (p.K) {
-        case 1024: return launch_resident<E2m3Codes, 16, 1, SHIFTED>(p, stream);
+        case 1024:
+            if constexpr (!SHIFTED) {
+                if (resident_wide(p.M, p.N)) return launch_resident_tiles<E2m3Codes, 16, 1, 8, false>(p, stream);
+            }
+            return launch_resident<E2m3Codes, 16, 1, SHIFTED>(p, stream);
         case 2048: return launch_resident<E2m3Codes, 16, 2, SHIFTED>(p, stream);
     }
     if constexpr (!SHIFTED) {

@@ -286,6 +286,26 @@ def test_resident_weights_where_the_kernels_differ(tmp_path, M, N, K, int8, resi
     assert int(out[2 if int8 else 0]) == resident
 
 
+def test_resident_weights_of_128_channels_a_wave(tmp_path):
+    """The GPU test's table reaches them, and its other rows do not; they come with full ranges and more of Y than goes through the caches."""
+    from tests.test_gpu_e2m3 import RESIDENT, RESIDENT_WIDE
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text('#include "gemm_plan.h"\n#include <cstdio>\nint main() { int M, N; while (std::scanf("%d %d", &M, &N) == 2) '
+                                    'std::printf("%d %d\\n", qvggt::resident_wide(M, N), qvggt::resident_groups(N, 8) * qvggt::resident_ranges(M, N, 8)); }\n')
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+
+    def ask(problems):
+        out = subprocess.run([tmp_path / "d"], input="\n".join("%d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
+        return [(int(out[i]), int(out[i + 1])) for i in range(0, len(out), 2)]
+    assert all(wide for wide, _ in ask([p[:2] for p in RESIDENT_WIDE])) and not any(wide for wide, _ in ask([p[:2] for p in RESIDENT]))
+    rng = random.Random(3)
+    problems = [(int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(8192))))) for _ in range(20000)]
+    for (M, N), (wide, blocks) in zip(problems, ask(problems)):
+        if wide: assert 2 * M * N > 130e6 and 224 < blocks <= 256, (M, N)
+
+
 def test_resident_weights(tmp_path):
     """The GPU test's table reaches the kernel with every K it takes; no other K does, nor affine codes with those that kernel 1 does not write; the
     blocks of a launch have a compute unit each unless there are more groups of channels than that."""
