@@ -18,7 +18,7 @@ LIB = os.path.join(HERE, "libqvggt.so")
 CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))       # another Python does not find it
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["api.hip", "rotate_quant.hip", "rotate_quant_mfma.hip", "gemm_w4a4.hip", "nfds.hip",
-           "rotate_quant_general.hip", "rotate_quant_paley.hip", "gemm_e2m3.hip", "gemm_resident.hip",
+           "rotate_quant_general.hip", "rotate_quant_paley.hip", "gemm_e2m3.hip", "gemm_e2m3_256.hip", "gemm_resident.hip",
            "gemm_resident_1024_wide.hip", "gemm_resident_1280_2048.hip", "gemm_resident_1536_1792.hip", "gemm_resident_affine.hip", "linear_small.hip", "ceilings.hip", "calib.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

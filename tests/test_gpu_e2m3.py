@@ -393,6 +393,28 @@ def test_e2m3_gemm_shifted_in_divided_plans(M, N, K, plan):
     test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan)
 
 
+# 256-row tiles of K = 128, one step of the kernel (the others have an even number), with several tiles per block, and affine codes of too few steps for it
+@pytest.mark.parametrize("M,N,K", [(16381, 1024, 128), (65550, 2048, 128)])
+def test_e2m3_gemm_with_one_step_per_tile(M, N, K):
+    test_e2m3_gemm_in_every_tile_shape(M, N, K, "")
+
+
+@pytest.mark.parametrize("K", [128, 256, 512])
+def test_e2m3_gemm_shifted_with_few_steps(K):
+    """Half-integer codes against the sum in 64 bits."""
+    M, N = 16381, 1024
+    gen = torch.Generator(device=G.DEV).manual_seed(K)
+    qx = torch.randint(-7, 8, (M, K), generator=gen, device=G.DEV, dtype=torch.int8)
+    qw = torch.randint(-7, 8, (N, K), generator=gen, device=G.DEV, dtype=torch.int8)
+    (_, Xf), (_, Wf) = _e2m3(qx.cpu().numpy()), _e2m3(qw.cpu().numpy())
+    sx, zx = torch.rand(M, generator=gen, device=G.DEV) + 0.5, torch.randint(0, 16, (M,), generator=gen, device=G.DEV).float()
+    sw, wsum, Y = torch.rand(N, generator=gen, device=G.DEV) * 1e-3, qw.float().sum(1), torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV)
+    G.q.qvggt_e2m3_gemm_shifted(Xf, sx, zx, Wf, sw, wsum, None, M, N, K, Y)
+    want = (qx.double() @ qw.double().t() + (7.5 - zx.double())[:, None] * wsum.double()) * sx.double()[:, None] * sw.double()
+    # the sums are exact; three roundings to float32 and one to bf16
+    assert ((Y.double() - want).abs() <= want.abs() * (2.0 ** -8 + 2.0 ** -21)).all().item()
+
+
 # The kernel with the weights in registers (tests/test_gemm_plan.py holds these to the rule): every K, last steps of 1 to 31 tokens, last waves of 16, 32
 # and 48 channels and waves without any, ranges of unequal length, more groups of channels than compute units, Y through the caches (3056)
 RESIDENT = [(3001, 3088, 512), (40, 66064, 512), (2017, 4112, 768), (5001, 3312, 768), (2015, 4112, 1024), (10992, 3056, 1024), (10990, 1040, 1024),
