@@ -234,26 +234,27 @@ inline bool resident_wide(int M, int N)
     return N >= 2048 && N <= 8192 && steps(8) >= 36 && steps(8) <= steps(4);
 }
 
-// Its price in microseconds, to be compared with the tiles'.  Loading the weights into the registers costs 5.3 + 2.4 k before the first product, a
-// step of a block 0.735 k, and writing Y 0.112 per megabyte on top of that.  Fitted to 660 random problems of 200 to 137400 rows, all seven K, timed
-// with kernel 1 in front beside the tiles' plan: within 4 % of a call's time (rms).  The tiles' price is too high where the rows of Y are 64-byte pieces
-// but no whole lines (N = 32 mod 64: 13740 x 1280 -> 800 23.2 / 26.2, 37024 -> 224 27.6 / 29.6), hence the 1.06.  On other 3000 problems, with kernel 1 (K = 1024,
-// 2048) or a copy of the codes in front, the 1560 that come to this kernel are 1.20 times faster than in tiles on geometric average; 25 of them are
-// slower by more than 2 %, 11 of these with 272 to 368 channels and tens of thousands of tokens (90762 x 1792 -> 352 81.3 / 95.0).  us of the GEMM,
-// tiles / this one: 137400 x 1024 -> 4096 385 / 321, 32976 x 2048 -> 4096 161 / 128, 10992 x 1024 -> 4096 38.9 / 29.2, 10992 x 768 -> 3072 25.8 / 21.1,
-// 4096 x 1024 -> 4096 15.9 / 15.6, 2048 x 1024 -> 4096 9.5 / 10.7, 1374 x 2048 -> 4096 12.0 / 15.6.
+// Its price in microseconds, to be compared with the tiles'.  Loading the weights into the registers costs 5.5 + 2.4 k before the first product, a
+// step of a block 0.62 k, and writing Y 0.098 per megabyte on top of that.  Fitted to the products alone of 7 widths x 7 token counts at K = 512, 768 and 1024 (5 %, rms),
+// with 1.5 us more before the first step as calls run it, behind kernel 1: without them calls of few steps lose (with kernel 1, 2355 x 1024 -> 704, two steps, 10.4 in
+// tiles / 11.1 here, 585 x 1024 -> 2576 9.8 / 10.6).  Of 60 random calls of 400 to 60000 rows that this price brings here and the one of the kernel on 32x32
+// instructions (5.3 + 2.4 k, 0.735 k, 0.112) left in tiles, 5 % are gained on geometric average, 1.5 % lost at worst: us with kernel 1, tiles / this one:
+// 6452 x 2048 -> 3552 46.7 / 42.2, 2872 x 1536 -> 2928 23.7 / 20.3, 3697 x 1280 -> 2576 26.7 / 21.7, 4791 x 1024 -> 2720 23.1 / 21.3, 7690 x 1024 -> 1920 23.4 / 21.1,
+// 32648 x 1024 -> 448 39.9 / 35.4, 33436 x 1024 -> 256 34.1 / 34.6.  The tiles' price is too high where the rows of Y are 64-byte pieces but no whole lines (N = 32
+// mod 64: 13740 x 1280 -> 800, 37024 -> 224): 1.12.  Affine codes at K = 2048, whose kernel is short of registers, 1.05 (2844 x 2048 -> 3568 26.3 / 27.9).  us of the product, tiles / this one: 137400 x 1024 -> 4096 385 / 264, 32976 x 1024 -> 4096 90 / 71.6,
+// 10992 x 1024 -> 4096 38.9 / 28, 10992 x 768 -> 3072 25.8 / 18.5, 4096 x 1024 -> 4096 15.9 / 13.5, 2048 x 1024 -> 4096 9.5 / 9.6.
 inline double e2m3_resident_cost(int M, int N, int K)
 {
     const double k = K / 1024.0;
     const int steps = (M + 31) / 32, ranges = resident_ranges(M, N);
-    return 1.015 * (5.3 + 2.4 * k + 0.735 * k * ((steps + ranges - 1) / ranges) + 0.112e-6 * 2.0 * M * N);
+    return 1.015 * (5.5 + 2.4 * k + 0.62 * k * ((steps + ranges - 1) / ranges) + 0.098e-6 * 2.0 * M * N);
 }
 inline bool e2m3_resident(int M, int N, int K, bool shifted)
 {
     if (!e2m3_resident_k(K, shifted)) return false;
     double tiles;
     e2m3_gemm_plan(M, N, K, &tiles);
-    return e2m3_resident_cost(M, N, K) * (N % 64 == 32 ? 1.06 : 1.0) < tiles;
+    return e2m3_resident_cost(M, N, K) * (N % 64 == 32 ? 1.12 : 1.0) * (shifted && K == 2048 ? 1.05 : 1.0) < tiles;
 }
 
 // int8 blocks with the weights in registers: K = 1024, whose 256 channels take half of them (blocks come with K = 1024, 2048 and 4096; at 2048 they would
