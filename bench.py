@@ -302,7 +302,7 @@ def main():
     # the contraction is priced against the peak of the matrix instructions it runs on
     mfma_peak = FP6_PEAK_TOPS if headline == "e2m3" else INT8_PEAK_TOPS
     # the mean over the layers' launches, which more than one kernel takes (fc1 and fc2 at 100 frames: the first and the second)
-    gemm_kernels = {"e2m3": "resident_gemm_kernel and e2m3_gemm_kernel", "i8b": "resident_gemm_kernel and w4a4_gemm_tail_kernel"}.get(
+    gemm_kernels = {"e2m3": "resident_gemm_kernel and e2m3_256_kernel", "i8b": "resident_gemm_kernel and w4a4_gemm_tail_kernel"}.get(
         headline, "w4a4_gemm_kernel and w4a4_gemm_tail_kernel")
     roofline = dict(kernel=gemm_kernels, bound="mfma", achieved=gemm_tops,
                     peak=mfma_peak, unit="TFLOP/s" if headline == "e2m3" else "TOP/s",
