@@ -359,8 +359,9 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
         constexpr int b = decltype(b_c)::value, part = decltype(part_c)::value;
         constexpr bool FIRST = decltype(first_c)::value;
         e_wait_vmcnt<(ST - 3) * C::LPW_MIN>();
-        // a barrier alone: what __syncthreads() waits for besides, the LDS reads in flight, are fragments and scales of the stages just opened, which
-        // nothing overwrites before the next barrier
+        // A barrier, and of the LDS reads in flight, all of which __syncthreads() waits for, only the oldest: the scales read eight slots ago, whose place (PARTS = 1) is
+        // written during this stage.  The two to four reads after them are fragments of the stage just opened, which nothing overwrites before the next barrier.
+        if constexpr (PARTS == 1) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(CT == 4 && CODES::WREGS == 6 ? 2 : 1) : "memory");
         asm volatile("s_barrier" ::: "memory");
         using LP = std::integral_constant<int, (part + ST - 1) % PARTS>;  // the part that ring stage ps is refilled with
         const uint8_t *from = smem + cs;
