@@ -33,8 +33,8 @@ namespace qvggt {
 
 typedef int v6i __attribute__((ext_vector_type(6)));
 
-// 8 or 16 bytes per lane to base + lane_off, past the caches or through them.  A store of more than 8 wants one wait state before its registers are
-// written again, which the compiler does not put behind an asm block: the s_nop.
+// 8 or 16 bytes per lane to base + lane_off, past the caches or through them.  A store of more than 8 wants two wait states before its registers are
+// written again (the compiler puts s_nop 1 behind its own), which the compiler does not put behind an asm block.
 template <bool STREAM>
 __device__ inline void store_row(void *base, uint32_t lane_off, const uint32_t (&v)[2])
 {
@@ -46,8 +46,8 @@ template <bool STREAM>
 __device__ inline void store_row(void *base, uint32_t lane_off, const uint32_t (&v)[4])
 {
     const v4i w = {(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
-    if constexpr (STREAM) asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 0" ::"v"(lane_off), "v"(w), "s"(base) : "memory");
-    else asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 0" ::"v"(lane_off), "v"(w), "s"(base) : "memory");
+    if constexpr (STREAM) asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1" ::"v"(lane_off), "v"(w), "s"(base) : "memory");
+    else asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" ::"v"(lane_off), "v"(w), "s"(base) : "memory");
 }
 
 // An operand format.  A fragment is what an MFMA takes of 16 rows: 128 codes of each in E2M3 (two K-tiles of the format), 64 in int8 (one).  Lane l has
