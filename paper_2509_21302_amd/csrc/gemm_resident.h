@@ -323,10 +323,10 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 
     // ---- results: register r of accumulator [i][j] is token 16 i + 4 g + r of the step, channel j of the lane's
     typename CODES::Sums acc[2][GROUPS][CT];
-    // scales (and zero points) of the tokens whose results leave: read while the step before is multiplied into the other of two sets; where TIGHT, four
-    // tokens' at the last moment
-    constexpr int NS = TIGHT ? 1 : GROUPS, NB = TIGHT ? 1 : 2;
-    static_assert(NS == GROUPS || PARTS == 2, "scales that are read late have places that last");
+    // scales (and zero points) of the tokens whose results leave: read while the step before is multiplied into the other of two sets; where registers are short
+    // and the places last (PARTS = 2), four tokens' at the last moment
+    constexpr bool LATE = TIGHT && PARTS == 2;
+    constexpr int NS = LATE ? 1 : GROUPS, NB = LATE ? 1 : 2;
     float4 st[NB][NS], zt[NB][NS];
     float m0, m1, y0, y1;
     uint32_t out[CT / 2];
@@ -359,14 +359,18 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
         constexpr int b = decltype(b_c)::value, part = decltype(part_c)::value;
         constexpr bool FIRST = decltype(first_c)::value;
         e_wait_vmcnt<(ST - 3) * C::LPW_MIN>();
-        // A barrier, and of the LDS reads in flight, all of which __syncthreads() waits for, only the oldest: the scales read eight slots ago, whose place (PARTS = 1) is
-        // written during this stage.  The two to four reads after them are fragments of the stage just opened, which nothing overwrites before the next barrier.
-        if constexpr (PARTS == 1) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(CT == 4 && CODES::WREGS == 6 ? 2 : 1) : "memory");
+        constexpr int SLOTS = CT * FRAGS, ALL_SLOTS = SLOTS * PARTS, PERIOD = ALL_SLOTS / 16;
+        constexpr int SCALES_BEFORE = LATE ? 1 : 8;                      // slots from the scales' reads to the end of the stage
+        constexpr int READS_AFTER = SCALES_BEFORE / CT * (CODES::WREGS == 6 ? 2 : 1);      // the fragments' in these slots
+        static_assert(PARTS == 2 || (SCALES_BEFORE % CT == 0 && READS_AFTER >= 2), "what the barrier may leave in flight is newer than the scales");
+        // A barrier, and of the LDS reads in flight, all of which __syncthreads() waits for, only the older: the scales', whose place (PARTS = 1) is
+        // written during this stage.  The READS_AFTER behind them are fragments of the stage just opened, which nothing overwrites before the next barrier; half of them
+        // are waited for too, should the compiler have joined two.
+        if constexpr (PARTS == 1) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(READS_AFTER / 2) : "memory");
         asm volatile("s_barrier" ::: "memory");
         using LP = std::integral_constant<int, (part + ST - 1) % PARTS>;  // the part that ring stage ps is refilled with
         const uint8_t *from = smem + cs;
         const typename CODES::Sums zero = {0, 0, 0, 0};
-        constexpr int SLOTS = CT * FRAGS, ALL_SLOTS = SLOTS * PARTS, PERIOD = ALL_SLOTS / 16;
         e_static_for<SLOTS>([&](auto t_c) __attribute__((always_inline)) {
             constexpr int t = decltype(t_c)::value, u = t / CT, i = u % GROUPS, j = t % CT, un = u + D;
             acc[b][i][j] = CODES::multiply(F[u % R], W[(part * FRAGS + u) / GROUPS][j], part == 0 && u < GROUPS ? zero : acc[b][i][j]);
@@ -409,7 +413,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
                     }
                 });
             }
-            if constexpr (t == SLOTS - (TIGHT ? 1 : 8) && part == PARTS - 1) {      // for this step's results
+            if constexpr (t == SLOTS - SCALES_BEFORE && part == PARTS - 1) {      // for this step's results
                 sc = PARTS == 1 ? cs : after(sc);
 #pragma unroll
                 for (int i = 0; i < NS; ++i) read_scales(b_c, i);
