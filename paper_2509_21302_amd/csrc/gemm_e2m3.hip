@@ -29,7 +29,7 @@
 //
 // Tiles: 192 x 256 per block, one block per compute unit, four waves of 96 x 128 (192 accumulator registers each); 128 x 128 blocks, two per
 // compute unit, for problems of less than a round or so, and a kernel without shared stages for few tiles; 256 x 256 where many tokens fill
-// them (gemm_e2m3_256.hip; gemm_plan.h has the rule).  Enough
+// them, here for K of 128 to 512, else in gemm_e2m3_256.hip (gemm_plan.h has the rules).  Enough
 // tokens of K up to 2048 go to gemm_resident.h instead: what runs here of a size are few tokens, long K and the accumulator dump.
 // (256 x 128 blocks, two per compute unit, so that one block's epilogue runs under the other's K loop, were built and measured:
 // the K loop is not limited by the matrix pipes but by what feeds them, and 1.5 times the LDS traffic per MFMA ate the overlap.)
@@ -560,8 +560,8 @@ hipError_t run_codes_to_e2m3(const uint8_t *packed, int rows, int K, uint8_t *ou
 #define QVGGT_E2M3_FEW_KERNELS(TM, TN, KW, DEPTH)                                                                                   \
     {reinterpret_cast<const void *>(e2m3_gemm_few_kernel<TM, TN, KW, DEPTH, false>), E2m3FewCfg<TM, TN, KW>::LDS_BYTES}, \
     {reinterpret_cast<const void *>(e2m3_gemm_few_kernel<TM, TN, KW, DEPTH, true>), E2m3FewCfg<TM, TN, KW>::LDS_BYTES}
-static const LdsKernel e2m3_lds_kernel_list[] = {QVGGT_E2M3_KERNELS(3, 4, 2, 2, 5, 1),
-                                                 QVGGT_E2M3_KERNELS(2, 2, 2, 2, 4, 2),
+static const LdsKernel e2m3_lds_kernel_list[] = {QVGGT_E2M3_KERNELS(4, 4, 2, 2, 5, 1), QVGGT_E2M3_KERNELS(3, 4, 2, 2, 5, 1),
+                                                 QVGGT_E2M3_KERNELS(2, 2, 2, 2, 4, 2), QVGGT_E2M3_VARIANT(4, 4, 2, 2, 5, 1, false, false),
                                                  QVGGT_E2M3_VARIANT(3, 4, 2, 2, 5, 1, false, false), QVGGT_E2M3_VARIANT(2, 2, 2, 2, 4, 2, true, true),
                                                  QVGGT_E2M3_FEW_KERNELS(2, 2, 4, 4),
                                                  QVGGT_E2M3_FEW_KERNELS(1, 2, 4, 4), QVGGT_E2M3_FEW_KERNELS(1, 1, 8, 2)};
@@ -612,8 +612,8 @@ hipError_t launch_e2m3_shape(E2m3Plan::Shape shape, const E2m3Problem &p, hipStr
 {
     switch (shape) {
         case E2m3Plan::k256:
-            if (!SHIFTED || p.K >= 384) return run_e2m3_256<SHIFTED>(p, stream);
-            [[fallthrough]];
+            if (tiles256_k(p.K)) return run_e2m3_256<SHIFTED>(p, stream);
+            return launch_e2m3<4, 4, 2, 2, 5, 1, SHIFTED>(p, stream);
         case E2m3Plan::k192: return launch_e2m3<3, 4, 2, 2, 5, 1, SHIFTED>(p, stream);
         case E2m3Plan::k128: return launch_e2m3<2, 2, 2, 2, 4, 2, SHIFTED>(p, stream);
         case E2m3Plan::k64: return launch_e2m3_few<2, 2, 4, 4, SHIFTED>(p, stream);

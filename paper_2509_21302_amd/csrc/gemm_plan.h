@@ -7,6 +7,14 @@
 
 namespace qvggt {
 
+// 256 x 256 tiles of E2M3 codes and of int8 blocks: on the 16 x 16 matrix instructions (gemm_tiles256.h), where K has enough steps to pay for filling their ring of
+// stages; fewer in the kernels on 32 x 32 ones (gemm_e2m3.hip, gemm_w4a4.hip).  us, 32 x 32 / 16 x 16, K = 128: E2M3 16381 -> 1024 10.7 / 12.0, 30000 -> 4096
+// 46.4 / 50.0, affine 16381 -> 1024 11.3 / 12.7, int8 16381 -> 1024 10.9 / 12.8, 13741 -> 3056 47.9 / 49.7; K = 256: 10.9 / 11.6, 54.0 / 55.7, 11.3 / 11.9,
+// 11.6 / 12.7, 48.9 / 50.5, with a tail 13073 -> 14064 216 / 220; K = 512: affine 16381 -> 1024 13.1 / 13.4, 30000 -> 4096 69.3 / 72.2, 65550 -> 2048 80.3 / 79.9, int8
+// 14.1 / 14.6, 9000 -> 1552 21.2 / 21.6, 65550 -> 2048 96.6 / 95.7; K = 768: int8 16381 -> 1024 17.8 / 17.2, 65550 -> 2048 119 / 117, 9000 -> 1552 24.0 / 24.4;
+// K = 1280: 23.3 / 22.9, 171 / 162, 30.1 / 29.6; 3 to 7 % ahead at K = 2560 to 8192.
+constexpr bool tiles256_k(int K) { return K >= 768; }
+
 struct GemmPlan {
     enum Shape { kBig, kSmall, kDeep, kBigThenDeep } shape;
     int rows_main;      // kBigThenDeep: the token rows (whole 256-row tiles) that go to the big tiles

@@ -1,4 +1,4 @@
-// Products in tiles of 256 tokens x 256 channels, E2M3 and int8 codes: gemm_e2m3_256.hip and gemm_w4a4.hip have the kernels.
+// Products in tiles of 256 tokens x 256 channels, E2M3 and int8 codes, K of 768 and more (tiles256_k): gemm_e2m3_256.hip and gemm_w4a4.hip have the kernels.
 //
 // Four waves per block and compute unit, each with 128 x 128 of the tile: 256 accumulator registers, the least operand traffic per MFMA that the register
 // file allows.  Persistent blocks, XCD-contiguous tile ranges, operands from global memory straight into an LDS ring (global_load_lds_dwordx4, 1 KiB
@@ -52,8 +52,10 @@ struct Cfg256 {
     static constexpr int SC_SYM_GROUPS = BM / 64 + BN / 64 + BN / 128;
     static constexpr int SC_BYTES = SC_SYM_BYTES + (SHIFTED ? BM * 4 + BN * 4 : 0);     // then zero points f32, code sums f32
     static constexpr int SC_GROUPS = SC_SYM_GROUPS + (SHIFTED ? BM / 64 + BN / 64 : 0);
-    // scales of the tile and of the next, or where LDS does not hold both of the tile alone, which then takes MIN_PAIRS K-steps to have them everywhere
-    static constexpr int SC_BUFFERS = SHIFTED ? 1 : 2, MIN_PAIRS = SHIFTED ? 3 : 1;
+    // scales of the tile and of the next, or where LDS does not hold both of the tile alone.  They go out before the transfers of the tile's first K-step and have landed
+    // when all but the transfers of STAGES - 2 steps have: at the opening of its step STAGES - 2
+    static constexpr int SC_BUFFERS = SHIFTED ? 1 : 2;
+    static_assert(tiles256_k(768) && !tiles256_k(767) && 768 / 64 / KTILES >= STAGES - 1, "a tile of the least K has that step");
     static constexpr int EP_PITCH = 128 + 16, EP_BYTES = NW * 16 * EP_PITCH;
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + SC_BUFFERS * SC_BYTES + EP_BYTES;
     static_assert(BM % RB == 0 && BN % RB == 0 && NT % NW == 0, "tiles are whole blocks of the operand format, and every wave has as many pieces");
@@ -254,8 +256,8 @@ __device__ __forceinline__ void tiles256(
         // its LDS reads fetch the first fragments of the block's next tile: they live through the epilogue
         if (left == 1) {
             step(I1{}, BF{});
-        } else {                                                 // an odd number of K-steps: they are in the other buffer
-#pragma unroll
+        } else {                                                 // an odd number of K-steps (no K that calls have): they are in the other buffer.  Without this
+#pragma unroll                                                   // branch the compiler moves accumulators about in the loop, and the affine kernels use scratch memory
             for (int f = 0; f < NF; ++f)
 #pragma unroll
                 for (int e = 0; e < CODES::REGS; ++e) F[0][f][e] = F[1][f][e];

@@ -500,12 +500,12 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 // tiles through a ring of twice the stages (the same LDS), in one launch: a block goes on to the rest when it is done, with no second
 // launch behind the slowest block, and one block per compute unit has the LDS to keep seven K-tiles in flight, which is what a tile
 // without company is bound by.
-template <int CB, bool BLK>
+template <int CB, bool BLK, bool T256>
 __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void w4a4_gemm_tail_kernel(
     const uint8_t *__restrict__ Xq, const float *__restrict__ sx, const uint8_t *__restrict__ Wq,
     const float *__restrict__ sw, const uint16_t *__restrict__ bias, int M, int rows_main, int N, int K, uint16_t *__restrict__ Y)
 {
-    if constexpr (BLK) tiles256<Int8Tiles, false, false, true>(Xq, sx, Wq, sw, bias, rows_main, N, K, Y, nullptr, rows_main / 256, (N + 255) / 256, nullptr, nullptr);
+    if constexpr (T256) tiles256<Int8Tiles, false, false, true>(Xq, sx, Wq, sw, bias, rows_main, N, K, Y, nullptr, rows_main / 256, (N + 255) / 256, nullptr, nullptr);
     else w4a4_tiles<4, 4, 2, 2, 4, CB, false, false, BLK>(Xq, sx, Wq, sw, bias, rows_main, N, K, Y, nullptr, nullptr, nullptr);
     __syncthreads();                     // every wave is done with its LDS before the ring is laid out anew
     w4a4_tiles<2, 2, 2, 2, 8, CB, false, false, BLK, true>(Xq + (size_t)rows_main * (CB == 4 ? K / 2 : K), sx + rows_main, Wq, sw, bias,
@@ -664,15 +664,12 @@ __global__ __launch_bounds__(KW * 64, 1) void w4a4_gemm_few_kernel(
 // every instantiation launched below, with the dynamic LDS it needs: packed codes (plain, accumulator dump, affine), int8 codes
 // row-major and in blocks (plain, accumulator dump)
 #define QVGGT_GEMM_KERNELS(TM, TN, WM, WN, ST, MB)                                                                                        \
-    {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, false, false, true>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
-    QVGGT_GEMM_KERNELS_BIG(TM, TN, WM, WN, ST, MB)
-// the big tiles take blocks for the accumulator dump only: i8b_256_kernel
-#define QVGGT_GEMM_KERNELS_BIG(TM, TN, WM, WN, ST, MB)                                                                                    \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 4, false, false, false>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES}, \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 4, true, false, false>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 4, false, true, false>), StreamCfg<TM, TN, WM, WN, ST, true>::LDS_BYTES},   \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, false, false, false>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES}, \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, true, false, false>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
+    {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, false, false, true>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES},  \
     {reinterpret_cast<const void *>(w4a4_gemm_kernel<TM, TN, WM, WN, ST, MB, 8, true, false, true>), StreamCfg<TM, TN, WM, WN, ST, false>::LDS_BYTES}
 #define QVGGT_FEW_KERNELS(TM, TN, KW, D)                                                                                                  \
     {reinterpret_cast<const void *>(w4a4_gemm_few_kernel<TM, TN, KW, D, 4, false, false>), FewCfg<TM, TN, KW>::LDS_BYTES}, \
@@ -680,15 +677,15 @@ __global__ __launch_bounds__(KW * 64, 1) void w4a4_gemm_few_kernel(
     {reinterpret_cast<const void *>(w4a4_gemm_few_kernel<TM, TN, KW, D, 8, false, false>), FewCfg<TM, TN, KW>::LDS_BYTES}, \
     {reinterpret_cast<const void *>(w4a4_gemm_few_kernel<TM, TN, KW, D, 8, false, true>), FewCfg<TM, TN, KW>::LDS_BYTES}
 static constexpr int TAIL_LDS_BYTES = std::max({StreamCfg<4, 4, 2, 2, 4>::LDS_BYTES, StreamCfg<2, 2, 2, 2, 8>::LDS_BYTES, Cfg256<Int8Tiles, false>::LDS_BYTES});
-static const LdsKernel gemm_lds_kernel_list[] = {QVGGT_GEMM_KERNELS_BIG(4, 4, 2, 2, 4, 1), QVGGT_GEMM_KERNELS(2, 2, 2, 2, 3, 2),
+static const LdsKernel gemm_lds_kernel_list[] = {QVGGT_GEMM_KERNELS(4, 4, 2, 2, 4, 1), QVGGT_GEMM_KERNELS(2, 2, 2, 2, 3, 2),
                                                  {reinterpret_cast<const void *>(i8b_256_kernel), Cfg256<Int8Tiles, false>::LDS_BYTES},
                                                  QVGGT_GEMM_KERNELS(2, 2, 2, 2, 8, 1),
                                                  QVGGT_FEW_KERNELS(2, 2, 4, 2), QVGGT_FEW_KERNELS(1, 2, 4, 2), QVGGT_FEW_KERNELS(1, 1, 8, 2),
-                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<4, false>), TAIL_LDS_BYTES},
-                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, false>), TAIL_LDS_BYTES},
-                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, true>), TAIL_LDS_BYTES}};
+                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<4, false, false>), TAIL_LDS_BYTES},
+                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, false, false>), TAIL_LDS_BYTES},
+                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, true, false>), TAIL_LDS_BYTES},
+                                                 {reinterpret_cast<const void *>(w4a4_gemm_tail_kernel<8, true, true>), TAIL_LDS_BYTES}};
 #undef QVGGT_GEMM_KERNELS
-#undef QVGGT_GEMM_KERNELS_BIG
 #undef QVGGT_FEW_KERNELS
 static const LdsKernels gemm_lds_kernels(gemm_lds_kernel_list);
 
@@ -700,9 +697,7 @@ static hipError_t launch_gemm(const uint8_t *Xq, const float *sx, const uint8_t 
     using C = StreamCfg<TM, TN, WM, WN, STAGES, ASYM>;
     // the variant that also writes the raw accumulators is a separate instantiation: the production kernel carries none of it
     const bool debug = acc_debug != nullptr;
-    constexpr bool DUMP_ONLY = BLK && TM == 4;       // the others: i8b_256_kernel
-    if (DUMP_ONLY && !debug) return hipErrorInvalidValue;
-    auto kern = w4a4_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, CB, DUMP_ONLY, ASYM, BLK>;
+    auto kern = w4a4_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, CB, false, ASYM, BLK>;
     if constexpr (!ASYM) {
         if (debug) kern = w4a4_gemm_kernel<TM, TN, WM, WN, STAGES, MINB, CB, true, false, BLK>;
     } else {
@@ -727,8 +722,11 @@ static hipError_t launch_gemm_tail(const uint8_t *Xq, const float *sx, const uin
     if ((CB == 4 ? K / 2 : K) / KT_BYTES < StreamCfg<2, 2, 2, 2, 8>::MIN_KTILES) return hipErrorInvalidValue;      // no plan asks for it
     hipError_t e = prepare_device();
     if (e != hipSuccess) return e;
-    w4a4_gemm_tail_kernel<CB, BLK><<<256, 256, TAIL_LDS_BYTES, stream>>>(Xq, sx, Wq, sw, reinterpret_cast<const uint16_t *>(bias), M, rows_main, N,
-                                                                         K, reinterpret_cast<uint16_t *>(Y));
+    auto kern = w4a4_gemm_tail_kernel<CB, BLK, BLK>;
+    if constexpr (BLK) {
+        if (!tiles256_k(K)) kern = w4a4_gemm_tail_kernel<CB, BLK, false>;
+    }
+    kern<<<256, 256, TAIL_LDS_BYTES, stream>>>(Xq, sx, Wq, sw, reinterpret_cast<const uint16_t *>(bias), M, rows_main, N, K, reinterpret_cast<uint16_t *>(Y));
     return hipGetLastError();
 }
 
@@ -782,7 +780,7 @@ static hipError_t gemm_by_plan(const uint8_t *Xq, const float *sx, const uint8_t
     switch (plan.shape) {
         case GemmPlan::kBig:
             if constexpr (BLK) {
-                if (acc_debug == nullptr) return launch_i8b_256(Xq, sx, Wq, sw, bias, M, N, K, Y, stream);
+                if (acc_debug == nullptr && tiles256_k(K)) return launch_i8b_256(Xq, sx, Wq, sw, bias, M, N, K, Y, stream);
             }
             return QVGGT_ROWS(4, 4, 4, 1, 0, M);
         case GemmPlan::kSmall: return QVGGT_ROWS(2, 2, 3, 2, 0, M);

@@ -209,6 +209,22 @@ def test_e2m3_plan_where_the_shapes_differ(tmp_path, M, N, K, plan):
     assert (shape if int(rows) == M else f"{shape}+{rest}") == plan
 
 
+def test_256_row_tiles_of_short_k(tmp_path):
+    """K below 768 runs on the 32 x 32 instructions, which measured up to 15 % faster there; the GPU tests reach both kinds in whole
+    plans of 256-row tiles that the weights in registers do not take."""
+    from tests.test_gpu_e2m3 import SHIFTED_SHORT_K, SHORT_K
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text('#include "gemm_plan.h"\n#include <cstdio>\nusing namespace qvggt;\nint main() { int M, N, K, s; while (std::scanf("%d %d %d %d", &M, &N, &K, &s) == 4) {'
+                                    'const E2m3Plan p = e2m3_gemm_plan(M, N, K); std::printf("%d %d\\n", p.shape == E2m3Plan::k256 && p.rows_main == M && !e2m3_resident(M, N, K, s != 0), tiles256_k(K)); } }\n')
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+    problems = [(*p, 0) for p in SHORT_K] + [(*p, 1) for p in SHIFTED_SHORT_K]
+    out = subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
+    assert [(int(a), int(b)) for a, b in zip(out[::2], out[1::2])] == [(1, p[2] >= 768) for p in problems]
+    assert {p[2] for p in problems} == {128, 256, 512, 768}
+
+
 VARIANT_DRIVER = r"""
 #include "gemm_plan.h"
 #include <cstdio>

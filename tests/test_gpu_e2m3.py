@@ -393,22 +393,46 @@ def test_e2m3_gemm_shifted_in_divided_plans(M, N, K, plan):
     test_e2m3_gemm_shifted_in_every_tile_shape(M, N, K, plan)
 
 
-# 256-row tiles of K = 128, one step of the kernel (the others have an even number), with several tiles per block, and affine codes of too few steps for it
-@pytest.mark.parametrize("M,N,K", [(16381, 1024, 128), (65550, 2048, 128)])
+# 256-row tiles of short K, which run on the 32 x 32 instructions, with several tiles per block
+SHORT_K = [(16381, 1024, 128), (65550, 2048, 128), (98460, 144, 256)]
+
+
+@pytest.mark.parametrize("M,N,K", SHORT_K)
 def test_e2m3_gemm_with_one_step_per_tile(M, N, K):
     test_e2m3_gemm_in_every_tile_shape(M, N, K, "")
 
 
-@pytest.mark.parametrize("K", [128, 256, 512])
-def test_e2m3_gemm_shifted_with_few_steps(K):
+def _blocks_of_values(v):
+    """[rows, K] numbers of the format, position i of a row its i-th -> E2M3 blocks"""
+    rows, K = v.shape
+    mag = v.abs()
+    e = torch.where(mag < 1, 0, torch.floor(torch.log2(mag.clamp(min=1))) + 1)
+    m = torch.where(e == 0, mag * 8, (mag / torch.exp2(e - 1) - 1) * 8)
+    bits = ((v < 0) * 32 + e * 8 + m).to(torch.int32).view(rows, K // 64, 2, 8, 4)
+    word = bits[..., 0] | bits[..., 1] << 6 | bits[..., 2] << 12 | bits[..., 3] << 18
+    blob = torch.stack([word & 255, word >> 8 & 255, word >> 16], dim=-1).to(torch.uint8).view(rows, K // 64, 2, 24)
+    unit = torch.cat([blob[..., :16].reshape(rows, K // 64, 32), blob[..., 16:].reshape(rows, K // 64, 16)], dim=2)
+    out = torch.full(((rows + 127) // 128, K // 64, 128, 48), 0xA5, dtype=torch.uint8, device=v.device)
+    r = torch.arange(rows, device=v.device)
+    out[r // 128, :, r % 128] = unit
+    return out.view(-1)
+
+
+# tests/test_gemm_plan.py holds them to the 256-row tiles; several tiles per block in those of 144 channels
+SHIFTED_SHORT_K = [(16381, 1024, 128), (98310, 144, 128), (16381, 1024, 256), (98457, 144, 256), (16381, 1024, 512), (115951, 144, 512),
+                   (16381, 1024, 768), (121253, 144, 768)]
+
+
+@pytest.mark.parametrize("M,N,K", SHIFTED_SHORT_K)
+def test_e2m3_gemm_shifted_with_few_steps(M, N, K):
     """Half-integer codes against the sum in 64 bits."""
-    M, N = 16381, 1024
     gen = torch.Generator(device=G.DEV).manual_seed(K)
-    qx = torch.randint(-7, 8, (M, K), generator=gen, device=G.DEV, dtype=torch.int8)
-    qw = torch.randint(-7, 8, (N, K), generator=gen, device=G.DEV, dtype=torch.int8)
-    (_, Xf), (_, Wf) = _e2m3(qx.cpu().numpy()), _e2m3(qw.cpu().numpy())
+    qx = torch.randint(0, 16, (M, K), generator=gen, device=G.DEV).float() - 7.5
+    qw = torch.randint(-7, 8, (N, K), generator=gen, device=G.DEV).float()
+    Xf, Wf = _blocks_of_values(qx), _blocks_of_values(qw)
+    assert np.array_equal(G.decode_e2m3_rows(Xf.cpu().numpy(), 200, K), qx[:200].double().cpu().numpy())
     sx, zx = torch.rand(M, generator=gen, device=G.DEV) + 0.5, torch.randint(0, 16, (M,), generator=gen, device=G.DEV).float()
-    sw, wsum, Y = torch.rand(N, generator=gen, device=G.DEV) * 1e-3, qw.float().sum(1), torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV)
+    sw, wsum, Y = torch.rand(N, generator=gen, device=G.DEV) * 1e-3, qw.sum(1), torch.empty(M, N, dtype=torch.bfloat16, device=G.DEV)
     G.q.qvggt_e2m3_gemm_shifted(Xf, sx, zx, Wf, sw, wsum, None, M, N, K, Y)
     want = (qx.double() @ qw.double().t() + (7.5 - zx.double())[:, None] * wsum.double()) * sx.double()[:, None] * sw.double()
     # the sums are exact; three roundings to float32 and one to bf16
