@@ -120,6 +120,15 @@ def test_gpu_tests_reach_the_plans_they_are_named_for(plans):
     assert {p[3] for p in BOTH_TILE_SHAPES if p[2] != 1024} == {p[3] for p in BOTH_TILE_SHAPES}
 
 
+def test_gpu_tests_reach_several_big_tiles_per_block(plans):
+    """int8 blocks: more than one tile for each of 256 blocks, none of the last ones whole, at K of either body of the tiles."""
+    from tests.test_gpu_int8_blocks import BIG_TILES
+    for (M, N, K, want), (shape, rows) in zip(BIG_TILES, plans([(*p[:3], 8, 0, 0) for p in BIG_TILES])):
+        main = M if want == "big" else rows
+        assert shape == want and K != 1024 and N % 256 and M % 128 and (main + 255) // 256 * ((N + 255) // 256) > 264, (M, N, K, shape)
+    assert {(K < 768, want) for _, _, K, want in BIG_TILES} == {(True, "big"), (False, "big"), (True, "big+deep"), (False, "big+deep")}
+
+
 E2M3_DRIVER = r"""
 #include "gemm_plan.h"
 #include <cstdio>

@@ -82,6 +82,34 @@ def test_i8b_gemm_both_tile_shapes(M, N, K):
     assert np.array_equal(acc[torch.from_numpy(rows).to(G.DEV)].cpu().numpy(), oracle.int_gemm(qx[rows], qw))
 
 
+# 256-row tiles, several per block, last ones of a few rows and channels, alone and with a rest; K of both bodies that blocks have (tests/test_gemm_plan.py holds
+# them to the plan)
+BIG_TILES = [(39527, 528, 128, "big"), (39654, 528, 512, "big"), (39410, 528, 768, "big"), (39282, 528, 1280, "big"), (35194, 3728, 256, "big+deep"),
+             (32775, 912, 768, "big+deep"), (32782, 784, 4096, "big+deep")]
+
+
+def _device_blocks(codes):
+    out = torch.full((G.q.qvggt_i8b_bytes(*codes.shape),), 0x5A, dtype=torch.int8, device=G.DEV)
+    G.q.qvggt_int8_to_blocks(codes, *codes.shape, out)
+    return out
+
+
+@pytest.mark.parametrize("M,N,K", [p[:3] for p in BIG_TILES])
+@pytest.mark.parametrize("with_bias", [True, False])
+def test_i8b_gemm_several_big_tiles_per_block(M, N, K, with_bias):
+    """Every row equals the row-major kernel's."""
+    g = torch.Generator(device=G.DEV).manual_seed(M + K)
+    Xl = torch.randint(-128, 128, (M, K), generator=g, device=G.DEV, dtype=torch.int8)
+    Wl = torch.randint(-128, 128, (N, K), generator=g, device=G.DEV, dtype=torch.int8)
+    dx, dw = torch.rand(M, device=G.DEV, generator=g) + 0.1, torch.rand(N, device=G.DEV, generator=g) * 1e-3
+    bias = torch.randn(N, device=G.DEV, generator=g).to(torch.bfloat16) if with_bias else None
+    Y = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device=G.DEV)
+    want = Y.clone()
+    G.q.qvggt_i8b_gemm(_device_blocks(Xl), dx, _device_blocks(Wl), dw, bias, M, N, K, Y, None)
+    G.q.qvggt_i8_gemm(Xl, dx, Wl, dw, bias, M, N, K, want, None)
+    assert torch.equal(Y, want)              # the row behind the last one is not written
+
+
 # The kernel with the weights in registers (tests/test_gemm_plan.py holds these to the rule): last steps of 1 to 31 tokens, ranges of unequal length, last
 # waves of 16 and 48 channels and waves without any, more groups of channels than compute units, Y past the caches and through them (3056)
 RESIDENT = [(2017, 4112), (10993, 3056), (8223, 3120), (20995, 1040), (300, 66064)]
