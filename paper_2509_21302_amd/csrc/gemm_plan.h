@@ -245,24 +245,32 @@ inline bool resident_wide(int M, int N)
 // Its price in microseconds, to be compared with the tiles'.  Loading the weights into the registers costs 5.5 + 2.4 k before the first product, a
 // step of a block 0.62 k, and writing Y 0.098 per megabyte on top of that.  Fitted to the products alone of 7 widths x 7 token counts at K = 512, 768 and 1024 (5 %, rms),
 // with 1.5 us more before the first step as calls run it, behind kernel 1: without them calls of few steps lose (with kernel 1, 2355 x 1024 -> 704, two steps, 10.4 in
-// tiles / 11.1 here, 585 x 1024 -> 2576 9.8 / 10.6).  Of 60 random calls of 400 to 60000 rows that this price brings here and the one of the kernel on 32x32
-// instructions (5.3 + 2.4 k, 0.735 k, 0.112) left in tiles, 5 % are gained on geometric average, 1.5 % lost at worst: us with kernel 1, tiles / this one:
-// 6452 x 2048 -> 3552 46.7 / 42.2, 2872 x 1536 -> 2928 23.7 / 20.3, 3697 x 1280 -> 2576 26.7 / 21.7, 4791 x 1024 -> 2720 23.1 / 21.3, 7690 x 1024 -> 1920 23.4 / 21.1,
-// 32648 x 1024 -> 448 39.9 / 35.4, 33436 x 1024 -> 256 34.1 / 34.6.  The tiles' price is too high where the rows of Y are 64-byte pieces but no whole lines (N = 32
-// mod 64: 13740 x 1280 -> 800, 37024 -> 224): 1.12.  Affine codes at K = 2048, whose kernel is short of registers, 1.05 (2844 x 2048 -> 3568 26.3 / 27.9).  us of the product, tiles / this one: 137400 x 1024 -> 4096 385 / 264, 32976 x 1024 -> 4096 90 / 71.6,
-// 10992 x 1024 -> 4096 38.9 / 28, 10992 x 768 -> 3072 25.8 / 18.5, 4096 x 1024 -> 4096 15.9 / 13.5, 2048 x 1024 -> 4096 9.5 / 9.6.
+// tiles / 11.1 here, 585 x 1024 -> 2576 9.8 / 10.6).  Held against 1880 random calls of all seven K and of affine codes, with kernel 1 in front, that the two prices put within a
+// third of each other: the choice is 0.5 % slower than the better of the two on geometric average; and 2 % faster than the choice among kernels on 32x32 instructions,
+// 1 % of the calls being slower than by that one by 4 % and more (6441 x 768 -> 2336 21.6 / 23.2).
+// us with kernel 1, tiles / this one: 6452 x 2048 -> 3552 46.7 / 42.2, 2872 x 1536 -> 2928 23.7 / 20.3, 3697 x 1280 -> 2576 26.7 / 21.7, 4791 x 1024 -> 2720 23.1 / 21.3,
+// 7690 x 1024 -> 1920 23.4 / 21.1, 32648 x 1024 -> 448 39.9 / 35.4, 33436 x 1024 -> 256 34.1 / 34.6, 3617 x 2048 -> 3648 28.8 / 30.0.  us of the product, tiles / this one:
+// 137400 x 1024 -> 4096 385 / 264, 32976 x 1024 -> 4096 90 / 71.6, 10992 x 1024 -> 4096 38.9 / 28, 10992 x 768 -> 3072 25.8 / 18.5, 4096 x 1024 -> 4096 15.9 / 13.5,
+// 2048 x 1024 -> 4096 9.5 / 9.6.
 inline double e2m3_resident_cost(int M, int N, int K)
 {
     const double k = K / 1024.0;
     const int steps = (M + 31) / 32, ranges = resident_ranges(M, N);
     return 1.015 * (5.5 + 2.4 * k + 0.62 * k * ((steps + ranges - 1) / ranges) + 0.098e-6 * 2.0 * M * N);
 }
+// The tiles' price is too high where the rows of Y are 64-byte pieces but no whole lines (N = 32 mod 64), the more the shorter K.  Of 250 such calls within a sixth of each
+// other, those that 1 + 61 / K puts on the wrong side cost 0.6 % in all; 1.12 for every K cost twice that (with kernel 1, tiles / this one: 48869 x 1024 -> 160 47.0 / 42.8,
+// 23603 x 1024 -> 288 33.4 / 31.5; 4787 x 512 -> 3744 18.8 / 19.7).  K = 1280 alone is better off with it (37024 -> 224 63.8 / 65.9).
+// This kernel's is too low where the weights are more than an XCD's L2 of 4 MiB holds with anything else, all of which read them all: 3617 x 2048 -> 3648 28.8 / 30.0,
+// 3693 -> 3392 28.7 / 29.5, 3725 x 1792 -> 3200 31.4 / 32.1, of 380 calls of 1024 to 4096 channels in one round of tiles, the wrong side costs
+// 0.4 % in all without the 1.04, 0.2 with it.
 inline bool e2m3_resident(int M, int N, int K, bool shifted)
 {
     if (!e2m3_resident_k(K, shifted)) return false;
     double tiles;
     e2m3_gemm_plan(M, N, K, &tiles);
-    return e2m3_resident_cost(M, N, K) * (N % 64 == 32 ? 1.12 : 1.0) * (shifted && K == 2048 ? 1.05 : 1.0) < tiles;
+    const double pieces = N % 64 != 32 ? 1.0 : K == 1280 ? 1.12 : 1.0 + 61.0 / K, spill = (long long)N * K > (4 << 20) ? 1.04 : 1.0;
+    return e2m3_resident_cost(M, N, K) * pieces * spill < tiles;
 }
 
 // int8 blocks with the weights in registers: K = 1024, whose 256 channels take half of them (blocks come with K = 1024, 2048 and 4096; at 2048 they would

@@ -300,6 +300,8 @@ int main()
     (2796, 4576, 1024, True, False), (3383, 3680, 1024, True, False), (5567, 2080, 1024, True, False), (6278, 1888, 1024, True, False), (9968, 1248, 1024, True, False),
     (23358, 1360, 1024, True, True), (117758, 3648, 1024, True, True), (10993, 3056, 1024, True, True),      # 63.1 / 57.3, 529 / 453
     (13740, 800, 1280, False, False), (13119, 1056, 1280, False, False), (37024, 224, 1280, False, False),   # 23.2 / 26.2, 25.4 / 27.4, 27.6 / 29.6
+    (3617, 3648, 2048, False, False), (3693, 3392, 2048, False, False), (3725, 3200, 1792, False, False),       # 28.8 / 30.0, 28.7 / 29.5, 31.4 / 32.1
+    (48869, 160, 1024, False, True), (23603, 288, 1024, False, True), (19952, 416, 1024, False, True),      # 47.0 / 42.8, 33.4 / 31.5, 30.3 / 28.9
     (10992, 4096, 1024, False, True), (32976, 4096, 2048, False, True), (10992, 3072, 768, False, True)])
 def test_resident_weights_where_the_kernels_differ(tmp_path, M, N, K, int8, resident):
     gxx = shutil.which("g++")
@@ -309,6 +311,17 @@ def test_resident_weights_where_the_kernels_differ(tmp_path, M, N, K, int8, resi
     subprocess.run([gxx, "-std=c++17", "-O1", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
     out = subprocess.run([tmp_path / "d"], input=f"{M} {N} {K} 0", capture_output=True, text=True, check=True).stdout.split()
     assert int(out[2 if int8 else 0]) == resident
+
+
+def test_resident_weights_where_affine_codes_differ(tmp_path):
+    """K = 2048, us behind kernel 1, tiles / weights in registers: 64.0 / 58.0, 61.7 / 54.2."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "d.cpp").write_text(RESIDENT_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
+    out = subprocess.run([tmp_path / "d"], input="18571 1248 2048 1\n15510 1504 2048 1", capture_output=True, text=True, check=True).stdout.split()
+    assert out[::3] == ["1", "1"]
 
 
 def test_resident_weights_of_128_channels_a_wave(tmp_path):

@@ -321,7 +321,7 @@ def test_linear_e2m3_few_rows(M, K, N):
 E2M3_PLANS = [(1, 16, 4096, "32"), (33, 48, 2048, "32"), (33, 48, 8192, "32"), (200, 1040, 4096, "32"), (64, 4096, 4096, "32"),
               (31, 144, 1024, "32x64"), (97, 2064, 128, "32x64"), (500, 1024, 4096, "32x64"), (300, 384, 256, "32x64"), (385, 3088, 2048, "32x64"),
               (700, 1040, 2048, "64"), (1374, 1024, 4096, "64"),
-              (1374, 3072, 1024, "128"), (1000, 2064, 1024, "128"), (5500, 3056, 768, "128"), (2000, 4000, 2048, "128"),
+              (1374, 3072, 1024, "128"), (1000, 2064, 1024, "128"), (5500, 3056, 768, "128"), (2000, 4000, 2048, "128"), (1001, 2064, 4096, "128"),
               (10992, 1024, 4096, "192"), (2749, 3104, 1024, "192"), (8300, 1040, 2048, "192"),
               (13741, 3056, 512, "256"), (10992, 4096, 1024, "256"),
               (16500, 4096, 1024, "256+32x64"), (16600, 1024, 2048, "256+32")]
