@@ -64,7 +64,7 @@ struct E2m3Problem {
     }
 };
 
-// Tiles of 256 tokens x 256 channels (gemm_e2m3_256.hip), K with tiles256_k.
+// Tiles of 256 tokens x 256 channels (gemm_e2m3_256.hip), where e2m3_tiles256 says so.
 template <bool SHIFTED>
 hipError_t run_e2m3_256(const E2m3Problem &p, hipStream_t stream);
 

@@ -29,7 +29,7 @@
 //
 // Tiles: 192 x 256 per block, one block per compute unit, four waves of 96 x 128 (192 accumulator registers each); 128 x 128 blocks, two per
 // compute unit, for problems of less than a round or so, and a kernel without shared stages for few tiles; 256 x 256 where many tokens fill
-// them, here for K of 128 to 512, else in gemm_e2m3_256.hip (gemm_plan.h has the rules).  Enough
+// them, here or, where K and the tiles are many, in gemm_e2m3_256.hip (gemm_plan.h has the rules).  Enough
 // tokens of K up to 2048 go to gemm_resident.h instead: what runs here of a size are few tokens, long K and the accumulator dump.
 // (256 x 128 blocks, two per compute unit, so that one block's epilogue runs under the other's K loop, were built and measured:
 // the K loop is not limited by the matrix pipes but by what feeds them, and 1.5 times the LDS traffic per MFMA ate the overlap.)
@@ -612,7 +612,7 @@ hipError_t launch_e2m3_shape(E2m3Plan::Shape shape, const E2m3Problem &p, hipStr
 {
     switch (shape) {
         case E2m3Plan::k256:
-            if (tiles256_k(p.K)) return run_e2m3_256<SHIFTED>(p, stream);
+            if (e2m3_tiles256(p.M, p.N, p.K)) return run_e2m3_256<SHIFTED>(p, stream);
             return launch_e2m3<4, 4, 2, 2, 5, 1, SHIFTED>(p, stream);
         case E2m3Plan::k192: return launch_e2m3<3, 4, 2, 2, 5, 1, SHIFTED>(p, stream);
         case E2m3Plan::k128: return launch_e2m3<2, 2, 2, 2, 4, 2, SHIFTED>(p, stream);

@@ -34,7 +34,7 @@ template <bool SHIFTED>
 hipError_t run_e2m3_256(const E2m3Problem &p, hipStream_t stream)
 {
     using C = Cfg256<E2m3Tiles, SHIFTED>;
-    if (!tiles256_k(p.K)) return hipErrorInvalidValue;
+    if (p.K < TILES256_LEAST_K) return hipErrorInvalidValue;
     const int tiles_m = (p.M + C::BM - 1) / C::BM, tiles_n = (p.N + C::BN - 1) / C::BN;
     auto kern = e2m3_streams_y(p.M, p.N) ? e2m3_256_kernel<false, SHIFTED, true> : e2m3_256_kernel<false, SHIFTED, false>;
     if constexpr (!SHIFTED) {

@@ -7,13 +7,34 @@
 
 namespace qvggt {
 
-// 256 x 256 tiles of E2M3 codes and of int8 blocks: on the 16 x 16 matrix instructions (gemm_tiles256.h), where K has enough steps to pay for filling their ring of
-// stages; fewer in the kernels on 32 x 32 ones (gemm_e2m3.hip, gemm_w4a4.hip).  us, 32 x 32 / 16 x 16, K = 128: E2M3 16381 -> 1024 10.7 / 12.0, 30000 -> 4096
-// 46.4 / 50.0, affine 16381 -> 1024 11.3 / 12.7, int8 16381 -> 1024 10.9 / 12.8, 13741 -> 3056 47.9 / 49.7; K = 256: 10.9 / 11.6, 54.0 / 55.7, 11.3 / 11.9,
-// 11.6 / 12.7, 48.9 / 50.5, with a tail 13073 -> 14064 216 / 220; K = 512: affine 16381 -> 1024 13.1 / 13.4, 30000 -> 4096 69.3 / 72.2, 65550 -> 2048 80.3 / 79.9, int8
-// 14.1 / 14.6, 9000 -> 1552 21.2 / 21.6, 65550 -> 2048 96.6 / 95.7; K = 768: int8 16381 -> 1024 17.8 / 17.2, 65550 -> 2048 119 / 117, 9000 -> 1552 24.0 / 24.4;
-// K = 1280: 23.3 / 22.9, 171 / 162, 30.1 / 29.6; 3 to 7 % ahead at K = 2560 to 8192.
-constexpr bool tiles256_k(int K) { return K >= 768; }
+// Which 256 x 256 tiles of E2M3 codes and of int8 blocks are on the 16 x 16 matrix instructions (gemm_tiles256.h) and which on the 32 x 32 ones (gemm_e2m3.hip,
+// gemm_w4a4.hip).  The 16 x 16 ones take less power, which bounds whole rounds of the chip, but about 2 us more of a launch's first and last tiles, and where K is short
+// more of every tile.  t: tiles per compute unit.  Time of 32 x 32 over that of 16 x 16, the means of 3 to 6 problems of a bin (650 in all):
+//              t < 0.6   0.6 - 0.8   0.8 - 0.95   0.95 - 1   1 - 2   2 - 5   more
+//   int8  768   0.91       0.94        0.93         0.95      1.01    1.01    1.02
+//        1280   0.98       0.96        0.98                   1.00    1.03    1.05
+//        2048   0.97       0.99        1.06         1.02      1.03    1.04    1.04
+//        3072   0.99       1.03                     1.03      1.06    1.06    1.06
+//        8192   0.98       1.06        1.10         1.05      1.06    1.07    1.10
+//   E2M3  768              0.93        0.96         0.96      0.98    1.00    0.98
+//        1280              0.94        0.97         1.01      1.00    1.01    1.02
+//        2048              0.97        0.97         0.99      1.01    1.02    1.01
+//        3072              1.00        1.01         1.00      1.03    1.03    1.04
+//        8192              1.06        1.05         1.02      1.06    1.04    1.05
+// Affine E2M3 codes as plain ones.  us: int8 blocks 11660 x 768 -> 736 13.0 / 15.2, 12870 x 1024 -> 768 15.2 / 17.5, 24705 x 8192 -> 1056 193 / 175; E2M3
+// 25447 x 1280 -> 480 16.8 / 18.0, 16381 x 128 -> 1024 10.7 / 12.0, 32976 x 4096 -> 2048 144 / 137.
+constexpr int TILES256_LEAST_K = 768;
+constexpr double tiles256_per_unit(int M, int N) { return (double)((M + 255) / 256) * ((N + 255) / 256) / 256.0; }
+constexpr bool e2m3_tiles256(int M, int N, int K)
+{
+    const double t = tiles256_per_unit(M, N);
+    return t > 1.0 ? K >= 1280 : K * (t - 0.3) >= 1400.0;
+}
+constexpr bool i8b_tiles256(int M, int N, int K)
+{
+    const double t = tiles256_per_unit(M, N);
+    return t > 1.0 ? K >= TILES256_LEAST_K : K * (t - 0.5) >= 640.0;
+}
 
 struct GemmPlan {
     enum Shape { kBig, kSmall, kDeep, kBigThenDeep } shape;

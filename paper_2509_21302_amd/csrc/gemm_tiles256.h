@@ -1,4 +1,4 @@
-// Products in tiles of 256 tokens x 256 channels, E2M3 and int8 codes, K of 768 and more (tiles256_k): gemm_e2m3_256.hip and gemm_w4a4.hip have the kernels.
+// Products in tiles of 256 tokens x 256 channels, E2M3 and int8 codes, K of 768 and more (e2m3_tiles256, i8b_tiles256): gemm_e2m3_256.hip and gemm_w4a4.hip have the kernels.
 //
 // Four waves per block and compute unit, each with 128 x 128 of the tile: 256 accumulator registers, the least operand traffic per MFMA that the register
 // file allows.  Persistent blocks, XCD-contiguous tile ranges, operands from global memory straight into an LDS ring (global_load_lds_dwordx4, 1 KiB
@@ -55,7 +55,7 @@ struct Cfg256 {
     // scales of the tile and of the next, or where LDS does not hold both of the tile alone.  They go out before the transfers of the tile's first K-step and have landed
     // when all but the transfers of STAGES - 2 steps have: at the opening of its step STAGES - 2
     static constexpr int SC_BUFFERS = SHIFTED ? 1 : 2;
-    static_assert(tiles256_k(768) && !tiles256_k(767) && 768 / 64 / KTILES >= STAGES - 1, "a tile of the least K has that step");
+    static_assert(TILES256_LEAST_K / 64 / KTILES >= STAGES - 1, "a tile of the least K has that step");
     static constexpr int EP_PITCH = 128 + 16, EP_BYTES = NW * 16 * EP_PITCH;
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + SC_BUFFERS * SC_BYTES + EP_BYTES;
     static_assert(BM % RB == 0 && BN % RB == 0 && NT % NW == 0, "tiles are whole blocks of the operand format, and every wave has as many pieces");

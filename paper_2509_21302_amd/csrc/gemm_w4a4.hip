@@ -724,7 +724,7 @@ static hipError_t launch_gemm_tail(const uint8_t *Xq, const float *sx, const uin
     if (e != hipSuccess) return e;
     auto kern = w4a4_gemm_tail_kernel<CB, BLK, BLK>;
     if constexpr (BLK) {
-        if (!tiles256_k(K)) kern = w4a4_gemm_tail_kernel<CB, BLK, false>;
+        if (!i8b_tiles256(rows_main, N, K)) kern = w4a4_gemm_tail_kernel<CB, BLK, false>;
     }
     kern<<<256, 256, TAIL_LDS_BYTES, stream>>>(Xq, sx, Wq, sw, reinterpret_cast<const uint16_t *>(bias), M, rows_main, N, K, reinterpret_cast<uint16_t *>(Y));
     return hipGetLastError();
@@ -780,7 +780,7 @@ static hipError_t gemm_by_plan(const uint8_t *Xq, const float *sx, const uint8_t
     switch (plan.shape) {
         case GemmPlan::kBig:
             if constexpr (BLK) {
-                if (acc_debug == nullptr && tiles256_k(K)) return launch_i8b_256(Xq, sx, Wq, sw, bias, M, N, K, Y, stream);
+                if (acc_debug == nullptr && i8b_tiles256(M, N, K)) return launch_i8b_256(Xq, sx, Wq, sw, bias, M, N, K, Y, stream);
             }
             return QVGGT_ROWS(4, 4, 4, 1, 0, M);
         case GemmPlan::kSmall: return QVGGT_ROWS(2, 2, 3, 2, 0, M);

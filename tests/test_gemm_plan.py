@@ -120,12 +120,13 @@ def test_gpu_tests_reach_the_plans_they_are_named_for(plans):
     assert {p[3] for p in BOTH_TILE_SHAPES if p[2] != 1024} == {p[3] for p in BOTH_TILE_SHAPES}
 
 
-def test_gpu_tests_reach_several_big_tiles_per_block(plans):
+def test_gpu_tests_reach_several_big_tiles_per_block(plans, tiles256):
     """int8 blocks: more than one tile for each of 256 blocks, none of the last ones whole, at K of either body of the tiles."""
     from tests.test_gpu_int8_blocks import BIG_TILES
     for (M, N, K, want), (shape, rows) in zip(BIG_TILES, plans([(*p[:3], 8, 0, 0) for p in BIG_TILES])):
         main = M if want == "big" else rows
         assert shape == want and K != 1024 and N % 256 and M % 128 and (main + 255) // 256 * ((N + 255) // 256) > 264, (M, N, K, shape)
+    assert [t[3] for t in tiles256([(*p[:3], 0) for p in BIG_TILES])] == [p[2] >= 768 for p in BIG_TILES]
     assert {(K < 768, want) for _, _, K, want in BIG_TILES} == {(True, "big"), (False, "big"), (True, "big+deep"), (False, "big+deep")}
 
 
@@ -218,20 +219,59 @@ def test_e2m3_plan_where_the_shapes_differ(tmp_path, M, N, K, plan):
     assert (shape if int(rows) == M else f"{shape}+{rest}") == plan
 
 
-def test_256_row_tiles_of_short_k(tmp_path):
-    """K below 768 runs on the 32 x 32 instructions, which measured up to 15 % faster there; the GPU tests reach both kinds in whole
-    plans of 256-row tiles that the weights in registers do not take."""
-    from tests.test_gpu_e2m3 import SHIFTED_SHORT_K, SHORT_K
+TILES256_DRIVER = r"""
+#include "gemm_plan.h"
+#include <cstdio>
+using namespace qvggt;
+int main()
+{
+    int M, N, K, shifted;
+    while (std::scanf("%d %d %d %d", &M, &N, &K, &shifted) == 4) {
+        const E2m3Plan p = e2m3_gemm_plan(M, N, K);
+        std::printf("%d %d %d %d\n", p.shape == E2m3Plan::k256 && !e2m3_resident(M, N, K, shifted != 0), e2m3_tiles256(p.rows_main, N, K), e2m3_streams_y(p.rows_main, N),
+                    i8b_tiles256(M, N, K));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def tiles256(tmp_path_factory):
+    """tiles256([(M, N, K, shifted), ...]) -> [(in 256-row E2M3 tiles, on the 16 x 16 instructions, Y past the caches, int8 tiles on the 16 x 16 ones), ...]"""
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no host C++ compiler")
-    (tmp_path / "d.cpp").write_text('#include "gemm_plan.h"\n#include <cstdio>\nusing namespace qvggt;\nint main() { int M, N, K, s; while (std::scanf("%d %d %d %d", &M, &N, &K, &s) == 4) {'
-                                    'const E2m3Plan p = e2m3_gemm_plan(M, N, K); std::printf("%d %d\\n", p.shape == E2m3Plan::k256 && p.rows_main == M && !e2m3_resident(M, N, K, s != 0), tiles256_k(K)); } }\n')
-    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp_path / "d", tmp_path / "d.cpp"], check=True)
-    problems = [(*p, 0) for p in SHORT_K] + [(*p, 1) for p in SHIFTED_SHORT_K]
-    out = subprocess.run([tmp_path / "d"], input="\n".join("%d %d %d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
-    assert [(int(a), int(b)) for a, b in zip(out[::2], out[1::2])] == [(1, p[2] >= 768) for p in problems]
-    assert {p[2] for p in problems} == {128, 256, 512, 768}
+    tmp = tmp_path_factory.mktemp("tiles256")
+    (tmp / "d.cpp").write_text(TILES256_DRIVER)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o", tmp / "d", tmp / "d.cpp"], check=True)
+
+    def ask(problems):
+        out = subprocess.run([tmp / "d"], input="\n".join("%d %d %d %d" % p for p in problems), capture_output=True, text=True, check=True).stdout.split()
+        return [tuple(int(v) for v in out[i:i + 4]) for i in range(0, len(out), 4)]
+    return ask
+
+
+def test_256_row_tiles_where_the_instructions_differ(tiles256):
+    """us, 32 x 32 / 16 x 16: few tiles or short K are the former's (10.7 / 12.0, 10.9 / 11.6, 16.8 / 18.0, 17.0 / 18.2; int8 13.0 / 15.2, 15.2 / 17.5), many of long K the latter's."""
+    e2m3 = [(16381, 1024, 128, 0), (16381, 1024, 256, 0), (25447, 480, 1280, 0), (4102, 2912, 1536, 0), (32976, 2048, 4096, 0), (9000, 1552, 8192, 0), (137400, 1024, 4096, 0)]
+    int8 = [(16381, 1024, 128, 0), (11660, 736, 768, 0), (12870, 768, 1024, 0), (32976, 1024, 4096, 0), (65550, 2048, 2048, 0), (24705, 1056, 8192, 0)]
+    assert [t[1] for t in tiles256(e2m3)] == [0, 0, 0, 0, 1, 1, 1]
+    assert [t[3] for t in tiles256(int8)] == [0, 0, 0, 1, 1, 1]
+
+
+def test_256_row_tiles_keep_their_least_k(tiles256):
+    """The ring of stages and the one set of scales of affine codes want K of 768 and more."""
+    rng = random.Random(5)
+    problems = [(int(math.exp(rng.uniform(0, math.log(1 << 21)))), 16 * int(math.exp(rng.uniform(0, math.log(4096)))), K, 0) for K in (128, 256, 512) for _ in range(3000)]
+    assert not any(t[1] or t[3] for t in tiles256(problems))
+
+
+def test_gpu_tests_reach_every_256_row_kernel(tiles256):
+    """Plain codes and affine ones, without the dump: both instructions, each with both kinds of store."""
+    from tests.test_gpu_e2m3 import CACHED_PLANS, CALL_PLANS, E2M3_PLANS, SHIFTED_SHORT_K, SHORT_K
+    for shifted, problems in ((0, E2M3_PLANS + CACHED_PLANS + CALL_PLANS + SHORT_K), (1, CACHED_PLANS + CALL_PLANS + SHIFTED_SHORT_K)):
+        assert {t[1:3] for t in tiles256([(*p[:3], shifted) for p in problems]) if t[0]} == {(0, 0), (0, 1), (1, 0), (1, 1)}
+    assert all(t[0] for t in tiles256([(*p, 0) for p in SHORT_K] + [(*p, 1) for p in SHIFTED_SHORT_K]))
 
 
 VARIANT_DRIVER = r"""
