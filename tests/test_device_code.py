@@ -1,5 +1,5 @@
-"""What the compiled kernels have to keep to and no run shows: wait states behind instructions in asm blocks, which the compiler does not see, and LDS reads that
-a barrier in an asm block has to wait for.  The sources are compiled to assembly here as the library is built."""
+"""What the compiled kernels have to keep to and no run shows: wait states behind instructions in asm blocks, which the compiler does not see, LDS reads that
+a barrier in an asm block has to wait for, and registers without scratch memory.  The sources are compiled to assembly here as the library is built."""
 import os
 import re
 import shutil
@@ -10,25 +10,29 @@ import pytest
 
 from paper_2509_21302_amd import build as B
 
-SOURCES = ("gemm_resident_1024_wide.hip", "gemm_resident_1280_2048.hip", "gemm_resident_affine.hip")
+SOURCES = tuple(s for s in B.SOURCES if s.startswith(("gemm_resident", "gemm_e2m3")))
 
 
 def _compile(source, out):
     subprocess.run([B.HIPCC, *B.FLAGS, *B.FLAGS_OF.get(source, []), "--cuda-device-only", "-S", os.path.join(B.CSRC, source), "-o", out],
                    check=True, capture_output=True)
-    kernels, name = {}, None
+    kernels, scratch, name = {}, {}, None
     for line in out.read_text().splitlines():
         line = line.split(";")[0].strip()
         m = re.fullmatch(r"(_Z\w+):", line)
         if m: name = m[1]
+        m = re.fullmatch(r"\.amdhsa_kernel (\w+)", line)
+        if m: described = m[1]
+        m = re.fullmatch(r"\.amdhsa_private_segment_fixed_size (\d+)", line)
+        if m: scratch[described] = int(m[1])
         if line.startswith(".section"): name = None
         if name and (re.match(r"[a-z]", line) or re.fullmatch(r"\.L\w+:", line)): kernels.setdefault(name, []).append(line)
-    return kernels
+    return kernels, scratch
 
 
 @pytest.fixture(scope="module")
 def assembly(tmp_path_factory):
-    """source -> {kernel: its lines of instructions and labels}; the sources compile side by side."""
+    """source -> ({kernel: its lines of instructions and labels}, {kernel: bytes of scratch memory a lane}); the sources compile side by side."""
     if shutil.which(B.HIPCC) is None:
         pytest.skip("hipcc is not installed")
     tmp = tmp_path_factory.mktemp("asm")
@@ -66,7 +70,7 @@ def test_wide_stores_keep_their_data(assembly):
         assert len(overwritten_stores([store, *between, "v_add_u32_e32 v138, s42, v208"])) == bad
         assert len(overwritten_stores([store, *between, "v_mfma_f32_16x16x128_f8f6f4 v[140:143], v[0:5], a[30:35], 0"])) == bad
     assert not overwritten_stores([store, "v_add_u32_e32 v142, s42, v138"])
-    kernels = assembly["gemm_resident_1024_wide.hip"]
+    kernels = assembly["gemm_resident_1024_wide.hip"][0]
     assert kernels and sum("store_dwordx4" in l for k in kernels.values() for l in k) >= 8
     assert not [(k, *s) for k, lines in kernels.items() for s in overwritten_stores(lines)]
 
@@ -113,8 +117,15 @@ def test_barriers_wait_for_the_scales(assembly, source, kernel, stage_bytes):
             "s_cbranch_scc1 .L0", "s_endpgm"]
     for n, bad in ((0, 0), (1, 0), (2, 1), (3, 1)):
         assert len(scales_read_across_barriers([l % n if "%d" in l else l for l in loop], 12288)) == bad
-    kernels = [lines for name, lines in assembly[source].items() if "resident_gemm_kernel" in name and kernel in name]
+    kernels = [lines for name, lines in assembly[source][0].items() if "resident_gemm_kernel" in name and kernel in name]
     assert kernels
     for lines in kernels:
         assert sum("offset:%d" % stage_bytes in l for l in lines) >= 3 and sum(l == "s_barrier" for l in lines) >= 4
         assert not scales_read_across_barriers(lines, stage_bytes)
+
+
+def test_no_kernel_uses_scratch_memory(assembly):
+    """The weights in registers, 256 x 256 tiles and the rest of the E2M3 GEMM: several are at the last register."""
+    scratch = {k: b for _, sizes in assembly.values() for k, b in sizes.items()}
+    assert sum("resident_gemm_kernel" in k for k in scratch) >= 21 and sum("e2m3_256_kernel" in k for k in scratch) == 5 and sum("e2m3_gemm" in k for k in scratch) >= 20
+    assert not {k: b for k, b in scratch.items() if b}
