@@ -277,12 +277,12 @@ def main():
         ceilings = dict(copy_GBps=2.0 * (1 << 30) / t_copy / 1e6, copy_frac_hbm_peak=2.0 * (1 << 30) / t_copy / 1e6 / HBM_PEAK_GBS,
                         copy="elementwise kernel, 1 GiB in + 1 GiB out")
     if not args.headline_only:
-        # register-only loops of the two matrix instructions: one wave per SIMD, 16 independent accumulators, tens of milliseconds each
+        # register-only loops of the two matrix instructions (16 x 16) on codes: one wave per SIMD, 32 independent accumulators, some milliseconds each
         sink = torch.empty(65536, dtype=torch.float32, device=dev)
         iters = 4000
-        for kind, name, kk in ((0, "mfma_int8_register_only_TOPS", 32), (1, "mfma_fp6_register_only_TFLOPS", 64)):
+        for kind, name, kk in ((0, "mfma_int8_register_only_TOPS", 64), (1, "mfma_fp6_register_only_TFLOPS", 128)):
             t = event_ms(lambda: q.qvggt_mfma_ceiling(kind, iters, sink), 3)
-            ceilings[name] = 256 * 4 * iters * 16 * (2.0 * 32 * 32 * kk) / (t * 1e-3) / 1e12
+            ceilings[name] = 256 * 4 * iters * 32 * (2.0 * 16 * 16 * kk) / (t * 1e-3) / 1e12
         ceilings["mfma_int8_frac_peak"] = ceilings["mfma_int8_register_only_TOPS"] / INT8_PEAK_TOPS
         ceilings["mfma_fp6_frac_peak"] = ceilings["mfma_fp6_register_only_TFLOPS"] / FP6_PEAK_TOPS
         del sink

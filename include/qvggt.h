@@ -478,11 +478,11 @@ int qvggt_calib_loss_grad(const float *R, const float *V, const float *y_ref, co
 int qvggt_calib_descent_step(float *theta, const float *grad, int n, float lr, float floor, void *stream);
 
 /*
- * Measurement helper (used by the benchmark, not by the path): a register-only loop of the matrix instruction a GEMM is
- * built on, to state what the matrix pipes of this board sustain when nothing has to be fed to them.  One launch runs
- * 256 blocks x 4 waves x iters x 16 instructions; kind 0: v_mfma_i32_32x32x32_i8 (2 * 32 * 32 * 32 operations each), kind 1:
- * v_mfma_f32_32x32x64_f8f6f4 on E2M3 operands (2 * 32 * 32 * 64 each).  sink: device f32 [65536], overwritten.  QVGGT_ERR_ARG
- * for another kind or iters outside 1 .. 2^24.
+ * Measurement helper (used by the benchmark, not by the path): a register-only loop of the matrix instruction that the GEMMs of
+ * many tokens are built on, to state what the matrix pipes of this board sustain on codes of a normal distribution when nothing has
+ * to be fed to them.  One launch runs 256 blocks x 4 waves x iters x 32 instructions; kind 0: v_mfma_i32_16x16x64_i8 (2 * 16 * 16 * 64
+ * operations each), kind 1: v_mfma_f32_16x16x128_f8f6f4 on E2M3 operands (2 * 16 * 16 * 128 each).  sink: device f32 [65536],
+ * overwritten.  QVGGT_ERR_ARG for another kind or iters outside 1 .. 2^24.
  */
 int qvggt_mfma_ceiling(int kind, int iters, float *sink, void *stream);
 

@@ -62,7 +62,8 @@ struct GemmPlan {
 // Measured (us, big / small / tail): packed codes 10992 x 768 -> 3072 42.6 / 33.6 / 38.1, 32976 x 256 -> 3072 56 / 50 / 55,
 // 32976 x 1024 -> 1024 50 / 40 / 45, 32976 x 4096 -> 1024 137 / 130 / 113; int8 blocks 32976 x 4096 -> 1024 140 / 156 / 118,
 // 20000 x 4096 -> 1024 89 / 92 / 71; just past one round of small tiles (big / small) int8 rows 9591 x 4096 -> 896 43 / 66,
-// int8 blocks 22039 x 4096 -> 304 45 / 62, 2247 x 2048 -> 4256 27 / 36, packed codes 39144 x 5120 -> 160 48 / 55.
+// int8 blocks 22039 x 4096 -> 304 45 / 62, 2247 x 2048 -> 4256 27 / 36, packed codes 39144 x 5120 -> 160 48 / 55.  These and the prices of int8 blocks' big tiles are of
+// the 32x32x32 instruction; where i8b_tiles256 has them on the 16x16x64 one they take 2 to 10 % less.
 // affine and dump: affine activation codes, the accumulator dump (their two tile loops do not fit the registers together: two launches).
 inline GemmPlan int8_instruction_gemm_plan(int M, int N, int K, int code_bits, bool affine, bool dump, double *cost = nullptr)
 {
@@ -256,7 +257,9 @@ inline int resident_ranges(int M, int N, int CT = 4) { return std::max(1, std::m
 // K = 1024, E2M3, no zero points: 128 channels a wave instead of 64 halve what a product reads from LDS and what comes from memory, and take 3 us more
 // to load.  us, 64 / 128 channels: 4096 channels, 10992 tokens (22 steps of a block) 30.1 / 28.3, 24576 (48) 58.3 / 53.1, 65536 (128) 137 / 127; 3072, 16384 (25)
 // 29.9 / 31.5, 24576 (37) 42.5 / 41.2, 65536 (98) 105 / 97; 2048, 32976 (33) 37.2 / 38.4, 65536 (64) 70.2 / 65.7; 1536, 65536 (49) 53.3 / 56.2; 1040, where the
-// wider groups leave a third of the chip idle, 44.9 / 48.3.  At K = 768 and 512, which were built as well, equal or slower up to 65536 tokens.
+// wider groups leave a third of the chip idle, 44.9 / 48.3; on another box 6144, 12288 50.6 / 46.7; 8192, 8192 44.1 / 41.9, 14000 70.4 / 65.8.  Beyond 8192
+// channels it depends on how the groups divide the chip: 8208, 14000 74.9 / 67.4; 12288, 6000 47.0 / 48.2, 16000 115 / 108; 16384, 4608 47.9 / 51.3, 16000 147 / 140.
+// At K = 768 and 512, which were built as well, equal or slower up to 65536 tokens.
 inline bool resident_wide(int M, int N)
 {
     auto steps = [&](int CT) { const int s = (M + 128 / CT - 1) / (128 / CT), r = resident_ranges(M, N, CT); return (s + r - 1) / r; };
@@ -295,13 +298,14 @@ inline bool e2m3_resident(int M, int N, int K, bool shifted)
 }
 
 // int8 blocks with the weights in registers: K = 1024, whose 256 channels take half of them (blocks come with K = 1024, 2048 and 4096; at 2048 they would
-// take all).  Few tiles stay with the kernels made for them: alone, those take less than the 8 us that this one needs to begin.  So do few tokens, whose
-// time is the weights' (40 x 66064 19.8 / 23.4, 300 x 66064 53.2 / 47.6).  The others by price
-// in microseconds, fitted to 234 random problems of 100 to 137400 rows (its own within 5 %, rms).  256s cost 4 us more where the rows of Y are 32-byte
+// take all).  Few tiles stay with the kernels made for them: alone, those take less than this one (2748 x 1024 7.7 / 9.0 us).  So do few tokens, whose
+// time is the weights' (40 x 66064 20.6 / 22.1, 300 x 66064 49.6 / 43.9).  The others by price
+// in microseconds.  The price is that of this kernel on the 32x32x32 instruction, fitted to 234 random problems of 100 to 137400 rows (its own within 5 %, rms), and a tenth
+// to a fifth too high for the one that runs: calls priced level stay in tiles and are the slower for it (20000 x 512 16.1 / 13.7, 65536 x 1024 71.0 / 63.6).  256s cost 4 us more where the rows of Y are 32-byte
 // pieces of lines, 1 where they are 64-byte ones (at 4 there too, one round of them with N = 32 mod 64 came here and lost: 2796 x 4576 23.6 / 27.5,
 // 5567 x 2080 25.4 / 28.1, 10392 x 992 30.0 / 30.8).  As calls run it, behind kernel 1, the 1620 of 3000 other problems that it gives to this kernel are
-// 1.18 times faster than in tiles on geometric average; 13 are slower by more than 2 %, by 6 % at worst.  us of the GEMM, tiles / this
-// one: 137400 x 4096 637 / 527, 32976 x 4096 153 / 125, 32976 x 1024 41.1 / 36.5, 10992 x 3072 40.9 / 36.7, 2748 x 1024 7.4 / 10.4.
+// 1.18 times faster than in tiles on geometric average; 13 are slower by more than 2 %, by 6 % at worst (both kernels on 32x32x32).  us of the GEMM as they are now,
+// tiles / this one: 137400 x 4096 561 / 452, 32976 x 4096 144 / 120, 32976 x 1024 43.4 / 33.2, 10992 x 3072 42.8 / 34.0.
 inline bool i8b_resident(int M, int N, int K)
 {
     if (K != 1024 || M < 256 || int8_instruction_few_tiles(M, N, K, 8, true) != FewTiles::kNone) return false;

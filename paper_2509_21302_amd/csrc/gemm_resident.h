@@ -21,7 +21,7 @@
 // us, 137400 x 1024 -> 4096 on one box, 32x32 MFMAs 306, 64 channels a wave 290, 128 channels 264 (half the LDS reads and transfers per product; without
 // stores 64 channels 224, also without the results' arithmetic 195, MFMAs alone 165; the stores alone take 181); 32976 tokens 79 / 75.5 / 71.6.  int8 codes: 24 frames
 // of fc1 and fc2 with kernel 1 343 -> 333.  Tried and not better: fragments read 4 to 7 units ahead instead of 3, stores of wider scope, a wait that
-// counts the stores as well.
+// counts the stores as well.  K = 2048 reads its fragments two ahead: with three it needs 28 bytes of scratch memory a lane, affine codes 76.
 //
 // The sizes are instantiated in several files, gemm_resident*.hip, which compile side by side (one file of all takes as long as the rest of the library).
 #pragma once
