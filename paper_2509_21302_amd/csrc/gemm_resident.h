@@ -13,8 +13,8 @@
 // are the MFMA's row operand, and a lane's columns are neighbouring channels: no transposition, a store instruction writes four whole lines or eight.
 //
 // The MFMAs are the 16 x 16 ones: the board's power is what bounds this kernel, and they need less of it.  A register-only loop on codes of a normal
-// distribution runs at 7.4 PFLOP/s with 16x16x128 and at 6.7 with 32x32x64 (int8 codes 4.1 and 3.5 POP/s).  And a lane then reads 24 bytes of 16 rows, all in
-// different banks, where rows r and r + 16 met in one.  What one wave per SIMD issues is the next limit: an MFMA of 16 cycles hides two other
+// distribution runs at 7.4 PFLOP/s with 16x16x128 and at 6.7 with 32x32x64 (int8 codes 4.1 and 3.5 POP/s).  fragments.h has where a
+// lane reads.  What one wave per SIMD issues is the next limit: an MFMA of 16 cycles hides two other
 // instructions that do not wait for each other, each further one costs 4 cycles, 8 if it needs the result of the one before.  So a result's
 // instructions are dealt out over four slots, and the scalar bookkeeping over the stage.
 //
@@ -26,6 +26,7 @@
 // The sizes are instantiated in several files, gemm_resident*.hip, which compile side by side (one file of all takes as long as the rest of the library).
 #pragma once
 #include "e2m3.h"
+#include "fragments.h"
 #include "gemm_plan.h"
 #include "resident.h"
 
@@ -51,7 +52,7 @@ __device__ inline void store_row(void *base, uint32_t lane_off, const uint32_t (
 }
 
 // An operand format.  A fragment is what an MFMA takes of 16 rows: 128 codes of each in E2M3 (two K-tiles of the format), 64 in int8 (one).  Lane l has
-// row l % 16 and the (l / 16)-th quarter of its codes.  A step of 32 tokens has as many fragments as E2M3 K-tiles, twice as many as int8 ones (TILE_UNITS).
+// row l % 16 and a quarter of its codes (fragments.h).  A step of 32 tokens has as many fragments as E2M3 K-tiles, twice as many as int8 ones (TILE_UNITS).
 struct E2m3Codes {
     typedef v6i Weights;                                               // a lane's share of a fragment
     typedef v8i Fragment;                                              // as the matrix builtin takes it: E2M3 numbers fill six of the eight registers
@@ -61,17 +62,16 @@ struct E2m3Codes {
     {
         return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(f, __builtin_shufflevector(w, w, 0, 1, 2, 3, 4, 5, -1, -1), s, 2, 2, 0, UNIT_SCALE_ONE, 0, UNIT_SCALE_ONE);
     }
-    // quarter q of row r: 16 bytes of K-tile q / 2 here (its other 8 are at 32 + 8 (q % 2) of the row)
-    static __device__ inline uint32_t first(int r, int q) { return r * U_BYTES + (q & 1) * 16; }
+    static __device__ inline uint32_t place(int r, int q, int tile_bytes) { return e2m3_place(r, q, tile_bytes); }
 };
-// "int8 blocks": K-tiles of 64 bytes a row, four 16-byte chunks whose places are swizzled with bits 2 and 3 of the row
+// "int8 blocks": K-tiles of 64 bytes a row
 struct Int8Codes {
     typedef v4i Weights;
     typedef v4i Fragment;
     typedef v4i Sums;
     static constexpr int TILE_UNITS = 2, ROW_BYTES = 64, WREGS = 4, KTILES = 1;
     static __device__ inline Sums multiply(Fragment f, Weights w, Sums s) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(f, w, s, 0, 0, 0); }
-    static __device__ inline uint32_t first(int r, int q) { return r * 64 + ((q ^ (r >> 2 & 3)) << 4); }
+    static __device__ inline uint32_t place(int r, int q, int) { return i8_place(r, q); }
 };
 
 // Pins values to one half of the register file at this point (accumulator and ordinary registers: the matrix instructions read either).
@@ -238,10 +238,10 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
         for (int j = 0; j < CT; ++j) {
             const int r = CT * c % chans + j;
             if constexpr (CODES::KTILES == 1) {
-                from[j] = place(r, g ^ (r >> 2 & 3));
+                from[j] = place(r, i8_quarter(g) ^ (r >> 2 & 3));
             } else {
-                from[j] = (g >> 1) * C::W_TILE + place(r, g & 1);
-                from_hi[j] = (g >> 1) * C::W_TILE + place(r, 2) + (g & 1) * 8;
+                from[j] = e2m3_tile(g) * C::W_TILE + place(r, e2m3_blob(g));
+                from_hi[j] = e2m3_tile(g) * C::W_TILE + place(r, 2) + e2m3_blob(g) * 8;
             }
         }
         const uint8_t *const w_smem = smem + 2 * C::STRIDE + wave * (C::W_SLOTS * C::W_TILE);
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 #pragma unroll
         for (int f = 0; f < R; ++f) { F[f][6] = 0; F[f][7] = 0; }
     }
-    const uint32_t frag = CODES::first(c, g) + (CODES::KTILES == 2 ? (g >> 1) * C::TILE_BYTES : 0), g8 = (g & 1) * 8;
+    const uint32_t frag = CODES::place(c, g, C::TILE_BYTES), g8 = e2m3_blob(g) * 8;
     // fragment u of a stage: tokens 16 (u % GROUPS) .. of its K-step u / GROUPS
     constexpr auto place = [](int u) constexpr { return u / GROUPS * CODES::KTILES * C::TILE_BYTES + u % GROUPS * 16 * CODES::ROW_BYTES; };
     auto read_lo = [&](auto f_c, int u, const uint8_t *stage) {

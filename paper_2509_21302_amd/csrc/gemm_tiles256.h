@@ -6,34 +6,35 @@
 // rows.  K-step p is in registers, p + 1 has landed and is read while p is multiplied, later ones are on their way, and p's stage is refilled.
 //
 // The MFMAs are the 16 x 16 ones.  On codes of a normal distribution the register-only rate under the board's power limit is 7.4 PFLOP/s with 16x16x128 (E2M3)
-// and 6.7 with 32x32x64, 4.1 and 3.5 POP/s with 16x16x64 and 32x32x32 (int8); and a fragment's 16 rows lie in different LDS banks, where rows r and r + 16 shared one.
+// and 6.7 with 32x32x64, 4.1 and 3.5 POP/s with 16x16x64 and 32x32x32 (int8).
 // Epilogue: accumulators from AGPRs, scale + bias, bf16, 16 tokens x 64 channels at a time through a wave-private LDS tile, whose way back
 // is hidden under the arithmetic of the next 16, stores of whole 128-byte lines.
 #pragma once
 #include "e2m3.h"
+#include "fragments.h"
 #include "gemm_plan.h"
 
 namespace qvggt {
 
 // An operand format: blocks of RB rows with the K-tiles outermost, ROW_BYTES of a row per K-tile.  A K-step is what an MFMA takes: KTILES K-tiles.  Lane (c, q) of a
-// fragment has row c's q-th quarter of the K-step: 16 bytes at first() of K-tile q * KTILES / 4, and in E2M3 8 more.
+// fragment has a quarter of row c's: 16 bytes at place() of the stage, and in E2M3 8 more.
 struct E2m3Tiles {
     typedef v8i Fragment;
     typedef v4f Sums;
     typedef float Sum;
     static constexpr int ROW_BYTES = U_BYTES, KTILES = 2, STAGES = 3, REGS = 6;
     static __device__ inline Sums multiply(Fragment a, Fragment b, Sums s) { return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, s, 2, 2, 0, UNIT_SCALE_ONE, 0, UNIT_SCALE_ONE); }
-    static __device__ inline int first(int c, int q) { return c * U_BYTES + (q & 1) * 16; }
+    static __device__ inline int place(int c, int q, int tile_bytes) { return e2m3_place(c, q, tile_bytes); }
     static __device__ inline float sum(float a) { return a; }
 };
-// "int8 blocks": four 16-byte chunks a row, whose places are swizzled with bits 2 and 3 of the row
+// "int8 blocks"
 struct Int8Tiles {
     typedef v4i Fragment;
     typedef v4i Sums;
     typedef int Sum;
     static constexpr int ROW_BYTES = 64, KTILES = 1, STAGES = 4, REGS = 4;
     static __device__ inline Sums multiply(Fragment a, Fragment b, Sums s) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, s, 0, 0, 0); }
-    static __device__ inline int first(int c, int q) { return c * 64 + ((q ^ (c >> 2 & 3)) << 4); }
+    static __device__ inline int place(int c, int q, int) { return i8_place(c, q); }
     static __device__ inline float sum(int a) { return (float)a; }
 };
 
@@ -160,9 +161,9 @@ __device__ __forceinline__ void tiles256(
             for (int f = 0; f < NF; ++f) { F[b][f][6] = 0; F[b][f][7] = 0; }
     }
     const int c = lane & 15, q = lane >> 4;
-    const int at = CODES::first(c, q) + q * C::KTILES / 4 * C::TILE_BYTES;
+    const int at = CODES::place(c, q, C::TILE_BYTES);
     const int w_lane = at + (C::BM + wn * TN * 16) * CODES::ROW_BYTES, x_lane = at + wm * TM * 16 * CODES::ROW_BYTES;
-    const int hi = 32 - (q & 1) * 8;                            // from the lane's first 16 bytes to its last 8
+    const int hi = e2m3_rest(q);                                // from the lane's first 16 bytes to its last 8
     auto place = [](int f, const uint8_t *wp, const uint8_t *xp) __attribute__((always_inline)) { return (f < TN ? wp + f * 16 * CODES::ROW_BYTES : xp + (f - TN) * 16 * CODES::ROW_BYTES); };
     auto read_lo = [&](auto b_c, int f, const uint8_t *wp, const uint8_t *xp) __attribute__((always_inline)) {
         constexpr int b = decltype(b_c)::value;
