@@ -257,7 +257,7 @@ inline int resident_ranges(int M, int N, int CT = 4) { return std::max(1, std::m
 // K = 1024, E2M3, no zero points: 128 channels a wave instead of 64 halve what a product reads from LDS and what comes from memory, and take 3 us more
 // to load.  us, 64 / 128 channels: 4096 channels, 10992 tokens (22 steps of a block) 30.1 / 28.3, 24576 (48) 58.3 / 53.1, 65536 (128) 137 / 127; 3072, 16384 (25)
 // 29.9 / 31.5, 24576 (37) 42.5 / 41.2, 65536 (98) 105 / 97; 2048, 32976 (33) 37.2 / 38.4, 65536 (64) 70.2 / 65.7; 1536, 65536 (49) 53.3 / 56.2; 1040, where the
-// wider groups leave a third of the chip idle, 44.9 / 48.3; on another box 6144, 12288 50.6 / 46.7; 8192, 8192 44.1 / 41.9, 14000 70.4 / 65.8.  Beyond 8192
+// wider groups leave a third of the chip idle, 44.9 / 48.3; on another board 6144, 12288 50.6 / 46.7; 8192, 8192 44.1 / 41.9, 14000 70.4 / 65.8.  Beyond 8192
 // channels it depends on how the groups divide the chip: 8208, 14000 74.9 / 67.4; 12288, 6000 47.0 / 48.2, 16000 115 / 108; 16384, 4608 47.9 / 51.3, 16000 147 / 140.
 // At K = 768 and 512, which were built as well, equal or slower up to 65536 tokens.
 inline bool resident_wide(int M, int N)
